@@ -1,0 +1,57 @@
+"""GPU parity where a dispatch rule changes kernels: the smallest and largest sizes of each path, the edges of its
+tiles and the operand alignments that it has to tell apart.  Same oracle and bars as test_gpu_ops.py."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2201_11990_amd as M
+from paper_2201_11990_amd import binding as B
+from parity import TOL, assert_close, dev, to_np
+from test_gpu_ops import DT, gemm_oracle, randn
+
+pytestmark = pytest.mark.gpu
+
+
+def operands(layout, Mm, N, K, dtype, seed=3):
+    return (randn((Mm, K) if layout != B.GEMM_TN else (K, Mm), dtype, seed),
+            randn((N, K) if layout == B.GEMM_NT else (K, N), dtype, seed + 1, 0.3))
+
+
+def shifted(t, by):
+    """The same values on the device, ``by`` elements past an allocation's start: contiguous, but aligned to one element only."""
+    buf = torch.empty(t.numel() + by, dtype=t.dtype, device="cuda")
+    out = buf[by:].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+# fp32 matrix-instruction GEMM: one element; K shorter than a chunk of 16 and than a wave's share; the 32, 64 and 128 tiles
+# with remainders on every side; widths that are no multiple of 4 take the scalar accesses.
+F32_SHAPES = [(1, 4, 4), (1, 1, 1), (33, 36, 20), (31, 64, 132), (900, 1156, 44), (1000, 3076, 20), (2044, 2052, 36), (66, 130, 17)]
+
+
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("shape", F32_SHAPES)
+def test_fp32_gemm_tiles_and_remainders(layout, shape):
+    Mm, N, K = shape
+    A, Bm = operands(layout, Mm, N, K, "fp32")
+    C = torch.full((Mm, N), float("nan"), device="cuda")
+    M.mtnlg_gemm(layout, dev(A), dev(Bm), C)
+    want = gemm_oracle(layout, A, Bm)
+    assert_close(C, want, TOL["fp32"], f"f32 gemm {layout} {shape}")
+    M.mtnlg_gemm(layout, dev(A), dev(Bm), C, epilogue=B.EPI_ACCUMULATE)
+    assert_close(C, 2 * want, TOL["fp32"], f"f32 gemm {layout} {shape} accumulate")
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+def test_vector_gemm_takes_operands_aligned_to_one_element(dtype, layout):
+    Mm, N, K = 70, 68, 52   # bf16: a K (NT, NN) or an M and N (TN) that the bf16 kernels do not take
+    A, Bm = operands(layout, Mm, N, K, dtype)
+    bias, res = randn((N,), dtype, 7), randn((Mm, N), dtype, 8)
+    want = gemm_oracle(layout, A, Bm) + to_np(bias) + to_np(res)
+    for which in range(5):
+        t = [shifted(x, 1 if i == which else 0) for i, x in enumerate((A, Bm, bias, res, torch.zeros(Mm, N, dtype=DT[dtype])))]
+        M.mtnlg_gemm(layout, t[0], t[1], t[4], bias=t[2], aux=t[3], epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
+        assert_close(t[4], want, TOL[dtype], f"gemm {layout} {dtype} operand {which} shifted")
