@@ -55,3 +55,27 @@ def test_vector_gemm_takes_operands_aligned_to_one_element(dtype, layout):
         t = [shifted(x, 1 if i == which else 0) for i, x in enumerate((A, Bm, bias, res, torch.zeros(Mm, N, dtype=DT[dtype])))]
         M.mtnlg_gemm(layout, t[0], t[1], t[4], bias=t[2], aux=t[3], epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
         assert_close(t[4], want, TOL[dtype], f"gemm {layout} {dtype} operand {which} shifted")
+
+
+# Token search of the embedding gradient: less than one 64-token mask, more than one round of 4096 tokens; vocabulary rows
+# that are no multiple of the 8 of a workgroup; columns beyond one 2048-column chunk; one id that takes most tokens.
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("b,s,h,V,vs", [(1, 3, 8, 8, 0), (1, 63, 2056, 24, 8), (2, 4133, 40, 16, 1000), (3, 1400, 4104, 40, 5)])
+def test_embedding_token_search_and_positions(dtype, b, s, h, V, vs):
+    T = b * s
+    g = torch.Generator().manual_seed(5)
+    tokens = torch.randint(max(0, vs - 3), vs + V + 3, (T,), generator=g, dtype=torch.int32)
+    tokens[torch.rand(T, generator=g) < 0.4] = vs + V - 1
+    E, P, dx = randn((V, h), dtype, 1), randn((s, h), dtype, 2), randn((T, h), dtype, 3)
+    desc = B.head_desc(h, V, vs, s, b, dtype)
+    x = torch.full((T, h), float("nan"), dtype=DT[dtype], device="cuda")
+    M.mtnlg_embedding_fwd(desc, tokens.cuda(), dev(E), dev(P), x)
+    assert_close(x, oracle.embedding_fwd(to_np(tokens), to_np(E), to_np(P), s, vs), TOL[dtype], "embedding")
+    x2 = torch.empty_like(x)   # with a hook between the lookup and the positions: the same values bit for bit
+    M.mtnlg_embedding_fwd(desc, tokens.cuda(), dev(E), dev(P), x2, reduce=lambda *a: None)
+    assert torch.equal(x, x2)
+    dE, dP = torch.full((V, h), float("nan"), dtype=DT[dtype], device="cuda"), torch.empty((s, h), dtype=DT[dtype], device="cuda")
+    M.mtnlg_embedding_bwd(desc, tokens.cuda(), dev(dx), dE, dP)
+    dE_o, dP_o = oracle.embedding_bwd(to_np(tokens), to_np(dx), V, s, vs)
+    assert_close(dE, dE_o, TOL[dtype], "embedding gradient")
+    assert_close(dP, dP_o, TOL[dtype], "position gradient")
