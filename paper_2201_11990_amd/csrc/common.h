@@ -69,10 +69,11 @@ __device__ __forceinline__ float wave_max(float v) {
 // themselves (s_waitcnt vmcnt(N) before the barrier that publishes a stage).  The LDS address
 // travels in M0, which each statement declares as clobbered.
 typedef __attribute__((ext_vector_type(4))) int dma_rsrc_t;
-__device__ __forceinline__ dma_rsrc_t dma_rsrc(const void *base) {   // base: the same in every lane
+// base: the same in every lane; records: bytes the bounds check lets through, offsets beyond read zeros
+__device__ __forceinline__ dma_rsrc_t dma_rsrc(const void *base, uint32_t records = 0xFFFFFFFFu) {
   const uint64_t a = (uint64_t)base;
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  return dma_rsrc_t{(int)lo, (int)(hi & 0xFFFF), -1, 0x00020000};
+  return dma_rsrc_t{(int)lo, (int)(hi & 0xFFFF), (int)records, 0x00020000};
 }
 // LDS byte address of a pointer into shared memory (what M0 takes)
 __device__ __forceinline__ uint32_t lds_address(const void *p) {
@@ -220,11 +221,12 @@ int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const v
 // ws (nullable): scratch for the split-K tail, see gemm_mfma_workspace_bytes
 // prof_class: kernel class the launch is timed under (-1: MTNLG_K_GEMM_NT + layout)
 // tile: one of gemm_tile, or -1 to let gemm_mfma_pick_tile choose (what every product call does)
-enum gemm_tile { GEMM_TILE_GENERAL_256 = 0, GEMM_TILE_GENERAL_128, GEMM_TILE_STREAM_256x256, GEMM_TILE_STREAM_256x320 };
+enum gemm_tile { GEMM_TILE_STREAM_256x256 = 0, GEMM_TILE_STREAM_256x320, GEMM_TILE_RAGGED_256, GEMM_TILE_RAGGED_128,
+                 GEMM_TILE_RAGGED_128_K2 };
 int gemm_mfma_bf16(int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B,
                    void *C, const void *bias, void *aux, uint32_t epi, void *ws, size_t ws_bytes,
                    hipStream_t stream, int prof_class = -1, int tile = -1);
-int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, bool have_workspace);
+int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes);
 size_t gemm_mfma_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K);
 int attention_fwd_simple(int dtype, int b, int s, int n, int d, float scale, const void *qkv,
                          void *a, float *lse, hipStream_t stream);

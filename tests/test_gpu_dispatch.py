@@ -79,3 +79,52 @@ def test_embedding_token_search_and_positions(dtype, b, s, h, V, vs):
     dE_o, dP_o = oracle.embedding_bwd(to_np(tokens), to_np(dx), V, s, vs)
     assert_close(dE, dE_o, TOL[dtype], "embedding gradient")
     assert_close(dP, dP_o, TOL[dtype], "position gradient")
+
+
+# bf16 MFMA GEMM, one shape or more per tile kind: 128 x 128 (one element wide, less than a tile, K tails), the same with two
+# K groups (even and odd numbers of slabs), 256 x 256 with ragged edges, and the aligned 256 x 256 and 256 x 320 tiles.  In
+# the weight-gradient form K is not even a multiple of 8.
+BF16_TILES = [(1, 8, 8), (129, 136, 72), (256, 128, 192), (136, 264, 1032), (72, 136, 1096), (2047, 8184, 72), (2048, 8192, 128),
+              (2048, 10240, 64)]
+
+
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("shape", BF16_TILES)
+def test_bf16_gemm_tile_kinds_and_ragged_edges(layout, shape):
+    Mm, N, K = shape
+    if layout == B.GEMM_TN and K % 64:
+        Mm, K = (Mm + 7) // 8 * 8 if Mm < 2000 else Mm // 8 * 8, K - 5
+    A, Bm = operands(layout, Mm, N, K, "bf16")
+    want = gemm_oracle(layout, A, Bm)
+    a, b = dev(A), dev(Bm)
+    C = torch.full((Mm, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    M.mtnlg_gemm(layout, a, b, C)
+    assert_close(C, want, TOL["bf16"], f"bf16 gemm {layout} {shape}")
+    bias, res = randn((N,), "bf16", 7), randn((Mm, N), "bf16", 8)
+    C.fill_(float("nan"))
+    M.mtnlg_gemm(layout, a, b, C, bias=dev(bias), aux=dev(res), epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
+    assert_close(C, want + to_np(bias) + to_np(res), TOL["bf16"], f"bf16 gemm {layout} {shape} bias + residual")
+    C32 = torch.full((Mm, N), float("nan"), device="cuda")
+    M.mtnlg_gemm(layout, a, b, C32, epilogue=B.EPI_OUT_F32)
+    assert_close(C32, want, TOL["fp32"], f"bf16 gemm {layout} {shape} fp32 out")
+    M.mtnlg_gemm(layout, a, b, C32, epilogue=B.EPI_OUT_F32 | B.EPI_ACCUMULATE)
+    assert_close(C32, 2 * want, TOL["fp32"], f"bf16 gemm {layout} {shape} fp32 accumulate")
+
+
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+def test_bf16_gemm_writes_nothing_outside_a_ragged_result(layout):
+    """Guard rows before and after C and poisoned memory after A and B: edges of every tile kind stay inside."""
+    for Mm, N, K in [(136, 264, 1032), (72, 136, 72)]:
+        A, Bm = operands(layout, Mm, N, K, "bf16")
+
+        def fenced(t):
+            buf = torch.full((t.numel() + 8192,), float("nan"), dtype=torch.bfloat16, device="cuda")
+            v = buf[4096:4096 + t.numel()].view(t.shape)
+            v.copy_(t)
+            return v
+
+        buf = torch.full((Mm * N + 8192,), 7.0, dtype=torch.bfloat16, device="cuda")
+        C = buf[4096:4096 + Mm * N].view(Mm, N)
+        M.mtnlg_gemm(layout, fenced(A), fenced(Bm), C)
+        assert_close(C, gemm_oracle(layout, A, Bm), TOL["bf16"], f"fenced {layout}")
+        assert bool((buf[:4096] == 7.0).all()) and bool((buf[4096 + Mm * N:] == 7.0).all())
