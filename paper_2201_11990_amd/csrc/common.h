@@ -222,7 +222,7 @@ int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const v
 // prof_class: kernel class the launch is timed under (-1: MTNLG_K_GEMM_NT + layout)
 // tile: one of gemm_tile, or -1 to let gemm_mfma_pick_tile choose (what every product call does)
 enum gemm_tile { GEMM_TILE_STREAM_256x256 = 0, GEMM_TILE_STREAM_256x320, GEMM_TILE_RAGGED_256, GEMM_TILE_RAGGED_128,
-                 GEMM_TILE_RAGGED_128_K2 };
+                 GEMM_TILE_RAGGED_128_DEEP };
 int gemm_mfma_bf16(int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B,
                    void *C, const void *bias, void *aux, uint32_t epi, void *ws, size_t ws_bytes,
                    hipStream_t stream, int prof_class = -1, int tile = -1);

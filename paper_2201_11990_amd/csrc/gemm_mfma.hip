@@ -3,8 +3,8 @@
 // One kernel, gemm_stream_kernel: v_mfma_f32_16x16x32_bf16, both operands moved global -> LDS by DMA through a ring of stages
 // with the loads spread over the slab, transposing LDS reads for row-contiguous operands.  Described at its definition.
 //   256 x 256 and 256 x 320 tiles on 2 x 4 waves for aligned problems (M a multiple of 256, N of the tile width, K of 64 --
-//   every GEMM of the MT-NLG slice); 256 x 256 with ragged edges; 128 x 128 on 2 x 2 waves with ragged edges, alone or with
-//   two K groups of four waves in a workgroup, for problems with too few large tiles to fill the chip.
+//   every GEMM of the MT-NLG slice); 256 x 256 with ragged edges; 128 x 128 on 2 x 2 waves with ragged edges and short or
+//   deep rings, for problems with too few large tiles to fill the chip.
 // gemm_mfma_pick_tile chooses per problem.  Ragged problems: any M, N a multiple of 8, K a multiple of 8 where an operand
 // is K-contiguous and anything in the weight-gradient form, whose M is a multiple of 8 (16-byte accesses never straddle
 // a row's end).
@@ -154,6 +154,7 @@ __device__ __forceinline__ void tile_coords(const GemmArgs &g, int pid, int &tm,
 //     256 x 256: A in a ring of two 32 KB stages, B in a ring of three (B is the operand that comes from HBM
 //                for the first time: the weights); 160 KB.
 //     256 x 320: A two stages of 32 KB, B two of 40 KB; 144 KB.   N a multiple of 320.
+//     128 x 128: stages of 16 KB; A two and B three (80 KB, two workgroups a compute unit), or four each (DEEP).
 //   The wider tile moves 10 % fewer operand bytes per FLOP from L2 into LDS ((BM + BN) / (BM BN)), which is
 //   what holds the clock down under the board's power limit, and it covers the layer's forward, input-gradient
 //   and FC weight-gradient shapes in whole rounds of 256 tiles; it pays with a ring one stage shorter and with
@@ -169,12 +170,12 @@ __device__ __forceinline__ void tile_coords(const GemmArgs &g, int pid, int &tm,
 //     of a k-row permuted (tr_pos below) so that the fragment reads spread over all banks;
 //     MFMA fragments are two transposing 8-byte LDS reads (ds_read_b64_tr_b16: a 16-lane group reads
 //     4 k-rows x 16 rows and every lane receives the 4 k values of its own row).
-//   A slab (two k-steps of 32) is four phases, one per pair of 16-row blocks of the wave tile, each issuing
+//   A slab (two k-steps of 32) is one phase per pair of 16-row blocks of the wave tile (four, or two of the 128-row tile), each issuing
 //   both k-steps of its 2 x TN accumulator blocks back to back and loading the A fragments of the next phase;
 //   the B fragments are held for the whole slab.  The one workgroup barrier per slab sits before the last
 //   phase (whose fragments are already in registers), which then reads the first A fragments and, block by
 //   block as its MFMAs release the registers, the B fragments of the next slab.
-//   Aligned problems only: M a multiple of BM, N of BN, K of 64.
+//   Without RAG aligned problems only: M a multiple of BM, N of BN, K of 64.
 
 // Position of the 16-byte unit u of k-row k inside a row-contiguous stage's k-row of UPR units (an involution
 // in u for every k).  A transposing fragment read touches, per 16-lane group, k-rows k0 .. k0+3 (k0 a multiple
@@ -198,16 +199,16 @@ __device__ __forceinline__ void wait_dma_and_barrier() {   // at most N of this 
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-template <int BM, int BN, int WGM, int WGN, int WGK, bool AT, bool BT, bool PLAIN16, bool RAG>
-__global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2) void gemm_stream_kernel(GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) char smem_all[];
-  constexpr int NWAVES = WGM * WGN;   // waves of one K group
+template <int BM, int BN, int WGM, int WGN, int DEEP, bool AT, bool BT, bool PLAIN16, bool RAG>
+__global__ __launch_bounds__(64 * WGM * WGN, WGM * WGN == 8 ? 1 : 2) void gemm_stream_kernel(GemmArgs g) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int NWAVES = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
   constexpr int NPH = TM / 2;   // phases of a slab
   static_assert(NPH == 4 || NPH == 2, "the phases of a slab are written out below");
   constexpr int A_STAGE = BM * BK * 2, B_STAGE = BN * BK * 2;
-  constexpr int RING_B = stream_ring_b(BN);
-  constexpr int A_RING = 2 * A_STAGE, B_RING = RING_B * B_STAGE;
+  constexpr int RING_B = DEEP ? DEEP : stream_ring_b(BN);
+  constexpr int A_RING = (DEEP ? DEEP : 2) * A_STAGE, B_RING = RING_B * B_STAGE;
   constexpr int NIA = BM / 8 / NWAVES, NIB = BN / 8 / NWAVES;   // DMA instructions (1 KB each) per wave, operand and slab
   const int nk_all = (int)((g.K + BK - 1) / BK);
   int pid, slab0 = 0, slab1 = nk_all, part_id = -1;
@@ -224,12 +225,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
   int tm, tn;
   tile_coords(g, pid, tm, tn);
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
-  const int kgroup = WGK > 1 ? wave_all / NWAVES : 0, wave = wave_all % NWAVES;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave: a scalar
   const int wm = wave / WGN, wn = wave % WGN;
   const bf16 *Abase = AT ? g.A + m0 : g.A + m0 * g.lda;
   const bf16 *Bbase = BT ? g.B + n0 : g.B + n0 * g.ldb;
-  char *const smem = smem_all + kgroup * (A_RING + B_RING);   // this K group's rings
 
   // DMA addressing.  Instruction q of an operand fills LDS bytes [1024 q, 1024 q + 1024) of the stage, lane l
   // the 16 bytes at 16 l; wave w issues the instructions NI w .. NI w + NI - 1.
@@ -417,11 +416,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
     }
   };
 
-  // Two K groups take the first and the second half of the slabs and run the same number of iterations (they share the
-  // workgroup barrier); with an odd count the second group's last slab lies past K and is all zeros.
-  const int nk = (slab1 - slab0 + WGK - 1) / WGK;
-  const int slab_first = slab0 + kgroup * nk;
-  auto slab_k = [&](int it) { return (int64_t)(slab_first + (RAG || it < nk ? it : nk - 1)) * BK; };
+  const int nk = slab1 - slab0;
+  // slabs past the last: of a ragged problem they lie beyond K (zeros) or in the next part; otherwise the last one again
+  auto slab_k = [&](int it) { return (int64_t)(slab0 + (RAG || it < nk ? it : nk - 1)) * BK; };
   char *const aring = smem, *const bring = smem + A_RING;
   constexpr int NM = 4 * TN;                                  // MFMAs of a phase
   constexpr int RAQ = (AT ? 2 : 1) * 4, RBJ = (BT ? 2 : 1) * 2;   // LDS read instructions of read_aq / read_bj
@@ -457,7 +454,32 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
   };
   using std::integral_constant;
 
-  if constexpr (RING_B == 3) {
+  if constexpr (DEEP > 0) {
+    // DEEP stages each way: the stage of slab `it` is free from the barrier of slab `it` on, and slab it + DEEP goes there,
+    // A right after that barrier (last phase), B in phase 0 of slab it + 1; slab it + 1 is complete at the barrier of
+    // slab `it` once only slabs it + 2 .. it + DEEP - 1 are outstanding.
+    static_assert(NPH == 2, "two phases a slab");
+#pragma unroll
+    for (int d = 0; d < DEEP; ++d) {
+      issue_a(slab_k(d), aring + d * A_STAGE, 0, NIA);
+      if (d < DEEP - 1) issue_b(slab_k(d), bring + d * B_STAGE, 0, NIB);
+    }
+    wait_dma_and_barrier<(DEEP - 2) * (NIA + NIB) + NIA>();   // slab 0 landed
+    read_aq(aring, 0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) read_bj(bring, j);
+    int cur = 0, last = DEEP - 1;   // stages of slabs `it` and it - 1
+    for (int it = 0; it < nk; ++it) {
+      const int nxt = cur + 1 == DEEP ? 0 : cur + 1;
+      phase(integral_constant<int, 0>{}, aring + cur * A_STAGE, nullptr, nullptr,
+            [&] { issue_b(slab_k(it - 1 + DEEP), bring + last * B_STAGE, 0, NIB); }, integral_constant<int, NIB>{});
+      wait_dma_and_barrier<(DEEP - 2) * (NIA + NIB)>();
+      phase(integral_constant<int, NPH - 1>{}, nullptr, aring + nxt * A_STAGE, bring + nxt * B_STAGE,
+            [&] { issue_a(slab_k(it + DEEP), aring + cur * A_STAGE, 0, NIA); }, integral_constant<int, NIA>{});
+      last = cur;
+      cur = nxt;
+    }
+  } else if constexpr (RING_B == 3) {
     // prologue: A slab 0, B slabs 0 and 1, first half of A slab 1
     issue_a(slab_k(0), aring, 0, NIA);
     issue_b(slab_k(0), bring, 0, NIB);
@@ -536,43 +558,13 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
   // The lane and wave numbers pass through an empty asm statement here: the epilogue's addresses then cannot be
   // computed ahead of the main loop, where they would occupy registers the loop needs (the 320-column tile has
   // 160 of 256 in accumulators).
-  int elane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ewave = wave_all;
+  int elane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ewave = wave;
   asm volatile("" : "+v"(elane), "+s"(ewave));
-  const int ewn = ewave % WGN;
-  // With two K groups each wave first gives half of its partial tile to its twin in the other group and adds the half it
-  // receives (lane-private 16-byte slots in LDS, group 0's partial first in both sums): it then owns RM of the rows.
-  constexpr int RM = WM / WGK, FM = TM / WGK;
-  const int erow = (ewave % NWAVES) / WGN * WM + (ewave / NWAVES) * RM;   // first row of the tile that this wave stores
-  f32x4 sum[WGK > 1 ? FM : 1][WGK > 1 ? TN : 1];
-  char *patches = smem_all;
-  if constexpr (WGK > 1) {
-    constexpr int SLOT = FM * TN * 64 * 16;
-    f32x4 *give = reinterpret_cast<f32x4 *>(smem_all + ewave * SLOT) + elane;
-    const f32x4 *take = reinterpret_cast<const f32x4 *>(smem_all + (ewave ^ NWAVES) * SLOT) + elane;
-    const bool first = ewave < NWAVES;
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        give[(i * TN + j) * 64] = first ? acc[FM + i][j] : acc[i][j];
-        sum[i][j] = first ? acc[i][j] : acc[FM + i][j];
-      }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) sum[i][j] += take[(i * TN + j) * 64];
-    patches = smem_all + 2 * NWAVES * SLOT;
-  }
-  auto block = [&](int i, int j) -> const f32x4 & {
-    if constexpr (WGK > 1) return sum[i][j];
-    else return acc[i][j];
-  };
-  constexpr int RP = WN == 80 || RM == 32 ? 32 : 64;        // rows per pass
+  const int ewm = ewave / WGN, ewn = ewave % WGN;
+  constexpr int RP = WN == 80 ? 32 : 64;        // rows per pass
   constexpr int SEG = WN / 8;                   // 8-column segments per row
   constexpr int NRD = RP * SEG / 64;            // read instructions per pass
-  static_assert(RM % RP == 0 && (RP * SEG) % 64 == 0, "epilogue passes must tile the wave tile");
-  static_assert(WGK == 1 || WGK == 2, "two K groups exchange halves");
+  static_assert(WM % RP == 0 && (RP * SEG) % 64 == 0, "epilogue passes must tile the wave tile");
   if (PLAIN16 && part_id < 0) {
     // bf16 output with at most a bias: round before the transposition, which halves the LDS
     // traffic of the patch and leaves the second half of the epilogue a plain 16-byte copy.
@@ -580,7 +572,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
     // u ^ ((r >> 1) & 7); 80 columns: 256 B per row (10 units used), unit u at u ^ (r & 15)
     // (8-byte block stores and 16-byte row reads both conflict-free).
     constexpr int PROW = WN == 64 ? 128 : 256;
-    char *patch = patches + ewave * (RP * PROW);
+    char *patch = smem + ewave * (RP * PROW);
     auto unit_pos = [](int unit, int row) { return WN == 64 ? (unit ^ ((row >> 1) & 7)) : (unit ^ (row & 15)); };
     static_assert(WN == 64 || WN == 80, "patch layouts exist for these wave tile widths");
     const int g4 = elane >> 4;
@@ -595,9 +587,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
         for (int e = 0; e < 4; ++e) bias4[j][e] = (float)bv[e];
       }
     }
-    bf16 *cbase = static_cast<bf16 *>(g.C) + (m0 + erow) * g.ldc + n0 + ewn * WN;
+    bf16 *cbase = static_cast<bf16 *>(g.C) + (m0 + ewm * WM) * g.ldc + n0 + ewn * WN;
 #pragma unroll
-    for (int p = 0; p < RM / RP; ++p) {
+    for (int p = 0; p < WM / RP; ++p) {
 #pragma unroll
       for (int i = 0; i < RP / 16; ++i)
 #pragma unroll
@@ -605,7 +597,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
           const int row = (elane & 15) + i * 16, unit = 2 * j + (g4 >> 1);
           bf16x4 h;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) h[e] = (bf16)(block(p * (RP / 16) + i, j)[e] + bias4[j][e]);
+          for (int e = 0; e < 4; ++e) h[e] = (bf16)(acc[p * (RP / 16) + i][j][e] + bias4[j][e]);
           *reinterpret_cast<bf16x4 *>(patch + row * PROW + (unit_pos(unit, row) << 4) + (g4 & 1) * 8) = h;
         }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -613,15 +605,15 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
       for (int t = 0; t < NRD; ++t) {
         const int q = t * 64 + elane, row = q / SEG, cv = q % SEG;
         const bf16x8 o = *reinterpret_cast<const bf16x8 *>(patch + row * PROW + (unit_pos(cv, row) << 4));
-        if (!RAG || (m0 + erow + p * RP + row < g.M && n0 + ewn * WN + cv * 8 < g.N))
+        if (!RAG || (m0 + ewm * WM + p * RP + row < g.M && n0 + ewn * WN + cv * 8 < g.N))
           *reinterpret_cast<bf16x8 *>(cbase + (int64_t)(p * RP + row) * g.ldc + cv * 8) = o;
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // patch is rewritten by the next pass
     }
   } else {
     constexpr int PITCH = WN + 4;   // floats; 68 and 84 both leave 16-byte block stores of 16 rows conflict-free
-    constexpr int NP = RM / RP;
-    float *patch = reinterpret_cast<float *>(patches) + ewave * (RP * PITCH);
+    constexpr int NP = WM / RP;
+    float *patch = reinterpret_cast<float *>(smem) + ewave * (RP * PITCH);
     const bool whole = part_id < 0;
     // The bias joins in the accumulator layout (4 consecutive columns per lane), and the values a residual or a
     // GeLU' read from aux are fetched two passes ahead, in the registers the accumulators of finished passes
@@ -636,8 +628,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
         bias_h[j] = *reinterpret_cast<const bf16x4 *>(static_cast<const bf16 *>(g.ea.bias) + n0 + ewn * WN + j * 16 + 4 * (elane >> 4));
     }
     const bool pre_aux = (flags & (MTNLG_EPI_RESIDUAL | MTNLG_EPI_GELU_GRAD)) != 0;
-    const bf16 *aux_base = static_cast<const bf16 *>(g.ea.aux) + (m0 + erow) * g.ldc + n0 + ewn * WN;
-    const int64_t aux_zero = -((m0 + erow) * g.ldc + n0 + ewn * WN);   // element (0, 0), for positions outside
+    const bf16 *aux_base = static_cast<const bf16 *>(g.ea.aux) + (m0 + ewm * WM) * g.ldc + n0 + ewn * WN;
+    const int64_t aux_zero = -((m0 + ewm * WM) * g.ldc + n0 + ewn * WN);   // element (0, 0), for positions outside
     bf16x8 pre[NP][NRD];
     auto preload = [&](auto P) {
       constexpr int p = decltype(P)::value;
@@ -647,7 +639,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
           for (int t = 0; t < NRD; ++t) {
             const int q = t * 64 + elane, row = q / SEG, cv = q % SEG;
             int64_t off = (int64_t)(p * RP + row) * g.ldc + cv * 8;
-            if (RAG && (m0 + erow + p * RP + row >= g.M || n0 + ewn * WN + cv * 8 >= g.N)) off = aux_zero;
+            if (RAG && (m0 + ewm * WM + p * RP + row >= g.M || n0 + ewn * WN + cv * 8 >= g.N)) off = aux_zero;
             pre[p][t] = *reinterpret_cast<const bf16x8 *>(aux_base + off);
           }
         }
@@ -663,7 +655,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
       for (int i = 0; i < RP / 16; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          f32x4 o = block(p * (RP / 16) + i, j);
+          f32x4 o = acc[p * (RP / 16) + i][j];
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[e] += (float)bias_h[j][e];
           *reinterpret_cast<f32x4 *>(patch + ((elane & 15) + i * 16) * PITCH + j * 16 + 4 * (elane >> 4)) = o;
@@ -678,7 +670,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, WGM * WGN * WGK == 8 ? 1 : 2)
         const f32x4 hi = *reinterpret_cast<const f32x4 *>(patch + row * PITCH + cv * 8 + 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
-        const int trow = erow + p * RP + row, tcol = ewn * WN + cv * 8;   // position in the tile
+        const int trow = ewm * WM + p * RP + row, tcol = ewn * WN + cv * 8;   // position in the tile
         if (!whole) {  // K-part of a tail tile: raw fp32 partial, summed by splitk_reduce_kernel
           store8(g.partial + (int64_t)part_id * (BM * BN) + trow * BN + tcol, v);
         } else if (!RAG || (m0 + trow < g.M && n0 + tcol < g.N)) {
@@ -766,29 +758,29 @@ int plan_launch(GemmArgs &g, void *ws, size_t ws_bytes, bool allow_split, unsign
 }
 
 // Streaming kernel.  Without RAG: M a multiple of BM, N of BN, K of 64.  Only 256 x 256 tiles split a last round along K.
-template <int BM, int BN, int WGM, int WGN, int WGK, bool AT, bool BT, bool RAG>
+template <int BM, int BN, int WGM, int WGN, int DEEP, bool AT, bool BT, bool RAG>
 int launch_stream(const GemmArgs &in, void *ws, size_t ws_bytes, hipStream_t st) {
   GemmArgs g = in;
   if (!RAG && (g.M % BM || g.N % BN || g.K % BK)) return MTNLG_UNSUPPORTED_SHAPE;
   unsigned grid;
   SplitPlan plan;
   MTNLG_TRY((plan_launch<BM, BN>(g, ws, ws_bytes, BM == 256 && BN == 256, &grid, &plan)));
-  constexpr int smem = WGK * (2 * BM + stream_ring_b(BN) * BN) * BK * 2;
+  constexpr int smem = DEEP ? DEEP * (BM + BN) * BK * 2 : (2 * BM + stream_ring_b(BN) * BN) * BK * 2;
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    if (hipFuncSetAttribute((const void *)gemm_stream_kernel<BM, BN, WGM, WGN, WGK, AT, BT, false, RAG>,
+    if (hipFuncSetAttribute((const void *)gemm_stream_kernel<BM, BN, WGM, WGN, DEEP, AT, BT, false, RAG>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess ||
-        hipFuncSetAttribute((const void *)gemm_stream_kernel<BM, BN, WGM, WGN, WGK, AT, BT, true, RAG>,
+        hipFuncSetAttribute((const void *)gemm_stream_kernel<BM, BN, WGM, WGN, DEEP, AT, BT, true, RAG>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
       return MTNLG_HIP_ERROR;
     attr_mark_set(attr_done, device);
   }
   // bf16 output with nothing but an optional bias: the epilogue that rounds before it transposes
   if ((g.ea.flags & ~(uint32_t)MTNLG_EPI_BIAS) == 0)
-    gemm_stream_kernel<BM, BN, WGM, WGN, WGK, AT, BT, true, RAG><<<dim3(grid), 64 * WGM * WGN * WGK, smem, st>>>(g);
+    gemm_stream_kernel<BM, BN, WGM, WGN, DEEP, AT, BT, true, RAG><<<dim3(grid), 64 * WGM * WGN, smem, st>>>(g);
   else
-    gemm_stream_kernel<BM, BN, WGM, WGN, WGK, AT, BT, false, RAG><<<dim3(grid), 64 * WGM * WGN * WGK, smem, st>>>(g);
+    gemm_stream_kernel<BM, BN, WGM, WGN, DEEP, AT, BT, false, RAG><<<dim3(grid), 64 * WGM * WGN, smem, st>>>(g);
   MTNLG_TRY(check_launch());
   if (plan.tail > 0) {
     splitk_reduce_kernel<BM, BN><<<dim3(8, plan.tail), 256, 0, st>>>(g);
@@ -800,25 +792,25 @@ int launch_stream(const GemmArgs &in, void *ws, size_t ws_bytes, hipStream_t st)
 template <bool AT, bool BT>
 int launch_tile(int tile, const GemmArgs &g, void *ws, size_t ws_bytes, hipStream_t st) {
   switch (tile) {
-    case GEMM_TILE_STREAM_256x256: return launch_stream<256, 256, 2, 4, 1, AT, BT, false>(g, ws, ws_bytes, st);
-    case GEMM_TILE_STREAM_256x320: return launch_stream<256, 320, 2, 4, 1, AT, BT, false>(g, ws, ws_bytes, st);
-    case GEMM_TILE_RAGGED_256: return launch_stream<256, 256, 2, 4, 1, AT, BT, true>(g, ws, ws_bytes, st);
-    case GEMM_TILE_RAGGED_128: return launch_stream<128, 128, 2, 2, 1, AT, BT, true>(g, ws, ws_bytes, st);
-    case GEMM_TILE_RAGGED_128_K2: return launch_stream<128, 128, 2, 2, 2, AT, BT, true>(g, ws, ws_bytes, st);
+    case GEMM_TILE_STREAM_256x256: return launch_stream<256, 256, 2, 4, 0, AT, BT, false>(g, ws, ws_bytes, st);
+    case GEMM_TILE_STREAM_256x320: return launch_stream<256, 320, 2, 4, 0, AT, BT, false>(g, ws, ws_bytes, st);
+    case GEMM_TILE_RAGGED_256: return launch_stream<256, 256, 2, 4, 0, AT, BT, true>(g, ws, ws_bytes, st);
+    case GEMM_TILE_RAGGED_128: return launch_stream<128, 128, 2, 2, 0, AT, BT, true>(g, ws, ws_bytes, st);
+    case GEMM_TILE_RAGGED_128_DEEP: return launch_stream<128, 128, 2, 2, 4, AT, BT, true>(g, ws, ws_bytes, st);
     default: return MTNLG_INVALID_ARG;
   }
 }
 
-// Estimated microseconds of a problem with nk 64-k slabs on each kind of tile: fits to measurements between 1024 and 8192
-// rows and columns, K 1024 to 8192, one MI355X.
+// Estimated microseconds of a problem with nk 64-k slabs on each kind of tile: fits to measurements between 256 and 8192
+// rows and columns, K 256 to 8192, weights not in the caches, one MI355X.
 //   256 x 256: 1.45 us a slab and 8 per round of 256 tiles; a last round split along K has fewer slabs, and its fp32
 //     partial tiles (256 KB each, written and read once) cost 0.05 us apiece.  256 x 320: 25 % more area at 0.97 of the
 //     cost per FLOP.
-//   128 x 128: a compute unit holds two workgroups, and the L2 -> LDS traffic of its smaller tile (twice the bytes per
-//     FLOP) is what bounds it: 0.88 us a slab for a full round of 512, 0.72 for a lone workgroup per unit, whose DMA
-//     latency nothing covers; with two K groups the workgroup covers its own: 0.5 us a slab, 6 for the exchange.
-// 2048^3 (256 tiles of 128 x 128; us): 256 x 256 split four ways 40, 128 x 128 26, two K groups 23; K = 8192: 70, 82, 68;
-// 2048 x 8192 x 2048: 51, 65, 87.
+//   128 x 128: twice the L2 -> LDS bytes per FLOP, which bounds it, so it is for problems with too few large tiles.  Short
+//     rings: two workgroups a compute unit, 1.0 us a slab for a full round of 512; a lone workgroup (0.88) waits for its
+//     DMA.  Rings of four stages: one workgroup a unit, 0.53 us a slab.
+// Measured (us; 256 x 256, split along K where that pays / 128 x 128 / with deep rings): 2048^3 42 / 28 / 21,
+// 2048 x 2048 x 8192 71 / 112 / 72, 1024 x 6144 x 2048 46 / 37 / 42, 2048 x 8192 x 2048 53 / 75 / 83, 256 x 960 x 512 13 / 9.3 / 7.5.
 double time_256(int64_t tiles, int nk, bool can_split, size_t ws_bytes) {
   const double slab = 1.45, round = 8.0;
   if (can_split) {
@@ -830,9 +822,9 @@ double time_256(int64_t tiles, int nk, bool can_split, size_t ws_bytes) {
 }
 double time_128(int64_t tiles, int nk) {
   const int64_t full = tiles / 512, rest = tiles % 512;
-  return (double)full * (0.88 * nk + 5.0) + (rest == 0 ? 0.0 : rest <= 256 ? 0.72 * nk + 2.5 : 0.88 * nk + 5.0);
+  return (double)full * (1.0 * nk + 6.0) + (rest == 0 ? 0.0 : rest <= 256 ? 0.88 * nk + 2.0 : 1.0 * nk + 6.0);
 }
-double time_128_k2(int64_t tiles, int nk) { return (double)((tiles + 255) / 256) * (0.5 * nk + 6.0); }
+double time_128_deep(int64_t tiles, int nk) { return (double)((tiles + 255) / 256) * (0.53 * nk + 4.5); }
 
 // Whether every byte offset of a tile's DMA stays below RAG_RECORDS
 bool ragged_fits(bool at, bool bt, int64_t lda, int64_t ldb) {
@@ -858,7 +850,7 @@ int gemm_mfma_pick_tile(int, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
   if (aligned && N % 320 == 0)
     offer(GEMM_TILE_STREAM_256x320, time_256(tiles(256, 320), nk, false, 0) * 1.25 * GEMM_COST_256x320);
   offer(GEMM_TILE_RAGGED_128, time_128(tiles(128, 128), nk));
-  offer(GEMM_TILE_RAGGED_128_K2, time_128_k2(tiles(128, 128), nk));
+  offer(GEMM_TILE_RAGGED_128_DEEP, time_128_deep(tiles(128, 128), nk));
   return pick;
 }
 

@@ -81,8 +81,8 @@ def test_embedding_token_search_and_positions(dtype, b, s, h, V, vs):
     assert_close(dP, dP_o, TOL[dtype], "position gradient")
 
 
-# bf16 MFMA GEMM, one shape or more per tile kind: 128 x 128 (one element wide, less than a tile, K tails), the same with two
-# K groups (even and odd numbers of slabs), 256 x 256 with ragged edges, and the aligned 256 x 256 and 256 x 320 tiles.  In
+# bf16 MFMA GEMM, one shape or more per tile kind: 128 x 128 (one element wide, less than a tile, K tails), the same with deep
+# rings (more and fewer slabs than stages), 256 x 256 with ragged edges, and the aligned 256 x 256 and 256 x 320 tiles.  In
 # the weight-gradient form K is not even a multiple of 8.
 BF16_TILES = [(1, 8, 8), (129, 136, 72), (256, 128, 192), (136, 264, 1032), (72, 136, 1096), (2047, 8184, 72), (2048, 8192, 128),
               (2048, 10240, 64)]
