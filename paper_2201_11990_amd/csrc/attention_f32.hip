@@ -1,0 +1,372 @@
+// Causal softmax attention, forward and backward, on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32): scores,
+// probabilities and sums stay in fp32.  This is the attention of the fp32 path and of the bf16 head sizes that the
+// bf16 kernels do not take (elements are widened on load).  Head sizes: multiples of 8 up to 256; sequences up to 4096.
+//
+//   S[t,u] = scale * q_t . k_u  (u <= t),  P = rowsoftmax(S),  a_t = sum_u P[t,u] v_u
+//   lse[t] = log sum_u exp(S[t,u])
+// backward, with D_t = da_t . a_t = sum_u P[t,u] dP[t,u]:
+//   dP[t,u] = da_t . v_u,  dS = P o (dP - D),  dq_t = scale sum_u dS[t,u] k_u,
+//   dk_u = scale sum_t dS[t,u] q_t,  dv_u = sum_t P[t,u] da_t
+//
+// Bound by the fp32 matrix rate where there are enough rows, else by each wave's chain of loads, MFMAs and exponentials.
+// A wave owns 16 rows of one side (queries forward and for dq, keys for dk / dv) and walks the other side 16 or 32 rows
+// at a time; fragments are loaded from global memory straight into the registers the MFMAs read (at this matrix rate a
+// wave asks the caches for 8 bytes a cycle), so there is no LDS, no barrier, and a wave stops at its own diagonal.  The four
+// waves of a workgroup own neighbouring rows and share what they load in the L1; a head's workgroups go to one XCD
+// where the number of heads allows it; workgroups with the most work start first.
+//
+// Lane l = 16 g + r.  Two fragment forms of a 16-row block X:
+//   Rows: element (c, e) = X[r][16 c + 4 g + e]; an MFMA per (c, e) contracts over columns.  With Rows of both sides a
+//         lane holds S[streamed row 4 g + i][own row r], i = 0..3.
+//   Cols: element (block, e) = X[4 g + e][column], NB consecutive columns per lane and group of 16 NB; an MFMA per
+//         (block, e) contracts over the rows, and its other operand for e is exactly that accumulator element: P
+//         and dS are used where they were computed.
+#include "common.h"
+
+namespace mtnlg {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+#define MFMA4(a, b, c) __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0)
+
+template <typename E, int DP>
+struct Rows {
+  static constexpr int NC = DP / 16;
+  f32x4 v[NC];
+  // rows first .. first + 15 of the matrix at base (pitch ld); rows past the end repeat the last one; columns past d are 0
+  __device__ __forceinline__ void load(const E *base, int64_t ld, int first, int rows, int d, int g, int r) {
+    const int row = first + r < rows ? first + r : rows - 1;
+    const E *p = base + row * ld;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int col = 16 * c + 4 * g;
+      if (16 * c + 16 > DP - 32) {   // d lies in (DP - 32, DP]
+        const f32x4 t = load4(p + (col < d ? col : 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[c][e] = col < d ? t[e] : 0.0f;
+      } else {
+        v[c] = load4(p + col);
+      }
+    }
+  }
+};
+
+template <int DP>
+struct Blocks {   // DP / 16 accumulator blocks over columns, in the order of Cols
+  static constexpr int N4 = DP / 64, N2 = DP % 64 / 32, N = DP / 16;
+  f32x4 b[N];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int i = 0; i < N; ++i) b[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  // row r of the result times mul: a lane holds 16 (or 8) consecutive columns per group
+  template <typename E>
+  __device__ __forceinline__ void store(E *row, int d, float mul, int g) const {
+    auto put = [&](int col, f32x4 x) {
+      if (col >= d) return;
+      x *= mul;
+      if constexpr (sizeof(E) == 4) *reinterpret_cast<f32x4 *>(row + col) = x;
+      else *reinterpret_cast<bf16x4 *>(row + col) = bf16x4{(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
+    };
+#pragma unroll
+    for (int q = 0; q < N4; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        put(64 * q + 16 * g + 4 * i, f32x4{b[4 * q][i], b[4 * q + 1][i], b[4 * q + 2][i], b[4 * q + 3][i]});
+    if constexpr (N2 > 0) {
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+        put(64 * N4 + 8 * g + 4 * v, f32x4{b[4 * N4][2 * v], b[4 * N4 + 1][2 * v], b[4 * N4][2 * v + 1], b[4 * N4 + 1][2 * v + 1]});
+    }
+  }
+};
+
+template <typename E, int DP>
+struct Cols {
+  static constexpr int N4 = Blocks<DP>::N4, N2 = Blocks<DP>::N2;
+  f32x4 v4[N4 > 0 ? N4 : 1][4];
+  f32x2 v2[4];
+  // columns past d repeat valid ones: what they produce is not stored
+  __device__ __forceinline__ void load(const E *base, int64_t ld, int first, int rows, int d, int g, int r) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = first + 4 * g + e < rows ? first + 4 * g + e : rows - 1;
+      const E *p = base + row * ld;
+#pragma unroll
+      for (int q = 0; q < N4; ++q) {
+        const int col = 64 * q + 4 * r;
+        v4[q][e] = load4(p + (64 * q + 64 <= DP - 32 || col < d ? col : 0));
+      }
+      if constexpr (N2 > 0) {
+        const int col = 64 * N4 + 2 * r;
+        const E *pp = p + (col < d ? col : 0);
+        if constexpr (sizeof(E) == 4) {
+          v2[e] = *reinterpret_cast<const f32x2 *>(pp);
+        } else {
+          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+          const bf16x2 t = *reinterpret_cast<const bf16x2 *>(pp);
+          v2[e] = f32x2{(float)t[0], (float)t[1]};
+        }
+      }
+    }
+  }
+  // acc += this^T x, x: element e belongs to row 4 g + e of the block
+  __device__ __forceinline__ void accumulate(Blocks<DP> &acc, const f32x4 &x) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int q = 0; q < N4; ++q)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc.b[4 * q + b] = MFMA4(v4[q][e][b], x[e], acc.b[4 * q + b]);
+      if constexpr (N2 > 0) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc.b[4 * N4 + b] = MFMA4(v2[e][b], x[e], acc.b[4 * N4 + b]);
+      }
+    }
+  }
+};
+
+template <typename E, int DP>
+__device__ __forceinline__ f32x4 product(const Rows<E, DP> &streamed, const Rows<E, DP> &own) {
+  f32x4 lo = {0.0f, 0.0f, 0.0f, 0.0f}, hi = {0.0f, 0.0f, 0.0f, 0.0f};   // two chains: an MFMA waits for its accumulator
+#pragma unroll
+  for (int c = 0; c < Rows<E, DP>::NC; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) {
+      lo = MFMA4(streamed.v[c][e], own.v[c][e], lo);
+      hi = MFMA4(streamed.v[c][e + 1], own.v[c][e + 1], hi);
+    }
+  return lo + hi;
+}
+
+// sum / maximum over the four lanes that share lane % 16
+__device__ __forceinline__ float quad_sum(float v) {
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
+__device__ __forceinline__ float quad_max(float v) {
+  v = fmaxf(v, __shfl_xor(v, 16, 64));
+  return fmaxf(v, __shfl_xor(v, 32, 64));
+}
+
+struct Where {   // grid: (heads, 64-row blocks, batch); a wave owns rows row0 .. row0 + 15
+  int lane, g, r, row0, head, batch;
+  __device__ __forceinline__ Where(bool last_first) {
+    lane = threadIdx.x & 63;
+    g = lane >> 4;
+    r = lane & 15;
+    const int blk = last_first ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+    row0 = blk * 64 + 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    head = blockIdx.x;
+    batch = blockIdx.z;
+  }
+};
+
+template <typename E, int DP>
+__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
+                                                           E *__restrict__ a, float *__restrict__ lse) {
+  const Where w(true);
+  if (w.row0 >= s) return;
+  const int64_t ld = (int64_t)n * 3 * d;
+  const E *base = qkv + (int64_t)w.batch * s * ld + (int64_t)w.head * 3 * d;
+  const int q = w.row0 + w.r;
+  Rows<E, DP> qf, kf[2];
+  qf.load(base, ld, w.row0, s, d, w.g, w.r);
+  const int last = w.row0 + 15 < s ? w.row0 + 15 : s - 1;   // last key any row of the wave sees
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) kf[kb].load(base + d, ld, 16 * kb, s, d, w.g, w.r);
+  Blocks<DP> o;
+  o.clear();
+  float m = -INFINITY, l = 0.0f;   // l: this lane's share of the row sum
+  for (int k0 = 0; k0 <= last; k0 += 32) {
+    Cols<E, DP> vf[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) vf[kb].load(base + 2 * d, ld, k0 + 16 * kb, s, d, w.g, w.r);
+    f32x4 p[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) p[kb] = product(kf[kb], qf) * scale;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) kf[kb].load(base + d, ld, k0 + 32 + 16 * kb, s, d, w.g, w.r);   // of the next step
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (k0 + 16 * kb + 4 * w.g + i > q) p[kb][i] = -INFINITY;
+        mx = fmaxf(mx, p[kb][i]);
+      }
+    const float m_new = fmaxf(m, quad_max(mx));   // finite: key 0 is never masked
+    const float alpha = expf(m - m_new);
+    float sum = 0.0f;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        p[kb][i] = expf(p[kb][i] - m_new);
+        sum += p[kb][i];
+      }
+    l = l * alpha + sum;
+    m = m_new;
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+      for (int i = 0; i < Blocks<DP>::N; ++i) o.b[i] *= alpha;
+    }
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) vf[kb].accumulate(o, p[kb]);
+  }
+  l = quad_sum(l);
+  if (q >= s) return;
+  o.store(a + ((int64_t)w.batch * s + q) * ((int64_t)n * d) + (int64_t)w.head * d, d, 1.0f / l, w.g);
+  if (w.g == 0) lse[((int64_t)w.batch * n + w.head) * s + q] = m + logf(l);
+}
+
+// dq, and D for the kernel below
+template <typename E, int DP>
+__global__ __launch_bounds__(256) void attn_bwd_dq_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
+                                                              const E *__restrict__ a, const float *__restrict__ lse,
+                                                              const E *__restrict__ da, E *__restrict__ dqkv,
+                                                              float *__restrict__ D) {
+  const Where w(true);
+  if (w.row0 >= s) return;
+  const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
+  const E *base = qkv + (int64_t)w.batch * s * ld + (int64_t)w.head * 3 * d;
+  const int64_t po = (int64_t)w.batch * s * pld + (int64_t)w.head * d, st = ((int64_t)w.batch * n + w.head) * s;
+  const int q = w.row0 + w.r, qc = q < s ? q : s - 1;
+  Rows<E, DP> qf, dof, kf, vf;
+  float dsum;
+  {  // D on the diagonal of dO a^T, by the same MFMAs as dP: where a row has one key (a = v) the two cancel exactly
+    Rows<E, DP> af;
+    af.load(a + po, pld, w.row0, s, d, w.g, w.r);
+    dof.load(da + po, pld, w.row0, s, d, w.g, w.r);
+    const f32x4 t = product(af, dof);
+    const float mine = (w.r & 2) ? ((w.r & 1) ? t[3] : t[2]) : ((w.r & 1) ? t[1] : t[0]);
+    dsum = __shfl(mine, 16 * (w.r >> 2) + w.r, 64);
+  }
+  if (q < s && w.g == 0) D[st + q] = dsum;
+  qf.load(base, ld, w.row0, s, d, w.g, w.r);
+  const float ls = lse[st + qc];
+  const int last = w.row0 + 15 < s ? w.row0 + 15 : s - 1;
+  kf.load(base + d, ld, 0, s, d, w.g, w.r);
+  vf.load(base + 2 * d, ld, 0, s, d, w.g, w.r);
+  Blocks<DP> dq;
+  dq.clear();
+  for (int k0 = 0; k0 <= last; k0 += 16) {
+    Cols<E, DP> kc;
+    kc.load(base + d, ld, k0, s, d, w.g, w.r);
+    const f32x4 sc = product(kf, qf) * scale, dp = product(vf, dof);
+    kf.load(base + d, ld, k0 + 16, s, d, w.g, w.r);   // of the next step
+    vf.load(base + 2 * d, ld, k0 + 16, s, d, w.g, w.r);
+    f32x4 ds;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ds[i] = k0 + 4 * w.g + i > q ? 0.0f : expf(sc[i] - ls) * (dp[i] - dsum);
+    kc.accumulate(dq, ds);
+  }
+  if (q < s) dq.store(dqkv + ((int64_t)w.batch * s + q) * ld + (int64_t)w.head * 3 * d, d, scale, w.g);
+}
+
+template <typename E, int DP>
+__global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
+                                                               const float *__restrict__ lse, const float *__restrict__ D,
+                                                               const E *__restrict__ da, E *__restrict__ dqkv) {
+  const Where w(false);
+  if (w.row0 >= s) return;
+  const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
+  const E *base = qkv + (int64_t)w.batch * s * ld + (int64_t)w.head * 3 * d;
+  const E *dab = da + (int64_t)w.batch * s * pld + (int64_t)w.head * d;
+  const int64_t st = ((int64_t)w.batch * n + w.head) * s;
+  const int key = w.row0 + w.r;
+  Rows<E, DP> kf, vf, qf, of;
+  kf.load(base + d, ld, w.row0, s, d, w.g, w.r);
+  vf.load(base + 2 * d, ld, w.row0, s, d, w.g, w.r);
+  Blocks<DP> dk, dv;
+  dk.clear();
+  dv.clear();
+  qf.load(base, ld, w.row0, s, d, w.g, w.r);
+  of.load(dab, pld, w.row0, s, d, w.g, w.r);
+  for (int q0 = w.row0; q0 < s; q0 += 16) {
+    Cols<E, DP> oc, qcol;
+    oc.load(dab, pld, q0, s, d, w.g, w.r);
+    qcol.load(base, ld, q0, s, d, w.g, w.r);
+    float ls[4], dd[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = q0 + 4 * w.g + i < s ? q0 + 4 * w.g + i : s - 1;
+      ls[i] = lse[st + q];
+      dd[i] = D[st + q];
+    }
+    const f32x4 sc = product(qf, kf) * scale, dp = product(of, vf);
+    qf.load(base, ld, q0 + 16, s, d, w.g, w.r);   // of the next step
+    of.load(dab, pld, q0 + 16, s, d, w.g, w.r);
+    f32x4 p, ds;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = q0 + 4 * w.g + i;
+      p[i] = q < key || q >= s ? 0.0f : expf(sc[i] - ls[i]);
+      ds[i] = p[i] * (dp[i] - dd[i]);
+    }
+    oc.accumulate(dv, p);
+    qcol.accumulate(dk, ds);
+  }
+  if (key >= s) return;
+  E *out = dqkv + ((int64_t)w.batch * s + key) * ld + (int64_t)w.head * 3 * d;
+  dk.store(out + d, d, scale, w.g);
+  dv.store(out + 2 * d, d, 1.0f, w.g);
+}
+
+template <typename E, int DP>
+int fwd_launch(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
+  LaunchScope scope(MTNLG_K_ATTN_FWD, st);
+  attn_fwd_f32_kernel<E, DP><<<dim3(n, (s + 63) / 64, b), 256, 0, st>>>(s, n, d, scale, (const E *)qkv, (E *)a, lse);
+  return check_launch();
+}
+
+template <typename E, int DP>
+int bwd_launch(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
+               void *dqkv, void *ws, hipStream_t st) {
+  float *D = (float *)ws;
+  const dim3 grid(n, (s + 63) / 64, b);
+  LaunchScope scope(MTNLG_K_ATTN_BWD, st);
+  attn_bwd_dq_f32_kernel<E, DP><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, (const E *)a, lse, (const E *)da, (E *)dqkv, D);
+  MTNLG_TRY(check_launch());
+  attn_bwd_dkv_f32_kernel<E, DP><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, lse, D, (const E *)da, (E *)dqkv);
+  return check_launch();
+}
+
+// fn<E, DP>, DP: the head size rounded up to a multiple of 32
+#define BY_HEAD_SIZE(fn, E, ...)                       \
+  switch ((d + 31) / 32) {                             \
+    case 1: return fn<E, 32>(__VA_ARGS__);             \
+    case 2: return fn<E, 64>(__VA_ARGS__);             \
+    case 3: return fn<E, 96>(__VA_ARGS__);             \
+    case 4: return fn<E, 128>(__VA_ARGS__);            \
+    case 5: return fn<E, 160>(__VA_ARGS__);            \
+    case 6: return fn<E, 192>(__VA_ARGS__);            \
+    case 7: return fn<E, 224>(__VA_ARGS__);            \
+    case 8: return fn<E, 256>(__VA_ARGS__);            \
+    default: return MTNLG_UNSUPPORTED_SHAPE;           \
+  }
+
+}  // namespace
+
+int attention_fwd_f32(int dtype, int b, int s, int n, int d, float scale, const void *qkv, void *a,
+                      float *lse, hipStream_t stream) {
+  if (d % 8 || d > 256 || s > ATTENTION_F32_MAX_SEQ || n > 65535 || b > 65535)
+    return MTNLG_UNSUPPORTED_SHAPE;
+  if (dtype == MTNLG_F32) BY_HEAD_SIZE(fwd_launch, float, b, s, n, d, scale, qkv, a, lse, stream)
+  if (dtype == MTNLG_BF16) BY_HEAD_SIZE(fwd_launch, bf16, b, s, n, d, scale, qkv, a, lse, stream)
+  return MTNLG_INVALID_ARG;
+}
+
+int attention_bwd_f32(int dtype, int b, int s, int n, int d, float scale, const void *qkv,
+                      const void *a, const float *lse, const void *da, void *dqkv, void *ws,
+                      hipStream_t stream) {
+  if (d % 8 || d > 256 || s > ATTENTION_F32_MAX_SEQ || n > 65535 || b > 65535)
+    return MTNLG_UNSUPPORTED_SHAPE;
+  if (dtype == MTNLG_F32) BY_HEAD_SIZE(bwd_launch, float, b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream)
+  if (dtype == MTNLG_BF16) BY_HEAD_SIZE(bwd_launch, bf16, b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream)
+  return MTNLG_INVALID_ARG;
+}
+
+}  // namespace mtnlg

@@ -35,6 +35,16 @@ template <typename E> __device__ __forceinline__ void load8(const E *p, float (&
     for (int i = 0; i < 4; ++i) { out[i] = a[i]; out[4 + i] = b[i]; }
   }
 }
+// 4 consecutive elements as floats (16 bytes of float, 8 of bf16)
+template <typename E>
+__device__ __forceinline__ f32x4 load4(const E *p) {
+  if constexpr (sizeof(E) == 4) {
+    return *reinterpret_cast<const f32x4 *>(p);
+  } else {
+    const bf16x4 t = *reinterpret_cast<const bf16x4 *>(p);
+    return f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
+  }
+}
 template <typename E> __device__ __forceinline__ void store8(E *p, const float (&in)[8]) {
   if constexpr (sizeof(E) == 2) {
     bf16x8 t;
@@ -228,9 +238,9 @@ int gemm_mfma_bf16(int layout, int64_t M, int64_t N, int64_t K, const void *A, c
                    hipStream_t stream, int prof_class = -1, int tile = -1);
 int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes);
 size_t gemm_mfma_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K);
-int attention_fwd_simple(int dtype, int b, int s, int n, int d, float scale, const void *qkv,
+int attention_fwd_f32(int dtype, int b, int s, int n, int d, float scale, const void *qkv,
                          void *a, float *lse, hipStream_t stream);
-int attention_bwd_simple(int dtype, int b, int s, int n, int d, float scale, const void *qkv,
+int attention_bwd_f32(int dtype, int b, int s, int n, int d, float scale, const void *qkv,
                          const void *a, const float *lse, const void *da, void *dqkv, void *ws,
                          hipStream_t stream);
 
@@ -238,7 +248,7 @@ int attention_bwd_simple(int dtype, int b, int s, int n, int d, float scale, con
 bool attention_mfma_supported(int dtype, int d);
 // ... and whether it takes this problem (grid limits, 32-bit byte offsets inside one sequence)
 bool attention_mfma_takes(int dtype, int b, int s, int n, int d);
-constexpr int ATTENTION_SIMPLE_MAX_SEQ = 4096;   // the vector-ALU kernels hold one row of scores in LDS
+constexpr int ATTENTION_F32_MAX_SEQ = 4096;   // sequence limit of the fp32 matrix-instruction kernels
 size_t attention_bwd_workspace_bytes(int b, int s, int n, int d);
 int attention_fwd_mfma(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse,
                        hipStream_t stream);

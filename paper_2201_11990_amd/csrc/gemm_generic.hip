@@ -28,16 +28,6 @@ struct F32GemmArgs {
   int tiles_m, tiles_n;
 };
 
-// 4 consecutive elements as floats (16 bytes of float, 8 of bf16)
-template <typename E>
-__device__ __forceinline__ f32x4 load4(const E *p) {
-  if constexpr (sizeof(E) == 4) {
-    return *reinterpret_cast<const f32x4 *>(p);
-  } else {
-    const bf16x4 t = *reinterpret_cast<const bf16x4 *>(p);
-    return f32x4{(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
-  }
-}
 template <typename E, int NB>
 __device__ __forceinline__ void load_rows(const E *p, float (&out)[NB]) {
   if constexpr (NB == 4) {

@@ -8,6 +8,7 @@ import oracle
 import paper_2201_11990_amd as M
 from paper_2201_11990_amd import binding as B
 from parity import TOL, assert_close, dev, to_np
+import test_gpu_ops
 from test_gpu_ops import DT, gemm_oracle, randn
 
 pytestmark = pytest.mark.gpu
@@ -128,3 +129,12 @@ def test_bf16_gemm_writes_nothing_outside_a_ragged_result(layout):
         M.mtnlg_gemm(layout, fenced(A), fenced(Bm), C)
         assert_close(C, gemm_oracle(layout, A, Bm), TOL["bf16"], f"fenced {layout}")
         assert bool((buf[:4096] == 7.0).all()) and bool((buf[4096 + Mm * N:] == 7.0).all())
+
+
+# fp32 matrix-instruction attention: head sizes at and between the multiples of 32 that it is compiled for, sequences around
+# the 16 rows of a wave, the 32 keys of a forward step and the 64 rows of a workgroup.
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("b,s,n,d", [(2, 17, 3, 24), (1, 65, 2, 72), (1, 129, 8, 96), (2, 100, 9, 104), (1, 15, 2, 136), (1, 79, 1, 168),
+                                     (1, 33, 2, 192), (1, 90, 2, 200), (2, 70, 2, 232), (1, 64, 1, 256), (3, 1, 2, 40)])
+def test_attention_at_every_compiled_head_size(dtype, b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
