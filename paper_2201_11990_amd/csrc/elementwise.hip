@@ -121,48 +121,105 @@ static int ln_fwd_launch(int64_t T, int64_t h, const void *x, const void *partia
 }
 
 // ---------------------------------------------------------------- LayerNorm bwd
-// One 1024-thread workgroup walks `rows_per` consecutive token rows; a thread owns the
-// same NV groups of 8 columns in every row, so the column sums
+// A 1024-thread workgroup walks `rows_per` consecutive token rows, R = 16 / GW at a time, GW waves to a row; a thread
+// owns the same NV groups of 8 columns in every row of its group, so the column sums
 //   dgamma = sum_t dout*xhat,  dbeta = sum_t dout,  (CS) colsum = sum_t dx
 // build up in its registers while the rows stream through once from HBM:
 //   pass 1 over the row: xhat, dxh = dout*gamma -> row sums m1 = mean(dxh), m2 = mean(dxh*xhat)
-//   pass 2 (row re-read, L2-resident): dx = dres + rs * (dxh - m1 - xhat*m2)
-// Workgroup b leaves its column sums in ws[o][b][h]; a second kernel adds them in a
-// fixed order.
+//   pass 2: dx = dres + rs * (dxh - m1 - xhat*m2)
+// GW is what covers the row with NV = 1 (one wave up to 512 columns, all 16 from 4097 on): a row of 2048 columns on all
+// 16 waves left three of four idle.  With NV = 1 the row stays in registers between the passes and the next row's loads
+// are issued before this row's reduction; with more, pass 2 reads it again from L2 (holding three groups of two operands
+// costs half the waves that hide latency).  8192 x 2048: 81 -> 31 us; 2048 x 20480 (NV = 3): 104 us, 4.4 TB/s.
+// The groups' sums are added through LDS; workgroup b leaves its column sums in ws[o][b][h]; a second kernel adds
+// them in a fixed order.
 constexpr int LNB_THREADS = 1024, LNB_MAX_WGS = 256;
 
-template <typename E, int NV, bool CS>
+// 8 consecutive elements as loaded
+template <typename E> struct Raw8;
+template <> struct Raw8<bf16> {
+  bf16x8 v;
+  __device__ __forceinline__ void load(const bf16 *p) { v = *reinterpret_cast<const bf16x8 *>(p); }
+  __device__ __forceinline__ float operator[](int e) const { return (float)v[e]; }
+};
+template <> struct Raw8<float> {
+  f32x4 a, b;
+  __device__ __forceinline__ void load(const float *p) {
+    a = *reinterpret_cast<const f32x4 *>(p);
+    b = *reinterpret_cast<const f32x4 *>(p + 4);
+  }
+  __device__ __forceinline__ float operator[](int e) const { return e < 4 ? a[e] : b[e - 4]; }
+};
+
+template <typename E, int NV, int GW, bool CS>
 __global__ __launch_bounds__(LNB_THREADS) void ln_bwd_fused_kernel(
     int64_t T, int64_t h, int rows_per, const E *__restrict__ x, const E *__restrict__ gamma,
     const float *__restrict__ mean, const float *__restrict__ rstd, const E *__restrict__ dout,
     const E *__restrict__ dres, E *__restrict__ dx, float *__restrict__ ws) {
-  __shared__ float red[2][LNB_THREADS / 64];
-  const int nvec = (int)(h / 8);
+  constexpr int NW = LNB_THREADS / 64, R = NW / GW, GT = 64 * GW;   // waves, row groups, threads of a group
+  constexpr bool HOLD = NV == 1;
+  constexpr int NOUT = CS ? 3 : 2;
+  __shared__ float red[2][NW];
+  __shared__ float part[R > 1 ? R - 1 : 1][R > 1 ? GT * 8 : 1];   // column sums of groups 1 .. R - 1, one output at a time
+  const int nvec = (int)(h / 8), grp = (threadIdx.x >> 6) / GW, gt = threadIdx.x % GT;
   const int64_t row0 = (int64_t)blockIdx.x * rows_per;
   const int64_t row1 = row0 + rows_per < T ? row0 + rows_per : T;
   float dg[NV][8] = {}, db[NV][8] = {}, cs[CS ? NV : 1][8] = {};
-  for (int64_t row = row0; row < row1; ++row) {
-    const float mu = mean[row], rs = rstd[row];
+  Raw8<E> hx, hd, hr;   // HOLD: this thread's columns of the row about to be processed
+  float gam[8];
+  const bool col_ok = gt < nvec;
+  auto fetch = [&](int64_t row) {   // threads beyond the row and groups beyond the last row repeat what is there
+    const int64_t at = (row < row1 ? row : row1 - 1) * h + (int64_t)(col_ok ? gt : nvec - 1) * 8;
+    hx.load(x + at);
+    hd.load(dout + at);
+    hr.load((dres ? dres : dout) + at);
+  };
+  if constexpr (HOLD) {
+    load8(gamma + (int64_t)(col_ok ? gt : nvec - 1) * 8, gam);
+    fetch(row0 + grp);
+  }
+  for (int64_t base = row0; base < row1; base += R) {
+    const int64_t row = base + grp;
+    const bool row_ok = row < row1;
+    const float mu = row_ok ? mean[row] : 0.0f, rs = row_ok ? rstd[row] : 0.0f;
     float s1 = 0.0f, s2 = 0.0f;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int j = threadIdx.x + i * LNB_THREADS;
-      if (j < nvec) {
-        float xv[8], dv[8], g[8];
-        load8(x + row * h + (int64_t)j * 8, xv);
-        load8(dout + row * h + (int64_t)j * 8, dv);
-        load8(gamma + (int64_t)j * 8, g);
+    float xh1[8], dh1[8], res[8];
+    if constexpr (HOLD) {
+      if (col_ok && row_ok) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float xh = (xv[e] - mu) * rs, dh = dv[e] * g[e];
-          s1 += dh;
-          s2 += dh * xh;
-          dg[i][e] += dv[e] * xh;
-          db[i][e] += dv[e];
+          const float dv = hd[e];
+          xh1[e] = (hx[e] - mu) * rs;
+          dh1[e] = dv * gam[e];
+          res[e] = dres ? hr[e] : 0.0f;
+          s1 += dh1[e];
+          s2 += dh1[e] * xh1[e];
+          dg[0][e] += dv * xh1[e];
+          db[0][e] += dv;
+        }
+      }
+      fetch(row + R);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int j = gt + i * GT;
+        if (j < nvec && row_ok) {
+          float xv[8], dv[8], g[8];
+          load8(x + row * h + (int64_t)j * 8, xv);
+          load8(dout + row * h + (int64_t)j * 8, dv);
+          load8(gamma + (int64_t)j * 8, g);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float xh = (xv[e] - mu) * rs, dh = dv[e] * g[e];
+            s1 += dh;
+            s2 += dh * xh;
+            dg[i][e] += dv[e] * xh;
+            db[i][e] += dv[e];
+          }
         }
       }
     }
-    // both row sums through one pair of barriers
+    // both row sums of every group through one pair of barriers
     s1 = wave_sum(s1);
     s2 = wave_sum(s2);
     __syncthreads();
@@ -173,139 +230,162 @@ __global__ __launch_bounds__(LNB_THREADS) void ln_bwd_fused_kernel(
     __syncthreads();
     float m1 = 0.0f, m2 = 0.0f;
 #pragma unroll
-    for (int w = 0; w < LNB_THREADS / 64; ++w) {
-      m1 += red[0][w];
-      m2 += red[1][w];
+    for (int w = 0; w < GW; ++w) {
+      m1 += red[0][grp * GW + w];
+      m2 += red[1][grp * GW + w];
     }
     m1 /= (float)h;
     m2 /= (float)h;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int j = threadIdx.x + i * LNB_THREADS;
-      if (j < nvec) {
-        float xv[8], dv[8], g[8], o[8];
-        load8(x + row * h + (int64_t)j * 8, xv);
-        load8(dout + row * h + (int64_t)j * 8, dv);
-        load8(gamma + (int64_t)j * 8, g);
-        if (dres) load8(dres + row * h + (int64_t)j * 8, o);
+    if constexpr (HOLD) {
+      if (col_ok && row_ok) {
+        float o[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float xh = (xv[e] - mu) * rs, dh = dv[e] * g[e];
-          o[e] = (dres ? o[e] : 0.0f) + rs * (dh - m1 - xh * m2);
-          if constexpr (CS) cs[i][e] += to_f32(from_f32<E>(o[e]));  // the stored value
+          o[e] = res[e] + rs * (dh1[e] - m1 - xh1[e] * m2);
+          if constexpr (CS) cs[0][e] += to_f32(from_f32<E>(o[e]));  // the stored value
         }
-        store8(dx + row * h + (int64_t)j * 8, o);
+        store8(dx + row * h + (int64_t)gt * 8, o);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int j = gt + i * GT;
+        if (j < nvec && row_ok) {
+          float xv[8], dv[8], g[8], o[8];
+          load8(x + row * h + (int64_t)j * 8, xv);
+          load8(dout + row * h + (int64_t)j * 8, dv);
+          load8(gamma + (int64_t)j * 8, g);
+          if (dres) load8(dres + row * h + (int64_t)j * 8, o);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float xh = (xv[e] - mu) * rs, dh = dv[e] * g[e];
+            o[e] = (dres ? o[e] : 0.0f) + rs * (dh - m1 - xh * m2);
+            if constexpr (CS) cs[i][e] += to_f32(from_f32<E>(o[e]));  // the stored value
+          }
+          store8(dx + row * h + (int64_t)j * 8, o);
+        }
       }
     }
   }
   const int64_t stride = (int64_t)gridDim.x * h;
+  if constexpr (R > 1) {
+    // group 0 adds the other groups' sums in order, one output after the other
+    auto add_groups = [&](float (&v)[8], int out) {
+      __syncthreads();
+      if (grp > 0) store8(&part[grp - 1][gt * 8], v);
+      __syncthreads();
+      if (grp == 0 && col_ok) {
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int j = threadIdx.x + i * LNB_THREADS;
-    if (j < nvec) {
-      float *o = ws + (int64_t)blockIdx.x * h + (int64_t)j * 8;
-      store8(o, dg[i]);
-      store8(o + stride, db[i]);
-      if constexpr (CS) store8(o + 2 * stride, cs[i]);
+        for (int k = 1; k < R; ++k) {
+          float t[8];
+          load8(&part[k - 1][gt * 8], t);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] += t[e];
+        }
+        store8(ws + out * stride + (int64_t)blockIdx.x * h + (int64_t)gt * 8, v);
+      }
+    };
+    add_groups(dg[0], 0);
+    add_groups(db[0], 1);
+    if constexpr (CS) add_groups(cs[0], 2);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int j = gt + i * GT;
+      if (j < nvec) {
+        float *o = ws + (int64_t)blockIdx.x * h + (int64_t)j * 8;
+        store8(o, dg[i]);
+        store8(o + stride, db[i]);
+        if constexpr (NOUT == 3) store8(o + 2 * stride, cs[i]);
+      }
     }
   }
 }
 
 // ---------------------------------------------------------------- column reductions
-// Stage 1: workgroup (bx, by) owns 512 columns [bx*512, +512) and the rows
-// t = by*4 + wave, stepping by 4*gridDim.y.  Lane l owns columns 8l..8l+7 of
-// the strip.  MODE 0: sum of in.  MODE 1 (LayerNorm): out0 = sum dout*xhat,
-// out1 = sum dout, and, if dx != NULL, out2 = sum dx.
-// Partials land in ws as [nout][gridDim.y][C] floats; stage 2 adds them up in a
-// fixed order, so results do not depend on scheduling.
-constexpr int CR_COLS = 512;
+// Stage 1: workgroup (bx, by) of 16 waves owns 512 columns [bx*512, +512) and the rows t = by*16 + wave, stepping by
+// 16*gridDim.y.  Lane l owns columns 8l..8l+7 of the strip; four rows are in flight per wave.  Partials land in ws as
+// [gridDim.y][C] floats; stage 2 adds them up in a fixed order, so results do not depend on scheduling.  Bound by HBM; with
+// four waves and one row in flight the few workgroups of a narrow matrix could not ask for enough bytes (8192 x 2048:
+// 35 -> 10 us).
+constexpr int CR_COLS = 512, CR_WAVES = 16;
 
-template <typename E, int MODE>
-__global__ __launch_bounds__(256) void colreduce_stage1(int64_t T, int64_t C,
-                                                        const E *__restrict__ in,
-                                                        const E *__restrict__ x,
-                                                        const float *__restrict__ mean,
-                                                        const float *__restrict__ rstd,
-                                                        const E *__restrict__ dx,
-                                                        float *__restrict__ ws) {
-  constexpr int NOUT = MODE == 0 ? 1 : 3;
-  __shared__ float red[4][NOUT][CR_COLS];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t c0 = (int64_t)blockIdx.x * CR_COLS + lane * 8;
-  float acc[NOUT][8] = {};
+template <typename E>
+__global__ __launch_bounds__(64 * CR_WAVES) void colreduce_stage1(int64_t T, int64_t C, const E *__restrict__ in,
+                                                                  float *__restrict__ ws) {
+  __shared__ float red[CR_WAVES][CR_COLS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t c0 = (int64_t)blockIdx.x * CR_COLS + lane * 8, step = (int64_t)CR_WAVES * gridDim.y;
+  float acc[8] = {};
   if (c0 < C) {
-    for (int64_t t = (int64_t)blockIdx.y * 4 + wave; t < T; t += 4 * (int64_t)gridDim.y) {
-      float a[8];
-      load8(in + t * C + c0, a);
-      if constexpr (MODE == 0) {
+    int64_t t = (int64_t)blockIdx.y * CR_WAVES + wave;
+    for (; t + 3 * step < T; t += 4 * step) {
+      Raw8<E> a[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[0][e] += a[e];
-      } else {
-        float xv[8];
-        load8(x + t * C + c0, xv);
-        const float mu = mean[t], rs = rstd[t];
+      for (int i = 0; i < 4; ++i) a[i].load(in + (t + i * step) * C + c0);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          acc[0][e] += a[e] * ((xv[e] - mu) * rs);
-          acc[1][e] += a[e];
-        }
-        if (dx) {
-          load8(dx + t * C + c0, xv);
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) acc[2][e] += xv[e];
-        }
-      }
+        for (int e = 0; e < 8; ++e) acc[e] += a[i][e];
+    }
+    for (; t < T; t += step) {
+      Raw8<E> a;
+      a.load(in + t * C + c0);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += a[e];
     }
   }
-#pragma unroll
-  for (int o = 0; o < NOUT; ++o)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) red[wave][o][lane * 8 + e] = acc[o][e];
+  store8(&red[wave][lane * 8], acc);
   __syncthreads();
-  for (int i = threadIdx.x; i < NOUT * CR_COLS; i += 256) {
-    int o = i / CR_COLS, c = i % CR_COLS;
-    int64_t col = (int64_t)blockIdx.x * CR_COLS + c;
-    if (col < C) {
-      float s = red[0][o][c] + red[1][o][c] + red[2][o][c] + red[3][o][c];
-      ws[((int64_t)o * gridDim.y + blockIdx.y) * C + col] = s;
-    }
+  const int64_t col = (int64_t)blockIdx.x * CR_COLS + threadIdx.x;
+  if (threadIdx.x < CR_COLS && col < C) {
+    float s = red[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < CR_WAVES; ++w) s += red[w][threadIdx.x];
+    ws[(int64_t)blockIdx.y * C + col] = s;
   }
 }
 
 // Stage 2: out_o[c] (+)= sum_r ws[o][r][c] for up to three outputs o = blockIdx.y.
-// A workgroup owns 64 columns; wave w adds rows w, w+4, ... in order, the four wave
-// sums are then added in order: a fixed summation tree, independent of scheduling.
+// A workgroup owns 64 columns; wave w adds rows w, w+16, ... in order, four in flight, the sixteen wave sums are then added in
+// order: a fixed summation tree, independent of scheduling.  (Four waves and two rows in flight: 11 us for 256 rows of 2048
+// columns, all of it latency; 5 us now.)
 struct Stage2Outs {
   void *out[3];
 };
 template <typename O>
-__global__ __launch_bounds__(256) void colreduce_stage2(int64_t C, int nrb, const float *__restrict__ ws,
-                                                        Stage2Outs outs, int accumulate) {
-  __shared__ float part[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__global__ __launch_bounds__(1024) void colreduce_stage2(int64_t C, int nrb, const float *__restrict__ ws,
+                                                         Stage2Outs outs, int accumulate) {
+  __shared__ float part[16][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t c = (int64_t)blockIdx.x * 64 + lane;
   const float *src = ws + (int64_t)blockIdx.y * nrb * C;
-  float s0 = 0.0f, s1 = 0.0f;
+  float s = 0.0f;
   if (c < C) {
     int r = wave;
-    for (; r + 4 < nrb; r += 8) {
-      s0 += src[(int64_t)r * C + c];
-      s1 += src[(int64_t)(r + 4) * C + c];
+    for (; r + 48 < nrb; r += 64) {
+      float v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = src[(int64_t)(r + 16 * i) * C + c];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s += v[i];
     }
-    if (r < nrb) s0 += src[(int64_t)r * C + c];
+    for (; r < nrb; r += 16) s += src[(int64_t)r * C + c];
   }
-  part[wave][lane] = s0 + s1;
+  part[wave][lane] = s;
   __syncthreads();
   if (wave == 0 && c < C) {
-    float s = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
+    float t = part[0][lane];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) t += part[w][lane];
     O *out = static_cast<O *>(outs.out[blockIdx.y]);
-    if (accumulate) s += to_f32(out[c]);
-    out[c] = from_f32<O>(s);
+    if (accumulate) t += to_f32(out[c]);
+    out[c] = from_f32<O>(t);
   }
 }
 
 static int colreduce_rowblocks(int64_t T) {
-  int64_t rb = (T + 63) / 64;  // at least 16 rows per wave
+  int64_t rb = (T + 63) / 64;  // at least 4 rows per wave
   if (rb < 1) rb = 1;
   if (rb > 32) rb = 32;
   return (int)rb;
@@ -318,9 +398,9 @@ static void stage2_launch(int64_t C, int nrb, const float *ws, int nout, void *o
   dim3 grid((unsigned)((C + 63) / 64), (unsigned)nout);
   Stage2Outs outs{{o0, o1, o2}};
   if (out_f32)
-    colreduce_stage2<float><<<grid, 256, 0, st>>>(C, nrb, ws, outs, accumulate);
+    colreduce_stage2<float><<<grid, 1024, 0, st>>>(C, nrb, ws, outs, accumulate);
   else
-    colreduce_stage2<E><<<grid, 256, 0, st>>>(C, nrb, ws, outs, accumulate);
+    colreduce_stage2<E><<<grid, 1024, 0, st>>>(C, nrb, ws, outs, accumulate);
 }
 
 static int ln_bwd_workgroups(int64_t T) { return (int)(T < LNB_MAX_WGS ? T : LNB_MAX_WGS); }
@@ -331,27 +411,32 @@ static int ln_bwd_launch(int64_t T, int64_t h, const void *x, const void *gamma,
                          void *dgamma, void *dbeta, void *colsum_dx, int grad_f32, int accumulate,
                          void *workspace, hipStream_t st) {
   const int nvec = (int)(h / 8);
-  const int rows_per = (int)((T + LNB_MAX_WGS - 1) / LNB_MAX_WGS);
+  // waves to a row, and at least as many rows to a workgroup as it takes at a time: fewer partial sums to add
+  const int gw = nvec <= 64 ? 1 : nvec <= 128 ? 2 : nvec <= 256 ? 4 : nvec <= 512 ? 8 : 16;
+  int rows_per = (int)((T + LNB_MAX_WGS - 1) / LNB_MAX_WGS);
+  if (rows_per < 16 / gw) rows_per = 16 / gw;
   const int nwg = (int)((T + rows_per - 1) / rows_per);  // <= ln_bwd_workgroups(T)
   float *ws = (float *)workspace;
-#define LNB(NV, CS)                                                                                  \
-  ln_bwd_fused_kernel<E, NV, CS><<<dim3((unsigned)nwg), LNB_THREADS, 0, st>>>(                       \
+#define LNB(NV, GW, CS)                                                                              \
+  ln_bwd_fused_kernel<E, NV, GW, CS><<<dim3((unsigned)nwg), LNB_THREADS, 0, st>>>(                   \
       T, h, rows_per, (const E *)x, (const E *)gamma, mean, rstd, (const E *)dout, (const E *)dres, \
       (E *)dx, ws)
+#define LNB_BY_WIDTH(CS)                         \
+  do {                                           \
+    if (gw == 1) LNB(1, 1, CS);                  \
+    else if (gw == 2) LNB(1, 2, CS);             \
+    else if (gw == 4) LNB(1, 4, CS);             \
+    else if (gw == 8) LNB(1, 8, CS);             \
+    else if (nvec <= 1024) LNB(1, 16, CS);       \
+    else if (nvec <= 2048) LNB(2, 16, CS);       \
+    else if (nvec <= 3072) LNB(3, 16, CS);       \
+    else if (nvec <= 4096) LNB(4, 16, CS);       \
+    else return MTNLG_UNSUPPORTED_SHAPE;         \
+  } while (0)
   LaunchScope scope(MTNLG_K_LN_BWD, st);
-  if (colsum_dx) {
-    if (nvec <= 1024) LNB(1, true);
-    else if (nvec <= 2048) LNB(2, true);
-    else if (nvec <= 3072) LNB(3, true);
-    else if (nvec <= 4096) LNB(4, true);
-    else return MTNLG_UNSUPPORTED_SHAPE;
-  } else {
-    if (nvec <= 1024) LNB(1, false);
-    else if (nvec <= 2048) LNB(2, false);
-    else if (nvec <= 3072) LNB(3, false);
-    else if (nvec <= 4096) LNB(4, false);
-    else return MTNLG_UNSUPPORTED_SHAPE;
-  }
+  if (colsum_dx) LNB_BY_WIDTH(true);
+  else LNB_BY_WIDTH(false);
+#undef LNB_BY_WIDTH
 #undef LNB
   MTNLG_TRY(check_launch());
   stage2_launch<E>(h, nwg, ws, colsum_dx ? 3 : 2, dgamma, dbeta, colsum_dx, grad_f32, accumulate, st);
@@ -364,8 +449,7 @@ static int colsum_launch(int64_t T, int64_t C, const void *in, void *out, int ou
   const int nrb = colreduce_rowblocks(T);
   dim3 grid((unsigned)((C + CR_COLS - 1) / CR_COLS), (unsigned)nrb);
   LaunchScope scope(MTNLG_K_COLSUM, st);
-  colreduce_stage1<E, 0><<<grid, 256, 0, st>>>(T, C, (const E *)in, nullptr, nullptr, nullptr, nullptr,
-                                               (float *)workspace);
+  colreduce_stage1<E><<<grid, 64 * CR_WAVES, 0, st>>>(T, C, (const E *)in, (float *)workspace);
   MTNLG_TRY(check_launch());
   stage2_launch<E>(C, nrb, (const float *)workspace, 1, out, nullptr, nullptr, out_f32, accumulate, st);
   return check_launch();

@@ -138,3 +138,38 @@ def test_bf16_gemm_writes_nothing_outside_a_ragged_result(layout):
                                      (1, 33, 2, 192), (1, 90, 2, 200), (2, 70, 2, 232), (1, 64, 1, 256), (3, 1, 2, 40)])
 def test_attention_at_every_compiled_head_size(dtype, b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
+
+
+# LayerNorm backward: the widths between which the number of waves to a row changes (512, 1024, 2048, 4096 columns) and the
+# row count per thread (8192, 16384, 24576); fewer rows than a workgroup takes at a time, and several turns of the row loop.
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("T,h", [(1, 8), (3, 512), (700, 512), (259, 520), (40, 1024), (9, 1032), (1030, 2048), (5, 2056), (600, 4096),
+                                 (3, 4104), (300, 8192), (2, 8200), (2, 16392), (2, 24584)])
+def test_layernorm_backward_widths_and_rows(dtype, T, h):
+    x, dout, dres = randn((T, h), dtype, 1), randn((T, h), dtype, 2), randn((T, h), dtype, 3)
+    gamma = randn((h,), dtype, 4)
+    _, mean, rstd = oracle.layernorm_fwd(to_np(x), to_np(gamma), np.zeros(h), 1e-5)
+    mean_d, rstd_d = (torch.tensor(v, dtype=torch.float32, device="cuda") for v in (mean, rstd))
+    ws = torch.empty(M.mtnlg_layernorm_bwd_workspace(T, h), dtype=torch.uint8, device="cuda")
+    o_dx, o_dg, o_db = oracle.layernorm_bwd(to_np(x), to_np(gamma), mean, rstd, to_np(dout))
+    for res in (None, dres):
+        dx = torch.full((T, h), float("nan"), dtype=DT[dtype], device="cuda")
+        dg, db, cs = (torch.full((h,), float("nan"), device="cuda") for _ in range(3))
+        M.mtnlg_layernorm_bwd(dev(x), dev(gamma), mean_d, rstd_d, dev(dout), dx, dg, db, ws, grad_f32=True,
+                              dres=None if res is None else dev(res), colsum_dx=None if res is None else cs)
+        want = o_dx if res is None else o_dx + to_np(res)
+        assert_close(dx, want, TOL[dtype], f"dx {T} {h}")
+        assert_close(dg, o_dg, TOL[dtype], f"dgamma {T} {h}")
+        assert_close(db, o_db, TOL[dtype], f"dbeta {T} {h}")
+        if res is not None:
+            assert_close(cs, to_np(dx).sum(0), TOL["fp32"], f"column sum of the stored dx {T} {h}")
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("T,C", [(1, 8), (15, 520), (64, 512), (65, 1032), (700, 64), (2049, 520), (5000, 8)])
+def test_column_sums_row_remainders(dtype, T, C):
+    x = randn((T, C), dtype, 5)
+    ws = torch.empty(M.mtnlg_colsum_workspace(T, C), dtype=torch.uint8, device="cuda")
+    out = torch.full((C,), float("nan"), device="cuda")
+    M.mtnlg_colsum(dev(x), out, ws)
+    assert_close(out, to_np(x).sum(0), TOL["fp32"], f"colsum {T} {C}")
