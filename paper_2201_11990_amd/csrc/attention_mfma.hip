@@ -5,11 +5,13 @@
 //   backward with D_t = da_t . a_t :  dP = da v^T,  dS = P o (dP - D),
 //   dq = scale dS k,  dk = scale dS^T q,  dv = P^T da.
 //
-// Three kernels, one geometry.  A workgroup owns 128 (or, forward only, 256) rows of one side (queries for
-// forward and dq, keys for dk/dv), 16 or 32 per wave on eight waves, held in registers as MFMA
-// B operands (groups of 16, one row per lane column); the other side streams through
+// Three kernels of eight waves.  A workgroup owns rows of one side (forward: 128 or 256 queries, 16 or 32 per wave;
+// dq and dk/dv: 64 queries or keys, 16 per wave, each half of the workgroup on one half of every tile), held in
+// registers as MFMA B operands (groups of 16, one row per lane column); the other side streams through
 // LDS in tiles of 64 rows, brought in by LDS DMA (buffer_load ... lds, no staging
-// registers) three tiles deep, one workgroup barrier per tile.
+// registers) three tiles deep, one workgroup barrier per tile.  What bounds them: no single unit.  Between two barriers a
+// wave runs LDS reads, MFMAs, the softmax and the DMA issue in one chain, and the waves of a workgroup run it in step, so
+// the times of the four add up; taking any one out shortened a tile by no more than that one's own time.
 //
 // All products are v_mfma_f32_16x16x32_bf16 with the streamed tile as the A operand, so a
 // product block comes out as C[tile row 4 (lane/16) + i][own row lane%16], i = 0..3:
@@ -63,48 +65,65 @@ struct Tile {
   }
   static __device__ __forceinline__ int off(int row, int u) { return (row * UPR + (u ^ mask(row))) * 16; }
 
-  // Wave `wave` brings rows 16 wave .. 16 wave + 15 of the tile whose first row is row0 of the
-  // matrix behind rs (row pitch ld_bytes) to LDS byte address `stage` with NI DMA instructions;
-  // rows past the end repeat the last row.  Instruction i fills 1024 consecutive LDS bytes, lane l
-  // the 16 bytes at 16 l.
-  template <int TAG>
-  static __device__ __forceinline__ void dma_one(dma_rsrc_t rs, int row0, int rows_total, uint32_t ld_bytes,
-                                                 uint32_t stage, int wave, int lane, int i) {
-    const int p = i * 64 + lane;
-    const int r = 16 * wave + p / UPR, u = (p % UPR) ^ mask(16 * wave + p / UPR);
-    int gr = row0 + r;
-    gr = gr < rows_total ? gr : rows_total - 1;
-    dma16<TAG>(rs, stage + (wave * NI + i) * 1024, gr * ld_bytes + u * 16);
+  // Byte offset, from the tile's first row in memory (row pitch ld_bytes), of what lane `lane` moves in DMA instruction i of
+  // the wave that brings rows 16 quarter .. + 15: instruction i fills 1024 consecutive LDS bytes, lane l the 16 at 16 l.
+  static __device__ __forceinline__ uint32_t dma_offset(uint32_t ld_bytes, int quarter, int lane, int i) {
+    const int p = i * 64 + lane, r = 16 * quarter + p / UPR, u = (p % UPR) ^ mask(r);
+    return r * ld_bytes + u * 16;
   }
   // Byte offsets of a lane's fragment reads inside a tile.  mask() looks at the low four bits of a
-  // row only, so a block of 16 rows further down is a constant distance away.
+  // row only, so a block of 16 rows further down is a constant distance away; and the offsets of the k-steps and
+  // column blocks differ by an XOR of bits that the row part leaves empty (head size 160, whose mask touches the low two
+  // bits of a unit only: by a constant, and one bit for odd column blocks).  One register each instead of one per step.
   struct Lane {
-    int nat[D / 32];   // row lane%16, 16-byte unit 4 kk + lane/16
-    int tr[D / 16];    // as address supplier of a transposing read: row 4 (lane/16) + L/4, columns 16 cblk + 4 (L%4) .. + 3, L = lane%16
+    uint32_t n0;   // row lane%16, 16-byte unit lane/16
+    uint32_t t0;   // as address supplier of a transposing read: row 4 (lane/16) + L/4, columns 4 (L%4) .. + 3, L = lane%16
     __device__ __forceinline__ explicit Lane(int lane) {
-      const int g = lane >> 4, L = lane & 15;
-#pragma unroll
-      for (int kk = 0; kk < D / 32; ++kk) nat[kk] = off(L, 4 * kk + g);
-#pragma unroll
-      for (int cb = 0; cb < D / 16; ++cb) {
-        const int col = cb * 16 + 4 * (L & 3);
-        tr[cb] = off(4 * g + (L >> 2), col >> 3) + (col & 7) * 2;
-      }
+      const int g = lane >> 4, L = lane & 15, col = 4 * (L & 3);
+      n0 = (uint32_t)off(L, g);
+      t0 = (uint32_t)(off(4 * g + (L >> 2), col >> 3) + (col & 7) * 2);
+    }
+    // once per tile: keeps the compiler from holding every offset in a register of its own across tiles
+    __device__ __forceinline__ void here() { asm volatile("" : "+v"(n0), "+v"(t0)); }
+    __device__ __forceinline__ uint32_t nat(int kk) const { return D == 160 ? n0 + kk * 64 : n0 ^ (kk * 64); }
+    __device__ __forceinline__ uint32_t tr(int cblk) const {
+      return D == 160 ? (t0 ^ ((cblk & 1) * 32)) + (cblk >> 1) * 64 : t0 ^ (cblk * 32);
     }
   };
   static constexpr int ROWS16 = 16 * UPR * 16;   // bytes of 16 tile rows
   // A operand contracting over columns: lane l holds row 16 blk + l%16, columns 32 kk + 8 (l/16) .. + 7
   static __device__ __forceinline__ bf16x8 nat(const char *t, const Lane &ln, int blk, int kk) {
-    return *reinterpret_cast<const bf16x8 *>(t + ln.nat[kk] + blk * ROWS16);
+    return *reinterpret_cast<const bf16x8 *>(t + ln.nat(kk) + blk * ROWS16);
   }
   // A operand contracting over tile rows 32 ks .. 32 ks + 31: lane l holds column 16 cblk + l%16 and,
   // with g = l/16, tile rows 32 ks + 4 g .. + 3 (elements 0-3) and 32 ks + 16 + 4 g .. + 3 (4-7).
   static __device__ __forceinline__ bf16x8 tr(const char *t, const Lane &ln, int cblk, int ks) {
-    const char *p = t + ln.tr[cblk] + 2 * ks * ROWS16;
+    const char *p = t + ln.tr(cblk) + 2 * ks * ROWS16;
     const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_ptr)p);
     const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_ptr)(p + ROWS16));
     const i16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
+  }
+};
+
+// The stream of a matrix's 64-row tiles into LDS: the descriptor of the next tile to fetch.  Its base moves by a tile and
+// its size shrinks by one in scalar registers; a lane's offsets never change, and rows past the end of the matrix lie
+// outside the descriptor and arrive as zeros.  (Offsets computed per instruction took a multiplication and five more
+// vector instructions each, on kernels bound by vector issue.)
+struct TileStream {
+  uint64_t base;
+  int left;   // bytes from base to the end of the matrix
+  int tile_bytes;
+  __device__ __forceinline__ TileStream(const void *first, int64_t bytes, int64_t tile) {
+    const uint64_t a = (uint64_t)first;
+    base = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a);
+    left = __builtin_amdgcn_readfirstlane(bytes > 0 ? (int)bytes : 0);
+    tile_bytes = __builtin_amdgcn_readfirstlane(tile < 0x7FFFFFFF ? (int)tile : 0x7FFFFFFF);   // a tile beyond that is the only one
+  }
+  __device__ __forceinline__ dma_rsrc_t rsrc() const { return dma_rsrc((const void *)base, (uint32_t)left); }
+  __device__ __forceinline__ void advance() {
+    base += (uint32_t)tile_bytes;
+    left = left > tile_bytes ? left - tile_bytes : 0;
   }
 };
 
@@ -167,77 +186,104 @@ template <typename V>
 __device__ __forceinline__ void arrive(V &v) {
   asm volatile("" : "+v"(v));
 }
-// An accumulator block that only MFMAs touch inside the main loop stays in the accumulation
-// registers: without this hint at the top of the loop body the compiler moves every block to the
-// ordinary registers and back once per tile.
-__device__ __forceinline__ void keep_acc(f32x4 &v) {
-  asm volatile("" : "+a"(v));
-}
-
 // sum / maximum over the four lanes that share lane % 16
 __device__ __forceinline__ float quad_sum(float v) {
   v += __shfl_xor(v, 16, 64);
   return v + __shfl_xor(v, 32, 64);
 }
+// v_permlane{16,32}_swap of a value with itself leaves the two halves of every pair side by side; unlike a shuffle
+// through LDS it costs a vector instruction's latency, which the forward kernel pays twice in every tile's chain.
 __device__ __forceinline__ float quad_max(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16, 64));
-  return fmaxf(v, __shfl_xor(v, 32, 64));
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  const unsigned a = __builtin_bit_cast(unsigned, v);
+  const u32x2 p = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(a, a, false, false));
+  v = fmaxf(__builtin_bit_cast(float, p[0]), __builtin_bit_cast(float, p[1]));
+  const unsigned b = __builtin_bit_cast(unsigned, v);
+  const u32x2 q = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(b, b, false, false));
+  return fmaxf(__builtin_bit_cast(float, q[0]), __builtin_bit_cast(float, q[1]));
 }
 
-// Which rows (queries in the forward and dq kernels, keys in the dk/dv kernel) a wave owns.
-// Under the causal mask a 64-row block b works on b + 1 of the 64-row tiles the workgroup streams
-// (or, for keys, on all tiles from b on), so blocks taken in order would leave the workgroups of a
-// head with 1 .. s/64 tiles of work.  With eight waves the two halves of a workgroup therefore take
-// blocks p and nb - 1 - p (nb blocks in the sequence): every workgroup then computes nb + 1 wave-halves
+// Number of a wave's IPW DMA instructions that go out by step `step` of the STEPS MFMA steps of a tile (both runs counted):
+// spread evenly, because the texture path takes 16 cycles for each and a wave that meets a full queue waits.
+template <int IPW, int STEPS>
+constexpr int dma_by(int step) { return ((step + 1) * IPW + STEPS - 1) / STEPS; }
+
+// Which rows a wave of the forward kernel owns.
+// Under the causal mask a 64-row block b works on b + 1 of the 64-row tiles the workgroup streams, so blocks taken in order
+// would leave the workgroups of a head with 1 .. s/64 tiles of work.  The two halves of a workgroup therefore take
+// blocks p and nb - 1 - p (nb blocks of 64 G rows in the sequence): every workgroup then computes nb + 1 wave-halves
 // of tiles, and while only one half has work in a tile it has the compute unit to itself.  With an
 // odd nb the middle block is alone in its workgroup and the other half only helps to move tiles.
-// Four waves of 32 rows (G = 2) keep consecutive 128-row blocks.
-template <int G, int W = 8 / G>
-struct RowBlocks {
+template <int G>
+struct PairedBlocks {
   int row0;        // first row of this wave
-  int first_tile;  // lowest and highest 64-row block of the workgroup: the tile range that the
-  int last_tile;   //   forward / dq kernels (0 .. last) and the dk/dv kernel (first .. end) stream
+  int last_tile;   // highest 64-row block of the workgroup: it streams tiles 0 .. last
   bool idle;       // wave-uniform: this wave owns no rows
-  __device__ RowBlocks(int s, int pair, int wave) {
-    const int nb = (s + 63) / 64;
-    if (W == 4) {
-      row0 = pair * 128 + wave * 32;
-      first_tile = 2 * pair;
-      last_tile = 2 * pair + 1 < nb ? 2 * pair + 1 : nb - 1;
-      idle = false;
-    } else {
-      // eight waves: the two halves own blocks lo and hi of 64 G rows from opposite ends of the sequence
-      constexpr int TPB = G;   // 64-row tiles per block
-      const int nblk = (nb + TPB - 1) / TPB;
-      const int lo = pair, hi = nblk - 1 - pair, half = wave >> 2;
-      row0 = (half ? hi : lo) * (64 * G) + (wave & 3) * (16 * G);
-      first_tile = lo * TPB;
-      last_tile = hi * TPB + TPB - 1 < nb ? hi * TPB + TPB - 1 : nb - 1;
-      idle = half && hi == lo;
-    }
+  __device__ PairedBlocks(int s, int pair, int wave) {
+    const int nb = (s + 63) / 64, nblk = (nb + G - 1) / G;
+    const int lo = pair, hi = nblk - 1 - pair, half = wave >> 2;
+    row0 = (half ? hi : lo) * (64 * G) + (wave & 3) * (16 * G);
+    last_tile = hi * G + G - 1 < nb ? hi * G + G - 1 : nb - 1;
+    idle = half && hi == lo;
   }
-  // workgroups along x for a sequence of s rows
-  static int grid(int s) {
-    const int nb = (s + 63) / 64;
-    return W == 4 ? (s + 127) / 128 : ((nb + G - 1) / G + 1) / 2;
+  static int count(int s) { return (((s + 63) / 64 + G - 1) / G + 1) / 2; }
+};
+
+// The backward kernels: a workgroup owns one 64-row block (queries for dq, keys for dk / dv), 16 rows to each of waves 0-3
+// and again to waves 4-7: the two halves of the workgroup take the first and the last 32 rows of every streamed
+// tile, and their partial results are merged through LDS at the end.  Half the tile per wave halves the registers
+// of its scores and its chain per tile, and no wave idles while the mask leaves work to the other half only.  Blocks are
+// handed out in the order of falling work, so a compute unit that got a long block gets a short one after it.  Measured with
+// paired blocks and whole tiles before, dq + dk/dv at 4 x 2048 tokens x 16 heads: head size 64 279 us, 128 477, 160 475;
+// now 163, 430, 430.  (In the forward kernel, which has fewer registers to save, the merge costs more than it gives.)
+__host__ __device__ inline int row_blocks(int s) { return (s + 63) / 64; }
+
+// Which head a workgroup works on, and at which place of the head's order of blocks: heads run fastest, so where heads x
+// sequences is a multiple of 8 all workgroups of a head run on one XCD (they are dealt out in turn) and its L2 serves
+// every tile after the first reading.  Measured with the blocks running fastest before, forward at 4 x 2048 x 16 heads:
+// head size 64 61-64 us, 128 113-116, 160 122; now 55, 102, 105.  (Neighbouring heads on one XCD, instead of every
+// eighth: backward 2 % slower.)
+struct HeadBlock {
+  int head, batch, order;
+  __device__ HeadBlock(int n, int heads) {   // heads: n x the sequences of a grid row
+    const int hb = blockIdx.x % heads;
+    head = hb % n;
+    batch = blockIdx.y * (heads / n) + hb / n;
+    order = blockIdx.x / heads;
+  }
+  // Sequences that share a grid row: up to 2^16 workgroups are 256 for each compute unit, enough for the order to even
+  // out (2^9 or 2^10: backward up to 10 % slower), and the grid stays within its limits for every batch.
+  static int sequences(int b, int n, int count) {
+    const int fit = (1 << 16) / (n * count);
+    return fit < 1 ? 1 : fit < b ? fit : b;
   }
 };
 
+// Partial accumulators of waves 4-7 to waves 0-3 through LDS: 16-byte slots per lane, conflict-free.
+__device__ __forceinline__ f32x4 *merge_slots(char *smem, int wave, int lane, int blocks) {
+  return reinterpret_cast<f32x4 *>(smem) + (wave & 3) * (blocks * 64) + lane;
+}
+
 // ------------------------------------------------------------------ forward
-template <int D, int G, int W = 8 / G>
-__global__ __launch_bounds__(64 * W) void attn_fwd_kernel(int s, int n, float scale, const bf16 *__restrict__ qkv,
+template <int D, int G>
+__global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int heads, float scale, const bf16 *__restrict__ qkv,
                                                       bf16 *__restrict__ a, float *__restrict__ lse) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES;
-  const int j = blockIdx.y, bi = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, lr = lane & 15;
+  const HeadBlock hb(n, heads);
+  const int j = hb.head, bi = hb.batch;
+  if (bi >= b) return;   // past the last sequence of the last grid row
+  const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
   const int64_t ld = (int64_t)n * 3 * D;
   const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * D;
-  const RowBlocks<G, W> rb(s, blockIdx.x, wave);
+  // From the thread number and not the scalar: with a scalar condition for masked tiles the compiler lays the tile's code
+  // out per path and holds 60 registers more (head size 160, 32 rows per wave: 256 and 27 spilled, 163 us; now 208, 105).
+  const PairedBlocks<G> rb(s, hb.order, threadIdx.x >> 6);
   const int qw = rb.row0;
   const float c = scale * kLog2e;
-  const typename T::Lane ln(lane);
+  typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
   int qc[G];
@@ -265,28 +311,32 @@ __global__ __launch_bounds__(64 * W) void attn_fwd_kernel(int s, int n, float sc
   }
 
   const int ntiles = rb.last_tile + 1;
-  // Who brings what: with four waves wave w brings rows 16 w .. 16 w + 15 of the K tile and of
-  // the V tile; with eight, waves 0-3 bring the K tile, waves 4-7 the V tile.
-  constexpr int IPW = (W == 4 ? 2 : 1) * T::NI;   // DMA instructions per wave and tile
-  const int quarter = W == 4 ? wave : (wave & 3), half = W == 4 ? 0 : (wave >> 2);
-  const dma_rsrc_t rk = dma_rsrc(base + D + half * D), rv = dma_rsrc(base + 2 * D);
-  // DMA instruction i (of IPW) of tile t (clamped to the last one) into ring stage st.  A tile's
-  // DMAs go out one per step of the first MFMA run of the tile before: a burst of them would hold
-  // the waves at the issue port of the texture path.
-  auto issue_one = [&](auto tag, int t, int st, int i) {
-    constexpr int TAG = decltype(tag)::value;
-    const int tt = t < ntiles ? t : ntiles - 1;
-    if (W == 8 || i < T::NI)
-      T::template dma_one<TAG>(rk, tt * 64, s, (uint32_t)(ld * 2), smem_addr + st * STAGE + half * T::BYTES, quarter, lane, i);
-    else
-      T::template dma_one<TAG>(rv, tt * 64, s, (uint32_t)(ld * 2), smem_addr + st * STAGE + T::BYTES, quarter, lane, i - T::NI);
-  };
-  auto issue = [&](int t, int st) {
+  // Waves 0-3 bring the K tile, waves 4-7 the V tile, 16 rows each.  The DMAs of tile it + 2 are spread over
+  // the MFMA steps of tile it (dma_by).
+  constexpr int IPW = T::NI;   // DMA instructions per wave and tile
+  const int quarter = wave & 3, half = wave >> 2;
+  TileStream kv(base + D + half * D, ((int64_t)s * ld - (j * 3 + 1 + half) * D) * 2, 64 * ld * 2);
+  uint32_t dma_off[IPW];
 #pragma unroll
-    for (int i = 0; i < IPW; ++i) issue_one(Burst{}, t, st, i);
+  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(ld * 2), quarter, lane, i);
+  auto issue_one = [&](auto tag, int st, int i) {   // instruction i of the stream's next tile into ring stage st
+    constexpr int TAG = decltype(tag)::value;
+    dma16<TAG>(kv.rsrc(), smem_addr + st * STAGE + half * T::BYTES + (quarter * IPW + i) * 1024, dma_off[i]);
   };
-  issue(0, 0);
-  issue(1, 1);
+  constexpr int STEPS = 2 * KK + DB;   // MFMA steps of a tile
+  auto issue_step = [&](int step, int st) {
+#pragma unroll
+    for (int i = 0; i < IPW; ++i)
+      if (i >= (step ? dma_by<IPW, STEPS>(step - 1) : 0) && i < dma_by<IPW, STEPS>(step)) issue_one(Spread{}, st, i);
+  };
+  auto issue = [&](int st) {
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) issue_one(Burst{}, st, i);
+  };
+  issue(0);
+  kv.advance();
+  issue(1);
+  kv.advance();
 #pragma unroll
   for (int qg = 0; qg < G; ++qg)
 #pragma unroll
@@ -294,11 +344,12 @@ __global__ __launch_bounds__(64 * W) void attn_fwd_kernel(int s, int n, float sc
   int cur = 0;
   for (int it = 0; it < ntiles; ++it) {
     wait_and_barrier<IPW>();   // tile it landed everywhere, tile it-1 no longer read
+    ln.here();
     const int nn = cur == 0 ? 2 : cur - 1;   // stage of tile it + 2
     const char *Kt = smem + cur * STAGE, *Vt = Kt + T::BYTES;
     const int kv0 = it * 64;
     if (rb.idle || kv0 > qw + (16 * G - 1)) {  // wave-uniform: every (query, key) pair of this wave is masked
-      issue(it + 2, nn);
+      issue(nn);
     } else {
       f32x4 sc[G][4];
 #pragma unroll
@@ -321,9 +372,7 @@ __global__ __launch_bounds__(64 * W) void attn_fwd_kernel(int s, int n, float sc
                 for (int qg = 0; qg < G; ++qg)
                   sc[qg][2 * (i & 1) + h] = MFMA16(kfr[i & 3][h], qf[qg][i >> 1], sc[qg][2 * (i & 1) + h]);
             },
-            [&](int i) {
-              if (i < IPW) issue_one(Spread{}, it + 2, nn, i);
-            });
+            [&](int i) { issue_step(i, nn); });
       }
       // element (qg, kb, e): key kv0 + 16 kb + 4 g + e, query qc[qg]
       if (kv0 + 63 > qw) {  // wave-uniform: this tile crosses the diagonal for some row
@@ -393,9 +442,11 @@ __global__ __launch_bounds__(64 * W) void attn_fwd_kernel(int s, int n, float sc
 #pragma unroll
                 for (int qg = 0; qg < G; ++qg)
                   o[qg][2 * (i % HB) + h] = MFMA16(vfr[i & 3][h], pf[i / HB][qg], o[qg][2 * (i % HB) + h]);
-            });
+            },
+            [&](int i) { issue_step(2 * KK + i, nn); });
       }
     }
+    kv.advance();
     cur = cur == 2 ? 0 : cur + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped look-ahead tiles
@@ -420,438 +471,408 @@ __global__ __launch_bounds__(64 * W) void attn_fwd_kernel(int s, int n, float sc
 }
 
 // ------------------------------------------------------------------ backward: dq (and D)
-template <int D, int G, int W = 8 / G>
-__global__ __launch_bounds__(64 * W) void attn_bwd_dq_kernel(int s, int n, float scale, const bf16 *__restrict__ qkv,
+template <int D>
+__global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, int heads, float scale, const bf16 *__restrict__ qkv,
                                                          const bf16 *__restrict__ a, const float *__restrict__ lse,
                                                          const bf16 *__restrict__ da, bf16 *__restrict__ dqkv,
                                                          float *__restrict__ Dvec) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES;
-  const int j = blockIdx.y, bi = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, lr = lane & 15;
+  const HeadBlock hb(n, heads);
+  const int j = hb.head, bi = hb.batch, block = row_blocks(s) - 1 - hb.order;
+  if (bi >= b) return;   // past the last sequence of the last grid row
+  const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
   const int64_t ld = (int64_t)n * 3 * D, pld = (int64_t)n * D;
   const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * D;
-  const RowBlocks<G, W> rb(s, blockIdx.x, wave);
-  const int qw = rb.row0;
+  const int qw = block * 64 + ((threadIdx.x >> 6) & 3) * 16;   // from the thread number: as in the forward kernel
+  const int k_half = (wave >> 2) * 32;   // first key of this wave's half of a tile
   const float c = scale * kLog2e;
-  const typename T::Lane ln(lane);
+  typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
-  int qc[G];
-  bf16x8 qf[G][KK], dof[G][KK];
-  float dsum[G], lse2[G];
-#pragma unroll
-  for (int qg = 0; qg < G; ++qg) {
-    const int q = qw + 16 * qg + lr;
-    qc[qg] = q < s ? q : s - 1;
-    const bf16 *dar = da + ((int64_t)bi * s + qc[qg]) * pld + (int64_t)j * D;
-    const bf16 *ar = a + ((int64_t)bi * s + qc[qg]) * pld + (int64_t)j * D;
-    float ds = 0.0f;
+  const int q = qw + lr, qc = q < s ? q : s - 1;
+  bf16x8 qf[KK], dof[KK];
+  float dsum = 0.0f;
+  {
+    const bf16 *dar = da + ((int64_t)bi * s + qc) * pld + (int64_t)j * D;
+    const bf16 *ar = a + ((int64_t)bi * s + qc) * pld + (int64_t)j * D;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      qf[qg][kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)qc[qg] * ld + 32 * kk + 8 * g);
-      dof[qg][kk] = *reinterpret_cast<const bf16x8 *>(dar + 32 * kk + 8 * g);
+      qf[kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)qc * ld + 32 * kk + 8 * g);
+      dof[kk] = *reinterpret_cast<const bf16x8 *>(dar + 32 * kk + 8 * g);
       const bf16x8 av = *reinterpret_cast<const bf16x8 *>(ar + 32 * kk + 8 * g);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) ds += (float)dof[qg][kk][i] * (float)av[i];
+      for (int i = 0; i < 8; ++i) dsum += (float)dof[kk][i] * (float)av[i];
     }
-    dsum[qg] = quad_sum(ds);
-    lse2[qg] = lse[((int64_t)bi * n + j) * s + qc[qg]] * kLog2e;
-    if (q < s && g == 0 && !rb.idle) Dvec[((int64_t)bi * n + j) * s + q] = dsum[qg];
+    dsum = quad_sum(dsum);
   }
+  float lse2 = lse[((int64_t)bi * n + j) * s + qc] * kLog2e;
+  if (q < s && g == 0 && wave < 4) Dvec[((int64_t)bi * n + j) * s + q] = -dsum;   // as the dk/dv kernel starts its accumulators
 
-  f32x4 dq[G][DB];
+  f32x4 dq[DB];
 #pragma unroll
-  for (int qg = 0; qg < G; ++qg)
+  for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dq[qg][db][e] = 0.0f;
+    for (int e = 0; e < 4; ++e) dq[db][e] = 0.0f;
 
-  const int ntiles = rb.last_tile + 1;
+  const int ntiles = block + 1;
   // tile DMAs as in the forward kernel
-  constexpr int IPW = (W == 4 ? 2 : 1) * T::NI;
-  const int quarter = W == 4 ? wave : (wave & 3), half = W == 4 ? 0 : (wave >> 2);
-  const dma_rsrc_t rk = dma_rsrc(base + D + half * D), rv = dma_rsrc(base + 2 * D);
-  auto issue_one = [&](auto tag, int t, int st, int i) {
+  constexpr int IPW = T::NI;   // DMA instructions per wave and tile
+  const int quarter = wave & 3, half = wave >> 2;
+  TileStream kv(base + D + half * D, ((int64_t)s * ld - (j * 3 + 1 + half) * D) * 2, 64 * ld * 2);
+  uint32_t dma_off[IPW];
+#pragma unroll
+  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(ld * 2), quarter, lane, i);
+  auto issue_one = [&](auto tag, int st, int i) {   // instruction i of the stream's next tile into ring stage st
     constexpr int TAG = decltype(tag)::value;
-    const int tt = t < ntiles ? t : ntiles - 1;
-    if (W == 8 || i < T::NI)
-      T::template dma_one<TAG>(rk, tt * 64, s, (uint32_t)(ld * 2), smem_addr + st * STAGE + half * T::BYTES, quarter, lane, i);
-    else
-      T::template dma_one<TAG>(rv, tt * 64, s, (uint32_t)(ld * 2), smem_addr + st * STAGE + T::BYTES, quarter, lane, i - T::NI);
+    dma16<TAG>(kv.rsrc(), smem_addr + st * STAGE + half * T::BYTES + (quarter * IPW + i) * 1024, dma_off[i]);
   };
-  auto issue = [&](int t, int st) {
+  constexpr int STEPS = KK + DB / 2;   // MFMA steps of a tile
+  auto issue_step = [&](int step, int st) {
 #pragma unroll
-    for (int i = 0; i < IPW; ++i) issue_one(Burst{}, t, st, i);
+    for (int i = 0; i < IPW; ++i)
+      if (i >= (step ? dma_by<IPW, STEPS>(step - 1) : 0) && i < dma_by<IPW, STEPS>(step)) issue_one(Spread{}, st, i);
   };
-  issue(0, 0);
-  issue(1, 1);
+  auto issue = [&](int st) {
 #pragma unroll
-  for (int qg = 0; qg < G; ++qg) {
+    for (int i = 0; i < IPW; ++i) issue_one(Burst{}, st, i);
+  };
+  issue(0);
+  kv.advance();
+  issue(1);
+  kv.advance();
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      arrive(qf[qg][kk]);
-      arrive(dof[qg][kk]);
-    }
-    arrive(lse2[qg]);
-    arrive(dsum[qg]);
+  for (int kk = 0; kk < KK; ++kk) {
+    arrive(qf[kk]);
+    arrive(dof[kk]);
   }
+  arrive(lse2);
+  arrive(dsum);
   int cur = 0;
   for (int it = 0; it < ntiles; ++it) {
     wait_and_barrier<IPW>();
-#pragma unroll
-    for (int qg = 0; qg < G; ++qg)
-#pragma unroll
-      for (int db = 0; db < DB; ++db) keep_acc(dq[qg][db]);
+    ln.here();
     const int nn = cur == 0 ? 2 : cur - 1;
-    const char *Kt = smem + cur * STAGE, *Vt = Kt + T::BYTES;
-    const int kv0 = it * 64;
-    if (rb.idle || kv0 > qw + (16 * G - 1)) {
-      issue(it + 2, nn);
+    const char *Kt = smem + cur * STAGE + k_half * (T::ROWS16 / 16), *Vt = Kt + T::BYTES;
+    const int kv0 = it * 64 + k_half;
+    if (kv0 > qw + 15) {
+      issue(nn);
     } else {
-      f32x4 sc[G][4], pc[G][4];
+      f32x4 sc[2], pc[2];   // pc accumulates dP - D
 #pragma unroll
-      for (int qg = 0; qg < G; ++qg)
+      for (int kb = 0; kb < 2; ++kb) {
+        pc[kb] = f32x4{-dsum, -dsum, -dsum, -dsum};
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) sc[qg][kb][e] = pc[qg][kb][e] = 0.0f;
-      {  // step i: k-step i / 2, key blocks 2 (i % 2) and + 1
-        bf16x8 kfr[2][2], vfr[2][2];
-        pipelined<2 * KK, 1>(
+        for (int e = 0; e < 4; ++e) sc[kb][e] = 0.0f;
+      }
+      {  // step i: k-step i
+        constexpr int P = 2;   // steps that the reads run ahead
+        bf16x8 kfr[P + 1][2], vfr[P + 1][2];
+        pipelined<KK, P>(
             [&](int i) {
 #pragma unroll
               for (int h = 0; h < 2; ++h) {
-                kfr[i & 1][h] = T::nat(Kt, ln, 2 * (i & 1) + h, i >> 1);
-                vfr[i & 1][h] = T::nat(Vt, ln, 2 * (i & 1) + h, i >> 1);
+                kfr[i % (P + 1)][h] = T::nat(Kt, ln, h, i);
+                vfr[i % (P + 1)][h] = T::nat(Vt, ln, h, i);
               }
             },
             [&](int i) {
 #pragma unroll
-              for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int qg = 0; qg < G; ++qg) {
-                  sc[qg][2 * (i & 1) + h] = MFMA16(kfr[i & 1][h], qf[qg][i >> 1], sc[qg][2 * (i & 1) + h]);
-                  pc[qg][2 * (i & 1) + h] = MFMA16(vfr[i & 1][h], dof[qg][i >> 1], pc[qg][2 * (i & 1) + h]);
-                }
+              for (int h = 0; h < 2; ++h) {
+                sc[h] = MFMA16(kfr[i % (P + 1)][h], qf[i], sc[h]);
+                pc[h] = MFMA16(vfr[i % (P + 1)][h], dof[i], pc[h]);
+              }
             },
-            [&](int i) {
-              if (i < IPW) issue_one(Spread{}, it + 2, nn, i);
-            });
+            [&](int i) { issue_step(i, nn); });
       }
-      // dS^T = P^T o (dP^T - D); element (qg, kb, e): key kv0 + 16 kb + 4 g + e, query qc[qg]
-      const bool diag = kv0 + 63 > qw;  // wave-uniform: diagonal (or past-the-end keys) in this tile
-      // one half of the tile's keys at a time: dS of key blocks 2 ks, 2 ks + 1, then their 2 DB
-      // MFMAs, step i = output blocks 2 i, 2 i + 1
+      // dS^T = P^T o (dP^T - D); element (kb, e): key kv0 + 16 kb + 4 g + e, query qc
+      constexpr int PT = 3;
+      bf16x8 ktr[PT + 1][2];
+      auto load = [&](int i) {   // step i: output blocks 2 i, 2 i + 1
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        bf16x8 df[G], ktr[4][2];
-        auto load = [&](int i) {
+        for (int h = 0; h < 2; ++h) ktr[i % (PT + 1)][h] = T::tr(Kt, ln, 2 * i + h, 0);
+      };
+      pipelined_start<DB / 2, PT>(load);
+      if (kv0 + 31 > qw) {  // wave-uniform: diagonal (or past-the-end keys) among this wave's keys
 #pragma unroll
-          for (int h = 0; h < 2; ++h) ktr[i & 3][h] = T::tr(Kt, ln, 2 * i + h, ks);
-        };
-        pipelined_start<DB / 2, 3>(load);
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int qg = 0; qg < G; ++qg)
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int kb = 2 * ks + h;
-              float p = fast_exp2(fmaf(sc[qg][kb][e], c, -lse2[qg]));
-              if (diag && kv0 + 16 * kb + 4 * g + e > qc[qg]) p = 0.0f;
-              sc[qg][kb][e] = p * (pc[qg][kb][e] - dsum[qg]);
-            }
-#pragma unroll
-        for (int qg = 0; qg < G; ++qg) df[qg] = pack2(sc[qg][2 * ks], sc[qg][2 * ks + 1]);
-        pipelined_run<DB / 2, 3>(
-            load,
-            [&](int i) {
-#pragma unroll
-              for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int qg = 0; qg < G; ++qg) dq[qg][2 * i + h] = MFMA16(ktr[i & 3][h], df[qg], dq[qg][2 * i + h]);
-            },
-            [](int) {});
+          for (int e = 0; e < 4; ++e)
+            if (kv0 + 16 * kb + 4 * g + e > qc) sc[kb][e] = -INFINITY;
       }
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[kb][e] = fast_exp2(fmaf(sc[kb][e], c, -lse2)) * pc[kb][e];
+      const bf16x8 df = pack2(sc[0], sc[1]);
+      pipelined_run<DB / 2, PT>(
+          load,
+          [&](int i) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) dq[2 * i + h] = MFMA16(ktr[i % (PT + 1)][h], df, dq[2 * i + h]);
+          },
+          [&](int i) { issue_step(KK + i, nn); });
     }
+    kv.advance();
     cur = cur == 2 ? 0 : cur + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
+  __syncthreads();   // the rings are no longer read
+  f32x4 *slots = merge_slots(smem, wave, lane, DB);
+  if (wave >= 4) {
 #pragma unroll
-  for (int qg = 0; qg < G; ++qg) {
-    const int q = qw + 16 * qg + lr;
-    if (q < s && !rb.idle) {
-      bf16 *out = dqkv + ((int64_t)bi * s + q) * ld + (int64_t)j * 3 * D;
+    for (int db = 0; db < DB; ++db) slots[db * 64] = dq[db];
+  }
+  __syncthreads();
+  if (wave < 4 && q < s) {
+    bf16 *out = dqkv + ((int64_t)bi * s + q) * ld + (int64_t)j * 3 * D;
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        bf16x4 v;
+    for (int db = 0; db < DB; ++db) {
+      const f32x4 sum = dq[db] + slots[db * 64];
+      bf16x4 v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (bf16)(dq[qg][db][e] * scale);
-        *reinterpret_cast<bf16x4 *>(out + db * 16 + 4 * g) = v;
-      }
+      for (int e = 0; e < 4; ++e) v[e] = (bf16)(sum[e] * scale);
+      *reinterpret_cast<bf16x4 *>(out + db * 16 + 4 * g) = v;
     }
   }
 }
 
 // ------------------------------------------------------------------ backward: dk, dv
-template <int D, int G>
-__global__ __launch_bounds__(512 / G) void attn_bwd_dkv_kernel(int s, int n, float scale, const bf16 *__restrict__ qkv,
+template <int D>
+__global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, int heads, float scale, const bf16 *__restrict__ qkv,
                                                            const float *__restrict__ lse,
                                                            const float *__restrict__ Dvec,
                                                            const bf16 *__restrict__ da, bf16 *__restrict__ dqkv) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES + 512;   // Q tile, dO tile, lse[64], D[64]
-  const int j = blockIdx.y, bi = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, lr = lane & 15;
+  const HeadBlock hb(n, heads);
+  const int j = hb.head, bi = hb.batch, block = hb.order;
+  if (bi >= b) return;   // past the last sequence of the last grid row
+  const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
   const int64_t ld = (int64_t)n * 3 * D, pld = (int64_t)n * D;
   const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * D;
   const bf16 *dab = da + (int64_t)bi * s * pld + (int64_t)j * D;
-  const RowBlocks<G> rb(s, blockIdx.x, wave);
-  // a wave without keys gets a first key beyond any sequence: every tile test below then skips it,
-  // and no register is spent on a flag (this kernel has none to spare at head size 160)
-  const int kw = rb.idle ? (1 << 30) : rb.row0;
+  const int kw = block * 64 + ((threadIdx.x >> 6) & 3) * 16;   // (head size 160: 194 registers instead of 230)
+  const int q_half = (wave >> 2) * 32;   // first query of this wave's half of a tile
   const float c = scale * kLog2e;
-  const typename T::Lane ln(lane);
+  typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
-  int key[G];
-  bf16x8 kf[G][KK], vf[G][KK];
+  const int key = kw + lr, keyc = key < s ? key : s - 1;
+  bf16x8 kf[KK], vf[KK];
 #pragma unroll
-  for (int kg = 0; kg < G; ++kg) {
-    key[kg] = kw + 16 * kg + lr;
-    const int keyc = key[kg] < s ? key[kg] : s - 1;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      kf[kg][kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)keyc * ld + D + 32 * kk + 8 * g);
-      vf[kg][kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)keyc * ld + 2 * D + 32 * kk + 8 * g);
-    }
+  for (int kk = 0; kk < KK; ++kk) {
+    kf[kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)keyc * ld + D + 32 * kk + 8 * g);
+    vf[kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)keyc * ld + 2 * D + 32 * kk + 8 * g);
   }
-  f32x4 dk[G][DB], dv[G][DB];
+  f32x4 dk[DB], dv[DB];
 #pragma unroll
-  for (int kg = 0; kg < G; ++kg)
+  for (int db = 0; db < DB; ++db)
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dk[kg][db][e] = dv[kg][db][e] = 0.0f;
+    for (int e = 0; e < 4; ++e) dk[db][e] = dv[db][e] = 0.0f;
 
-  const int t_first = rb.first_tile, ntiles = (s + 63) / 64 - t_first;
+  const int t_first = block, ntiles = row_blocks(s) - t_first;
   // tile DMAs as in the forward kernel (Q tile and dO tile), plus one instruction per wave for the
-  // tile's lse values (even waves) or D values (odd waves); those arrive two or four times over, so
-  // that every wave issues the same number of memory operations, which the counted waits rely on
-  constexpr int IPW = G * T::NI;
-  const int quarter = G == 2 ? wave : (wave & 3), half = G == 2 ? 0 : (wave >> 2);
-  const dma_rsrc_t rq = dma_rsrc(half ? dab : base), ro = dma_rsrc(dab);
-  const uint32_t pitch_q = (uint32_t)((half ? pld : ld) * 2);
-  const dma_rsrc_t rstat = dma_rsrc(((wave & 1) ? Dvec : lse) + ((int64_t)bi * n + j) * s);
-  auto issue_one = [&](auto tag, int t, int st, int i) {   // i == IPW: the statistics
+  // tile's lse values (even waves) or -D values (odd waves); those arrive four times over, so that every wave
+  // issues the same number of memory operations, which the counted waits rely on
+  constexpr int IPW = T::NI;
+  const int quarter = wave & 3, half = wave >> 2;
+  const int64_t pitch = half ? pld : ld, row0 = (int64_t)t_first * 64;
+  TileStream qo(half ? dab + row0 * pld : base + row0 * ld, ((s - row0) * pitch - (half ? j : 3 * j) * D) * 2, 64 * pitch * 2);
+  TileStream stats(((wave & 1) ? Dvec : lse) + ((int64_t)bi * n + j) * s + row0, (s - row0) * 4, 256);
+  uint32_t dma_off[IPW];
+#pragma unroll
+  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(pitch * 2), quarter, lane, i);
+  auto issue_one = [&](auto tag, int st, int i) {   // i == IPW: the statistics
     constexpr int TAG = decltype(tag)::value;
-    const int tt = t < ntiles ? t : ntiles - 1;
-    const int row0 = (t_first + tt) * 64;
     const uint32_t stage = smem_addr + st * STAGE;
     if (i == IPW) {
-      int qq = row0 + lane;
-      qq = qq < s ? qq : s - 1;
-      dma4<TAG>(rstat, stage + 2 * T::BYTES + (wave & 1) * 256, qq * 4);
-    } else if (G == 1 || i < T::NI) {
-      T::template dma_one<TAG>(rq, row0, s, pitch_q, stage + half * T::BYTES, quarter, lane, i);
+      dma4<TAG>(stats.rsrc(), stage + 2 * T::BYTES + (wave & 1) * 256, lane * 4);
     } else {
-      T::template dma_one<TAG>(ro, row0, s, (uint32_t)(pld * 2), stage + T::BYTES, quarter, lane, i - T::NI);
+      dma16<TAG>(qo.rsrc(), stage + half * T::BYTES + (quarter * IPW + i) * 1024, dma_off[i < IPW ? i : 0]);
     }
   };
-  auto issue = [&](int t, int st) {
+  constexpr int STEPS = KK + DB;   // MFMA steps of a tile; the statistics count as instruction IPW
+  auto issue_step = [&](int step, int st) {
 #pragma unroll
-    for (int i = 0; i <= IPW; ++i) issue_one(Burst{}, t, st, i);
+    for (int i = 0; i <= IPW; ++i)
+      if (i >= (step ? dma_by<IPW + 1, STEPS>(step - 1) : 0) && i < dma_by<IPW + 1, STEPS>(step)) issue_one(Spread{}, st, i);
   };
-  issue(0, 0);
-  issue(1, 1);
+  auto advance = [&] {
+    qo.advance();
+    stats.advance();
+  };
+  auto issue = [&](int st) {
 #pragma unroll
-  for (int kg = 0; kg < G; ++kg)
+    for (int i = 0; i <= IPW; ++i) issue_one(Burst{}, st, i);
+  };
+  issue(0);
+  advance();
+  issue(1);
+  advance();
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      arrive(kf[kg][kk]);
-      arrive(vf[kg][kk]);
-    }
+  for (int kk = 0; kk < KK; ++kk) {
+    arrive(kf[kk]);
+    arrive(vf[kk]);
+  }
   int cur = 0;
   for (int it = 0; it < ntiles; ++it) {
     wait_and_barrier<IPW + 1>();
+    ln.here();
     const int nn = cur == 0 ? 2 : cur - 1;
-    const char *Qt = smem + cur * STAGE, *Ot = Qt + T::BYTES;
-    const float *stat = reinterpret_cast<const float *>(Qt + 2 * T::BYTES);
-    const int q0 = (t_first + it) * 64;
-    if (q0 + 63 < kw) {  // wave-uniform: no query of the tile sees a key of this wave
-      issue(it + 2, nn);
+    const char *Qt = smem + cur * STAGE + q_half * (T::ROWS16 / 16), *Ot = Qt + T::BYTES;
+    const float *stat = reinterpret_cast<const float *>(smem + cur * STAGE + 2 * T::BYTES) + q_half;
+    const int q0 = (t_first + it) * 64 + q_half;
+    if (q0 + 31 < kw) {  // wave-uniform: none of this wave's queries sees one of its keys
+      issue(nn);
     } else {
-      f32x4 sc[G][4], pc[G][4];
+      f32x4 sc[2], pc[2];   // pc accumulates dP - D
 #pragma unroll
-      for (int kg = 0; kg < G; ++kg)
+      for (int qb = 0; qb < 2; ++qb) {
+        pc[qb] = *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
 #pragma unroll
-        for (int qb = 0; qb < 4; ++qb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) sc[kg][qb][e] = pc[kg][qb][e] = 0.0f;
-      {  // step i: k-step i / 2, query blocks 2 (i % 2) and + 1
+        for (int e = 0; e < 4; ++e) sc[qb][e] = 0.0f;
+      }
+      {  // step i: k-step i
         bf16x8 qfr[3][2], ofr[3][2];
-        pipelined<2 * KK, 2>(
+        pipelined<KK, 2>(
             [&](int i) {
 #pragma unroll
               for (int h = 0; h < 2; ++h) {
-                qfr[i % 3][h] = T::nat(Qt, ln, 2 * (i & 1) + h, i >> 1);
-                ofr[i % 3][h] = T::nat(Ot, ln, 2 * (i & 1) + h, i >> 1);
+                qfr[i % 3][h] = T::nat(Qt, ln, h, i);
+                ofr[i % 3][h] = T::nat(Ot, ln, h, i);
               }
             },
             [&](int i) {
 #pragma unroll
-              for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int kg = 0; kg < G; ++kg) {
-                  sc[kg][2 * (i & 1) + h] = MFMA16(qfr[i % 3][h], kf[kg][i >> 1], sc[kg][2 * (i & 1) + h]);
-                  pc[kg][2 * (i & 1) + h] = MFMA16(ofr[i % 3][h], vf[kg][i >> 1], pc[kg][2 * (i & 1) + h]);
-                }
+              for (int h = 0; h < 2; ++h) {
+                sc[h] = MFMA16(qfr[i % 3][h], kf[i], sc[h]);
+                pc[h] = MFMA16(ofr[i % 3][h], vf[i], pc[h]);
+              }
             },
-            [&](int i) {
-              if (i < IPW) issue_one(Spread{}, it + 2, nn, i);
-              if (i == 2 * KK - 1) issue_one(Spread{}, it + 2, nn, IPW);
-            });
+            [&](int i) { issue_step(i, nn); });
       }
-      // element (kg, qb, e): query q0 + 16 qb + 4 g + e, key key[kg]
-      const bool edge = q0 < kw + 16 * G || q0 + 63 >= s;  // wave-uniform: diagonal or past-the-end queries
+      // element (qb, e): query q0 + 16 qb + 4 g + e, key `key`
+      bf16x8 otr[4], qtr[4];
+      auto load = [&](int i) {   // step i: output block i
+        otr[i & 3] = T::tr(Ot, ln, i, 0);
+        qtr[i & 3] = T::tr(Qt, ln, i, 0);
+      };
+      pipelined_start<DB, 3>(load);
+      if (q0 < kw + 16 || q0 + 31 >= s) {  // wave-uniform: diagonal or past-the-end queries
 #pragma unroll
-      for (int qb = 0; qb < 4; ++qb) {
-        const f32x4 ls = *reinterpret_cast<const f32x4 *>(stat + 16 * qb + 4 * g);
-        const f32x4 dd = *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
-#pragma unroll
-        for (int kg = 0; kg < G; ++kg)
+        for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int qq = q0 + 16 * qb + 4 * g + e;
-            float p = fast_exp2(fmaf(sc[kg][qb][e], c, -ls[e] * kLog2e));
-            if (edge && (qq < key[kg] || qq >= s)) p = 0.0f;
-            sc[kg][qb][e] = p;
-            pc[kg][qb][e] = p * (pc[kg][qb][e] - dd[e]);
+            if (qq < key || qq >= s) sc[qb][e] = -INFINITY;
           }
       }
-      {  // step i: query half i / DB, output block i % DB
-        bf16x8 pf[2][G], df[2][G], otr[4], qtr[4];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+      for (int qb = 0; qb < 2; ++qb) {
+        const f32x4 ls = *reinterpret_cast<const f32x4 *>(stat + 16 * qb + 4 * g);
 #pragma unroll
-          for (int kg = 0; kg < G; ++kg) {
-            pf[ks][kg] = pack2(sc[kg][2 * ks], sc[kg][2 * ks + 1]);
-            df[ks][kg] = pack2(pc[kg][2 * ks], pc[kg][2 * ks + 1]);
-          }
-        pipelined<2 * DB, 3>(
-            [&](int i) {
-              otr[i & 3] = T::tr(Ot, ln, i % DB, i / DB);
-              qtr[i & 3] = T::tr(Qt, ln, i % DB, i / DB);
-            },
-            [&](int i) {
-#pragma unroll
-              for (int kg = 0; kg < G; ++kg) {
-                dv[kg][i % DB] = MFMA16(otr[i & 3], pf[i / DB][kg], dv[kg][i % DB]);
-                dk[kg][i % DB] = MFMA16(qtr[i & 3], df[i / DB][kg], dk[kg][i % DB]);
-              }
-            });
+        for (int e = 0; e < 4; ++e) {
+          sc[qb][e] = fast_exp2(fmaf(sc[qb][e], c, -ls[e] * kLog2e));
+          pc[qb][e] *= sc[qb][e];
+        }
       }
+      const bf16x8 pf = pack2(sc[0], sc[1]), df = pack2(pc[0], pc[1]);
+      pipelined_run<DB, 3>(
+          load,
+          [&](int i) {
+            dv[i] = MFMA16(otr[i & 3], pf, dv[i]);
+            dk[i] = MFMA16(qtr[i & 3], df, dk[i]);
+          },
+          [&](int i) { issue_step(KK + i, nn); });
     }
+    advance();
     cur = cur == 2 ? 0 : cur + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
+  __syncthreads();   // the rings are no longer read
+  f32x4 *slots = merge_slots(smem, wave, lane, 2 * DB);
+  if (wave >= 4) {
 #pragma unroll
-  for (int kg = 0; kg < G; ++kg) {
-    if (key[kg] < s) {
-      bf16 *out = dqkv + ((int64_t)bi * s + key[kg]) * ld + (int64_t)j * 3 * D;
+    for (int db = 0; db < DB; ++db) {
+      slots[db * 64] = dk[db];
+      slots[(DB + db) * 64] = dv[db];
+    }
+  }
+  __syncthreads();
+  if (wave < 4 && key < s) {
+    bf16 *out = dqkv + ((int64_t)bi * s + key) * ld + (int64_t)j * 3 * D;
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        bf16x4 ok, ov;
+    for (int db = 0; db < DB; ++db) {
+      const f32x4 sk = dk[db] + slots[db * 64], sv = dv[db] + slots[(DB + db) * 64];
+      bf16x4 ok, ov;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          ok[e] = (bf16)(dk[kg][db][e] * scale);
-          ov[e] = (bf16)dv[kg][db][e];
-        }
-        *reinterpret_cast<bf16x4 *>(out + D + db * 16 + 4 * g) = ok;
-        *reinterpret_cast<bf16x4 *>(out + 2 * D + db * 16 + 4 * g) = ov;
+      for (int e = 0; e < 4; ++e) {
+        ok[e] = (bf16)(sk[e] * scale);
+        ov[e] = (bf16)sv[e];
       }
+      *reinterpret_cast<bf16x4 *>(out + D + db * 16 + 4 * g) = ok;
+      *reinterpret_cast<bf16x4 *>(out + 2 * D + db * 16 + 4 * g) = ov;
     }
   }
 }
-
-// Row groups of 16 per wave and waves per workgroup.  Four waves of 32 rows (every LDS fragment feeds two MFMAs, one
-// wave per SIMD with 512 registers) measured slower than eight waves of 16 rows (twice the LDS reads, two waves per
-// SIMD to overlap the softmax arithmetic with the MFMAs) at head size 160, sequence 2048: forward 69 against 54 us,
-// dk/dv 119 against 86 us, dq 77 against 69 us.  Eight waves of 32 rows need 256 rows per workgroup: the forward
-// kernel takes that shape when the problem has enough workgroups (see fwd_launch); the backward kernels do not fit
-// the 256 registers a wave has at eight waves.
-constexpr int DKV_G = 1;
 
 // Forward with 32 rows per wave on eight waves (256 rows per workgroup): every K / V fragment read from LDS feeds two
 // MFMAs, which halves the kernel's LDS traffic -- its bound: each of the eight waves reads the whole K and V tile, the
 // V tile through half-rate transposing reads -- but halves the number of workgroups as well.  Taken when that still
 // leaves at least one workgroup per compute unit (the MT-NLG slice at micro-batch 1 has 16 heads x 8 = 128: it stays
-// with 16 rows per wave) and the head size is 128 or 160 (at 64 the variant measures 17 % slower).  Measured: 1.3B-shaped
-// layer (4 x 16 heads x 128) 168 -> 123 us, slice at micro-batch 4 167 -> 129 us, whole layer (128 heads) 326 -> 250 us.
+// with 16 rows per wave) and the head size is 128 or 160 (at 64 the variant measures 17 % slower).  Measured with the
+// kernel as it was before the grid ran heads first: 1.3B-shaped layer (4 x 16 heads x 128) 168 with 16 rows, 123 us with 32,
+// slice at micro-batch 4 167 and 129 us, whole layer (128 heads) 326 and 250 us.
 template <int D, int G>
 int fwd_launch_g(int b, int s, int n, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
   constexpr int smem = 3 * 2 * 64 * D * 2;
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, G, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) !=
+    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, G>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) !=
         hipSuccess)
       return MTNLG_HIP_ERROR;
     attr_mark_set(attr_done, device);
   }
+  const int count = PairedBlocks<G>::count(s), bx = HeadBlock::sequences(b, n, count), heads = n * bx;
   LaunchScope scope(MTNLG_K_ATTN_FWD, st);
-  attn_fwd_kernel<D, G, 8><<<dim3(RowBlocks<G, 8>::grid(s), n, b), 512, smem, st>>>(s, n, scale, (const bf16 *)qkv, (bf16 *)a, lse);
+  attn_fwd_kernel<D, G><<<dim3(heads * count, (b + bx - 1) / bx), 512, smem, st>>>(b, s, n, heads, scale, (const bf16 *)qkv, (bf16 *)a, lse);
   return check_launch();
 }
 
 template <int D>
 int fwd_launch(int b, int s, int n, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
-  if (D >= 128 && (int64_t)RowBlocks<2, 8>::grid(s) * n * b >= 256) return fwd_launch_g<D, 2>(b, s, n, scale, qkv, a, lse, st);
+  if (D >= 128 && (int64_t)PairedBlocks<2>::count(s) * n * b >= 256) return fwd_launch_g<D, 2>(b, s, n, scale, qkv, a, lse, st);
   return fwd_launch_g<D, 1>(b, s, n, scale, qkv, a, lse, st);
 }
 
-template <int D, int G>
-int bwd_dq_launch_g(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
-                    void *dqkv, float *Dvec, hipStream_t st) {
-  constexpr int smem_dq = 3 * 2 * 64 * D * 2;
-  static unsigned long long attr_done = 0;
-  int device;
-  if (!attr_is_set(attr_done, &device)) {
-    if (hipFuncSetAttribute((const void *)attn_bwd_dq_kernel<D, G, 8>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            smem_dq) != hipSuccess)
-      return MTNLG_HIP_ERROR;
-    attr_mark_set(attr_done, device);
-  }
-  attn_bwd_dq_kernel<D, G, 8><<<dim3(RowBlocks<G, 8>::grid(s), n, b), 512, smem_dq, st>>>(
-      s, n, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da, (bf16 *)dqkv, Dvec);
-  return check_launch();
-}
-
+// 16 rows per wave in both backward kernels: 32 do not fit the 256 registers a wave has at eight waves.
 template <int D>
 int bwd_launch(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                void *dqkv, void *ws, hipStream_t st) {
-  constexpr int smem_dkv = 3 * (2 * 64 * D * 2 + 512);
+  constexpr int smem_dq = 3 * 2 * 64 * D * 2, smem_dkv = 3 * (2 * 64 * D * 2 + 512);
+  static_assert(smem_dkv >= 4 * 2 * (D / 16) * 1024, "the merge of the two halves fits the rings");
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    if (hipFuncSetAttribute((const void *)attn_bwd_dkv_kernel<D, DKV_G>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            smem_dkv) != hipSuccess)
+    if (hipFuncSetAttribute((const void *)attn_bwd_dq_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dq) != hipSuccess ||
+        hipFuncSetAttribute((const void *)attn_bwd_dkv_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dkv) != hipSuccess)
       return MTNLG_HIP_ERROR;
     attr_mark_set(attr_done, device);
   }
   float *Dvec = (float *)ws;
+  const int bx = HeadBlock::sequences(b, n, row_blocks(s)), heads = n * bx;
+  const dim3 grid(heads * row_blocks(s), (b + bx - 1) / bx);
   LaunchScope scope(MTNLG_K_ATTN_BWD, st);
-  // 16 rows per wave in both backward kernels: with 32 the dq kernel spills at head size 128 (256 registers and 256
-  // bytes of scratch) and the dk/dv kernel does not fit at any
-  MTNLG_TRY((bwd_dq_launch_g<D, 1>(b, s, n, scale, qkv, a, lse, da, dqkv, Dvec, st)));
-  attn_bwd_dkv_kernel<D, DKV_G><<<dim3(RowBlocks<DKV_G>::grid(s), n, b), 512 / DKV_G, smem_dkv, st>>>(
-      s, n, scale, (const bf16 *)qkv, lse, Dvec, (const bf16 *)da, (bf16 *)dqkv);
+  attn_bwd_dq_kernel<D><<<grid, 512, smem_dq, st>>>(b, s, n, heads, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da,
+                                                    (bf16 *)dqkv, Dvec);
+  MTNLG_TRY(check_launch());
+  attn_bwd_dkv_kernel<D><<<grid, 512, smem_dkv, st>>>(b, s, n, heads, scale, (const bf16 *)qkv, lse, Dvec, (const bf16 *)da, (bf16 *)dqkv);
   return check_launch();
 }
 

@@ -140,6 +140,27 @@ def test_attention_at_every_compiled_head_size(dtype, b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
 
 
+# Matrix-core attention over more workgroups than a grid row takes (65536; a sequence here takes 17): sequences do not depend on
+# each other, so two calls on parts that fit one row each give the same bytes.
+def test_attention_batches_of_several_grid_rows():
+    b, s, n, d = 4001, 2, 17, 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    qkv = torch.randn(b * s, 3 * n * d, device="cuda", generator=gen).bfloat16()
+    da = torch.randn(b * s, n * d, device="cuda", generator=gen).bfloat16()
+
+    def run(lo, hi):
+        x, g = qkv[lo * s:hi * s], da[lo * s:hi * s]
+        a, dx = torch.full_like(g, float("nan")), torch.full_like(x, float("nan"))
+        lse = torch.full((hi - lo, n, s), float("nan"), device="cuda")
+        ws = torch.empty(M.mtnlg_attention_bwd_workspace(hi - lo, s, n, d), dtype=torch.uint8, device="cuda")
+        M.mtnlg_attention_fwd(hi - lo, s, n, d, 0.125, x, a, lse)
+        M.mtnlg_attention_bwd(hi - lo, s, n, d, 0.125, x, a, lse, g, dx, ws)
+        return a, lse, dx
+
+    for whole, first, second in zip(run(0, b), run(0, 2000), run(2000, b)):
+        assert torch.equal(whole, torch.cat([first, second]))
+
+
 # LayerNorm backward: the widths between which the number of waves to a row changes (512, 1024, 2048, 4096 columns) and the
 # row count per thread (8192, 16384, 24576); fewer rows than a workgroup takes at a time, and several turns of the row loop.
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
