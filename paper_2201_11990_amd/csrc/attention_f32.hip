@@ -1,6 +1,6 @@
 // Causal softmax attention, forward and backward, on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32): scores,
 // probabilities and sums stay in fp32.  This is the attention of the fp32 path and of the bf16 head sizes that the
-// bf16 kernels do not take (elements are widened on load).  Head sizes: multiples of 8 up to 256; sequences up to 4096.
+// bf16 kernels do not take.  Head sizes: multiples of 8 up to 256; sequences up to 4096.
 //
 //   S[t,u] = scale * q_t . k_u  (u <= t),  P = rowsoftmax(S),  a_t = sum_u P[t,u] v_u
 //   lse[t] = log sum_u exp(S[t,u])
@@ -9,6 +9,10 @@
 //   dk_u = scale sum_t dS[t,u] q_t,  dv_u = sum_t P[t,u] da_t
 //
 // Bound by the fp32 matrix rate where there are enough rows, else by each wave's chain of loads, MFMAs and exponentials.
+// bf16 inputs need not be widened for the products of two inputs (q k^T, da v^T, D): those run on the bf16 matrix
+// instructions with fp32 sums.  2 x 1024 tokens, 16 heads of 96, forward / backward: 162 / 540 us with all products on the
+// fp32 instructions, 109 / 350 us so.  (P and dS cut into three bf16 parts that add up to them exactly, for the other products:
+// slower, 237 us forward; the waves wait for loads by then, and 32-row steps leave fewer of them.)
 // A wave owns 16 rows of one side (queries forward and for dq, keys for dk / dv) and walks the other side 16 or 32 rows
 // at a time; fragments are loaded from global memory straight into the registers the MFMAs read (at this matrix rate a
 // wave asks the caches for 8 bytes a cycle), so there is no LDS, no barrier, and a wave stops at its own diagonal.  The four
@@ -18,6 +22,7 @@
 // Lane l = 16 g + r.  Two fragment forms of a 16-row block X:
 //   Rows: element (c, e) = X[r][16 c + 4 g + e]; an MFMA per (c, e) contracts over columns.  With Rows of both sides a
 //         lane holds S[streamed row 4 g + i][own row r], i = 0..3.
+//   (bf16: element (c, e) = X[r][32 c + 8 g + e], one MFMA per c.)
 //   Cols: element (block, e) = X[4 g + e][column], NB consecutive columns per lane and group of 16 NB; an MFMA per
 //         (block, e) contracts over the rows, and its other operand for e is exactly that accumulator element: P
 //         and dS are used where they were computed.
@@ -48,6 +53,30 @@ struct Rows {
         for (int e = 0; e < 4; ++e) v[c][e] = col < d ? t[e] : 0.0f;
       } else {
         v[c] = load4(p + col);
+      }
+    }
+  }
+};
+
+// bf16 rows stay bf16: lane l holds X[r][32 c + 8 g .. + 7], one v_mfma_f32_16x16x32_bf16 per c contracts over columns.
+// Products of bf16 elements are exact in fp32 and the sums are fp32, as after widening, at 16 times the rate.
+template <int DP>
+struct Rows<bf16, DP> {
+  static constexpr int NC = DP / 32;
+  typedef __attribute__((ext_vector_type(8), aligned(8))) bf16 bf16x8_8;   // rows need not be aligned to more
+  bf16x8 v[NC];
+  __device__ __forceinline__ void load(const bf16 *base, int64_t ld, int first, int rows, int d, int g, int r) {
+    const int row = first + r < rows ? first + r : rows - 1;
+    const bf16 *p = base + row * ld;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int col = 32 * c + 8 * g;
+      if (c == NC - 1) {   // d lies in (DP - 32, DP]
+        const bf16x8 t = *reinterpret_cast<const bf16x8_8 *>(p + (col < d ? col : 0));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[c][e] = col < d ? t[e] : (bf16)0.0f;
+      } else {
+        v[c] = *reinterpret_cast<const bf16x8_8 *>(p + col);
       }
     }
   }
@@ -132,12 +161,17 @@ template <typename E, int DP>
 __device__ __forceinline__ f32x4 product(const Rows<E, DP> &streamed, const Rows<E, DP> &own) {
   f32x4 lo = {0.0f, 0.0f, 0.0f, 0.0f}, hi = {0.0f, 0.0f, 0.0f, 0.0f};   // two chains: an MFMA waits for its accumulator
 #pragma unroll
-  for (int c = 0; c < Rows<E, DP>::NC; ++c)
+  for (int c = 0; c < Rows<E, DP>::NC; ++c) {
+    if constexpr (sizeof(E) == 2) {
+      lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(streamed.v[c], own.v[c], lo, 0, 0, 0);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 4; e += 2) {
-      lo = MFMA4(streamed.v[c][e], own.v[c][e], lo);
-      hi = MFMA4(streamed.v[c][e + 1], own.v[c][e + 1], hi);
+      for (int e = 0; e < 4; e += 2) {
+        lo = MFMA4(streamed.v[c][e], own.v[c][e], lo);
+        hi = MFMA4(streamed.v[c][e + 1], own.v[c][e + 1], hi);
+      }
     }
+  }
   return lo + hi;
 }
 
