@@ -193,14 +193,18 @@ __device__ __forceinline__ float quad_sum(float v) {
 }
 // v_permlane{16,32}_swap of a value with itself leaves the two halves of every pair side by side; unlike a shuffle
 // through LDS it costs a vector instruction's latency, which the forward kernel pays twice in every tile's chain.
+// The results are taken into scalars before they are reinterpreted: __builtin_bit_cast of an element of a vector reads
+// element 0 whichever is named (ROCm 7.2's clang), and the maximum of element 0 with itself folds away.
 __device__ __forceinline__ float quad_max(float v) {
   typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
   const unsigned a = __builtin_bit_cast(unsigned, v);
   const u32x2 p = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(a, a, false, false));
-  v = fmaxf(__builtin_bit_cast(float, p[0]), __builtin_bit_cast(float, p[1]));
+  const unsigned p0 = p[0], p1 = p[1];
+  v = fmaxf(__builtin_bit_cast(float, p0), __builtin_bit_cast(float, p1));
   const unsigned b = __builtin_bit_cast(unsigned, v);
   const u32x2 q = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(b, b, false, false));
-  return fmaxf(__builtin_bit_cast(float, q[0]), __builtin_bit_cast(float, q[1]));
+  const unsigned q0 = q[0], q1 = q[1];
+  return fmaxf(__builtin_bit_cast(float, q0), __builtin_bit_cast(float, q1));
 }
 
 // Number of a wave's IPW DMA instructions that go out by step `step` of the STEPS MFMA steps of a tile (both runs counted):

@@ -1,5 +1,7 @@
 """GPU parity where a dispatch rule changes kernels: the smallest and largest sizes of each path, the edges of its
 tiles and the operand alignments that it has to tell apart.  Same oracle and bars as test_gpu_ops.py."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -159,6 +161,38 @@ def test_attention_batches_of_several_grid_rows():
 
     for whole, first, second in zip(run(0, b), run(0, 2000), run(2000, b)):
         assert torch.equal(whole, torch.cat([first, second]))
+
+
+# One key that scores 100 (natural units) above all others, head by head at every position modulo 16 and, by sequence, in the
+# first tile, a middle one and the last: exponents taken from any but the maximum over all keys overflow.  208 rows: 16 heads x 3
+# sequences stay with 16 rows per wave in the forward kernel, x 18 take 32 at head sizes 128 and 160.
+@pytest.mark.parametrize("d", [64, 128, 160])
+@pytest.mark.parametrize("b", [3, 18])
+def test_attention_with_one_dominating_key(b, d):
+    s, n = 208, 16
+    g = torch.Generator().manual_seed(17)
+    qkv = torch.randn((b, s, n, 3, d), generator=g)
+    qkv[..., 0, 0] = 32.0
+    qkv[..., 1, 0] = 0.0
+    for bi in range(b):
+        for j in range(n):
+            first = (0, 64 + 16 * (bi // 3 % 8), 192)[bi % 3]
+            qkv[bi, first + j, j, 1, 0] = 104.0 * math.sqrt(d) / 32.0   # + the other products, a few units
+    qkv = qkv.reshape(b * s, 3 * n * d).to(torch.bfloat16)
+    da = randn((b * s, n * d), "bf16", 18)
+    dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
+    scale = 1.0 / math.sqrt(d)
+    a = torch.full((b * s, n * d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((b, n, s), float("nan"), device="cuda")
+    M.mtnlg_attention_fwd(b, s, n, d, scale, dev(qkv), a, lse)
+    ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+    dqkv = torch.full(qkv.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+    M.mtnlg_attention_bwd(b, s, n, d, scale, dev(qkv), a, lse, dev(da), dqkv, ws)
+    for name, t in (("a", a), ("lse", lse), ("dqkv", dqkv)):
+        bad = ~torch.isfinite(t.float())
+        assert not bool(bad.any()), f"{name}: {int(bad.sum())} of {bad.numel()} not finite"
+    assert_close(a, oracle.attention_fwd(dims, to_np(qkv)), TOL["bf16"], "attention out")
+    assert_close(dqkv, oracle.attention_bwd(dims, to_np(qkv), to_np(da)), TOL["bf16"], "attention dqkv")
 
 
 # LayerNorm backward: the widths between which the number of waves to a row changes (512, 1024, 2048, 4096 columns) and the
