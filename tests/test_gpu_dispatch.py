@@ -142,6 +142,60 @@ def test_attention_at_every_compiled_head_size(dtype, b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
 
 
+# An infinity or NaN in one token reaches only what depends on that token.  K and V of token t0: outputs and dq of the rows before it
+# stay as they were; Q and dO of token t0: dk and dv of the keys after it.  t0 at the start, inside and at the end of a 16-row
+# block, and the last token, whose block hangs over the end of the sequence.
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("t0", [0, 32, 37, 63, 89])
+@pytest.mark.parametrize("dtype,d", [("fp32", 24), ("fp32", 64), ("fp32", 96), ("bf16", 40), ("bf16", 96)])
+def test_attention_non_finite_token_stays_where_it_belongs(dtype, d, t0, bad):
+    b, s, n, col = 2, 90, 2, 5
+    dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
+    qkv, da = randn((b, s, n, 3, d), dtype, 51), randn((b, s, n, d), dtype, 52)
+    flat = lambda t: dev(t.reshape(b * s, -1))
+
+    def run(x, g):
+        a, dx = torch.full_like(g, 7.0, device="cuda").reshape(b * s, -1), torch.full_like(x, 7.0, device="cuda").reshape(b * s, -1)
+        lse = torch.full((b, n, s), 7.0, device="cuda")
+        ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+        M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), flat(x), a, lse)
+        M.mtnlg_attention_bwd(b, s, n, d, 1.0 / math.sqrt(d), flat(x), a, lse, flat(g), dx, ws)
+        return a.reshape(b, s, n, d), lse, dx.reshape(b, s, n, 3, d)
+
+    want_a = oracle.attention_fwd(dims, to_np(qkv).reshape(b * s, -1)).reshape(b, s, n, d)
+    want_dx = oracle.attention_bwd(dims, to_np(qkv).reshape(b * s, -1), to_np(da).reshape(b * s, -1)).reshape(b, s, n, 3, d)
+    _, lse0, _ = run(qkv, da)
+    for part in (1, 2):   # K, V of token t0 in head 1 of sequence 0
+        x = qkv.clone()
+        x[0, t0, 1, part, col] = bad
+        a, lse, dx = run(x, da)
+        for name, got, want in (("a", a, want_a), ("dq", dx[:, :, :, 0], want_dx[:, :, :, 0])):
+            assert_close(got[:, :, 0], want[:, :, 0], TOL[dtype], f"{name} of the other head")
+            assert_close(got[1], want[1], TOL[dtype], f"{name} of the other sequence")
+            if t0 > 0:
+                assert_close(got[0, :t0, 1], want[0, :t0, 1], TOL[dtype], f"{name} before token {t0}")
+        assert torch.equal(lse[1], lse0[1]) and torch.equal(lse[0, 0], lse0[0, 0])
+        if t0 > 0:
+            assert_close(lse[0, 1, :t0], to_np(lse0[0, 1, :t0]), TOL["fp32"], f"lse before token {t0}")
+        if part == 2:   # V enters one column of the output, in every later row
+            assert not bool(torch.isfinite(a[0, t0:, 1, col].float()).any())
+            rest = [c for c in range(d) if c != col]
+            assert_close(a[0, :, 1][:, rest], want_a[0, :, 1][:, rest], TOL[dtype], "the other columns")
+    for poison_q in (True, False):   # Q, dO of token t0
+        x, g = qkv.clone(), da.clone()
+        if poison_q:
+            x[0, t0, 1, 0, col] = bad
+        else:
+            g[0, t0, 1, col] = bad
+        _, _, dx = run(x, g)
+        for i in (1, 2):
+            assert_close(dx[1, :, :, i], want_dx[1, :, :, i], TOL[dtype], "the other sequence")
+            if t0 + 1 < s:
+                assert_close(dx[0, t0 + 1:, 1, i], want_dx[0, t0 + 1:, 1, i], TOL[dtype], f"d{'qkv'[i]} after token {t0}")
+            if not poison_q and i == 2:
+                assert not bool(torch.isfinite(dx[0, :t0 + 1, 1, 2, col].float()).any())
+
+
 # Matrix-core attention over more workgroups than a grid row takes (65536; a sequence here takes 17): sequences do not depend on
 # each other, so two calls on parts that fit one row each give the same bytes.
 def test_attention_batches_of_several_grid_rows():
