@@ -191,8 +191,8 @@ __device__ __forceinline__ int tr_pos(int u, int k) {
 }
 
 constexpr int stream_ring_b(int bn) { return bn == 320 ? 2 : 3; }   // stages of the B ring
-// Ragged problems: bytes a buffer descriptor covers (every valid offset lies below, see ragged_fits), an offset outside
-constexpr uint32_t RAG_RECORDS = 0x80000000u, RAG_OUTSIDE = 0xFFFFFFF0u;
+// Ragged problems: bytes a buffer descriptor covers (every valid offset lies below, see tile_reaches), an offset outside
+constexpr uint32_t RAG_RECORDS = 0xFFFFFFE0u, RAG_OUTSIDE = 0xFFFFFFF0u;
 
 template <int N>
 __device__ __forceinline__ void wait_dma_and_barrier() {   // at most N of this wave's DMAs still in flight
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, WGM * WGN == 8 ? 1 : 2) void gemm_s
   //   k-row through k & 3 and bit 3 only, so instructions i and i + 2 differ by 4 k-rows in every lane: two vector
   //   offsets, the rest in the scalar offset.  40 units per k-row: one vector offset per instruction.
   //   Ragged problems: one vector offset per instruction (rows and units past the edge repeat the last valid one; what
-  //   they produce is not stored), and lanes whose k lies past K take an offset beyond the buffer's 2 GiB, which the
+  //   they produce is not stored), and lanes whose k lies past K take an offset beyond the descriptor's size, which the
   //   hardware's bounds check turns into zeros in LDS.
   auto dma_offset_k = [&](int q, int64_t ld, int64_t left) -> uint32_t {
     int row = 8 * q + (lane >> 3);
@@ -826,31 +826,38 @@ double time_128(int64_t tiles, int nk) {
 }
 double time_128_deep(int64_t tiles, int nk) { return (double)((tiles + 255) / 256) * (0.53 * nk + 4.5); }
 
-// Whether every byte offset of a tile's DMA stays below RAG_RECORDS
-bool ragged_fits(bool at, bool bt, int64_t lda, int64_t ldb) {
-  auto reach = [](bool rowc, int64_t ld) { return (rowc ? 64 : 256) * ld * 2 + 1024; };
-  return reach(at, lda) < (int64_t)RAG_RECORDS && reach(bt, ldb) < (int64_t)RAG_RECORDS;
+// Whether the 32-bit byte offsets of a tile's DMA reach all it reads: of a K-contiguous operand 128 bytes in each of the tile's rows,
+// of a row-contiguous one the tile's width in each of 64 k-rows.  (Rows of 8 M elements and more on the 256-row tiles, of 16 M on the
+// 128-row tiles, 33 M row-contiguous.)
+bool tile_reaches(int layout, int64_t M, int64_t N, int64_t K, int bm, int bn) {
+  const bool at = layout == MTNLG_GEMM_TN, bt = layout != MTNLG_GEMM_NT;
+  auto reach = [&](bool rowc, int64_t rows, int tile) {
+    const int64_t lines = rowc ? BK : tile;
+    return ((lines < (rowc ? K : rows) ? lines : (rowc ? K : rows)) - 1) * (rowc ? rows : K) * 2 + (rowc ? 2 * tile : 2 * BK);
+  };
+  return reach(at, M, bm) <= (int64_t)RAG_RECORDS && reach(bt, N, bn) <= (int64_t)RAG_RECORDS;
 }
 
 }  // namespace
 
-// Which tile shape takes a problem: the least estimated time.  A last round is split along K if its
-// partial tiles fit the workspace.
-int gemm_mfma_pick_tile(int, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
-  if (M <= 0 || N <= 0 || K <= 0) return GEMM_TILE_RAGGED_128;
+// Which tile shape takes a problem: the least estimated time among those whose DMA reaches the operands, -1 if none does.  A last
+// round is split along K if its partial tiles fit the workspace.
+int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+  if (M <= 0 || N <= 0 || K <= 0) return -1;
   const int nk = (int)((K + BK - 1) / BK);
   double best = 1e300;
-  int pick = GEMM_TILE_RAGGED_128;
-  auto offer = [&](int tile, double t) {
-    if (t < best) { best = t; pick = tile; }
+  int pick = -1;
+  auto offer = [&](int tile, int bm, int bn, double t) {
+    if (t < best && tile_reaches(layout, M, N, K, bm, bn)) { best = t; pick = tile; }
   };
   auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const bool aligned = K % BK == 0 && M % 256 == 0;
-  offer(aligned && N % 256 == 0 ? GEMM_TILE_STREAM_256x256 : GEMM_TILE_RAGGED_256, time_256(tiles(256, 256), nk, true, ws_bytes));
+  offer(aligned && N % 256 == 0 ? GEMM_TILE_STREAM_256x256 : GEMM_TILE_RAGGED_256, 256, 256,
+        time_256(tiles(256, 256), nk, true, ws_bytes));
   if (aligned && N % 320 == 0)
-    offer(GEMM_TILE_STREAM_256x320, time_256(tiles(256, 320), nk, false, 0) * 1.25 * GEMM_COST_256x320);
-  offer(GEMM_TILE_RAGGED_128, time_128(tiles(128, 128), nk));
-  offer(GEMM_TILE_RAGGED_128_DEEP, time_128_deep(tiles(128, 128), nk));
+    offer(GEMM_TILE_STREAM_256x320, 256, 320, time_256(tiles(256, 320), nk, false, 0) * 1.25 * GEMM_COST_256x320);
+  offer(GEMM_TILE_RAGGED_128, 128, 128, time_128(tiles(128, 128), nk));
+  offer(GEMM_TILE_RAGGED_128_DEEP, 128, 128, time_128_deep(tiles(128, 128), nk));
   return pick;
 }
 
@@ -875,7 +882,6 @@ int gemm_mfma_bf16(int layout, int64_t M, int64_t N, int64_t K, const void *A, c
   const bool at = layout == MTNLG_GEMM_TN, bt = layout != MTNLG_GEMM_NT;
   if (at && M % 8) return MTNLG_UNSUPPORTED_SHAPE;
   if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C | (uintptr_t)bias | (uintptr_t)aux) & 3) return MTNLG_UNSUPPORTED_SHAPE;   // DMA: whole dwords
-  if (!ragged_fits(at, bt, at ? M : K, bt ? N : K)) return MTNLG_UNSUPPORTED_SHAPE;
   GemmArgs g;
   g.M = M; g.N = N; g.K = K;
   g.A = (const bf16 *)A; g.B = (const bf16 *)B;
@@ -887,6 +893,7 @@ int gemm_mfma_bf16(int layout, int64_t M, int64_t N, int64_t K, const void *A, c
   g.whole_tiles = 0; g.split = 1; g.part_slabs = 0; g.partial = nullptr;
   if (tile < 0)
     tile = gemm_mfma_pick_tile(layout, M, N, K, ws != nullptr ? ws_bytes : 0);
+  if (tile < 0) return MTNLG_UNSUPPORTED_SHAPE;
   LaunchScope scope(prof_class >= 0 ? prof_class : MTNLG_K_GEMM_NT + layout, stream);
   if (!at && !bt) return launch_tile<false, false>(tile, g, ws, ws_bytes, stream);
   if (!at && bt) return launch_tile<false, true>(tile, g, ws, ws_bytes, stream);

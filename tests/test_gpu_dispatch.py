@@ -1,5 +1,6 @@
 """GPU parity where a dispatch rule changes kernels: the smallest and largest sizes of each path, the edges of its
 tiles and the operand alignments that it has to tell apart.  Same oracle and bars as test_gpu_ops.py."""
+import ctypes
 import math
 
 import numpy as np
@@ -27,6 +28,40 @@ def shifted(t, by):
     out = buf[by:].view(t.shape)
     out.copy_(t)
     return out
+
+
+TILES = ("stream 256x256", "stream 256x320", "ragged 256", "ragged 128", "ragged 128 deep")   # enum gemm_tile
+
+
+def picked_tile(layout, Mm, N, K, ws_bytes=0):
+    """The tile that the dispatch takes for a bf16 product, None if the bf16 kernels do not take it."""
+    fn = B.lib()._ZN5mtnlg19gemm_mfma_pick_tileEilllm
+    fn.argtypes, fn.restype = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_size_t], ctypes.c_int
+    t = fn(layout, Mm, N, K, ws_bytes)
+    return None if t < 0 else TILES[t]
+
+
+# Rows so long that a tile's DMA offsets pass 2^31 bytes (K-contiguous from 4.2 M elements on, row-contiguous from 16.8 M): still
+# the bf16 kernels, and the right rows.
+@pytest.mark.parametrize("layout,shape", [(B.GEMM_NT, (136, 128, 9000008)), (B.GEMM_NN, (8, 16777224, 72)),
+                                          (B.GEMM_TN, (8, 16777224, 69)), (B.GEMM_TN, (16777224, 8, 72))])
+def test_bf16_gemm_on_very_long_rows(layout, shape):
+    Mm, N, K = shape
+    assert picked_tile(layout, Mm, N, K) is not None
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    a = torch.randn((K, Mm) if layout == B.GEMM_TN else (Mm, K), device="cuda", generator=gen, dtype=torch.bfloat16)
+    b = torch.randn((N, K) if layout == B.GEMM_NT else (K, N), device="cuda", generator=gen, dtype=torch.bfloat16)
+    C = torch.full((Mm, N), float("nan"), device="cuda")
+    M.mtnlg_gemm(layout, a, b, C, epilogue=B.EPI_OUT_F32)
+    want = torch.zeros((Mm, N), dtype=torch.float64, device="cuda")
+    for k0 in range(0, K, 1 << 18):
+        k = slice(k0, k0 + (1 << 18))
+        x = a[k].double().T.contiguous() if layout == B.GEMM_TN else a[:, k].double().contiguous()
+        want += x @ (b[:, k].double().T.contiguous() if layout == B.GEMM_NT else b[k].double())
+    # fp32 sums of K terms in one chain: relative error of about 2^-24 sqrt(K) of the result
+    tol = max(TOL["fp32"], 2.0 ** -24 * math.sqrt(K) * 4)
+    assert float((C - want).norm() / want.norm()) <= tol
+    assert float((C - want).abs().max() / want.square().mean().sqrt()) <= 8 * tol
 
 
 # fp32 matrix-instruction GEMM: one element; K shorter than a chunk of 16 and than a wave's share; the 32, 64 and 128 tiles
