@@ -227,6 +227,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A,
                  const void *B, void *C, const void *bias, void *aux, uint32_t epi,
                  hipStream_t stream);
+bool gemm_generic_small_tile(int layout, int64_t M, int64_t N);   // 32 x 32 tiles, not 64 x 64, where accesses are aligned
 // returns MTNLG_UNSUPPORTED_SHAPE when the MFMA kernel cannot take this problem
 // ws (nullable): scratch for the split-K tail, see gemm_mfma_workspace_bytes
 // prof_class: kernel class the launch is timed under (-1: MTNLG_K_GEMM_NT + layout)

@@ -269,17 +269,17 @@ int gemm_generic_of(int layout, const F32GemmArgs &a, bool vec, bool small, hipS
   return launch_f32<E, 4, 4, 1, 1, 4, 2, 1, true>(layout, a, st);
 }
 
+}  // namespace
+
 // 32 x 32 tiles (K split over eight waves) or 64 x 64 tiles (over four): rounds of 256 workgroups times the time of a
 // round at equal K.  Measured (us, K = 1024, 64 / 32): 256 x 256 23 / 10, 1024 x 1024 26 / 33, 1024 x 3072 NT 88 / 95,
 // TN 64 / 100; 256 x 1024 x 256 10 / 5; 2048^3 NT 187 / 228, TN 150 / 236 (115 TFLOP/s; nominal 157).  A round of the 64 x 64
 // tiles costs least where both operands are row-contiguous, whose loads cover whole lines.
-bool small_f32_tile(int layout, int64_t M, int64_t N) {
+bool gemm_generic_small_tile(int layout, int64_t M, int64_t N) {
   const double round64 = layout == MTNLG_GEMM_NT ? 25 : layout == MTNLG_GEMM_NN ? 22 : 20, round32 = 8.5;
   auto rounds = [&](int64_t t) { return (double)((((M + t - 1) / t) * ((N + t - 1) / t) + 255) / 256); };
   return rounds(32) * round32 < rounds(64) * round64;
 }
-
-}  // namespace
 
 int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A,
                  const void *B, void *C, const void *bias, void *aux, uint32_t epi,
@@ -292,8 +292,8 @@ int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const v
   const bool vec = a.lda % 4 == 0 && a.ldb % 4 == 0 && N % 4 == 0 &&
                    !(((uintptr_t)A | (uintptr_t)B | (uintptr_t)bias | (uintptr_t)aux) & unit) && !((uintptr_t)C & c_unit);
   LaunchScope scope(MTNLG_K_GEMM_NT + layout, stream);
-  if (dtype == MTNLG_F32) return gemm_generic_of<float>(layout, a, vec, small_f32_tile(layout, M, N), stream);
-  return gemm_generic_of<bf16>(layout, a, vec, small_f32_tile(layout, M, N), stream);
+  if (dtype == MTNLG_F32) return gemm_generic_of<float>(layout, a, vec, gemm_generic_small_tile(layout, M, N), stream);
+  return gemm_generic_of<bf16>(layout, a, vec, gemm_generic_small_tile(layout, M, N), stream);
 }
 
 }  // namespace mtnlg

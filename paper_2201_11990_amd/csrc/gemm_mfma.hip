@@ -757,11 +757,23 @@ int plan_launch(GemmArgs &g, void *ws, size_t ws_bytes, bool allow_split, unsign
   return MTNLG_OK;
 }
 
+// Whether the 32-bit byte offsets of a tile's DMA reach all it reads: of a K-contiguous operand 128 bytes in each of the tile's rows,
+// of a row-contiguous one the tile's width in each of 64 k-rows.  (Rows of 8 M elements and more on the 256-row tiles, of 16 M on the
+// 128-row tiles, 33 M row-contiguous.)
+bool tile_reaches(bool at, bool bt, int64_t M, int64_t N, int64_t K, int bm, int bn) {
+  auto reach = [&](bool rowc, int64_t rows, int tile) {
+    const int64_t lines = rowc ? BK : tile;
+    return ((lines < (rowc ? K : rows) ? lines : (rowc ? K : rows)) - 1) * (rowc ? rows : K) * 2 + (rowc ? 2 * tile : 2 * BK);
+  };
+  return reach(at, M, bm) <= (int64_t)RAG_RECORDS && reach(bt, N, bn) <= (int64_t)RAG_RECORDS;
+}
+
 // Streaming kernel.  Without RAG: M a multiple of BM, N of BN, K of 64.  Only 256 x 256 tiles split a last round along K.
 template <int BM, int BN, int WGM, int WGN, int DEEP, bool AT, bool BT, bool RAG>
 int launch_stream(const GemmArgs &in, void *ws, size_t ws_bytes, hipStream_t st) {
   GemmArgs g = in;
   if (!RAG && (g.M % BM || g.N % BN || g.K % BK)) return MTNLG_UNSUPPORTED_SHAPE;
+  if (!tile_reaches(AT, BT, g.M, g.N, g.K, BM, BN)) return MTNLG_UNSUPPORTED_SHAPE;
   unsigned grid;
   SplitPlan plan;
   MTNLG_TRY((plan_launch<BM, BN>(g, ws, ws_bytes, BM == 256 && BN == 256, &grid, &plan)));
@@ -826,18 +838,6 @@ double time_128(int64_t tiles, int nk) {
 }
 double time_128_deep(int64_t tiles, int nk) { return (double)((tiles + 255) / 256) * (0.53 * nk + 4.5); }
 
-// Whether the 32-bit byte offsets of a tile's DMA reach all it reads: of a K-contiguous operand 128 bytes in each of the tile's rows,
-// of a row-contiguous one the tile's width in each of 64 k-rows.  (Rows of 8 M elements and more on the 256-row tiles, of 16 M on the
-// 128-row tiles, 33 M row-contiguous.)
-bool tile_reaches(int layout, int64_t M, int64_t N, int64_t K, int bm, int bn) {
-  const bool at = layout == MTNLG_GEMM_TN, bt = layout != MTNLG_GEMM_NT;
-  auto reach = [&](bool rowc, int64_t rows, int tile) {
-    const int64_t lines = rowc ? BK : tile;
-    return ((lines < (rowc ? K : rows) ? lines : (rowc ? K : rows)) - 1) * (rowc ? rows : K) * 2 + (rowc ? 2 * tile : 2 * BK);
-  };
-  return reach(at, M, bm) <= (int64_t)RAG_RECORDS && reach(bt, N, bn) <= (int64_t)RAG_RECORDS;
-}
-
 }  // namespace
 
 // Which tile shape takes a problem: the least estimated time among those whose DMA reaches the operands, -1 if none does.  A last
@@ -845,10 +845,11 @@ bool tile_reaches(int layout, int64_t M, int64_t N, int64_t K, int bm, int bn) {
 int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
   if (M <= 0 || N <= 0 || K <= 0) return -1;
   const int nk = (int)((K + BK - 1) / BK);
+  const bool at = layout == MTNLG_GEMM_TN, bt = layout != MTNLG_GEMM_NT;
   double best = 1e300;
   int pick = -1;
   auto offer = [&](int tile, int bm, int bn, double t) {
-    if (t < best && tile_reaches(layout, M, N, K, bm, bn)) { best = t; pick = tile; }
+    if (t < best && tile_reaches(at, bt, M, N, K, bm, bn)) { best = t; pick = tile; }
   };
   auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const bool aligned = K % BK == 0 && M % 256 == 0;

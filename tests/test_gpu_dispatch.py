@@ -41,6 +41,25 @@ def picked_tile(layout, Mm, N, K, ws_bytes=0):
     return None if t < 0 else TILES[t]
 
 
+def gemm_on_tile(tile, layout, a, b, C, epilogue=0, bias=None, aux=None, workspace=None):
+    """A bf16 product on the named tile, whatever the dispatch would take."""
+    fn = B.lib()._ZN5mtnlg14gemm_mfma_bf16EilllPKvS1_PvS1_S2_jS2_mP12ihipStream_tii
+    vp, i64 = ctypes.c_void_p, ctypes.c_int64
+    fn.argtypes = [ctypes.c_int, i64, i64, i64, vp, vp, vp, vp, vp, ctypes.c_uint32, vp, ctypes.c_size_t, vp, ctypes.c_int, ctypes.c_int]
+    fn.restype = ctypes.c_int
+    ptr = lambda t: 0 if t is None else t.data_ptr()
+    K = a.shape[0] if layout == B.GEMM_TN else a.shape[1]
+    status = fn(layout, C.shape[0], C.shape[1], K, ptr(a), ptr(b), ptr(C), ptr(bias), ptr(aux), epilogue, ptr(workspace),
+                0 if workspace is None else workspace.numel(), torch.cuda.current_stream().cuda_stream, -1, TILES.index(tile))
+    assert status == 0
+
+
+def small_fp32_tile(layout, Mm, N):
+    fn = B.lib()._ZN5mtnlg23gemm_generic_small_tileEill
+    fn.argtypes, fn.restype = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64], ctypes.c_bool
+    return fn(layout, Mm, N)
+
+
 # Rows so long that a tile's DMA offsets pass 2^31 bytes (K-contiguous from 4.2 M elements on, row-contiguous from 16.8 M): still
 # the bf16 kernels, and the right rows.
 @pytest.mark.parametrize("layout,shape", [(B.GEMM_NT, (136, 128, 9000008)), (B.GEMM_NN, (8, 16777224, 72)),
@@ -64,7 +83,7 @@ def test_bf16_gemm_on_very_long_rows(layout, shape):
     assert float((C - want).abs().max() / want.square().mean().sqrt()) <= 8 * tol
 
 
-# fp32 matrix-instruction GEMM: one element; K shorter than a chunk of 16 and than a wave's share; the 32, 64 and 128 tiles
+# fp32 matrix-instruction GEMM: one element; K shorter than a chunk of 16 and than a wave's share; the 32 and 64 tiles
 # with remainders on every side; widths that are no multiple of 4 take the scalar accesses.
 F32_SHAPES = [(1, 4, 4), (1, 1, 1), (33, 36, 20), (31, 64, 132), (900, 1156, 44), (1000, 3076, 20), (2044, 2052, 36), (66, 130, 17)]
 
@@ -82,10 +101,35 @@ def test_fp32_gemm_tiles_and_remainders(layout, shape):
     assert_close(C, 2 * want, TOL["fp32"], f"f32 gemm {layout} {shape} accumulate")
 
 
+# The 64 x 64 tiles with several 32-k chunks for each of the four waves of a K split and a K tail; bf16: row lengths that are
+# multiples of 4 but not of 8.
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
-def test_vector_gemm_takes_operands_aligned_to_one_element(dtype, layout):
-    Mm, N, K = 70, 68, 52   # bf16: a K (NT, NN) or an M and N (TN) that the bf16 kernels do not take
+@pytest.mark.parametrize("shape", [(1020, 1020, 1044), (1024, 1012, 268), (960, 1020, 132)])
+def test_fp32_gemm_large_tile_with_long_k(dtype, layout, shape):
+    Mm, N, K = shape
+    assert not small_fp32_tile(layout, Mm, N)
+    assert dtype == "fp32" or N % 8 or K % 8   # not a product of the bf16 kernels
+    A, Bm = operands(layout, Mm, N, K, dtype)
+    bias, res = randn((N,), dtype, 7), randn((Mm, N), dtype, 8)
+    a, b = dev(A), dev(Bm)
+    want = gemm_oracle(layout, A, Bm)
+    C = torch.full((Mm, N), float("nan"), device="cuda")
+    M.mtnlg_gemm(layout, a, b, C, epilogue=B.EPI_OUT_F32 if dtype == "bf16" else 0)
+    assert_close(C, want, TOL["fp32"], f"{dtype} gemm {layout} {shape}")
+    out, Z = (torch.full((Mm, N), float("nan"), dtype=DT[dtype], device="cuda") for _ in range(2))
+    M.mtnlg_gemm(layout, a, b, out, bias=dev(bias), aux=dev(res), epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
+    assert_close(out, want + to_np(bias) + to_np(res), TOL[dtype], f"{dtype} gemm {layout} {shape} bias + residual")
+    M.mtnlg_gemm(layout, a, b, out, bias=dev(bias), aux=Z, epilogue=B.EPI_BIAS | B.EPI_GELU)
+    assert_close(Z, want + to_np(bias), TOL[dtype], f"{dtype} gemm {layout} {shape} pre-activation")
+    assert_close(out, oracle.gelu(want + to_np(bias)), TOL[dtype], f"{dtype} gemm {layout} {shape} GeLU")
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("Mm", [70, 72])   # 72: the weight-gradient form has 4-element accesses to lose
+def test_vector_gemm_takes_operands_aligned_to_one_element(dtype, layout, Mm):
+    N, K = 68, 52   # bf16: a K (NT, NN) or an N (TN) that the bf16 kernels do not take
     A, Bm = operands(layout, Mm, N, K, dtype)
     bias, res = randn((N,), dtype, 7), randn((Mm, N), dtype, 8)
     want = gemm_oracle(layout, A, Bm) + to_np(bias) + to_np(res)
@@ -122,31 +166,63 @@ def test_embedding_token_search_and_positions(dtype, b, s, h, V, vs):
 # bf16 MFMA GEMM, one shape or more per tile kind: 128 x 128 (one element wide, less than a tile, K tails), the same with deep
 # rings (more and fewer slabs than stages), 256 x 256 with ragged edges, and the aligned 256 x 256 and 256 x 320 tiles.  In
 # the weight-gradient form K is not even a multiple of 8.
-BF16_TILES = [(1, 8, 8), (129, 136, 72), (256, 128, 192), (136, 264, 1032), (72, 136, 1096), (2047, 8184, 72), (2048, 8192, 128),
-              (2048, 10240, 64)]
+BF16_TILES = [((1, 8, 8), "ragged 128"), ((129, 136, 72), "ragged 128"), ((256, 128, 192), "ragged 128"),
+              ((136, 264, 1032), "ragged 128 deep"), ((72, 136, 1096), "ragged 128 deep"), ((2047, 8184, 72), "ragged 256"),
+              ((2048, 8192, 128), "stream 256x256"), ((2048, 10240, 64), "stream 256x320")]
 
 
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
-@pytest.mark.parametrize("shape", BF16_TILES)
-def test_bf16_gemm_tile_kinds_and_ragged_edges(layout, shape):
+@pytest.mark.parametrize("shape,tile", BF16_TILES)
+def test_bf16_gemm_tile_kinds_and_ragged_edges(layout, shape, tile):
     Mm, N, K = shape
     if layout == B.GEMM_TN and K % 64:
         Mm, K = (Mm + 7) // 8 * 8 if Mm < 2000 else Mm // 8 * 8, K - 5
+    assert picked_tile(layout, Mm, N, K) == tile
+    check_bf16_gemm(layout, Mm, N, K, M.mtnlg_gemm)
+
+
+# Every tile by name, small enough for all elements: 1 slab to more than twice the stages of any of its rings, several tiles each
+# way, and (256 x 256) the last round split along K with a part of 8 slabs and one of fewer.
+NAMED = [("stream 256x256", 256, 256), ("stream 256x320", 256, 320), ("ragged 256", 264, 328), ("ragged 128", 136, 264),
+         ("ragged 128 deep", 264, 136)]
+
+
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5, 9])
+@pytest.mark.parametrize("tile,rows,cols", NAMED)
+def test_bf16_gemm_on_each_tile_by_slabs(layout, slabs, tile, rows, cols):
+    for Mm, N in ((rows, cols), (2 * rows, 3 * cols)) if slabs in (4, 9) else ((rows, cols),):
+        K = 64 * slabs - (16 if tile.startswith("ragged") else 0)
+        check_bf16_gemm(layout, Mm, N, K, lambda *a, **k: gemm_on_tile(tile, *a, **k))
+
+
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("tile,Mm,N,K", [("stream 256x256", 256, 512, 2048), ("stream 256x256", 512, 256, 64 * 25),
+                                         ("ragged 256", 264, 520, 64 * 31 + 8)])
+def test_bf16_gemm_split_along_k(layout, tile, Mm, N, K):
+    ws = torch.full((M.mtnlg_gemm_workspace(B.BF16, layout, Mm, N, K),), 0xFF, dtype=torch.uint8, device="cuda")
+    assert ws.numel() > 0
+    check_bf16_gemm(layout, Mm, N, K, lambda *a, **k: gemm_on_tile(tile, *a, workspace=ws, **k))
+    assert not bool((ws == 0xFF).all()), "the partial tiles went somewhere else"
+
+
+def check_bf16_gemm(layout, Mm, N, K, gemm):
     A, Bm = operands(layout, Mm, N, K, "bf16")
+    what = f"bf16 gemm {layout} {Mm} {N} {K}"
     want = gemm_oracle(layout, A, Bm)
     a, b = dev(A), dev(Bm)
     C = torch.full((Mm, N), float("nan"), dtype=torch.bfloat16, device="cuda")
-    M.mtnlg_gemm(layout, a, b, C)
-    assert_close(C, want, TOL["bf16"], f"bf16 gemm {layout} {shape}")
+    gemm(layout, a, b, C)
+    assert_close(C, want, TOL["bf16"], what)
     bias, res = randn((N,), "bf16", 7), randn((Mm, N), "bf16", 8)
     C.fill_(float("nan"))
-    M.mtnlg_gemm(layout, a, b, C, bias=dev(bias), aux=dev(res), epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
-    assert_close(C, want + to_np(bias) + to_np(res), TOL["bf16"], f"bf16 gemm {layout} {shape} bias + residual")
+    gemm(layout, a, b, C, bias=dev(bias), aux=dev(res), epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
+    assert_close(C, want + to_np(bias) + to_np(res), TOL["bf16"], f"{what} bias + residual")
     C32 = torch.full((Mm, N), float("nan"), device="cuda")
-    M.mtnlg_gemm(layout, a, b, C32, epilogue=B.EPI_OUT_F32)
-    assert_close(C32, want, TOL["fp32"], f"bf16 gemm {layout} {shape} fp32 out")
-    M.mtnlg_gemm(layout, a, b, C32, epilogue=B.EPI_OUT_F32 | B.EPI_ACCUMULATE)
-    assert_close(C32, 2 * want, TOL["fp32"], f"bf16 gemm {layout} {shape} fp32 accumulate")
+    gemm(layout, a, b, C32, epilogue=B.EPI_OUT_F32)
+    assert_close(C32, want, TOL["fp32"], f"{what} fp32 out")
+    gemm(layout, a, b, C32, epilogue=B.EPI_OUT_F32 | B.EPI_ACCUMULATE)
+    assert_close(C32, 2 * want, TOL["fp32"], f"{what} fp32 accumulate")
 
 
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])

@@ -46,9 +46,9 @@ def test_gemm_plain(dtype, layout, shape):
     assert_close(C, gemm_oracle(layout, A, Bm), TOL[dtype], f"gemm {layout} {shape}")
 
 
-# Aligned shapes that take the streaming kernel whole, every element against the oracle: one and several slabs of K
-# (the DMA ring's prologue and its clamped look-ahead), one and several tiles of both tile widths (N a multiple of
-# 320 takes the 256 x 320 tile in all three forms), several row tiles.
+# Aligned shapes, every element against the oracle: one and several slabs of K, one and several tiles of the widths 256 and
+# 320, several row tiles.  The dispatch takes 128 x 128 tiles for problems this small; test_gpu_dispatch.py runs each of the
+# streaming kernel's tiles by name.
 STREAM_SHAPES = [(256, 320, 64), (256, 640, 128), (512, 320, 192), (256, 256, 64), (512, 512, 128), (768, 960, 256)]
 
 
@@ -91,9 +91,9 @@ def test_gemm_fused_activation_backward_at_fp32_accuracy(shape):
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
 @pytest.mark.parametrize("shape", [(520, 776, 4104), (256, 512, 2048)])
 def test_gemm_split_k_tail_with_workspace(layout, shape):
-    """Few output tiles and a long K: with workspace the tiles are split along K and summed by a
-    second kernel; the result must match the oracle and, bit for bit in bf16 terms, stay within
-    tolerance of the unsplit run."""
+    """Few output tiles and a long K: with workspace the first shape's 256 x 256 tiles are split along K and summed by a
+    second kernel (the second shape takes 128 x 128 tiles either way; test_gpu_dispatch.py splits aligned tiles by name); the
+    result must match the oracle with and without workspace."""
     Mm, N, K = shape
     a_shape = (Mm, K) if layout != B.GEMM_TN else (K, Mm)
     b_shape = (N, K) if layout == B.GEMM_NT else (K, N)
