@@ -367,7 +367,7 @@ int mtnlg_stage_step_accumulate(const mtnlg_layer_desc *desc, int n_layers, cons
 
 size_t mtnlg_gemm_workspace(int dtype, int layout, int64_t M, int64_t N, int64_t K) {
   if (layout < 0 || layout > 2) return 0;
-  return dtype == MTNLG_BF16 ? gemm_mfma_workspace_bytes(layout, M, N, K) : 0;
+  return dtype == MTNLG_BF16 ? gemm_mfma_workspace_bytes(M, N, K) : 0;
 }
 
 int mtnlg_gemm(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B, void *C,

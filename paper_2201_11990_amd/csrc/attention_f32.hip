@@ -11,7 +11,7 @@
 // Bound by the fp32 matrix rate where there are enough rows, else by each wave's chain of loads, MFMAs and exponentials.
 // bf16 inputs need not be widened for the products of two inputs (q k^T, da v^T, D): those run on the bf16 matrix
 // instructions with fp32 sums.  2 x 1024 tokens, 16 heads of 96, forward / backward: 162 / 540 us with all products on the
-// fp32 instructions, 109 / 350 us so.  (P and dS cut into three bf16 parts that add up to them exactly, for the other products:
+// fp32 instructions, 104 / 327 us so.  (P and dS cut into three bf16 parts that add up to them exactly, for the other products:
 // slower, 237 us forward; the waves wait for loads by then, and 32-row steps leave fewer of them.)
 // A wave owns 16 rows of one side (queries forward and for dq, keys for dk / dv) and walks the other side 16 or 32 rows
 // at a time; fragments are loaded from global memory straight into the registers the MFMAs read (at this matrix rate a

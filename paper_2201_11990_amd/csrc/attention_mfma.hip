@@ -168,10 +168,6 @@ __device__ __forceinline__ void pipelined(L &&load, M &&mma, X &&extra) {
   pipelined_start<N, P>(load);
   pipelined_run<N, P>(load, mma, extra);
 }
-template <int N, int P, typename L, typename M>
-__device__ __forceinline__ void pipelined(L &&load, M &&mma) {
-  pipelined<N, P>(load, mma, [](int) {});
-}
 
 // wait until at most N of this wave's memory operations are outstanding, then the workgroup barrier
 template <int N>
@@ -453,7 +449,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
     kv.advance();
     cur = cur == 2 ? 0 : cur + 1;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the clamped look-ahead tiles
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the look-ahead tiles, which nobody reads
 
 #pragma unroll
   for (int qg = 0; qg < G; ++qg) {

@@ -12,7 +12,6 @@ typedef __bf16 bf16;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // Storage <-> fp32.  float -> bf16 is round-to-nearest-even (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ float to_f32(float v) { return v; }
@@ -22,7 +21,6 @@ template <> __device__ __forceinline__ float from_f32<float>(float v) { return v
 template <> __device__ __forceinline__ bf16 from_f32<bf16>(float v) { return (bf16)v; }
 
 // 8 consecutive elements as one unit (16 B for bf16, 32 B for float).
-template <typename E> struct Vec8 { E v[8]; };
 template <typename E> __device__ __forceinline__ void load8(const E *p, float (&out)[8]) {
   if constexpr (sizeof(E) == 2) {
     bf16x8 t = *reinterpret_cast<const bf16x8 *>(p);
@@ -238,7 +236,7 @@ int gemm_mfma_bf16(int layout, int64_t M, int64_t N, int64_t K, const void *A, c
                    void *C, const void *bias, void *aux, uint32_t epi, void *ws, size_t ws_bytes,
                    hipStream_t stream, int prof_class = -1, int tile = -1);
 int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes);
-size_t gemm_mfma_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K);
+size_t gemm_mfma_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int attention_fwd_f32(int dtype, int b, int s, int n, int d, float scale, const void *qkv,
                          void *a, float *lse, hipStream_t stream);
 int attention_bwd_f32(int dtype, int b, int s, int n, int d, float scale, const void *qkv,

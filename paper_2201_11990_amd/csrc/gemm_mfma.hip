@@ -181,12 +181,12 @@ __device__ __forceinline__ void tile_coords(const GemmArgs &g, int pid, int &tm,
 // in u for every k).  A transposing fragment read touches, per 16-lane group, k-rows k0 .. k0+3 (k0 a multiple
 // of 4) at two neighbouring units, and the four groups of a wave sit 8 k-rows apart.
 //   32 units (512-byte k-rows, every k-row starts on the same bank): k & 3 moves the 64-byte group, k bit 3 the
-//     32-byte pair inside it.
+//     32-byte pair inside it.  16 units (256-byte k-rows): the same.
 //   40 units (640-byte k-rows: consecutive k-rows already sit half the bank space apart): k bit 1 and k bit 3
 //     move the 32-byte pair inside the aligned 128-byte group, which keeps units 32 .. 39 in place.
 template <int UPR>
 __device__ __forceinline__ int tr_pos(int u, int k) {
-  if constexpr (UPR == 32 || UPR == 16) return (((u >> 2) ^ (k & 3)) << 2) | ((u & 3) ^ ((k >> 2) & 2));
+  if constexpr (UPR == 32) return (((u >> 2) ^ (k & 3)) << 2) | ((u & 3) ^ ((k >> 2) & 2));
   else return (u & ~7) | ((u & 7) ^ ((k & 2) | ((k >> 1) & 4)));
 }
 
@@ -864,8 +864,9 @@ int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_b
 
 // Room for the partial tiles of a 256 x 256 tiling's split last round.  What callers size their scratch by, so it
 // does not follow every choice of gemm_mfma_pick_tile: a problem that another tile takes may use none of it.  Aligned
-// problems that 256 x 320 tiles cover in less area of whole rounds ask for none.
-size_t gemm_mfma_workspace_bytes(int, int64_t M, int64_t N, int64_t K) {
+// problems of a width that only 320 divides, and those that 256 x 320 tiles cover in less area of whole rounds, ask for none
+// (with more than is asked for, 256 x 960 x 8192 would be split on ragged 256 x 256 tiles: estimated 37 us, 72 without).
+size_t gemm_mfma_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   if (M <= 0 || N <= 0 || K <= 0) return 0;
   const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
   const SplitPlan plan = plan_split(tiles256, (int)((K + BK - 1) / BK), 256, 256, 0);
