@@ -168,8 +168,9 @@ def optimizer_step_bench(weights, reps=3):
 
 
 # kernel symbol of each GEMM class in the rocprofv3 summaries: gemm_stream_kernel<BM, BN, A transposed, B transposed, ...>
-CLASS_SYMBOL = {"gemm_nt": r"gemm_stream_kernel<\d+, \d+, false, false", "gemm_nn": r"gemm_stream_kernel<\d+, \d+, false, true",
-                "gemm_tn": r"gemm_stream_kernel<\d+, \d+, true, true"}
+# kernel symbol of a GEMM class: gemm_stream_kernel<BM, BN, WGM, WGN, DEEP, A transposed, B transposed, ...>
+CLASS_SYMBOL = {cls: r"gemm_stream_kernel<(\d+, ){5}" + forms
+                for cls, forms in (("gemm_nt", "false, false"), ("gemm_nn", "false, true"), ("gemm_tn", "true, true"))}
 
 
 def counter_traffic(cls):
