@@ -127,29 +127,17 @@ static int ln_fwd_launch(int64_t T, int64_t h, const void *x, const void *partia
 // build up in its registers while the rows stream through once from HBM:
 //   pass 1 over the row: xhat, dxh = dout*gamma -> row sums m1 = mean(dxh), m2 = mean(dxh*xhat)
 //   pass 2: dx = dres + rs * (dxh - m1 - xhat*m2)
-// GW is what covers the row with NV = 1 (one wave up to 512 columns, all 16 from 4097 on): a row of 2048 columns on all
-// 16 waves left three of four idle.  With NV = 1 the row stays in registers between the passes and the next row's loads
+// GW is what covers the row with NV = 1 (one wave up to 512 columns, all 16 from 4097 on; all 16 for few rows too): a row of 2048
+// columns on all 16 waves left three of four idle.  With NV = 1 the row stays in registers between the passes and the next row's loads
 // are issued before this row's reduction; with more, pass 2 reads it again from L2 (holding three groups of two operands
 // costs half the waves that hide latency).  8192 x 2048: 81 -> 31 us; 2048 x 20480 (NV = 3): 104 us, 4.4 TB/s.
 // The groups' sums are added through LDS; workgroup b leaves its column sums in ws[o][b][h]; a second kernel adds
 // them in a fixed order.
 constexpr int LNB_THREADS = 1024, LNB_MAX_WGS = 256;
-
-// 8 consecutive elements as loaded
-template <typename E> struct Raw8;
-template <> struct Raw8<bf16> {
-  bf16x8 v;
-  __device__ __forceinline__ void load(const bf16 *p) { v = *reinterpret_cast<const bf16x8 *>(p); }
-  __device__ __forceinline__ float operator[](int e) const { return (float)v[e]; }
-};
-template <> struct Raw8<float> {
-  f32x4 a, b;
-  __device__ __forceinline__ void load(const float *p) {
-    a = *reinterpret_cast<const f32x4 *>(p);
-    b = *reinterpret_cast<const f32x4 *>(p + 4);
-  }
-  __device__ __forceinline__ float operator[](int e) const { return e < 4 ? a[e] : b[e - 4]; }
-};
+// Elements below which a row gets a whole workgroup whatever its width: with few rows the launch is a chain of latencies, and
+// groups that share a workgroup add the merge of their column sums to it.  bf16, us, whole workgroup / by width: 16 x 512 5.7 / 8.5,
+// 256 x 512 7.7 / 8.7, 64 x 2048 7.0 / 7.7, 64 x 4096 8.2 / 8.3; from 2^18 elements on 512 x 512 9.2 / 9.0, 256 x 1024 8.7 / 8.2.
+constexpr int64_t LNB_FEW = 1 << 18;
 
 template <typename E, int NV, int GW, bool CS>
 __global__ __launch_bounds__(LNB_THREADS) void ln_bwd_fused_kernel(
@@ -198,7 +186,7 @@ __global__ __launch_bounds__(LNB_THREADS) void ln_bwd_fused_kernel(
           db[0][e] += dv;
         }
       }
-      fetch(row + R);
+      if (base + R < row1) fetch(row + R);   // the same in the whole workgroup
     } else {
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
@@ -412,7 +400,7 @@ static int ln_bwd_launch(int64_t T, int64_t h, const void *x, const void *gamma,
                          void *workspace, hipStream_t st) {
   const int nvec = (int)(h / 8);
   // waves to a row, and at least as many rows to a workgroup as it takes at a time: fewer partial sums to add
-  const int gw = nvec <= 64 ? 1 : nvec <= 128 ? 2 : nvec <= 256 ? 4 : nvec <= 512 ? 8 : 16;
+  const int gw = T * h < LNB_FEW ? 16 : nvec <= 64 ? 1 : nvec <= 128 ? 2 : nvec <= 256 ? 4 : nvec <= 512 ? 8 : 16;
   int rows_per = (int)((T + LNB_MAX_WGS - 1) / LNB_MAX_WGS);
   if (rows_per < 16 / gw) rows_per = 16 / gw;
   const int nwg = (int)((T + rows_per - 1) / rows_per);  // <= ln_bwd_workgroups(T)

@@ -360,10 +360,11 @@ def test_attention_with_one_dominating_key(b, d):
     assert_close(dqkv, oracle.attention_bwd(dims, to_np(qkv), to_np(da)), TOL["bf16"], "attention dqkv")
 
 
-# LayerNorm backward: the widths between which the number of waves to a row changes (512, 1024, 2048, 4096 columns) and the
-# row count per thread (8192, 16384, 24576); fewer rows than a workgroup takes at a time, and several turns of the row loop.
+# LayerNorm backward: the widths between which the number of waves to a row changes (512, 1024, 2048, 4096 columns; below 2^18
+# elements all 16 whatever the width) and the row count per thread (8192, 16384, 24576); fewer rows than a workgroup takes at a time,
+# and several turns of the row loop with and without a remainder.
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("T,h", [(1, 8), (3, 512), (700, 512), (259, 520), (40, 1024), (9, 1032), (1030, 2048), (5, 2056), (600, 4096),
+@pytest.mark.parametrize("T,h", [(1, 8), (3, 512), (700, 512), (259, 520), (40, 1024), (9, 1032), (1030, 2048), (511, 512), (513, 512), (505, 520), (515, 1024), (300, 1032), (130, 2056), (1100, 8), (5, 2056), (600, 4096),
                                  (3, 4104), (300, 8192), (2, 8200), (2, 16392), (2, 24584)])
 def test_layernorm_backward_widths_and_rows(dtype, T, h):
     x, dout, dres = randn((T, h), dtype, 1), randn((T, h), dtype, 2), randn((T, h), dtype, 3)
