@@ -68,24 +68,27 @@ __global__ __launch_bounds__(256) void add_positions_kernel(int64_t h, int seq, 
 
 // dE[v] = sum over tokens t (in order) with tokens[t] == vocab_start + v of dx[t].
 // Workgroup (bx, by): the vocabulary rows bx + k 2^stride_log2, k < EB_ROWS, and columns 2048 by .. + 2047 (8 per thread).
-// The token ids are searched 64 at a time by a wave -- one ballot per vocabulary row gives the matching tokens as a bit
-// mask in LDS -- and the matching rows of dx are then added in token order, eight loads in flight.  Fixed order, no
-// atomics.  A workgroup's rows lie far apart because neighbouring ids tend to be about equally frequent: with 8
-// consecutive rows the workgroup of the 8 most frequent ids was the whole kernel's tail.
+// The token ids are searched 64 at a time by a wave: one ballot gives the tokens of any of the workgroup's rows as a bit
+// mask in LDS, a byte per token says which row.  The matching rows of dx are then fetched in token order, eight loads in flight
+// whatever rows they belong to, and each is added to its row.  Fixed order, no atomics.  A workgroup's rows lie far apart
+// because neighbouring ids tend to be about equally frequent: with 8 consecutive rows the workgroup of the 8 most
+// frequent ids was the whole kernel's tail.
 // Bound by HBM once the search is parallel (dE written, dx read: 346 MB at 2048 tokens, 6400 x 20480); with every
-// workgroup walking the ids one by one for one row the search was 99 % of 9560 us.
+// workgroup walking the ids one by one for one row the search was 99 % of 9560 us.  With few tokens it is a chain of latencies, or of
+// workgroups that have next to nothing to do: masks and fetches row by row took 11.4 us for 32 tokens in 16 rows of 256 (7.3 now),
+// 40 us for one token in 51200 rows of 16 (under 15 now), and 219 us where the call takes 196 now (2048 tokens, 6400 x 20480).
 __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {   // v: the same in every lane
   return ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
          (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
 }
-constexpr int EB_ROWS = 8, EB_GROUPS = 64;   // EB_GROUPS 64-token masks per row: 4096 tokens a round
+constexpr int EB_ROWS = 8, EB_GROUPS = 64;   // EB_GROUPS 64-token masks: 4096 tokens a round
 template <typename E>
 __global__ __launch_bounds__(256) void embedding_bwd_kernel(int64_t T, int64_t h, int vocab_local, int vocab_start,
                                                             int stride_log2, const int32_t *__restrict__ tokens,
                                                             const E *__restrict__ dx, E *__restrict__ dE) {
-  __shared__ unsigned long long mask[EB_ROWS][EB_GROUPS];
-  __shared__ unsigned long long groups[EB_ROWS];   // which masks of a row are not empty
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ unsigned long long mask[EB_GROUPS];
+  __shared__ unsigned char row_of[64 * EB_GROUPS];   // of the tokens in the masks
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int v0 = blockIdx.x;
   const int64_t c = (int64_t)blockIdx.y * 2048 + threadIdx.x * 8;
   float acc[EB_ROWS][8];
@@ -94,69 +97,62 @@ __global__ __launch_bounds__(256) void embedding_bwd_kernel(int64_t T, int64_t h
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[r][e] = 0.0f;
   for (int64_t t0 = 0; t0 < T; t0 += 64 * EB_GROUPS) {
-    int row[EB_GROUPS / 4];   // which of the workgroup's rows this lane's token of group 4 i + wave is, or -1
+    const int groups = (int)((T - t0 + 63) / 64 < EB_GROUPS ? (T - t0 + 63) / 64 : EB_GROUPS);
+    if (t0 > 0) __syncthreads();   // the masks of the previous round are no longer read
+    for (int q0 = wave; q0 < groups; q0 += 16) {
+      int id[4];   // four groups' loads in flight
 #pragma unroll
-    for (int i = 0; i < EB_GROUPS / 4; ++i) {
-      const int64_t t = t0 + (4 * i + wave) * 64 + lane;
-      const int64_t d = t < T ? (int64_t)tokens[t] - vocab_start : -1;
-      row[i] = d >= 0 && d < vocab_local && (d & ((1 << stride_log2) - 1)) == v0 ? (int)(d >> stride_log2) : -1;
-    }
-    __syncthreads();   // the masks of the previous round are no longer read
-#pragma unroll
-    for (int i = 0; i < EB_GROUPS / 4; ++i) {
-      unsigned long long m = 0;   // lane k < EB_ROWS: the mask of row k
-      if (__ballot(row[i] >= 0) != 0) {
-#pragma unroll
-        for (int k = 0; k < EB_ROWS; ++k) {
-          const unsigned long long b = __ballot(row[i] == k);
-          if (lane == k) m = b;
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int64_t t = t0 + (q0 + 4 * i) * 64 + lane;
+        id[i] = tokens[t < T ? t : T - 1];
       }
-      if (lane < EB_ROWS) mask[lane][4 * i + wave] = m;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int q = q0 + 4 * i;
+        if (q >= groups) break;
+        const int64_t d = (int64_t)id[i] - vocab_start;
+        const bool mine = t0 + q * 64 + lane < T && d >= 0 && d < vocab_local && (d & ((1 << stride_log2) - 1)) == v0;
+        if (mine) row_of[q * 64 + lane] = (unsigned char)(d >> stride_log2);
+        const unsigned long long b = __ballot(mine);
+        if (lane == 0) mask[q] = b;
+      }
     }
     __syncthreads();
-    for (int r = wave; r < EB_ROWS; r += 4) {
-      const unsigned long long b = __ballot(mask[r][lane] != 0);
-      if (lane == 0) groups[r] = b;
-    }
-    __syncthreads();
+    unsigned long long left = __ballot(lane < groups && mask[lane < groups ? lane : 0] != 0), word = 0;   // masks that are not empty
+    int base = 0;
+    // the next matching token of this round, or -1; the same in every thread
+    auto next = [&]() -> int {
+      if (word == 0) {
+        if (left == 0) return -1;
+        const int q = __builtin_ctzll(left);
+        left &= left - 1;
+        word = uniform64(mask[q]);
+        base = q * 64;
+      }
+      const int k = __builtin_ctzll(word);
+      word &= word - 1;
+      return base + k;
+    };
+    while (left != 0 || word != 0) {
+      int t[8], row[8];
+      Raw8<E> d[8];
 #pragma unroll
-    for (int r = 0; r < EB_ROWS; ++r) {
-      unsigned long long left = uniform64(groups[r]), word = 0;
-      int64_t base = 0;
-      // the next matching token, or -1; the same in every thread
-      auto next = [&]() -> int64_t {
-        if (word == 0) {
-          if (left == 0) return -1;
-          const int q = __builtin_ctzll(left);
-          left &= left - 1;
-          word = uniform64(mask[r][q]);
-          base = t0 + q * 64;
-        }
-        const int k = __builtin_ctzll(word);
-        word &= word - 1;
-        return base + k;
-      };
-      auto add = [&](const float (&d)[8]) {
+      for (int i = 0; i < 8; ++i) t[i] = next();
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[r][e] += d[e];
-      };
-      while (left != 0 || word != 0) {
-        int64_t t[8];
-        float d[8][8];
+      for (int i = 0; i < 8; ++i) row[i] = row_of[t[i] >= 0 ? t[i] : t[0]];
+      if (c < h) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) t[i] = next();
-        if (c < h) {
-          if (t[1] < 0) {   // a single match, the usual case
-            load8(dx + t[0] * h + c, d[0]);
-            add(d[0]);
-          } else {
+        for (int i = 0; i < 8; ++i)
+          if (t[i] >= 0) d[i].load(dx + (t0 + t[i]) * h + c);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) load8(dx + (t[i] >= 0 ? t[i] : t[0]) * h + c, d[i]);
+        for (int i = 0; i < 8; ++i) {
+          const int r_now = __builtin_amdgcn_readfirstlane(t[i] >= 0 ? row[i] : EB_ROWS);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-              if (t[i] >= 0) add(d[i]);
-          }
+          for (int r = 0; r < EB_ROWS; ++r)
+            if (r_now == r) {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) acc[r][e] += d[i][e];
+            }
         }
       }
     }
