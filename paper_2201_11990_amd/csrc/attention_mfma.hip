@@ -6,8 +6,8 @@
 //   dq = scale dS k,  dk = scale dS^T q,  dv = P^T da.
 //
 // Three kernels of eight waves.  A workgroup owns rows of one side (forward: 128 or 256 queries, 16 or 32 per wave;
-// dq and dk/dv: 64 queries or keys, 16 per wave, each half of the workgroup on one half of every tile), held in
-// registers as MFMA B operands (groups of 16, one row per lane column); the other side streams through
+// dq and dk/dv: 64 queries or keys, 16 per wave, each half of the workgroup on one half of every tile, or 128 with a block
+// to each half), held in registers as MFMA B operands (groups of 16, one row per lane column); the other side streams through
 // LDS in tiles of 64 rows, brought in by LDS DMA (buffer_load ... lds, no staging
 // registers) three tiles deep, one workgroup barrier per tile.  What bounds them: no single unit.  Between two barriers a
 // wave runs LDS reads, MFMAs, the softmax and the DMA issue in one chain, and the waves of a workgroup run it in step, so
@@ -226,7 +226,7 @@ struct PairedBlocks {
     last_tile = hi * G + G - 1 < nb ? hi * G + G - 1 : nb - 1;
     idle = half && hi == lo;
   }
-  static int count(int s) { return (((s + 63) / 64 + G - 1) / G + 1) / 2; }
+  static __host__ __device__ int count(int s) { return (((s + 63) / 64 + G - 1) / G + 1) / 2; }
 };
 
 // The backward kernels: a workgroup owns one 64-row block (queries for dq, keys for dk / dv), 16 rows to each of waves 0-3
@@ -238,24 +238,55 @@ struct PairedBlocks {
 // now 163, 430, 430.  (In the forward kernel, which has fewer registers to save, the merge costs more than it gives.)
 __host__ __device__ inline int row_blocks(int s) { return (s + 63) / 64; }
 
-// Which head a workgroup works on, and at which place of the head's order of blocks: heads run fastest, so where heads x
-// sequences is a multiple of 8 all workgroups of a head run on one XCD (they are dealt out in turn) and its L2 serves
-// every tile after the first reading.  Measured with the blocks running fastest before, forward at 4 x 2048 x 16 heads:
-// head size 64 61-64 us, 128 113-116, 160 122; now 55, 102, 105.  (Neighbouring heads on one XCD, instead of every
-// eighth: backward 2 % slower.)
+// Over many sequences the work evens out by itself, and what a workgroup costs besides its tiles (its own rows, the first
+// tiles, the merge, the results: 12-17 us at head sizes 128 and 160) counts instead.  PAIRED has half the workgroups: waves 0-3
+// and 4-7 own blocks p and nb - 1 - p and take whole tiles, as in the forward kernel, with nothing to merge.  32 x 16 heads of 160,
+// us: s 80 halves 64, paired 52; 128 88, 70; 256 175, 149; 768 699, 652.  16 heads, s = 1990: 103, 113.  bwd_paired() chooses.
+template <bool PAIRED>
+struct BackwardBlocks {
+  int block;      // this wave's 64-row block
+  int lo, hi;     // lowest and highest of the workgroup's
+  bool idle;      // wave-uniform: this wave owns no rows
+  __device__ BackwardBlocks(int s, int order, int wave) {
+    lo = order;
+    hi = PAIRED ? row_blocks(s) - 1 - order : order;
+    block = wave >> 2 ? hi : lo;
+    idle = PAIRED && wave >> 2 && hi == lo;
+  }
+  static __host__ __device__ int count(int s) { return PAIRED ? (row_blocks(s) + 1) / 2 : row_blocks(s); }
+};
+
+// Which head a workgroup works on, and at which place of the head's order of blocks.  The heads of all sequences are numbered
+// through and a grid row takes `group` of them, heads fastest: with a multiple of 8 all workgroups of a head run on one XCD (they
+// are dealt out in turn) and its L2 serves every tile after the first reading.  Measured with the blocks running fastest, forward
+// at 4 x 2048 x 16 heads: head size 64 61-64 us, 128 113-116, 160 122; with the heads fastest 55, 102, 105.
+// Rows of about 32 heads, 4 to an XCD, because with all heads in one row the L2 holds too little of each to serve it: forward
+// at 32 x 16 heads, s = 768, head size 64 97 us in one row, 71 in rows; 160 207, 168; backward of 64 at s = 1024 473, 418.
+// One row where (nearly) all workgroups are in flight at once or few wait, and the order by length matters more: forward at
+// 256 heads of 64, s = 320 (768 workgroups) 13.2 us in one row, 14.8 in rows; the backward by halves, of head size 64, does
+// better with 128 heads to a row.  The rows are evened out, and the last is as short as it has to be: places without work at
+// the end of every row unbalance the chip (128 x 100 heads, s = 1990, in rows of 32 places: backward 682 us instead of 577).
 struct HeadBlock {
   int head, batch, order;
-  __device__ HeadBlock(int n, int heads) {   // heads: n x the sequences of a grid row
-    const int hb = blockIdx.x % heads;
-    head = hb % n;
-    batch = blockIdx.y * (heads / n) + hb / n;
-    order = blockIdx.x / heads;
+  bool none;   // nothing left at this place of the last row
+  __device__ HeadBlock(int b, int n, int group, int count) {   // count: blocks of a head
+    const unsigned heads = (unsigned)b * (unsigned)n, first = blockIdx.y * (unsigned)group;
+    const unsigned here = heads - first < (unsigned)group ? heads - first : (unsigned)group;
+    const unsigned hb = first + blockIdx.x % here;
+    order = blockIdx.x / here;
+    head = hb % (unsigned)n;
+    batch = hb / (unsigned)n;
+    none = order >= count;
   }
-  // Sequences that share a grid row: up to 2^16 workgroups are 256 for each compute unit, enough for the order to even
-  // out (2^9 or 2^10: backward up to 10 % slower), and the grid stays within its limits for every batch.
-  static int sequences(int b, int n, int count) {
-    const int fit = (1 << 16) / (n * count);
-    return fit < 1 ? 1 : fit < b ? fit : b;
+  static int group(int b, int n, int count, int want, int few) {   // few: up to how many workgroups one row takes all
+    const int64_t heads = (int64_t)b * n;
+    int64_t rows = heads * count <= few || heads < want ? 1 : heads / want;
+    if (rows > 65535) rows = 65535;   // the grid's limit
+    const int64_t even = ((heads + rows - 1) / rows + 7) / 8 * 8;
+    return (int)(even < heads ? even : heads);
+  }
+  static dim3 grid(int b, int n, int group, int count) {
+    return dim3((unsigned)group * count, (unsigned)(((int64_t)b * n + group - 1) / group));
   }
 };
 
@@ -266,14 +297,14 @@ __device__ __forceinline__ f32x4 *merge_slots(char *smem, int wave, int lane, in
 
 // ------------------------------------------------------------------ forward
 template <int D, int G>
-__global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int heads, float scale, const bf16 *__restrict__ qkv,
+__global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int group, float scale, const bf16 *__restrict__ qkv,
                                                       bf16 *__restrict__ a, float *__restrict__ lse) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES;
-  const HeadBlock hb(n, heads);
+  const HeadBlock hb(b, n, group, PairedBlocks<G>::count(s));
   const int j = hb.head, bi = hb.batch;
-  if (bi >= b) return;   // past the last sequence of the last grid row
+  if (hb.none) return;
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
   const int64_t ld = (int64_t)n * 3 * D;
@@ -471,23 +502,26 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
 }
 
 // ------------------------------------------------------------------ backward: dq (and D)
-template <int D>
-__global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, int heads, float scale, const bf16 *__restrict__ qkv,
+template <int D, bool PAIRED>
+__global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, int group, float scale, const bf16 *__restrict__ qkv,
                                                          const bf16 *__restrict__ a, const float *__restrict__ lse,
                                                          const bf16 *__restrict__ da, bf16 *__restrict__ dqkv,
                                                          float *__restrict__ Dvec) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES;
-  const HeadBlock hb(n, heads);
-  const int j = hb.head, bi = hb.batch, block = row_blocks(s) - 1 - hb.order;
-  if (bi >= b) return;   // past the last sequence of the last grid row
+  constexpr int NB = PAIRED ? 4 : 2, NS = NB / 2;   // 16-row blocks and 32-row slots of a tile that a wave takes
+  const HeadBlock hb(b, n, group, BackwardBlocks<PAIRED>::count(s));
+  const int j = hb.head, bi = hb.batch;
+  if (hb.none) return;
+  // from the thread number: as in the forward kernel
+  const BackwardBlocks<PAIRED> bb(s, PAIRED ? hb.order : row_blocks(s) - 1 - hb.order, threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
   const int64_t ld = (int64_t)n * 3 * D, pld = (int64_t)n * D;
   const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * D;
-  const int qw = block * 64 + ((threadIdx.x >> 6) & 3) * 16;   // from the thread number: as in the forward kernel
-  const int k_half = (wave >> 2) * 32;   // first key of this wave's half of a tile
+  const int qw = bb.block * 64 + ((threadIdx.x >> 6) & 3) * 16;
+  const int k_half = PAIRED ? 0 : (wave >> 2) * 32;   // first key of a tile that this wave takes
   const float c = scale * kLog2e;
   typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
@@ -509,7 +543,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
     dsum = quad_sum(dsum);
   }
   float lse2 = lse[((int64_t)bi * n + j) * s + qc] * kLog2e;
-  if (q < s && g == 0 && wave < 4) Dvec[((int64_t)bi * n + j) * s + q] = -dsum;   // as the dk/dv kernel starts its accumulators
+  if (q < s && g == 0 && (PAIRED ? !bb.idle : wave < 4)) Dvec[((int64_t)bi * n + j) * s + q] = -dsum;   // as the dk/dv kernel starts its accumulators
 
   f32x4 dq[DB];
 #pragma unroll
@@ -517,7 +551,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
 #pragma unroll
     for (int e = 0; e < 4; ++e) dq[db][e] = 0.0f;
 
-  const int ntiles = block + 1;
+  const int ntiles = bb.hi + 1;
   // tile DMAs as in the forward kernel
   constexpr int IPW = T::NI;   // DMA instructions per wave and tile
   const int quarter = wave & 3, half = wave >> 2;
@@ -529,7 +563,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
     constexpr int TAG = decltype(tag)::value;
     dma16<TAG>(kv.rsrc(), smem_addr + st * STAGE + half * T::BYTES + (quarter * IPW + i) * 1024, dma_off[i]);
   };
-  constexpr int STEPS = KK + DB / 2;   // MFMA steps of a tile
+  constexpr int STEPS = NS * (KK + DB / 2);   // MFMA steps of a tile
   auto issue_step = [&](int step, int st) {
 #pragma unroll
     for (int i = 0; i < IPW; ++i)
@@ -557,68 +591,85 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
     const int nn = cur == 0 ? 2 : cur - 1;
     const char *Kt = smem + cur * STAGE + k_half * (T::ROWS16 / 16), *Vt = Kt + T::BYTES;
     const int kv0 = it * 64 + k_half;
-    if (kv0 > qw + 15) {
+    if (bb.idle || kv0 > qw + 15) {
       issue(nn);
     } else {
-      f32x4 sc[2], pc[2];   // pc accumulates dP - D
+      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
+      for (int kb = 0; kb < NB; ++kb) {
         pc[kb] = f32x4{-dsum, -dsum, -dsum, -dsum};
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[kb][e] = 0.0f;
       }
-      {  // step i: k-step i
+      {  // step i: k-step i / NS, key blocks 2 (i % NS) and + 1
         constexpr int P = 2;   // steps that the reads run ahead
         bf16x8 kfr[P + 1][2], vfr[P + 1][2];
-        pipelined<KK, P>(
+        pipelined<NS * KK, P>(
             [&](int i) {
 #pragma unroll
               for (int h = 0; h < 2; ++h) {
-                kfr[i % (P + 1)][h] = T::nat(Kt, ln, h, i);
-                vfr[i % (P + 1)][h] = T::nat(Vt, ln, h, i);
+                kfr[i % (P + 1)][h] = T::nat(Kt, ln, 2 * (i % NS) + h, i / NS);
+                vfr[i % (P + 1)][h] = T::nat(Vt, ln, 2 * (i % NS) + h, i / NS);
               }
             },
             [&](int i) {
 #pragma unroll
               for (int h = 0; h < 2; ++h) {
-                sc[h] = MFMA16(kfr[i % (P + 1)][h], qf[i], sc[h]);
-                pc[h] = MFMA16(vfr[i % (P + 1)][h], dof[i], pc[h]);
+                const int kb = 2 * (i % NS) + h;
+                sc[kb] = MFMA16(kfr[i % (P + 1)][h], qf[i / NS], sc[kb]);
+                pc[kb] = MFMA16(vfr[i % (P + 1)][h], dof[i / NS], pc[kb]);
               }
             },
             [&](int i) { issue_step(i, nn); });
       }
       // dS^T = P^T o (dP^T - D); element (kb, e): key kv0 + 16 kb + 4 g + e, query qc
-      constexpr int PT = 3;
+      constexpr int PT = 3, HB = DB / 2;
       bf16x8 ktr[PT + 1][2];
-      auto load = [&](int i) {   // step i: output blocks 2 i, 2 i + 1
+      auto load = [&](int i) {   // step i: key slot i / HB, output blocks 2 (i % HB) and + 1
 #pragma unroll
-        for (int h = 0; h < 2; ++h) ktr[i % (PT + 1)][h] = T::tr(Kt, ln, 2 * i + h, 0);
+        for (int h = 0; h < 2; ++h) ktr[i % (PT + 1)][h] = T::tr(Kt, ln, 2 * (i % HB) + h, i / HB);
       };
-      pipelined_start<DB / 2, PT>(load);
-      if (kv0 + 31 > qw) {  // wave-uniform: diagonal (or past-the-end keys) among this wave's keys
+      pipelined_start<NS * HB, PT>(load);
+      if (kv0 + 16 * NB - 1 > qw) {  // wave-uniform: diagonal (or past-the-end keys) among this wave's keys
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             if (kv0 + 16 * kb + 4 * g + e > qc) sc[kb][e] = -INFINITY;
       }
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[kb][e] = fast_exp2(fmaf(sc[kb][e], c, -lse2)) * pc[kb][e];
-      const bf16x8 df = pack2(sc[0], sc[1]);
-      pipelined_run<DB / 2, PT>(
+      bf16x8 df[NS];
+#pragma unroll
+      for (int ks = 0; ks < NS; ++ks) df[ks] = pack2(sc[2 * ks], sc[2 * ks + 1]);
+      pipelined_run<NS * HB, PT>(
           load,
           [&](int i) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) dq[2 * i + h] = MFMA16(ktr[i % (PT + 1)][h], df, dq[2 * i + h]);
+            for (int h = 0; h < 2; ++h)
+              dq[2 * (i % HB) + h] = MFMA16(ktr[i % (PT + 1)][h], df[i / HB], dq[2 * (i % HB) + h]);
           },
-          [&](int i) { issue_step(KK + i, nn); });
+          [&](int i) { issue_step(NS * KK + i, nn); });
     }
     kv.advance();
     cur = cur == 2 ? 0 : cur + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  auto store = [&](int db, const f32x4 &sum) {
+    bf16x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (bf16)(sum[e] * scale);
+    *reinterpret_cast<bf16x4 *>(dqkv + ((int64_t)bi * s + q) * ld + (int64_t)j * 3 * D + db * 16 + 4 * g) = v;
+  };
+  if constexpr (PAIRED) {
+    if (q < s && !bb.idle) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db) store(db, dq[db]);
+    }
+    return;
+  }
   __syncthreads();   // the rings are no longer read
   f32x4 *slots = merge_slots(smem, wave, lane, DB);
   if (wave >= 4) {
@@ -627,37 +678,33 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
   }
   __syncthreads();
   if (wave < 4 && q < s) {
-    bf16 *out = dqkv + ((int64_t)bi * s + q) * ld + (int64_t)j * 3 * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const f32x4 sum = dq[db] + slots[db * 64];
-      bf16x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (bf16)(sum[e] * scale);
-      *reinterpret_cast<bf16x4 *>(out + db * 16 + 4 * g) = v;
-    }
+    for (int db = 0; db < DB; ++db) store(db, dq[db] + slots[db * 64]);
   }
 }
 
 // ------------------------------------------------------------------ backward: dk, dv
-template <int D>
-__global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, int heads, float scale, const bf16 *__restrict__ qkv,
+template <int D, bool PAIRED>
+__global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, int group, float scale, const bf16 *__restrict__ qkv,
                                                            const float *__restrict__ lse,
                                                            const float *__restrict__ Dvec,
                                                            const bf16 *__restrict__ da, bf16 *__restrict__ dqkv) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES + 512;   // Q tile, dO tile, lse[64], D[64]
-  const HeadBlock hb(n, heads);
-  const int j = hb.head, bi = hb.batch, block = hb.order;
-  if (bi >= b) return;   // past the last sequence of the last grid row
+  constexpr int NB = PAIRED ? 4 : 2, NS = NB / 2;   // as in the dq kernel
+  constexpr bool LATE = PAIRED && D == 160;   // fewer fragments read ahead: no room in the registers
+  const HeadBlock hb(b, n, group, BackwardBlocks<PAIRED>::count(s));
+  const int j = hb.head, bi = hb.batch;
+  if (hb.none) return;
+  const BackwardBlocks<PAIRED> bb(s, hb.order, threadIdx.x >> 6);   // (from the thread number; head size 160: 194 registers instead of 230)
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
   const int64_t ld = (int64_t)n * 3 * D, pld = (int64_t)n * D;
   const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * D;
   const bf16 *dab = da + (int64_t)bi * s * pld + (int64_t)j * D;
-  const int kw = block * 64 + ((threadIdx.x >> 6) & 3) * 16;   // (head size 160: 194 registers instead of 230)
-  const int q_half = (wave >> 2) * 32;   // first query of this wave's half of a tile
+  const int kw = bb.block * 64 + ((threadIdx.x >> 6) & 3) * 16;
+  const int q_half = PAIRED ? 0 : (wave >> 2) * 32;   // first query of a tile that this wave takes
   const float c = scale * kLog2e;
   typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
@@ -675,7 +722,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
 #pragma unroll
     for (int e = 0; e < 4; ++e) dk[db][e] = dv[db][e] = 0.0f;
 
-  const int t_first = block, ntiles = row_blocks(s) - t_first;
+  const int t_first = bb.lo, ntiles = row_blocks(s) - t_first;
   // tile DMAs as in the forward kernel (Q tile and dO tile), plus one instruction per wave for the
   // tile's lse values (even waves) or -D values (odd waves); those arrive four times over, so that every wave
   // issues the same number of memory operations, which the counted waits rely on
@@ -696,7 +743,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
       dma16<TAG>(qo.rsrc(), stage + half * T::BYTES + (quarter * IPW + i) * 1024, dma_off[i < IPW ? i : 0]);
     }
   };
-  constexpr int STEPS = KK + DB;   // MFMA steps of a tile; the statistics count as instruction IPW
+  constexpr int STEPS = NS * (KK + DB);   // MFMA steps of a tile; the statistics count as instruction IPW
   auto issue_step = [&](int step, int st) {
 #pragma unroll
     for (int i = 0; i <= IPW; ++i)
@@ -727,45 +774,48 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
     const char *Qt = smem + cur * STAGE + q_half * (T::ROWS16 / 16), *Ot = Qt + T::BYTES;
     const float *stat = reinterpret_cast<const float *>(smem + cur * STAGE + 2 * T::BYTES) + q_half;
     const int q0 = (t_first + it) * 64 + q_half;
-    if (q0 + 31 < kw) {  // wave-uniform: none of this wave's queries sees one of its keys
+    if (bb.idle || q0 + 16 * NB - 1 < kw) {  // wave-uniform: none of this wave's queries sees one of its keys
       issue(nn);
     } else {
-      f32x4 sc[2], pc[2];   // pc accumulates dP - D
+      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
+      for (int qb = 0; qb < NB; ++qb) {
         pc[qb] = *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[qb][e] = 0.0f;
       }
-      {  // step i: k-step i
-        bf16x8 qfr[3][2], ofr[3][2];
-        pipelined<KK, 2>(
+      {  // step i: k-step i / NS, query blocks 2 (i % NS) and + 1
+        constexpr int P = LATE ? 1 : 2;
+        bf16x8 qfr[P + 1][2], ofr[P + 1][2];
+        pipelined<NS * KK, P>(
             [&](int i) {
 #pragma unroll
               for (int h = 0; h < 2; ++h) {
-                qfr[i % 3][h] = T::nat(Qt, ln, h, i);
-                ofr[i % 3][h] = T::nat(Ot, ln, h, i);
+                qfr[i % (P + 1)][h] = T::nat(Qt, ln, 2 * (i % NS) + h, i / NS);
+                ofr[i % (P + 1)][h] = T::nat(Ot, ln, 2 * (i % NS) + h, i / NS);
               }
             },
             [&](int i) {
 #pragma unroll
               for (int h = 0; h < 2; ++h) {
-                sc[h] = MFMA16(qfr[i % 3][h], kf[i], sc[h]);
-                pc[h] = MFMA16(ofr[i % 3][h], vf[i], pc[h]);
+                const int qb = 2 * (i % NS) + h;
+                sc[qb] = MFMA16(qfr[i % (P + 1)][h], kf[i / NS], sc[qb]);
+                pc[qb] = MFMA16(ofr[i % (P + 1)][h], vf[i / NS], pc[qb]);
               }
             },
             [&](int i) { issue_step(i, nn); });
       }
       // element (qb, e): query q0 + 16 qb + 4 g + e, key `key`
-      bf16x8 otr[4], qtr[4];
-      auto load = [&](int i) {   // step i: output block i
-        otr[i & 3] = T::tr(Ot, ln, i, 0);
-        qtr[i & 3] = T::tr(Qt, ln, i, 0);
+      constexpr int PT = LATE ? 2 : 3;
+      bf16x8 otr[PT + 1], qtr[PT + 1];
+      auto load = [&](int i) {   // step i: query slot i / DB, output block i % DB
+        otr[i % (PT + 1)] = T::tr(Ot, ln, i % DB, i / DB);
+        qtr[i % (PT + 1)] = T::tr(Qt, ln, i % DB, i / DB);
       };
-      pipelined_start<DB, 3>(load);
-      if (q0 < kw + 16 || q0 + 31 >= s) {  // wave-uniform: diagonal or past-the-end queries
+      if constexpr (!LATE) pipelined_start<NS * DB, PT>(load);
+      if (q0 < kw + 16 || q0 + 16 * NB - 1 >= s) {  // wave-uniform: diagonal or past-the-end queries
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < NB; ++qb)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int qq = q0 + 16 * qb + 4 * g + e;
@@ -773,7 +823,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
           }
       }
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb) {
+      for (int qb = 0; qb < NB; ++qb) {
         const f32x4 ls = *reinterpret_cast<const f32x4 *>(stat + 16 * qb + 4 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -781,19 +831,43 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
           pc[qb][e] *= sc[qb][e];
         }
       }
-      const bf16x8 pf = pack2(sc[0], sc[1]), df = pack2(pc[0], pc[1]);
-      pipelined_run<DB, 3>(
+      bf16x8 pf[NS], df[NS];
+#pragma unroll
+      for (int ks = 0; ks < NS; ++ks) {
+        pf[ks] = pack2(sc[2 * ks], sc[2 * ks + 1]);
+        df[ks] = pack2(pc[2 * ks], pc[2 * ks + 1]);
+      }
+      if constexpr (LATE) pipelined_start<NS * DB, PT>(load);
+      pipelined_run<NS * DB, PT>(
           load,
           [&](int i) {
-            dv[i] = MFMA16(otr[i & 3], pf, dv[i]);
-            dk[i] = MFMA16(qtr[i & 3], df, dk[i]);
+            dv[i % DB] = MFMA16(otr[i % (PT + 1)], pf[i / DB], dv[i % DB]);
+            dk[i % DB] = MFMA16(qtr[i % (PT + 1)], df[i / DB], dk[i % DB]);
           },
-          [&](int i) { issue_step(KK + i, nn); });
+          [&](int i) { issue_step(NS * KK + i, nn); });
     }
     advance();
     cur = cur == 2 ? 0 : cur + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  auto store = [&](int db, const f32x4 &sk, const f32x4 &sv) {
+    bf16 *out = dqkv + ((int64_t)bi * s + key) * ld + (int64_t)j * 3 * D;
+    bf16x4 ok, ov;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      ok[e] = (bf16)(sk[e] * scale);
+      ov[e] = (bf16)sv[e];
+    }
+    *reinterpret_cast<bf16x4 *>(out + D + db * 16 + 4 * g) = ok;
+    *reinterpret_cast<bf16x4 *>(out + 2 * D + db * 16 + 4 * g) = ov;
+  };
+  if constexpr (PAIRED) {
+    if (key < s && !bb.idle) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db) store(db, dk[db], dv[db]);
+    }
+    return;
+  }
   __syncthreads();   // the rings are no longer read
   f32x4 *slots = merge_slots(smem, wave, lane, 2 * DB);
   if (wave >= 4) {
@@ -805,19 +879,8 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
   }
   __syncthreads();
   if (wave < 4 && key < s) {
-    bf16 *out = dqkv + ((int64_t)bi * s + key) * ld + (int64_t)j * 3 * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const f32x4 sk = dk[db] + slots[db * 64], sv = dv[db] + slots[(DB + db) * 64];
-      bf16x4 ok, ov;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        ok[e] = (bf16)(sk[e] * scale);
-        ov[e] = (bf16)sv[e];
-      }
-      *reinterpret_cast<bf16x4 *>(out + D + db * 16 + 4 * g) = ok;
-      *reinterpret_cast<bf16x4 *>(out + 2 * D + db * 16 + 4 * g) = ov;
-    }
+    for (int db = 0; db < DB; ++db) store(db, dk[db] + slots[db * 64], dv[db] + slots[(DB + db) * 64]);
   }
 }
 
@@ -839,9 +902,9 @@ int fwd_launch_g(int b, int s, int n, float scale, const void *qkv, void *a, flo
       return MTNLG_HIP_ERROR;
     attr_mark_set(attr_done, device);
   }
-  const int count = PairedBlocks<G>::count(s), bx = HeadBlock::sequences(b, n, count), heads = n * bx;
+  const int count = PairedBlocks<G>::count(s), group = HeadBlock::group(b, n, count, 32, D >= 128 ? 511 : 768);   // (768: 3 a compute unit)
   LaunchScope scope(MTNLG_K_ATTN_FWD, st);
-  attn_fwd_kernel<D, G><<<dim3(heads * count, (b + bx - 1) / bx), 512, smem, st>>>(b, s, n, heads, scale, (const bf16 *)qkv, (bf16 *)a, lse);
+  attn_fwd_kernel<D, G><<<HeadBlock::grid(b, n, group, count), 512, smem, st>>>(b, s, n, group, scale, (const bf16 *)qkv, (bf16 *)a, lse);
   return check_launch();
 }
 
@@ -852,28 +915,63 @@ int fwd_launch(int b, int s, int n, float scale, const void *qkv, void *a, float
 }
 
 // 16 rows per wave in both backward kernels: 32 do not fit the 256 registers a wave has at eight waves.
-template <int D>
-int bwd_launch(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
-               void *dqkv, void *ws, hipStream_t st) {
+template <int D, bool PAIRED>
+int bwd_launch_p(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
+                 void *dqkv, void *ws, hipStream_t st) {
   constexpr int smem_dq = 3 * 2 * 64 * D * 2, smem_dkv = 3 * (2 * 64 * D * 2 + 512);
   static_assert(smem_dkv >= 4 * 2 * (D / 16) * 1024, "the merge of the two halves fits the rings");
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    if (hipFuncSetAttribute((const void *)attn_bwd_dq_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dq) != hipSuccess ||
-        hipFuncSetAttribute((const void *)attn_bwd_dkv_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dkv) != hipSuccess)
+    if (hipFuncSetAttribute((const void *)attn_bwd_dq_kernel<D, PAIRED>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dq) != hipSuccess ||
+        hipFuncSetAttribute((const void *)attn_bwd_dkv_kernel<D, PAIRED>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dkv) != hipSuccess)
       return MTNLG_HIP_ERROR;
     attr_mark_set(attr_done, device);
   }
   float *Dvec = (float *)ws;
-  const int bx = HeadBlock::sequences(b, n, row_blocks(s)), heads = n * bx;
-  const dim3 grid(heads * row_blocks(s), (b + bx - 1) / bx);
+  const int count = BackwardBlocks<PAIRED>::count(s), group = HeadBlock::group(b, n, count, PAIRED || D >= 128 ? 32 : 128, PAIRED ? 511 : 2047);
+  const dim3 grid = HeadBlock::grid(b, n, group, count);
   LaunchScope scope(MTNLG_K_ATTN_BWD, st);
-  attn_bwd_dq_kernel<D><<<grid, 512, smem_dq, st>>>(b, s, n, heads, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da,
-                                                    (bf16 *)dqkv, Dvec);
+  attn_bwd_dq_kernel<D, PAIRED><<<grid, 512, smem_dq, st>>>(b, s, n, group, scale, (const bf16 *)qkv, (const bf16 *)a, lse,
+                                                           (const bf16 *)da, (bf16 *)dqkv, Dvec);
   MTNLG_TRY(check_launch());
-  attn_bwd_dkv_kernel<D><<<grid, 512, smem_dkv, st>>>(b, s, n, heads, scale, (const bf16 *)qkv, lse, Dvec, (const bf16 *)da, (bf16 *)dqkv);
+  attn_bwd_dkv_kernel<D, PAIRED><<<grid, 512, smem_dkv, st>>>(b, s, n, group, scale, (const bf16 *)qkv, lse, Dvec, (const bf16 *)da,
+                                                             (bf16 *)dqkv);
   return check_launch();
+}
+
+// What either backward kernel takes for `heads` heads of nb blocks in `count` workgroups each, of nb tiles and fewer: the longest
+// workgroup where all run at once, else the work spread over the compute units and a part of a last, shortest workgroup.
+struct BackwardCost {
+  double tile, fixed, tail;   // us for each tile, for each workgroup; the part of the last workgroup
+  double time(int64_t heads, int nb, int count) const {
+    const double longest = nb * tile + fixed, shortest = (nb - count + 1) * tile + fixed;
+    if (heads * count <= 256) return longest;
+    const double spread = heads * count * ((2 * nb - count + 1) / 2.0 * tile + fixed) / 256 + tail * shortest;
+    return spread > longest ? spread : longest;
+  }
+};
+
+// Two blocks of a head in each workgroup?  At head size 128 and 160, where one workgroup at a time runs on a compute unit, whichever
+// the estimate says; its constants were fitted to 207 and 201 measured sizes (8 to 1024 heads, s 80 to 4096, both kernels), for
+// which the choice costs 0.4 % on average against the better of the two (10 % at most: 160, 96 heads, s = 384).  At head size 64, with three workgroups on a compute unit to
+// cover each other, only for sequences of two blocks that are more than one a unit: 512 heads, s = 80 26.0 us by halves, 23.3 paired;
+// 192, s = 128 17.0, 14.9; but 300, s = 192 31.2, 36.7 and 64, s = 128 11.3 against 13.3.
+template <int D>
+bool bwd_paired(int b, int s, int n) {
+  const int64_t heads = (int64_t)b * n;
+  const int nb = row_blocks(s);
+  if (D < 128) return nb == 2 && heads > 128;
+  constexpr BackwardCost halves = D == 128 ? BackwardCost{1.95, 12.0, 0.5} : BackwardCost{2.1, 14.5, 0.63};
+  constexpr BackwardCost pairs = D == 128 ? BackwardCost{2.6, 13.0, 0.75} : BackwardCost{3.2, 16.5, 0.67};
+  return pairs.time(heads, nb, (nb + 1) / 2) < halves.time(heads, nb, nb);
+}
+
+template <int D>
+int bwd_launch(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
+               void *dqkv, void *ws, hipStream_t st) {
+  if (bwd_paired<D>(b, s, n)) return bwd_launch_p<D, true>(b, s, n, scale, qkv, a, lse, da, dqkv, ws, st);
+  return bwd_launch_p<D, false>(b, s, n, scale, qkv, a, lse, da, dqkv, ws, st);
 }
 
 // The DMA addresses a sequence's rows with 32-bit byte offsets from its first row.

@@ -307,8 +307,8 @@ def test_attention_non_finite_token_stays_where_it_belongs(dtype, d, t0, bad):
                 assert not bool(torch.isfinite(dx[0, :t0 + 1, 1, 2, col].float()).any())
 
 
-# Matrix-core attention over more workgroups than a grid row takes (65536; a sequence here takes 17): sequences do not depend on
-# each other, so two calls on parts that fit one row each give the same bytes.
+# Matrix-core attention over very many heads, whose workgroups are dealt out in rows of a few heads each, in the backward kernels
+# of others than in the forward kernel: sequences do not depend on each other, so two calls on parts give the same bytes.
 def test_attention_batches_of_several_grid_rows():
     b, s, n, d = 4001, 2, 17, 64
     gen = torch.Generator(device="cuda").manual_seed(3)
@@ -326,6 +326,25 @@ def test_attention_batches_of_several_grid_rows():
 
     for whole, first, second in zip(run(0, b), run(0, 2000), run(2000, b)):
         assert torch.equal(whole, torch.cat([first, second]))
+
+
+# Many heads: the backward kernels with two blocks of a head to a workgroup (all but the last case; an even and an odd number of
+# blocks), every kernel with the heads in several grid rows, the last one shorter and no multiple of 8 (forward: the last three;
+# backward: all but the first two).
+@pytest.mark.parametrize("b,s,n,d", [(5, 192, 20, 128), (12, 100, 25, 64), (12, 130, 25, 128), (12, 130, 25, 160), (24, 128, 25, 64),
+                                     (12, 260, 25, 128), (12, 260, 25, 160), (20, 449, 13, 64)])
+def test_attention_of_many_heads(b, s, n, d):
+    qkv, da = randn((b * s, 3 * n * d), "bf16", 21), randn((b * s, n * d), "bf16", 22)
+    dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
+    scale = 1.0 / math.sqrt(d)
+    a = torch.full((b * s, n * d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((b, n, s), float("nan"), device="cuda")
+    M.mtnlg_attention_fwd(b, s, n, d, scale, dev(qkv), a, lse)
+    ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+    dqkv = torch.full(qkv.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+    M.mtnlg_attention_bwd(b, s, n, d, scale, dev(qkv), a, lse, dev(da), dqkv, ws)
+    assert_close(a, oracle.attention_fwd(dims, to_np(qkv)), TOL["bf16"], "attention out")
+    assert_close(dqkv, oracle.attention_bwd(dims, to_np(qkv), to_np(da)), TOL["bf16"], "attention dqkv")
 
 
 # One key that scores 100 (natural units) above all others, head by head at every position modulo 16 and, by sequence, in the
