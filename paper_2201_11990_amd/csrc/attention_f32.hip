@@ -16,8 +16,9 @@
 // A wave owns 16 rows of one side (queries forward and for dq, keys for dk / dv) and walks the other side 16 or 32 rows
 // at a time; fragments are loaded from global memory straight into the registers the MFMAs read (at this matrix rate a
 // wave asks the caches for 8 bytes a cycle), so there is no LDS, no barrier, and a wave stops at its own diagonal.  The four
-// waves of a workgroup own neighbouring rows and share what they load in the L1; a head's workgroups go to one XCD
-// where the number of heads allows it; workgroups with the most work start first.
+// waves of a workgroup own neighbouring rows and share what they load in the L1, or, in small fp32 calls, the same rows, with
+// the other side split between them; a head's workgroups go to one XCD where the number of heads allows it; workgroups with
+// the most work start first.
 //
 // Lane l = 16 g + r.  Two fragment forms of a 16-row block X:
 //   Rows: element (c, e) = X[r][16 c + 4 g + e]; an MFMA per (c, e) contracts over columns.  With Rows of both sides a
@@ -82,7 +83,9 @@ struct Rows<bf16, DP> {
   }
 };
 
-constexpr int SUM_ROWS = 128;
+// Rows that a wave sums in one chain.  (64 where the waves share the streamed side: with 128 dk and dv of some shapes came out up
+// to 5 % less exact than with whole chains in one wave, with 64 nowhere, at 0.7 % of the time.)
+constexpr int sum_rows(bool split) { return split ? 64 : 128; }
 
 template <int DP>
 struct Blocks {   // DP / 16 accumulator blocks over columns, in the order of Cols
@@ -92,8 +95,9 @@ struct Blocks {   // DP / 16 accumulator blocks over columns, in the order of Co
 #pragma unroll
     for (int i = 0; i < N; ++i) b[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
-  // fp32 results: sums over rows are taken SUM_ROWS at a time and added up here, because the error of one chain grows with its
-  // length (s = 2048, head size 64, dk against 64 bits: 1.08e-6 in one chain, 4.1e-7 so, at the same time up to head size 160).  A bf16 result does not show it.
+  // fp32 results: sums over rows are taken sum_rows() at a time and added up here, because the error of one chain grows with its
+  // length (s = 2048, head size 64, dk against 64 bits: 1.08e-6 in one chain, 4.1e-7 so, at the same time up to head size 160).
+  // A bf16 result does not show it.
   __device__ __forceinline__ void flush(Blocks &part) {
 #pragma unroll
     for (int i = 0; i < N; ++i) b[i] += part.b[i];
@@ -255,23 +259,45 @@ __device__ __forceinline__ float dot(const E *x, const E *y, int d, int g) {
   return quad_sum(t);
 }
 
-struct Where {   // grid: (heads, 64-row blocks, batch); a wave owns rows row0 .. row0 + 15
-  int lane, g, r, row0, head, batch;
+// Grid: (heads, blocks of rows, batch).  A wave owns rows row0 .. row0 + 15 and takes part `part` of the other side's steps.
+// A workgroup owns 64 rows, 16 to a wave, or (SPLIT) 16, of which every wave takes a quarter of the steps (every fourth one); the
+// partial results meet in LDS.
+template <bool SPLIT>
+struct Where {
+  int lane, g, r, row0, part, head, batch;
   __device__ __forceinline__ Where(bool last_first) {
     lane = threadIdx.x & 63;
     g = lane >> 4;
     r = lane & 15;
     const int blk = last_first ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
-    row0 = blk * 64 + 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    row0 = SPLIT ? blk * 16 : blk * 64 + 16 * wave;
+    part = SPLIT ? wave : 0;
     head = blockIdx.x;
     batch = blockIdx.z;
   }
 };
+template <int DP>
+struct Meeting {
+  f32x4 slot[3][Blocks<DP>::N][64];
+  __device__ __forceinline__ void add(Blocks<DP> &x, int part, int lane) {   // the sum of all parts, in part 0
+    if (part > 0) {
+#pragma unroll
+      for (int i = 0; i < Blocks<DP>::N; ++i) slot[part - 1][i][lane] = x.b[i];
+    }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int i = 0; i < Blocks<DP>::N; ++i) x.b[i] = (x.b[i] + slot[0][i][lane]) + (slot[1][i][lane] + slot[2][i][lane]);
+  }
+};
 
-template <typename E, int DP>
+template <typename E, int DP, bool SPLIT>
 __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
                                                            E *__restrict__ a, float *__restrict__ lse) {
-  const Where w(true);
+  const Where<SPLIT> w(true);
+  constexpr int STRIDE = SPLIT ? 128 : 32;
+  const int first = 32 * w.part;
   if (w.row0 >= s) return;
   const int64_t ld = (int64_t)n * 3 * d;
   const E *base = qkv + (int64_t)w.batch * s * ld + (int64_t)w.head * 3 * d;
@@ -280,13 +306,13 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, 
   qf.load(base, ld, w.row0, s, d, w.g, w.r);
   const int last = w.row0 + 15 < s ? w.row0 + 15 : s - 1;   // last key any row of the wave sees
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb) kf[kb].load(base + d, ld, 16 * kb, s, d, w.g, w.r);
+  for (int kb = 0; kb < 2; ++kb) kf[kb].load(base + d, ld, first + 16 * kb, s, d, w.g, w.r);
   constexpr bool PARTS = sizeof(E) == 4;
   Blocks<DP> o, total;
   o.clear();
   if constexpr (PARTS) total.clear();
   float m = -INFINITY, l = 0.0f;   // l: this lane's share of the row sum
-  for (int k0 = 0; k0 <= last; k0 += 32) {
+  for (int k0 = first; k0 <= last; k0 += STRIDE) {
     Cols<E, DP> vf[2];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) vf[kb].load(base + 2 * d, ld, k0 + 16 * kb, s, d, w.g, w.r);
@@ -294,7 +320,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, 
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) p[kb] = product(kf[kb], qf) * scale;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) kf[kb].load(base + d, ld, k0 + 32 + 16 * kb, s, d, w.g, w.r);   // of the next step
+    for (int kb = 0; kb < 2; ++kb) kf[kb].load(base + d, ld, k0 + STRIDE + 16 * kb, s, d, w.g, w.r);   // of the next step
     float mx = -INFINITY;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
@@ -303,14 +329,15 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, 
         if (k0 + 16 * kb + 4 * w.g + i > q) p[kb][i] = -INFINITY;
         mx = fmaxf(mx, p[kb][i]);
       }
-    const float m_new = fmaxf(m, quad_max(mx));   // finite: key 0 is never masked
-    const float alpha = expf(m - m_new);
+    const float m_new = fmaxf(m, quad_max(mx));   // finite: key 0 is never masked, but for a part that has seen none of a row's keys
+    const float shift = SPLIT && m_new == -INFINITY ? 0.0f : m_new;
+    const float alpha = expf(m - shift);
     float sum = 0.0f;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        p[kb][i] = expf(p[kb][i] - m_new);
+        p[kb][i] = expf(p[kb][i] - shift);
         sum += p[kb][i];
       }
     l = l * alpha + sum;
@@ -325,10 +352,31 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, 
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) vf[kb].accumulate(o, p[kb]);
     if constexpr (PARTS)
-      if ((k0 + 32) % SUM_ROWS == 0) total.flush(o);
+      if ((k0 / STRIDE + 1) % (sum_rows(SPLIT) / 32) == 0) total.flush(o);
   }
   if constexpr (PARTS) o.flush(total);
   l = quad_sum(l);
+  if constexpr (SPLIT) {   // every part's sums relative to the maximum of all
+    __shared__ float stat[2][4][16];
+    __shared__ Meeting<DP> meet;
+    if (w.g == 0) {
+      stat[0][w.part][w.r] = m;
+      stat[1][w.part][w.r] = l;
+    }
+    __syncthreads();
+    float top = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) top = fmaxf(top, stat[0][i][w.r]);
+    l = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) l = fmaf(stat[1][i][w.r], expf(stat[0][i][w.r] - top), l);
+    const float mul = expf(m - top);
+    m = top;
+#pragma unroll
+    for (int i = 0; i < Blocks<DP>::N; ++i) o.b[i] *= mul;
+    meet.add(o, w.part, w.lane);
+    if (w.part > 0) return;
+  }
   E *out = a + ((int64_t)w.batch * s + q) * ((int64_t)n * d) + (int64_t)w.head * d;
   float *out_lse = lse + ((int64_t)w.batch * n + w.head) * s + q;
   float z = 0.0f;
@@ -363,12 +411,14 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, 
 // dq, and D for the kernel below
 // (fp32, small head sizes: two waves per SIMD are asked for, with which the compiler keeps the accumulators in ordinary registers
 // instead of copying them at every step; 2 x 512 x 16 heads of 64, dq: 3 us less, 1 x 1990 x 16 of 32: 9 us less.)
-template <typename E, int DP>
+template <typename E, int DP, bool SPLIT>
 __global__ __launch_bounds__(256, sizeof(E) == 4 && DP <= 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
                                                               const E *__restrict__ a, const float *__restrict__ lse,
                                                               const E *__restrict__ da, E *__restrict__ dqkv,
                                                               float *__restrict__ D) {
-  const Where w(true);
+  const Where<SPLIT> w(true);
+  constexpr int STRIDE = SPLIT ? 64 : 16;
+  const int first = 16 * w.part;
   if (w.row0 >= s) return;
   const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
   const E *base = qkv + (int64_t)w.batch * s * ld + (int64_t)w.head * 3 * d;
@@ -384,30 +434,35 @@ __global__ __launch_bounds__(256, sizeof(E) == 4 && DP <= 64 ? 2 : 1) void attn_
     const float mine = (w.r & 2) ? ((w.r & 1) ? t[3] : t[2]) : ((w.r & 1) ? t[1] : t[0]);
     dsum = __shfl(mine, 16 * (w.r >> 2) + w.r, 64);
   }
-  if (q < s && w.g == 0) D[st + q] = dsum;
+  if (q < s && w.g == 0 && w.part == 0) D[st + q] = dsum;
   qf.load(base, ld, w.row0, s, d, w.g, w.r);
   const float ls = lse[st + qc];
   const int last = w.row0 + 15 < s ? w.row0 + 15 : s - 1;
-  kf.load(base + d, ld, 0, s, d, w.g, w.r);
-  vf.load(base + 2 * d, ld, 0, s, d, w.g, w.r);
+  kf.load(base + d, ld, first, s, d, w.g, w.r);
+  vf.load(base + 2 * d, ld, first, s, d, w.g, w.r);
   constexpr bool PARTS = sizeof(E) == 4;
   Blocks<DP> dq, total;
   dq.clear();
   if constexpr (PARTS) total.clear();
-  for (int k0 = 0; k0 <= last; k0 += 16) {
+  for (int k0 = first; k0 <= last; k0 += STRIDE) {
     Cols<E, DP> kc;
     kc.load(base + d, ld, k0, s, d, w.g, w.r);
     const f32x4 sc = product(kf, qf) * scale, dp = product(vf, dof);
-    kf.load(base + d, ld, k0 + 16, s, d, w.g, w.r);   // of the next step
-    vf.load(base + 2 * d, ld, k0 + 16, s, d, w.g, w.r);
+    kf.load(base + d, ld, k0 + STRIDE, s, d, w.g, w.r);   // of the next step
+    vf.load(base + 2 * d, ld, k0 + STRIDE, s, d, w.g, w.r);
     f32x4 ds;
 #pragma unroll
     for (int i = 0; i < 4; ++i) ds[i] = k0 + 4 * w.g + i > q ? 0.0f : expf(sc[i] - ls) * (dp[i] - dsum);
     kc.accumulate(dq, ds);
     if constexpr (PARTS)
-      if ((k0 + 16) % SUM_ROWS == 0) total.flush(dq);
+      if ((k0 / STRIDE + 1) % (sum_rows(SPLIT) / 16) == 0) total.flush(dq);
   }
   if constexpr (PARTS) dq.flush(total);
+  if constexpr (SPLIT) {
+    __shared__ Meeting<DP> meet;
+    meet.add(dq, w.part, w.lane);
+    if (w.part > 0) return;
+  }
   E *out = dqkv + ((int64_t)w.batch * s + q) * ld + (int64_t)w.head * 3 * d;
   float z = 0.0f;
   if (q < s) z = dq.store(out, d, scale, w.g);
@@ -424,11 +479,13 @@ __global__ __launch_bounds__(256, sizeof(E) == 4 && DP <= 64 ? 2 : 1) void attn_
   if (q < s) sum.store(out, d, scale, w.g);
 }
 
-template <typename E, int DP>
+template <typename E, int DP, bool SPLIT>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
                                                                const float *__restrict__ lse, const float *__restrict__ D,
                                                                const E *__restrict__ da, E *__restrict__ dqkv) {
-  const Where w(false);
+  const Where<SPLIT> w(false);
+  constexpr int STRIDE = SPLIT ? 64 : 16;
+  const int first = w.row0 + 16 * w.part;
   if (w.row0 >= s) return;
   const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
   const E *base = qkv + (int64_t)w.batch * s * ld + (int64_t)w.head * 3 * d;
@@ -446,9 +503,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int
     tk.clear();
     tv.clear();
   }
-  qf.load(base, ld, w.row0, s, d, w.g, w.r);
-  of.load(dab, pld, w.row0, s, d, w.g, w.r);
-  for (int q0 = w.row0; q0 < s; q0 += 16) {
+  qf.load(base, ld, first, s, d, w.g, w.r);
+  of.load(dab, pld, first, s, d, w.g, w.r);
+  for (int q0 = first; q0 < s; q0 += STRIDE) {
     Cols<E, DP> oc, qcol;
     oc.load(dab, pld, q0, s, d, w.g, w.r);
     qcol.load(base, ld, q0, s, d, w.g, w.r);
@@ -460,8 +517,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int
       dd[i] = D[st + q];
     }
     const f32x4 sc = product(qf, kf) * scale, dp = product(of, vf);
-    qf.load(base, ld, q0 + 16, s, d, w.g, w.r);   // of the next step
-    of.load(dab, pld, q0 + 16, s, d, w.g, w.r);
+    qf.load(base, ld, q0 + STRIDE, s, d, w.g, w.r);   // of the next step
+    of.load(dab, pld, q0 + STRIDE, s, d, w.g, w.r);
     f32x4 p, ds;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -472,7 +529,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int
     oc.accumulate(dv, p);
     qcol.accumulate(dk, ds);
     if constexpr (PARTS)
-      if ((q0 + 16) % SUM_ROWS == 0) {
+      if ((q0 / STRIDE + 1) % (sum_rows(SPLIT) / 16) == 0) {
         tk.flush(dk);
         tv.flush(dv);
       }
@@ -480,6 +537,13 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int
   if constexpr (PARTS) {
     dk.flush(tk);
     dv.flush(tv);
+  }
+  if constexpr (SPLIT) {
+    __shared__ Meeting<DP> meet;
+    meet.add(dk, w.part, w.lane);
+    __syncthreads();
+    meet.add(dv, w.part, w.lane);
+    if (w.part > 0) return;
   }
   E *out = dqkv + ((int64_t)w.batch * s + key) * ld + (int64_t)w.head * 3 * d;
   float z = 0.0f;
@@ -504,23 +568,44 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int
   if (key < s) sum.store(out + d, d, scale, w.g);
 }
 
-template <typename E, int DP>
-int fwd_launch(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
+// Which fp32 calls split the streamed side over the waves of a workgroup: those with up to 512 groups of 16 rows, two workgroups
+// for each compute unit, which leave most of the chip idle with 64 rows to a workgroup, so that a wave's chain of steps is the time.
+// us with 64 rows / 16 rows, forward, then backward: 1 head of 256, s = 256 81.9 / 28.1, 247 / 87; 4 of 64, s = 512 72 / 26,
+// 198 / 65; 16 of 64, s = 512 81 / 39, 214 / 103.  At 1024 groups it is between 0.5 and 1.2 of the time; at s <= 32 there is nothing to share.
+// (bf16 inputs have shorter chains, with their products of two inputs at 16 times the rate.)
+inline bool splits(int b, int s, int n) { return s > 32 && (int64_t)b * n * ((s + 15) / 16) <= 512; }
+
+template <typename E, int DP, bool SPLIT>
+int fwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
+  const dim3 grid(n, SPLIT ? (s + 15) / 16 : (s + 63) / 64, b);
   LaunchScope scope(MTNLG_K_ATTN_FWD, st);
-  attn_fwd_f32_kernel<E, DP><<<dim3(n, (s + 63) / 64, b), 256, 0, st>>>(s, n, d, scale, (const E *)qkv, (E *)a, lse);
+  attn_fwd_f32_kernel<E, DP, SPLIT><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, (E *)a, lse);
   return check_launch();
 }
+template <typename E, int DP>
+int fwd_launch(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
+  if constexpr (sizeof(E) == 4)
+    if (splits(b, s, n)) return fwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, st);
+  return fwd_launch_s<E, DP, false>(b, s, n, d, scale, qkv, a, lse, st);
+}
 
+template <typename E, int DP, bool SPLIT>
+int bwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
+                 void *dqkv, void *ws, hipStream_t st) {
+  float *D = (float *)ws;
+  const dim3 grid(n, SPLIT ? (s + 15) / 16 : (s + 63) / 64, b);
+  LaunchScope scope(MTNLG_K_ATTN_BWD, st);
+  attn_bwd_dq_f32_kernel<E, DP, SPLIT><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, (const E *)a, lse, (const E *)da, (E *)dqkv, D);
+  MTNLG_TRY(check_launch());
+  attn_bwd_dkv_f32_kernel<E, DP, SPLIT><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, lse, D, (const E *)da, (E *)dqkv);
+  return check_launch();
+}
 template <typename E, int DP>
 int bwd_launch(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                void *dqkv, void *ws, hipStream_t st) {
-  float *D = (float *)ws;
-  const dim3 grid(n, (s + 63) / 64, b);
-  LaunchScope scope(MTNLG_K_ATTN_BWD, st);
-  attn_bwd_dq_f32_kernel<E, DP><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, (const E *)a, lse, (const E *)da, (E *)dqkv, D);
-  MTNLG_TRY(check_launch());
-  attn_bwd_dkv_f32_kernel<E, DP><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, lse, D, (const E *)da, (E *)dqkv);
-  return check_launch();
+  if constexpr (sizeof(E) == 4)
+    if (splits(b, s, n)) return bwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
+  return bwd_launch_s<E, DP, false>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
 }
 
 // fn<E, DP>, DP: the head size rounded up to a multiple of 32
