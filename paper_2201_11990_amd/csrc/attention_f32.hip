@@ -16,7 +16,7 @@
 // A wave owns 16 rows of one side (queries forward and for dq, keys for dk / dv) and walks the other side 16 or 32 rows
 // at a time; fragments are loaded from global memory straight into the registers the MFMAs read (at this matrix rate a
 // wave asks the caches for 8 bytes a cycle), so there is no LDS, no barrier, and a wave stops at its own diagonal.  The four
-// waves of a workgroup own neighbouring rows and share what they load in the L1, or, in small fp32 calls, the same rows, with
+// waves of a workgroup own neighbouring rows and share what they load in the L1, or, in small calls, the same rows, with
 // the other side split between them; a head's workgroups go to one XCD where the number of heads allows it; workgroups with
 // the most work start first.
 //
@@ -568,11 +568,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int
   if (key < s) sum.store(out + d, d, scale, w.g);
 }
 
-// Which fp32 calls split the streamed side over the waves of a workgroup: those with up to 512 groups of 16 rows, two workgroups
+// Which calls split the streamed side over the waves of a workgroup: those with up to 512 groups of 16 rows, two workgroups
 // for each compute unit, which leave most of the chip idle with 64 rows to a workgroup, so that a wave's chain of steps is the time.
 // us with 64 rows / 16 rows, forward, then backward: 1 head of 256, s = 256 81.9 / 28.1, 247 / 87; 4 of 64, s = 512 72 / 26,
 // 198 / 65; 16 of 64, s = 512 81 / 39, 214 / 103.  At 1024 groups it is between 0.5 and 1.2 of the time; at s <= 32 there is nothing to share.
-// (bf16 inputs have shorter chains, with their products of two inputs at 16 times the rate.)
 inline bool splits(int b, int s, int n) { return s > 32 && (int64_t)b * n * ((s + 15) / 16) <= 512; }
 
 template <typename E, int DP, bool SPLIT>
@@ -584,8 +583,7 @@ int fwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, void 
 }
 template <typename E, int DP>
 int fwd_launch(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
-  if constexpr (sizeof(E) == 4)
-    if (splits(b, s, n)) return fwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, st);
+  if (splits(b, s, n)) return fwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, st);
   return fwd_launch_s<E, DP, false>(b, s, n, d, scale, qkv, a, lse, st);
 }
 
@@ -603,8 +601,7 @@ int bwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, const
 template <typename E, int DP>
 int bwd_launch(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                void *dqkv, void *ws, hipStream_t st) {
-  if constexpr (sizeof(E) == 4)
-    if (splits(b, s, n)) return bwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
+  if (splits(b, s, n)) return bwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
   return bwd_launch_s<E, DP, false>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
 }
 

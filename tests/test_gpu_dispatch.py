@@ -253,12 +253,13 @@ def test_attention_at_every_compiled_head_size(dtype, b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
 
 
-# ... in fp32 with 64 rows to a workgroup (above 512 groups of 16 rows, and up to 32 rows), and at the edges of the rule: the last
+# ... with 64 rows to a workgroup (above 512 groups of 16 rows, and up to 32 rows), and at the edges of the rule: the last
 # shapes with 16 rows to a workgroup and the streamed side split over its waves.
-@pytest.mark.parametrize("b,s,n,d", [(3, 100, 25, d) for d in (24, 64, 72, 104, 136, 168, 200, 232)]
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("b,s,n,d", [(3, 100, 25, d) for d in (24, 56, 72, 104, 136, 168, 200, 232)]
                          + [(1, 32, 2, 200), (1, 33, 3, 72), (4, 250, 8, 40), (3, 250, 11, 40), (1, 530, 2, 56)])
-def test_fp32_attention_by_rows_of_a_workgroup(b, s, n, d):
-    test_gpu_ops.test_attention_fwd_bwd("fp32", b, s, n, d)
+def test_attention_by_rows_of_a_workgroup(dtype, b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
 
 
 # An infinity or NaN in one token reaches only what depends on that token.  K and V of token t0: outputs and dq of the rows before it
@@ -267,7 +268,7 @@ def test_fp32_attention_by_rows_of_a_workgroup(b, s, n, d):
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 @pytest.mark.parametrize("t0", [0, 32, 37, 63, 89])
 @pytest.mark.parametrize("dtype,n,d", [("fp32", 2, 24), ("fp32", 2, 64), ("fp32", 2, 96), ("bf16", 2, 40), ("bf16", 2, 96),
-                                       ("fp32", 44, 24), ("fp32", 44, 96)])   # 44 heads: 64 rows to a workgroup, else 16
+                                       ("fp32", 44, 24), ("fp32", 44, 96), ("bf16", 44, 96)])   # 44 heads: 64 rows to a workgroup, else 16
 def test_attention_non_finite_token_stays_where_it_belongs(dtype, n, d, t0, bad):
     b, s, col = 2, 90, 5
     dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
