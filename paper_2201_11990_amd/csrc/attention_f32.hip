@@ -479,8 +479,17 @@ __global__ __launch_bounds__(256, sizeof(E) == 4 && DP <= 64 ? 2 : 1) void attn_
   if (q < s) sum.store(out, d, scale, w.g);
 }
 
+// What the compiler is told about waves per SIMD, so that it uses registers as the loop needs them: bf16, head sizes up to 32: 3-4,
+// accumulators in ordinary registers (16 heads of 24, s = 1024: dq + dk/dv 97 us, 90 so); up to 64: no more than 2, else 20 more values
+// go to and fro between the two kinds of register (16 heads of 56, s = 1024: 137 us, 134 so).
+template <typename E, int DP>
+constexpr int dkv_waves(int most) {
+  if (sizeof(E) == 2 && DP == 32) return most ? 4 : 3;
+  if (sizeof(E) == 2 && DP == 64) return most ? 2 : 1;
+  return most ? 8 : 1;
+}
 template <typename E, int DP, bool SPLIT>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dkv_waves<E, DP>(0), dkv_waves<E, DP>(1)))) void attn_bwd_dkv_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
                                                                const float *__restrict__ lse, const float *__restrict__ D,
                                                                const E *__restrict__ da, E *__restrict__ dqkv) {
   const Where<SPLIT> w(false);
