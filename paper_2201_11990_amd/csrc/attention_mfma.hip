@@ -234,8 +234,8 @@ struct PairedBlocks {
 // tile, and their partial results are merged through LDS at the end.  Half the tile per wave halves the registers
 // of its scores and its chain per tile, and no wave idles while the mask leaves work to the other half only.  Blocks are
 // handed out in the order of falling work, so a compute unit that got a long block gets a short one after it.  Measured with
-// paired blocks and whole tiles before, dq + dk/dv at 4 x 2048 tokens x 16 heads: head size 64 279 us, 128 477, 160 475;
-// now 163, 430, 430.  (In the forward kernel, which has fewer registers to save, the merge costs more than it gives.)
+// paired blocks and whole tiles before, dq + dk/dv at 2048 tokens x 16 heads: head size 64 75 us, 128 107, 160 121;
+// now 56, 92, 101.  (In the forward kernel, which has fewer registers to save, the merge costs more than it gives.)
 __host__ __device__ inline int row_blocks(int s) { return (s + 63) / 64; }
 
 // Over many sequences the work evens out by itself, and what a workgroup costs besides its tiles (its own rows, the first
