@@ -388,6 +388,12 @@ int mtnlg_gemm(int dtype, int layout, int64_t M, int64_t N, int64_t K, const voi
     return MTNLG_INVALID_ARG;
   if (dtype == MTNLG_F32) epilogue &= ~MTNLG_EPI_OUT_F32;
   hipStream_t st = (hipStream_t)stream;
+  if (gemm_wave_takes(dtype, layout, M, N, K, A, B, C, bias, aux)) {
+    const double other = dtype == MTNLG_F32 ? gemm_generic_time(layout, M, N, K)
+                                            : gemm_mfma_time(layout, M, N, K, workspace ? workspace_bytes : 0);
+    const int tile = gemm_wave_pick(dtype, layout, M, N, K, other);
+    if (tile) return gemm_wave(dtype, layout, M, N, K, A, B, C, bias, aux, epilogue, tile, st);
+  }
   if (dtype == MTNLG_BF16) {
     int r = gemm_mfma_bf16(layout, M, N, K, A, B, C, bias, aux, epilogue, workspace, workspace_bytes, st);
     if (r != MTNLG_UNSUPPORTED_SHAPE) return r;

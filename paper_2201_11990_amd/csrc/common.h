@@ -205,6 +205,91 @@ __device__ __forceinline__ void epilogue_store(const EpiArgs &ea, void *C, int64
   }
 }
 
+template <typename E> __device__ __forceinline__ float gelu_of(float z, bool erf_form) {
+  if constexpr (sizeof(E) == 2) { if (!erf_form) return gelu_tanh_fast_f(z); }
+  return gelu_f(z, erf_form);
+}
+template <typename E> __device__ __forceinline__ float gelu_grad_of(float z, bool erf_form) {
+  if constexpr (sizeof(E) == 2) { if (!erf_form) return gelu_tanh_grad_fast_f(z); }
+  return gelu_grad_f(z, erf_form);
+}
+// 4 consecutive outputs of row m at column n (n + 3 < N and everything aligned for 4-element accesses)
+template <typename E>
+__device__ __forceinline__ void epilogue4(const EpiArgs &ea, void *C, int64_t N, int64_t m, int64_t n, f32x4 v) {
+  const int64_t off = m * N + n;
+  if (ea.flags & MTNLG_EPI_BIAS) v += load4(static_cast<const E *>(ea.bias) + n);
+  auto put = [&](E *p, f32x4 x) {
+    if constexpr (sizeof(E) == 4) *reinterpret_cast<f32x4 *>(p) = x;
+    else *reinterpret_cast<bf16x4 *>(p) = bf16x4{(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
+  };
+  if (ea.flags & MTNLG_EPI_GELU) {
+    put(static_cast<E *>(ea.aux) + off, v);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = gelu_of<E>(v[e], (ea.flags & MTNLG_EPI_GELU_ERF) != 0);
+  }
+  if (ea.flags & (MTNLG_EPI_RESIDUAL | MTNLG_EPI_GELU_GRAD)) {
+    const f32x4 t = load4(static_cast<const E *>(ea.aux) + off);
+    if (ea.flags & MTNLG_EPI_RESIDUAL) {
+      v += t;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_of<E>(t[e], (ea.flags & MTNLG_EPI_GELU_ERF) != 0);
+    }
+  }
+  if (ea.flags & MTNLG_EPI_OUT_F32) {
+    float *c = static_cast<float *>(C) + off;
+    if (ea.flags & MTNLG_EPI_ACCUMULATE) v += load4(c);
+    *reinterpret_cast<f32x4 *>(c) = v;
+  } else {
+    E *c = static_cast<E *>(C) + off;
+    if (ea.flags & MTNLG_EPI_ACCUMULATE) v += load4(c);
+    put(c, v);
+  }
+}
+
+// One operand of v_mfma_f32_16x16x32_bf16 in N parts that add up to the 8 values of a chunk: bf16 elements are one part, fp32
+// elements three, each the rounded rest of the ones before it (8 + 8 + 8 bits: the rest after three is zero).
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+template <int N>
+struct Parts {
+  bf16x8 p[N];
+  __device__ __forceinline__ void of(const float (&x)[8]) {
+    // (-1, 0) and (0, -1); in registers, because the compiler writes the first as the inline constant of 32 bits, which is the second
+    unsigned first = 0xBF80u, second = 0xBF800000u;
+    asm("" : "+s"(first), "+s"(second));
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      float lo = x[e], hi = x[e + 1];
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const bf16x2 t = {(bf16)lo, (bf16)hi};
+        p[i][e] = t[0];
+        p[i][e + 1] = t[1];
+        if (i + 1 < N) {   // the rest in one instruction a value
+          lo = __builtin_amdgcn_fdot2_f32_bf16(t, __builtin_bit_cast(bf16x2, first), lo, false);
+          hi = __builtin_amdgcn_fdot2_f32_bf16(t, __builtin_bit_cast(bf16x2, second), hi, false);
+        }
+      }
+    }
+  }
+};
+// The product of a block in parts: fp32 sums of products that are exact.  Of three parts each way the six largest products; what is
+// left out is below 2^-26 of the product of the two values.  The largest (step 0) and the other five (steps 1 .. 5) belong in separate
+// accumulators: the matrix instructions round a product down to the last bits of a much larger accumulator, and in one
+// accumulator the small products moved every result by -2e-8 to -1e-7 of the typical one (1024 x 1024 x 1024 to 4096), which a sum over
+// the rows of the result shows (7.6e-7 instead of 3.1e-7 with fp32 instructions, and 1.7e-7 so).
+template <int N>
+__device__ __forceinline__ f32x4 mma_parts(const Parts<N> &b, const Parts<N> &a, f32x4 acc, int step) {
+  constexpr int PB[6] = {0, 2, 0, 1, 1, 0}, PA[6] = {0, 0, 2, 1, 0, 1};
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.p[N == 1 ? 0 : PB[step]], a.p[N == 1 ? 0 : PA[step]], acc, 0, 0, 0);
+}
+// Whether a sum of such products is what fp32 products would give: the parts cannot say an infinity, nor a value that rounds to one, nor
+// the last bits of a value below 2^-110.
+__device__ __forceinline__ bool parts_hold(float sum) {
+  const float t = fabsf(sum);
+  return t == 0.0f || (t > 0x1p-70f && t < INFINITY);
+}
+
 // ---- host side -------------------------------------------------------------
 // Brackets a launch with HIP events when per-class timing is on (profile.cpp).
 struct LaunchScope {
@@ -241,6 +326,14 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A,
                  const void *B, void *C, const void *bias, void *aux, uint32_t epi,
                  hipStream_t stream);
+double gemm_mfma_time(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes);   // estimated microseconds of that tile
+bool gemm_wave_takes(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B, const void *C,
+                     const void *bias, const void *aux);
+int gemm_wave(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B, void *C, const void *bias,
+              void *aux, uint32_t epi, int tile, hipStream_t stream);   // tile: 32 or 64
+// the faster of the two tiles if it is estimated below `other` microseconds, else 0
+int gemm_wave_pick(int dtype, int layout, int64_t M, int64_t N, int64_t K, double other);
+double gemm_generic_time(int layout, int64_t M, int64_t N, int64_t K);   // of an fp32 problem on 64 x 64 tiles
 bool gemm_generic_small_tile(int layout, int64_t M, int64_t N);   // 32 x 32 tiles, not 64 x 64, where accesses are aligned
 // returns MTNLG_UNSUPPORTED_SHAPE when the MFMA kernel cannot take this problem
 // ws (nullable): scratch for the split-K tail, see gemm_mfma_workspace_bytes

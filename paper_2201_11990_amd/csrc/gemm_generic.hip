@@ -1,15 +1,16 @@
-// GEMM on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32): the fp32 path of the library, and the bf16 problems
-// whose row lengths the bf16 kernels do not take (their elements are widened on load, which is exact).  Any M, N, K, any layout.
+// GEMM with operands loaded straight into registers: the large fp32 problems, and every problem whose row lengths the kernels that move
+// tiles by DMA do not take (bf16 elements are widened on load, which is exact).  Any M, N, K, any layout.
 //
-// What bounds it: the fp32 matrix rate (256 FLOP per clock and compute unit, a sixteenth of bf16), as long as there are
-// enough waves; below that the chain global memory -> registers -> MFMA of one wave.  At that rate an LDS tile buys
-// nothing: a 64 x 64 wave tile needs 8 KB of operands per 2048 cycles of MFMA, which the caches deliver, so the
-// fragments are loaded straight into the registers the MFMAs read, DEPTH chunks of 16 k ahead, with no barrier in
-// the loop.  The K axis of a workgroup's tile may be split over its waves (WGK); their partial tiles are added
-// through LDS in a fixed order, so a small M x N still fills the chip and a long K is a short chain.
-//   Chunk of 16 KH k: lane l = 16 g + r supplies k = 16 h + 4 g + e in MFMA 4 h + e (the k order inside a chunk is free as
-//   long as both operands agree).  KH = 2 takes both 64-byte halves of a K-contiguous line together: taken one chunk
-//   apart, the second half had often left the L1 cache (NT 1024 x 3072 x 1024 one chunk in flight: 96 -> 88 us).
+// fp32 values are cut into three bf16 parts that add up to them exactly, and the six largest of the nine products of parts run
+// on v_mfma_f32_16x16x32_bf16 (common.h: Parts): sums in fp32, an error below that of the fp32 instructions (1024 x 1024 x 4096 against
+// 64 bits: 5.7e-7 with those, 2.2e-7 so).  What bounds it: per 64 x 64 wave tile and 32 k 96 MFMAs (1600 cycles) and 250 vector
+// instructions for the parts (1100 cycles), which the two waves of a SIMD overlap little, and the 16 KB of operands that come
+// from L2 for them (9 TB/s over the chip).  On v_mfma_f32_16x16x4_f32 before: 1024 x 4096 x 1024 109 / 96 / 91 us (NT / NN / TN), now 76 / 64 /
+// 63; 2048^3 199 / 174 / 157, now 139 / 117 / 114.
+// The K axis of a workgroup's tile is split over its waves (WGK); their partial tiles are added through LDS in a fixed
+// order, so a small M x N still fills the chip and a long K is a short chain.
+//   Chunk of 32 k: lane l = 16 g + r supplies k = 16 h + 4 g + e as element 4 h + e of its operand (the k order inside a chunk is
+//   free as long as both operands agree), so both 64-byte halves of a K-contiguous line are taken together.
 //   K-contiguous operand: lane loads 4 consecutive k of row r of each 16-row block.
 //   Row-contiguous operand ([k][row]): lane loads NB consecutive rows NB r .. + NB - 1 at each of its 4 k; block b of
 //   the wave tile is then rows NB r + b, and the epilogue undoes that.
@@ -106,44 +107,12 @@ struct Frag {
   }
 };
 
-// 4 consecutive outputs of row m at column n (n + 3 < N and everything aligned for 4-element accesses)
-template <typename E>
-__device__ __forceinline__ void epilogue4(const EpiArgs &ea, void *C, int64_t N, int64_t m, int64_t n, f32x4 v) {
-  const int64_t off = m * N + n;
-  if (ea.flags & MTNLG_EPI_BIAS) v += load4(static_cast<const E *>(ea.bias) + n);
-  auto put = [&](E *p, f32x4 x) {
-    if constexpr (sizeof(E) == 4) *reinterpret_cast<f32x4 *>(p) = x;
-    else *reinterpret_cast<bf16x4 *>(p) = bf16x4{(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
-  };
-  if (ea.flags & MTNLG_EPI_GELU) {
-    put(static_cast<E *>(ea.aux) + off, v);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = gelu_f(v[e], (ea.flags & MTNLG_EPI_GELU_ERF) != 0);
-  }
-  if (ea.flags & (MTNLG_EPI_RESIDUAL | MTNLG_EPI_GELU_GRAD)) {
-    const f32x4 t = load4(static_cast<const E *>(ea.aux) + off);
-    if (ea.flags & MTNLG_EPI_RESIDUAL) {
-      v += t;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_f(t[e], (ea.flags & MTNLG_EPI_GELU_ERF) != 0);
-    }
-  }
-  if (ea.flags & MTNLG_EPI_OUT_F32) {
-    float *c = static_cast<float *>(C) + off;
-    if (ea.flags & MTNLG_EPI_ACCUMULATE) v += load4(c);
-    *reinterpret_cast<f32x4 *>(c) = v;
-  } else {
-    E *c = static_cast<E *>(C) + off;
-    if (ea.flags & MTNLG_EPI_ACCUMULATE) v += load4(c);
-    put(c, v);
-  }
-}
-
 // Workgroup of WGM x WGN x WGK waves, wave tile 16 TMB x 16 TNB.  VEC: every row length is a multiple of 4 elements and
 // every pointer aligned to 4 elements.
-template <typename E, int TMB, int TNB, int WGM, int WGN, int WGK, int KH, int DEPTH, bool AT, bool BT, bool VEC>
-__global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_f32_kernel(F32GemmArgs a) {
+template <typename E, int TMB, int TNB, int WGM, int WGN, int WGK, bool AT, bool BT, bool VEC>
+__global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm_f32_kernel(F32GemmArgs a) {
+  constexpr int KH = 2, CHUNK = 16 * KH;
+  constexpr int NP = sizeof(E) == 2 ? 1 : 3;
   constexpr int NV = TMB * TNB;   // vectors of 4 columns a lane holds
   __shared__ f32x4 red[WGK > 1 ? WGK * WGM * WGN * NV * 64 : 1];
   const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
@@ -160,7 +129,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_f32_kernel(F32GemmA
   const int64_t m0 = ((int64_t)tm * WGM + wm) * (16 * TMB), n0 = ((int64_t)tn * WGN + wn) * (16 * TNB);
 
   const E *A = static_cast<const E *>(a.A), *B = static_cast<const E *>(a.B);
-  const int nc_all = (int)((a.K + 16 * KH - 1) / (16 * KH)), per = (nc_all + WGK - 1) / WGK;
+  const int nc_all = (int)((a.K + CHUNK - 1) / CHUNK), per = (nc_all + WGK - 1) / WGK;
   const int c0 = wk * per, c1 = c0 + per < nc_all ? c0 + per : nc_all;   // this wave's chunks
 
   f32x4 acc[TMB][TNB];
@@ -169,36 +138,76 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_f32_kernel(F32GemmA
 #pragma unroll
     for (int j = 0; j < TNB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  Frag<E, TMB, KH, AT, VEC> af[DEPTH];
-  Frag<E, TNB, KH, BT, VEC> bf[DEPTH];
-  // Every condition in the loop is the same for the whole wave and held in a scalar register, and the first fetches are
+  Frag<E, TMB, KH, AT, VEC> af;
+  Frag<E, TNB, KH, BT, VEC> bf;
+  // Every condition in the loop is the same for the whole wave and held in a scalar register, and the fetches are
   // unconditional (clamped): fragments that are fetched on some paths only, under a condition the compiler takes for
   // divergent, were miscompiled (accumulators placed over live fragments).
-  auto fetch = [&](int d, int c) {
-    const int64_t k0 = (int64_t)(c < nc_all ? c : nc_all - 1) * (16 * KH);
-    af[d].fetch(A, a.lda, m0, a.M, k0, a.K, g, r);
-    bf[d].fetch(B, a.ldb, n0, a.N, k0, a.K, g, r);
-  };
+  auto start = [&](int c) { return (int64_t)(c < nc_all ? c : nc_all - 1) * CHUNK; };
+  af.fetch(A, a.lda, m0, a.M, start(c0), a.K, g, r);
+  bf.fetch(B, a.ldb, n0, a.N, start(c0), a.K, g, r);
+  for (int c = c0; c < c1; ++c) {
+    const int64_t k0 = (int64_t)c * CHUNK;
+    if (k0 + CHUNK > a.K) {   // uniform: the last chunk of a K that is no multiple of the chunk
+      af.clear_tail(k0, a.K, g);
+      bf.clear_tail(k0, a.K, g);
+    }
+    Parts<NP> ap[TMB], bp[TNB];
 #pragma unroll
-  for (int d = 0; d < DEPTH; ++d) fetch(d, c0 + d);
-  for (int c = c0; c < c1; c += DEPTH) {
+    for (int i = 0; i < TMB; ++i) ap[i].of(af.v[i]);
+    af.fetch(A, a.lda, m0, a.M, start(c + 1), a.K, g, r);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      if (c + d < c1) {
-        const int64_t k0 = (int64_t)(c + d) * (16 * KH);
-        if (k0 + 16 * KH > a.K) {   // uniform: the last chunk of a K that is no multiple of the chunk
-          af[d].clear_tail(k0, a.K, g);
-          bf[d].clear_tail(k0, a.K, g);
-        }
+    for (int j = 0; j < TNB; ++j) bp[j].of(bf.v[j]);
+    bf.fetch(B, a.ldb, n0, a.N, start(c + 1), a.K, g, r);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < TNB; ++j) {
+#pragma unroll
+      for (int i = 0; i < TMB; ++i) acc[i][j] = mma_parts(bp[j], ap[i], acc[i][j], 0);
+      if constexpr (NP > 1) {   // the smaller products in sums of their own (for one chunk: there are no registers to keep them)
+        f32x4 low[TMB];
+#pragma unroll
+        for (int i = 0; i < TMB; ++i) low[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int step = 1; step < 6; ++step)
+#pragma unroll
+          for (int i = 0; i < TMB; ++i) low[i] = mma_parts(bp[j], ap[i], low[i], step);
+#pragma unroll
+        for (int i = 0; i < TMB; ++i) acc[i][j] += low[i];
+      }
+    }
+  }
+  if constexpr (NP > 1) {
+    // The parts cannot say an infinity, nor a value that rounds to one, nor the last bits of a value below 2^-110.  Where
+    // a result is not finite or so small that such a value may be behind it, the wave takes its chunks once more on the fp32
+    // instructions.
+    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < TMB; ++i)
+#pragma unroll
+      for (int j = 0; j < TNB; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) odd = odd || !parts_hold(acc[i][j][e]);
+    if (__builtin_amdgcn_ballot_w64(odd) != 0) {
+#pragma unroll
+      for (int i = 0; i < TMB; ++i)
+#pragma unroll
+        for (int j = 0; j < TNB; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+      for (int c = c0; c < c1; ++c) {
+        const int64_t k0 = (int64_t)c * CHUNK;
+        af.fetch(A, a.lda, m0, a.M, k0, a.K, g, r);
+        bf.fetch(B, a.ldb, n0, a.N, k0, a.K, g, r);
+        af.clear_tail(k0, a.K, g);
+        bf.clear_tail(k0, a.K, g);
 #pragma unroll
         for (int e = 0; e < 4 * KH; ++e)
 #pragma unroll
           for (int i = 0; i < TMB; ++i)
 #pragma unroll
             for (int j = 0; j < TNB; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[d].v[j][e], af[d].v[i][e], acc[i][j], 0, 0, 0);
-        // the 64 x 64 tiles take a superfluous (clamped) last fetch rather than the branch, which costs them 10 %
-        if (TMB * TNB == 16 || c + d + DEPTH < c1) fetch(d, c + d + DEPTH);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf.v[j][e], af.v[i][e], acc[i][j], 0, 0, 0);
       }
     }
   }
@@ -245,7 +254,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_f32_kernel(F32GemmA
   }
 }
 
-template <typename E, int TMB, int TNB, int WGM, int WGN, int WGK, int KH, int DEPTH, bool VEC>
+template <typename E, int TMB, int TNB, int WGM, int WGN, int WGK, bool VEC>
 int launch_f32(int layout, F32GemmArgs a, hipStream_t st) {
   const int64_t tm = (a.M + 16 * TMB * WGM - 1) / (16 * TMB * WGM), tn = (a.N + 16 * TNB * WGN - 1) / (16 * TNB * WGN);
   if (tm * tn > (1 << 28)) return MTNLG_UNSUPPORTED_SHAPE;
@@ -254,31 +263,39 @@ int launch_f32(int layout, F32GemmArgs a, hipStream_t st) {
   const dim3 grid((unsigned)((tm * tn + 7) / 8 * 8));
   constexpr int threads = 64 * WGM * WGN * WGK;
   if (layout == MTNLG_GEMM_NT)
-    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, KH, DEPTH, false, false, VEC><<<grid, threads, 0, st>>>(a);
+    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, false, false, VEC><<<grid, threads, 0, st>>>(a);
   else if (layout == MTNLG_GEMM_NN)
-    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, KH, DEPTH, false, true, VEC><<<grid, threads, 0, st>>>(a);
+    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, false, true, VEC><<<grid, threads, 0, st>>>(a);
   else
-    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, KH, DEPTH, true, true, VEC><<<grid, threads, 0, st>>>(a);
+    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, true, true, VEC><<<grid, threads, 0, st>>>(a);
   return check_launch();
 }
 
 template <typename E>
 int gemm_generic_of(int layout, const F32GemmArgs &a, bool vec, bool small, hipStream_t st) {
-  if (!vec) return launch_f32<E, 2, 2, 1, 1, 4, 1, 2, false>(layout, a, st);
-  if (small) return launch_f32<E, 2, 2, 1, 1, 8, 1, 2, true>(layout, a, st);
-  return launch_f32<E, 4, 4, 1, 1, 4, 2, 1, true>(layout, a, st);
+  if (!vec) return launch_f32<E, 2, 2, 1, 1, 4, false>(layout, a, st);
+  if constexpr (sizeof(E) == 2)   // (small fp32 problems: gemm_wave)
+    if (small) return launch_f32<E, 2, 2, 1, 1, 8, true>(layout, a, st);
+  return launch_f32<E, 4, 4, 1, 1, 4, true>(layout, a, st);
 }
 
 }  // namespace
 
-// 32 x 32 tiles (K split over eight waves) or 64 x 64 tiles (over four): rounds of 256 workgroups times the time of a
-// round at equal K.  Measured (us, K = 1024, 64 / 32): 256 x 256 23 / 10, 1024 x 1024 26 / 33, 1024 x 3072 NT 88 / 95,
-// TN 64 / 100; 256 x 1024 x 256 10 / 5; 2048^3 NT 187 / 228, TN 150 / 236 (115 TFLOP/s; nominal 157).  A round of the 64 x 64
-// tiles costs least where both operands are row-contiguous, whose loads cover whole lines.
+// bf16 problems on these kernels: 32 x 32 tiles (K split over eight waves) or 64 x 64 tiles (over four), by rounds of 256 workgroups
+// times the time of a round at equal K on the fp32 instructions: measured then (us, K = 1024, 64 / 32) 256 x 256 23 / 10, 1024 x 1024
+// 26 / 33, 1024 x 3072 NT 88 / 95, TN 64 / 100.
 bool gemm_generic_small_tile(int layout, int64_t M, int64_t N) {
   const double round64 = layout == MTNLG_GEMM_NT ? 25 : layout == MTNLG_GEMM_NN ? 22 : 20, round32 = 8.5;
   auto rounds = [&](int64_t t) { return (double)((((M + t - 1) / t) * ((N + t - 1) / t) + 255) / 256); };
   return rounds(32) * round32 < rounds(64) * round64;
+}
+
+// fp32, 64 x 64 tiles: fitted to 120 measured problems (K 128 to 8192, 256 to 3072 tiles).
+double gemm_generic_time(int layout, int64_t M, int64_t N, int64_t K) {
+  const double rounds = (double)(((M + 63) / 64) * ((N + 63) / 64)) / 256;
+  const double per_k = layout == MTNLG_GEMM_NT ? 0.0137 : layout == MTNLG_GEMM_NN ? 0.0110 : 0.0108;
+  if (rounds <= 1) return 7.5 + 1.17 * per_k * (double)K;   // one wave on a SIMD
+  return 4.0 + (rounds < 2 ? 2 : rounds) * (3.5 + per_k * (double)K);
 }
 
 int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A,

@@ -842,11 +842,11 @@ double time_128_deep(int64_t tiles, int nk) { return (double)((tiles + 255) / 25
 
 // Which tile shape takes a problem: the least estimated time among those whose DMA reaches the operands, -1 if none does.  A last
 // round is split along K if its partial tiles fit the workspace.
-int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+static int pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes, double &best) {
+  best = 1e300;
   if (M <= 0 || N <= 0 || K <= 0) return -1;
   const int nk = (int)((K + BK - 1) / BK);
   const bool at = layout == MTNLG_GEMM_TN, bt = layout != MTNLG_GEMM_NT;
-  double best = 1e300;
   int pick = -1;
   auto offer = [&](int tile, int bm, int bn, double t) {
     if (t < best && tile_reaches(at, bt, M, N, K, bm, bn)) { best = t; pick = tile; }
@@ -860,6 +860,15 @@ int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_b
   offer(GEMM_TILE_RAGGED_128, 128, 128, time_128(tiles(128, 128), nk));
   offer(GEMM_TILE_RAGGED_128_DEEP, 128, 128, time_128_deep(tiles(128, 128), nk));
   return pick;
+}
+int gemm_mfma_pick_tile(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+  double t;
+  return pick_tile(layout, M, N, K, ws_bytes, t);
+}
+double gemm_mfma_time(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+  double t;
+  const int tile = pick_tile(layout, M, N, K, ws_bytes, t);
+  return tile == GEMM_TILE_RAGGED_128 ? t + 1.5 : t;   // its few-slab launches take that much longer than the choice between tiles needs to know
 }
 
 // Room for the partial tiles of a 256 x 256 tiling's split last round.  What callers size their scratch by, so it

@@ -206,6 +206,85 @@ def test_bf16_gemm_split_along_k(layout, tile, Mm, N, K):
     assert not bool((ws == 0xFF).all()), "the partial tiles went somewhere else"
 
 
+# Small problems and the fp32 ones: K split over the eight waves of a workgroup, 32 x 32 or 64 x 64 tiles.  Less than a tile and a
+# slab; fewer slabs than waves, as many, and a ninth; ragged on every side.
+WAVE_SHAPES = [(8, 8, 8), (40, 72, 104), (64, 64, 256), (72, 136, 520), (136, 40, 584), (96, 32, 1096)]
+
+
+def gemm_by_waves(tile, layout, a, b, C, epilogue=0, bias=None, aux=None):
+    fn = B.lib()._ZN5mtnlg9gemm_waveEiilllPKvS1_PvS1_S2_jiP12ihipStream_t
+    vp, i64 = ctypes.c_void_p, ctypes.c_int64
+    fn.argtypes = [ctypes.c_int, ctypes.c_int, i64, i64, i64, vp, vp, vp, vp, vp, ctypes.c_uint32, ctypes.c_int, vp]
+    ptr = lambda t: 0 if t is None else t.data_ptr()
+    K = a.shape[0] if layout == B.GEMM_TN else a.shape[1]
+    assert fn(B.F32 if a.dtype == torch.float32 else B.BF16, layout, C.shape[0], C.shape[1], K, ptr(a), ptr(b), ptr(C), ptr(bias), ptr(aux),
+              epilogue, tile, torch.cuda.current_stream().cuda_stream) == 0
+
+
+def gemm_without_lds(layout, a, b, C):   # fp32, 64 x 64 tiles, operands straight to registers
+    fn = B.lib()._ZN5mtnlg12gemm_genericEiilllPKvS1_PvS1_S2_jP12ihipStream_t
+    vp, i64 = ctypes.c_void_p, ctypes.c_int64
+    fn.argtypes = [ctypes.c_int, ctypes.c_int, i64, i64, i64, vp, vp, vp, vp, vp, ctypes.c_uint32, vp]
+    K = a.shape[0] if layout == B.GEMM_TN else a.shape[1]
+    assert fn(B.F32, layout, C.shape[0], C.shape[1], K, a.data_ptr(), b.data_ptr(), C.data_ptr(), 0, 0, 0,
+              torch.cuda.current_stream().cuda_stream) == 0
+
+
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("shape", WAVE_SHAPES)
+@pytest.mark.parametrize("tile", [32, 64])
+def test_gemm_with_k_split_over_waves(tile, shape, layout):
+    Mm, N, K = shape
+    check_bf16_gemm(layout, Mm, N, K - 5 if layout == B.GEMM_TN else K, lambda *a, **k: gemm_by_waves(tile, *a, **k))
+    K = K // 2 + 4   # fp32: slabs of 32
+    if layout == B.GEMM_TN:
+        K -= 3
+    A, Bm = operands(layout, Mm, N, K, "fp32")
+    bias, aux = randn((N,), "fp32", 7), randn((Mm, N), "fp32", 8)
+    want = gemm_oracle(layout, A, Bm)
+    C = torch.full((Mm, N), float("nan"), device="cuda")
+    gemm_by_waves(tile, layout, dev(A), dev(Bm), C)
+    assert_close(C, want, TOL["fp32"], f"fp32 waves {tile} {layout} {shape}")
+    gemm_by_waves(tile, layout, dev(A), dev(Bm), C, epilogue=B.EPI_ACCUMULATE)
+    assert_close(C, 2 * want, TOL["fp32"], f"fp32 waves {tile} {layout} {shape} accumulate")
+    gemm_by_waves(tile, layout, dev(A), dev(Bm), C, bias=dev(bias), aux=dev(aux), epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
+    assert_close(C, want + to_np(bias) + to_np(aux), TOL["fp32"], f"fp32 waves {tile} {layout} {shape} bias + residual")
+    gemm_by_waves(tile, layout, dev(A), dev(Bm), C, aux=dev(aux), epilogue=B.EPI_GELU_GRAD)
+    assert_close(C, want * oracle.gelu_grad(to_np(aux)), TOL["fp32"], f"fp32 waves {tile} {layout} {shape} GeLU'")
+
+
+# fp32 values in three bf16 parts: what the parts cannot say goes the way of the fp32 instructions.  Values whose third part or
+# whose rounded first part leaves bf16's range, an infinity, a NaN; 32 x 32, 64 x 64 and the 64 x 64 tiles without LDS.
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("route", [32, 64, 0])
+def test_fp32_gemm_at_the_ends_of_the_range(route, layout):
+    Mm, N, K = 96, 72, 136
+    gemm = (lambda *a: gemm_by_waves(route, *a)) if route else gemm_without_lds
+    A, Bm = operands(layout, Mm, N, K, "fp32")
+    for scale_a, scale_b in ((2.0 ** -118, 1.0), (2.0 ** -100, 2.0 ** -24), (2.0 ** 90, 2.0 ** 30)):
+        C = torch.full((Mm, N), float("nan"), device="cuda")
+        gemm(layout, dev(A * scale_a), dev(Bm * scale_b), C)
+        assert_close(C / scale_a / scale_b if scale_a < 1 else C * (1 / scale_a) * (1 / scale_b), gemm_oracle(layout, A, Bm), TOL["fp32"],
+                     f"fp32 gemm {route} {layout} scaled")
+    row = (lambda t, m: t[:, m]) if layout == B.GEMM_TN else (lambda t, m: t[m])
+    for bad in (float("inf"), float("nan"), 3.4e38):   # 3.4e38 rounds to an infinity in bf16
+        X, Y = A.clone(), Bm.clone()
+        row(X, 5)[7] = bad
+        if bad == 3.4e38:
+            row(X, 5)[:7] = row(X, 5)[8:] = 0.0
+            Y *= 0.25
+        C = torch.full((Mm, N), 7.0, device="cuda")
+        gemm(layout, dev(X), dev(Y), C)
+        x, y = (X.T if layout == B.GEMM_TN else X).double(), (Y.T if layout == B.GEMM_NT else Y).double()
+        want = x @ y
+        rest = [m for m in range(Mm) if m != 5]
+        assert_close(C[rest], want[rest].numpy(), TOL["fp32"], "the other rows")
+        if bad == 3.4e38:
+            assert_close(C[5] * 2.0 ** -100, want[5].numpy() * 2.0 ** -100, TOL["fp32"], "the row of the large value")
+        else:
+            assert torch.equal(torch.isnan(C[5].cpu()), torch.isnan(want[5])) and torch.equal(torch.isinf(C[5].cpu()), torch.isinf(want[5]))
+
+
 def check_bf16_gemm(layout, Mm, N, K, gemm):
     A, Bm = operands(layout, Mm, N, K, "bf16")
     what = f"bf16 gemm {layout} {Mm} {N} {K}"
