@@ -407,6 +407,8 @@ int mtnlg_attention_fwd(int dtype, int32_t b, int32_t s, int32_t n, int32_t d, f
   if (b <= 0 || s <= 0 || n <= 0 || d <= 0 || !(scale > 0.0f)) return MTNLG_INVALID_ARG;
   if (attention_mfma_takes(dtype, b, s, n, d))
     return attention_fwd_mfma(b, s, n, d, scale, qkv, a, lse, (hipStream_t)stream);
+  if (attention_exact_fwd_takes(dtype, b, s, n, d, qkv, a))
+    return attention_fwd_exact(b, s, n, d, scale, qkv, a, lse, (hipStream_t)stream);
   return attention_fwd_f32(dtype, b, s, n, d, scale, qkv, a, lse, (hipStream_t)stream);
 }
 
@@ -422,6 +424,8 @@ int mtnlg_attention_bwd(int dtype, int32_t b, int32_t s, int32_t n, int32_t d, f
   if (b <= 0 || s <= 0 || n <= 0 || d <= 0 || !(scale > 0.0f)) return MTNLG_INVALID_ARG;
   if (attention_mfma_takes(dtype, b, s, n, d))
     return attention_bwd_mfma(b, s, n, d, scale, qkv, a, lse, da, dqkv, workspace, (hipStream_t)stream);
+  if (attention_exact_bwd_takes(dtype, b, s, n, d, qkv, a, da, dqkv))
+    return attention_bwd_exact(b, s, n, d, scale, qkv, a, lse, da, dqkv, workspace, (hipStream_t)stream);
   return attention_bwd_f32(dtype, b, s, n, d, scale, qkv, a, lse, da, dqkv, workspace, (hipStream_t)stream);
 }
 

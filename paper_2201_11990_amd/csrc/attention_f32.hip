@@ -1,6 +1,6 @@
 // Causal softmax attention, forward and backward, on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32): scores,
-// probabilities and sums stay in fp32.  This is the attention of the fp32 path and of the bf16 head sizes that the
-// bf16 kernels do not take.  Head sizes: multiples of 8 up to 256; sequences up to 4096.
+// probabilities and sums stay in fp32.  This is the attention of the fp32 path, and of bf16 head sizes other than 64, 128 and 160 in
+// small calls and above 192 (the rest: the EXACT kernels of attention_mfma.hip).  Head sizes: multiples of 8 up to 256; sequences up to 4096.
 //
 //   S[t,u] = scale * q_t . k_u  (u <= t),  P = rowsoftmax(S),  a_t = sum_u P[t,u] v_u
 //   lse[t] = log sum_u exp(S[t,u])
@@ -12,7 +12,7 @@
 // bf16 inputs need not be widened for the products of two inputs (q k^T, da v^T, D): those run on the bf16 matrix
 // instructions with fp32 sums.  2 x 1024 tokens, 16 heads of 96, forward / backward: 162 / 540 us with all products on the
 // fp32 instructions, 104 / 327 us so.  (P and dS cut into three bf16 parts that add up to them exactly, for the other products:
-// slower, 237 us forward; the waves wait for loads by then, and 32-row steps leave fewer of them.)
+// slower here, 237 us forward: the waves wait for loads by then.  With tiles in LDS that is the better form.)
 // A wave owns 16 rows of one side (queries forward and for dq, keys for dk / dv) and walks the other side 16 or 32 rows
 // at a time; fragments are loaded from global memory straight into the registers the MFMAs read (at this matrix rate a
 // wave asks the caches for 8 bytes a cycle), so there is no LDS, no barrier, and a wave stops at its own diagonal.  The four
@@ -27,7 +27,7 @@
 //   Cols: element (block, e) = X[4 g + e][column], NB consecutive columns per lane and group of 16 NB; an MFMA per
 //         (block, e) contracts over the rows, and its other operand for e is exactly that accumulator element: P
 //         and dS are used where they were computed.
-#include "common.h"
+#include "attention_redo.h"
 
 namespace mtnlg {
 
@@ -193,70 +193,9 @@ __device__ __forceinline__ f32x4 product(const Rows<E, DP> &streamed, const Rows
   return lo + hi;
 }
 
-// sum / maximum over the four lanes that share lane % 16
-__device__ __forceinline__ float quad_sum(float v) {
-  v += __shfl_xor(v, 16, 64);
-  return v + __shfl_xor(v, 32, 64);
-}
 __device__ __forceinline__ float quad_max(float v) {
   v = fmaxf(v, __shfl_xor(v, 16, 64));
   return fmaxf(v, __shfl_xor(v, 32, 64));
-}
-
-// The slow path of all three kernels.  The loops above the diagonal multiply masked elements (P or dS = 0) with rows that the mask
-// hides, in the blocks of 16 or 32 rows that the diagonal crosses and in a last block that hangs over the end.  With finite inputs
-// that adds zero; an infinity or NaN in such a row would spread to rows that do not depend on it (0 x inf).  A wave whose result is
-// not finite therefore computes its 16 rows once more, on the vector ALU and one streamed row at a time, reading only what each
-// row depends on.  Four lanes share a row; lane g of them holds columns 16 c + 4 g .. + 3.  Operands are read from memory at every
-// use: held in registers they would cost the loop above its occupancy.  (A NaN in token 0, so that every wave comes here: 8.0 ms forward
-// and backward at 2 x 1024 x 16 heads of 96, 0.43 ms with finite inputs.  Checking the crossed blocks inside the loops instead: up to
-// 90 registers more in them.)
-template <typename E, int DP>
-struct Quarter {
-  static constexpr int NC = DP / 16;
-  f32x4 v[NC];
-  __device__ __forceinline__ void clear() {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) v[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-  __device__ __forceinline__ void add(float w, const E *row, int d, int g) {   // columns past d: anything, not stored
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int col = 16 * c + 4 * g;
-      const f32x4 t = load4(row + (col < d ? col : 0));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[c][e] = fmaf(w, t[e], v[c][e]);
-    }
-  }
-  __device__ __forceinline__ void store(E *row, int d, float mul, int g) const {
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int col = 16 * c + 4 * g;
-      if (col >= d) continue;
-      const f32x4 x = v[c] * mul;
-      if constexpr (sizeof(E) == 4) *reinterpret_cast<f32x4 *>(row + col) = x;
-      else *reinterpret_cast<bf16x4 *>(row + col) = bf16x4{(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
-    }
-  }
-};
-// Whether no lane of the wave has stored a non-finite value (z: 0 or NaN).  If one has, the stores are waited for: other lanes write
-// the same places next.
-__device__ __forceinline__ bool all_finite(float z) {
-  if (__builtin_amdgcn_ballot_w64(z != 0.0f) == 0) return true;
-  __threadfence_block();
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  return false;
-}
-template <typename E>   // the dot product of two rows, in all four lanes
-__device__ __forceinline__ float dot(const E *x, const E *y, int d, int g) {
-  float t = 0.0f;
-#pragma unroll 1
-  for (int col = 4 * g; col < d; col += 16) {
-    const f32x4 p = load4(x + col), q = load4(y + col);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) t = fmaf(p[e], q[e], t);
-  }
-  return quad_sum(t);
 }
 
 // Grid: (heads, blocks of rows, batch).  A wave owns rows row0 .. row0 + 15 and takes part `part` of the other side's steps.
@@ -385,27 +324,7 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, 
     if (w.g == 0) *out_lse = m + logf(l);
   }
   if (all_finite(z)) return;
-  const E *qrow = base + (q < s ? q : s - 1) * ld;
-  Quarter<E, DP> sum;
-  sum.clear();
-  m = -INFINITY;
-#pragma unroll 1
-  for (int u = 0; u <= last; ++u) {
-    const float sc = dot(qrow, base + d + u * ld, d, w.g) * scale;
-    if (u <= q) m = fmaxf(m, sc);
-  }
-  l = 0.0f;
-#pragma unroll 1
-  for (int u = 0; u <= last; ++u) {
-    const float p = expf(dot(qrow, base + d + u * ld, d, w.g) * scale - m);
-    if (u <= q) {
-      l += p;
-      sum.add(p, base + 2 * d + u * ld, d, w.g);
-    }
-  }
-  if (q >= s) return;
-  sum.store(out, d, 1.0f / l, w.g);
-  if (w.g == 0) *out_lse = m + logf(l);
+  redo_fwd<E, DP>(base, ld, s, d, scale, q, last, w.g, out, out_lse);
 }
 
 // dq, and D for the kernel below
@@ -467,16 +386,7 @@ __global__ __launch_bounds__(256, sizeof(E) == 4 && DP <= 64 ? 2 : 1) void attn_
   float z = 0.0f;
   if (q < s) z = dq.store(out, d, scale, w.g);
   if (all_finite(z)) return;
-  Quarter<E, DP> sum;
-  sum.clear();
-#pragma unroll 1
-  for (int u = 0; u <= last; ++u) {
-    const E *krow = base + d + u * ld;
-    const float dp = dot(da + po + qc * pld, krow + d, d, w.g);
-    const float p = expf(dot(base + qc * ld, krow, d, w.g) * scale - ls);
-    if (u <= q) sum.add(p * (dp - dsum), krow, d, w.g);
-  }
-  if (q < s) sum.store(out, d, scale, w.g);
+  redo_dq<E, DP>(base, ld, da + po, pld, s, d, scale, q, last, ls, dsum, w.g, out);
 }
 
 // What the compiler is told about waves per SIMD, so that it uses registers as the loop needs them: bf16, head sizes up to 32: 3-4,
@@ -558,23 +468,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dkv_waves<E
   float z = 0.0f;
   if (key < s) z = dk.store(out + d, d, scale, w.g) + dv.store(out + 2 * d, d, 1.0f, w.g);
   if (all_finite(z)) return;
-  const E *krow = base + d + (key < s ? key : s - 1) * ld;
-  auto prob = [&](int t) { return expf(dot(krow, base + t * ld, d, w.g) * scale - lse[st + t]); };
-  Quarter<E, DP> sum;   // dv, then dk
-  sum.clear();
-#pragma unroll 1
-  for (int t = w.row0; t < s; ++t) {
-    const float p = prob(t);
-    if (t >= key) sum.add(p, dab + t * pld, d, w.g);
-  }
-  if (key < s) sum.store(out + 2 * d, d, 1.0f, w.g);
-  sum.clear();
-#pragma unroll 1
-  for (int t = w.row0; t < s; ++t) {
-    const float p = prob(t), dp = dot(krow + d, dab + t * pld, d, w.g);
-    if (t >= key) sum.add(p * (dp - D[st + t]), base + t * ld, d, w.g);
-  }
-  if (key < s) sum.store(out + d, d, scale, w.g);
+  redo_dkv<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, D + st, w.g, out);
 }
 
 // Which calls split the streamed side over the waves of a workgroup: those with up to 512 groups of 16 rows, two workgroups

@@ -1,5 +1,5 @@
 // Fused causal softmax attention on the gfx950 matrix cores (bf16 in, fp32 softmax
-// and accumulation), forward and backward, for head sizes 64, 128 and 160.
+// and accumulation), forward and backward, for head sizes 64, 128 and 160; and with P and dS in fp32 (EXACT) for the others up to 192.
 //
 //   S = scale * q k^T (causal),  P = rowsoftmax(S),  a = P v,  lse = log sum exp(S)
 //   backward with D_t = da_t . a_t :  dP = da v^T,  dS = P o (dP - D),
@@ -27,8 +27,15 @@
 // first product (slot (g, e) of a 32-row step = tile row 4g + e for e < 4, 16 + 4g + e - 4
 // otherwise), so P and dS never leave the registers and nothing is transposed in software.
 // No atomics: every output element has one owner, results are run-to-run identical.
+//
+// EXACT: any head size d that is a multiple of 8, in tiles of D = d rounded up to 32 columns (the DMA brings zeros past d).  P and dS are
+// not rounded to bf16: each goes into the second product as three bf16 parts that add up to it (common.h: Parts), three MFMAs
+// where the other kernels have one; 17 against 9 a tile in all, but the chain between barriers stays the bound.  2 x 1024 tokens, 16 heads of
+// 96, forward / backward: 103 / 327 us on the fp32 instructions without LDS (attention_f32.hip), 22 / 61 here.  Inputs that are not finite
+// take the slow path of attention_redo.h.
 #include <math.h>
 
+#include "attention_redo.h"
 #include "common.h"
 
 namespace mtnlg {
@@ -46,20 +53,43 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 // 2^x on the transcendental unit (v_exp_f32): no denormal fix-up, 2^-inf = 0.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+// e^(s f - shift).  EXACT: f is the scale, whose rounding after a multiplication by log2 e would move every exponent the same way; else
+// f and shift have the factor log2 e.
+template <bool EXACT>
+__device__ __forceinline__ float weight(float s, float f, float shift) {
+  const float x = fmaf(s, f, -shift);
+  return fast_exp2(EXACT ? x * kLog2e : x);
+}
+// m + log(l), rounded about once: the reference maximum may lie up to 2^8 below the largest weight, and log(l) of such a sum is large
+// enough for its own rounding to show (2048 keys, 4 heads of 96: log-sum-exp 3.4e-7 off, rms, with m + logf(l), 1.8e-7 so; 3.0e-7 with a maximum that always follows).
+__device__ __forceinline__ float plus_log(float m, float l) {
+  int k;
+  const float f = frexpf(l, &k), t = k * 0x1.62e4p-1f;   // log l = k log 2 + log f, log 2 = 0x1.62e4p-1 + 1.4286068e-6; t is exact
+  const float sum = m + t, b = sum - m, rest = (m - (sum - b)) + (t - b);
+  return sum + (rest + fmaf((float)k, 1.4286068e-6f, logf(f)));
+}
+// rounded to fp32, never fused into an addition
+__device__ __forceinline__ float product_of(float x, float y) {
+  float p = x * y;
+  asm("" : "+v"(p));
+  return p;
+}
 
 // A 64-row x D-column bf16 tile in LDS, rows as in memory, the 16-byte units of a row
 // permuted by an XOR that depends on the row.  The masks are the ones a micro-benchmark of the
 // two fragment read patterns found fastest (cycles per wave instruction, two waves per SIMD):
-// head size 160: 4.5-4.9 for the 16-byte reads and 3.0 for the transposing reads (no conflicts);
+// head size 160: 4.5-4.9 for the 16-byte reads and 3.0 for the transposing reads (no conflicts; so 32 and 96, whose rows are an odd
+// number of 64-byte pieces too, and 192 as 64);
 // 64: the same; 128: 4.5 and 4.0 (no mask of this form is conflict-free for both at a row of
 // exactly 256 bytes).  The masks look at the low four bits of the row only.
 template <int D>
 struct Tile {
+  static constexpr bool ODD = D / 32 % 2 == 1;   // 32, 96, 160
   static constexpr int UPR = D / 8;        // 16-byte units per row
   static constexpr int BYTES = 64 * D * 2;
   static constexpr int NI = D / 32;        // DMA instructions per wave and tile (16 rows)
   static __device__ __forceinline__ int mask(int row) {
-    if constexpr (D == 160) return (row >> 1) & 3;
+    if constexpr (ODD) return (row >> 1) & 3;
     else if constexpr (D == 128) return row & 15;
     else return row & 7;
   }
@@ -67,14 +97,15 @@ struct Tile {
 
   // Byte offset, from the tile's first row in memory (row pitch ld_bytes), of what lane `lane` moves in DMA instruction i of
   // the wave that brings rows 16 quarter .. + 15: instruction i fills 1024 consecutive LDS bytes, lane l the 16 at 16 l.
-  static __device__ __forceinline__ uint32_t dma_offset(uint32_t ld_bytes, int quarter, int lane, int i) {
+  // (units past column d: outside any descriptor, they arrive as zeros)
+  static __device__ __forceinline__ uint32_t dma_offset(uint32_t ld_bytes, int quarter, int lane, int i, int d) {
     const int p = i * 64 + lane, r = 16 * quarter + p / UPR, u = (p % UPR) ^ mask(r);
-    return r * ld_bytes + u * 16;
+    return u * 8 < d ? r * ld_bytes + u * 16 : 0xFFFFFFF0u;
   }
   // Byte offsets of a lane's fragment reads inside a tile.  mask() looks at the low four bits of a
   // row only, so a block of 16 rows further down is a constant distance away; and the offsets of the k-steps and
-  // column blocks differ by an XOR of bits that the row part leaves empty (head size 160, whose mask touches the low two
-  // bits of a unit only: by a constant, and one bit for odd column blocks).  One register each instead of one per step.
+  // column blocks differ by an XOR of bits that the row part leaves empty (ODD, whose mask touches the low two
+  // bits of a unit only: by a constant, and one bit for odd column blocks; 192, the low three: one or two bits and a constant).  One register each instead of one per step.
   struct Lane {
     uint32_t n0;   // row lane%16, 16-byte unit lane/16
     uint32_t t0;   // as address supplier of a transposing read: row 4 (lane/16) + L/4, columns 4 (L%4) .. + 3, L = lane%16
@@ -85,9 +116,15 @@ struct Tile {
     }
     // once per tile: keeps the compiler from holding every offset in a register of its own across tiles
     __device__ __forceinline__ void here() { asm volatile("" : "+v"(n0), "+v"(t0)); }
-    __device__ __forceinline__ uint32_t nat(int kk) const { return D == 160 ? n0 + kk * 64 : n0 ^ (kk * 64); }
+    __device__ __forceinline__ uint32_t nat(int kk) const {
+      if constexpr (ODD) return n0 + kk * 64;
+      else if constexpr (D == 192) return (n0 ^ ((kk & 1) * 64)) + (kk >> 1) * 128;
+      else return n0 ^ (kk * 64);
+    }
     __device__ __forceinline__ uint32_t tr(int cblk) const {
-      return D == 160 ? (t0 ^ ((cblk & 1) * 32)) + (cblk >> 1) * 64 : t0 ^ (cblk * 32);
+      if constexpr (ODD) return (t0 ^ ((cblk & 1) * 32)) + (cblk >> 1) * 64;
+      else if constexpr (D == 192) return (t0 ^ ((cblk & 3) * 32)) + (cblk >> 2) * 128;
+      else return t0 ^ (cblk * 32);
     }
   };
   static constexpr int ROWS16 = 16 * UPR * 16;   // bytes of 16 tile rows
@@ -142,6 +179,36 @@ __device__ __forceinline__ bf16x8 pack2(const f32x4 &lo, const f32x4 &hi) {
   return o;
 }
 
+// the same with fp32 values kept: three parts
+template <bool EXACT>
+__device__ __forceinline__ Parts<EXACT ? 3 : 1> weights(const f32x4 &lo, const f32x4 &hi) {
+  Parts<EXACT ? 3 : 1> w;
+  if constexpr (EXACT) w.of({lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+  else w.p[0] = pack2(lo, hi);
+  return w;
+}
+template <int N>
+__device__ __forceinline__ f32x4 mma_weights(const bf16x8 &x, const Parts<N> &w, f32x4 acc) {
+#pragma unroll
+  for (int i = N - 1; i >= 0; --i) acc = MFMA16(x, w.p[i], acc);
+  return acc;
+}
+
+// columns 32 kk + 8 g .. + 7 of a row
+template <bool EXACT>
+__device__ __forceinline__ bf16x8 row_chunk(const bf16 *row, int col, int d) {
+  if constexpr (!EXACT) {
+    return *reinterpret_cast<const bf16x8 *>(row + col);
+  } else {   // rows are aligned to 8 bytes; columns past d are 0
+    typedef __attribute__((ext_vector_type(8), aligned(8))) bf16 bf16x8_8;
+    const bf16x8 t = *reinterpret_cast<const bf16x8_8 *>(row + (col < d ? col : 0));
+    bf16x8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = col < d ? t[e] : (bf16)0.0f;
+    return o;
+  }
+}
+
 // Steps 0 .. N-1 of a run of MFMAs whose A operands come from LDS: load(i) fetches the fragments
 // of step i, mma(i) multiplies with them, extra(i) is whatever else should issue during step i.
 // The loads run P steps ahead of the MFMAs, and nothing may be scheduled across a step boundary:
@@ -182,11 +249,7 @@ template <typename V>
 __device__ __forceinline__ void arrive(V &v) {
   asm volatile("" : "+v"(v));
 }
-// sum / maximum over the four lanes that share lane % 16
-__device__ __forceinline__ float quad_sum(float v) {
-  v += __shfl_xor(v, 16, 64);
-  return v + __shfl_xor(v, 32, 64);
-}
+// maximum over the four lanes that share lane % 16:
 // v_permlane{16,32}_swap of a value with itself leaves the two halves of every pair side by side; unlike a shuffle
 // through LDS it costs a vector instruction's latency, which the forward kernel pays twice in every tile's chain.
 // The results are taken into scalars before they are reinterpreted: __builtin_bit_cast of an element of a vector reads
@@ -296,8 +359,8 @@ __device__ __forceinline__ f32x4 *merge_slots(char *smem, int wave, int lane, in
 }
 
 // ------------------------------------------------------------------ forward
-template <int D, int G>
-__global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int group, float scale, const bf16 *__restrict__ qkv,
+template <int D, int G, bool EXACT>
+__global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int head_dim, int group, float scale, const bf16 *__restrict__ qkv,
                                                       bf16 *__restrict__ a, float *__restrict__ lse) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
@@ -307,13 +370,14 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
   if (hb.none) return;
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
-  const int64_t ld = (int64_t)n * 3 * D;
-  const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * D;
+  const int d = EXACT ? head_dim : D;
+  const int64_t ld = (int64_t)n * 3 * d;
+  const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * d;
   // From the thread number and not the scalar: with a scalar condition for masked tiles the compiler lays the tile's code
   // out per path and holds 60 registers more (head size 160, 32 rows per wave: 256 and 27 spilled, 163 us; now 208, 105).
   const PairedBlocks<G> rb(s, hb.order, threadIdx.x >> 6);
   const int qw = rb.row0;
-  const float c = scale * kLog2e;
+  const float c = scale * kLog2e, f = EXACT ? scale : c;
   typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
@@ -325,7 +389,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
     qc[qg] = q < s ? q : s - 1;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
-      qf[qg][kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)qc[qg] * ld + 32 * kk + 8 * g);
+      qf[qg][kk] = row_chunk<EXACT>(base + (int64_t)qc[qg] * ld, 32 * kk + 8 * g, d);
   }
   f32x4 o[G][DB];
 #pragma unroll
@@ -346,10 +410,10 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
   // the MFMA steps of tile it (dma_by).
   constexpr int IPW = T::NI;   // DMA instructions per wave and tile
   const int quarter = wave & 3, half = wave >> 2;
-  TileStream kv(base + D + half * D, ((int64_t)s * ld - (j * 3 + 1 + half) * D) * 2, 64 * ld * 2);
+  TileStream kv(base + d + half * d, ((int64_t)s * ld - (j * 3 + 1 + half) * d) * 2, 64 * ld * 2);
   uint32_t dma_off[IPW];
 #pragma unroll
-  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(ld * 2), quarter, lane, i);
+  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(ld * 2), quarter, lane, i, d);
   auto issue_one = [&](auto tag, int st, int i) {   // instruction i of the stream's next tile into ring stage st
     constexpr int TAG = decltype(tag)::value;
     dma16<TAG>(kv.rsrc(), smem_addr + st * STAGE + half * T::BYTES + (quarter * IPW + i) * 1024, dma_off[i]);
@@ -430,13 +494,13 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
         // 2^8 in the exponent's units (any reference gives the same sums; this one keeps p <= 256
         // and makes rescaling O rare).  Finite from the first tile on: key 0 is never masked.
         const float m_new = mx * c > m[qg] * c + 8.0f ? mx : m[qg];
-        const float mc = m_new * c;
+        const float mc = EXACT ? product_of(m_new, scale) : m_new * c;
         float rs = 0.0f;
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float p = fast_exp2(fmaf(sc[qg][kb][e], c, -mc));
+            const float p = weight<EXACT>(sc[qg][kb][e], f, mc);
             sc[qg][kb][e] = p;
             rs += p;
           }
@@ -456,11 +520,12 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
             for (int e = 0; e < 4; ++e) o[qg][db][e] *= alpha[qg];
       }
       {  // step i: key half i / (DB / 2), output blocks 2 (i % (DB / 2)) and + 1
-        bf16x8 pf[2][G], vfr[4][2];
+        Parts<EXACT ? 3 : 1> pf[2][G];
+        bf16x8 vfr[4][2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-          for (int qg = 0; qg < G; ++qg) pf[ks][qg] = pack2(sc[qg][2 * ks], sc[qg][2 * ks + 1]);
+          for (int qg = 0; qg < G; ++qg) pf[ks][qg] = weights<EXACT>(sc[qg][2 * ks], sc[qg][2 * ks + 1]);
         constexpr int HB = DB / 2;
         pipelined<2 * HB, 3>(
             [&](int i) {
@@ -472,7 +537,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
               for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int qg = 0; qg < G; ++qg)
-                  o[qg][2 * (i % HB) + h] = MFMA16(vfr[i & 3][h], pf[i / HB][qg], o[qg][2 * (i % HB) + h]);
+                  o[qg][2 * (i % HB) + h] = mma_weights(vfr[i & 3][h], pf[i / HB][qg], o[qg][2 * (i % HB) + h]);
             },
             [&](int i) { issue_step(2 * KK + i, nn); });
       }
@@ -486,24 +551,35 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
   for (int qg = 0; qg < G; ++qg) {
     const int q = qw + 16 * qg + lr;
     const float lsum = quad_sum(l[qg]);
+    bf16 *out = a + ((int64_t)bi * s + q) * ((int64_t)n * d) + (int64_t)j * d;
+    float *out_lse = lse + ((int64_t)bi * n + j) * s + q;
+    float z = 0.0f;   // EXACT: NaN where a result is not finite
     if (q < s && !rb.idle) {
       const float inv = 1.0f / lsum;
-      bf16 *out = a + ((int64_t)bi * s + q) * ((int64_t)n * D) + (int64_t)j * D;
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
+        if (EXACT && db * 16 + 4 * g >= d) continue;
         bf16x4 v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (bf16)(o[qg][db][e] * inv);
+        for (int e = 0; e < 4; ++e) {
+          const float x = o[qg][db][e] * inv;
+          if constexpr (EXACT) z = fmaf(x, 0.0f, z);
+          v[e] = (bf16)x;
+        }
         *reinterpret_cast<bf16x4 *>(out + db * 16 + 4 * g) = v;
       }
-      if (g == 0) lse[((int64_t)bi * n + j) * s + q] = (m[qg] * c + log2f(lsum)) * kLn2;
+      if (g == 0) *out_lse = EXACT ? plus_log(product_of(m[qg], scale), lsum) : (m[qg] * c + log2f(lsum)) * kLn2;
+    }
+    if constexpr (EXACT) {
+      const int first = qw + 16 * qg, last = first + 15 < s ? first + 15 : s - 1;
+      if (!all_finite(z)) redo_fwd<bf16, D>(base, ld, s, d, scale, q, last, g, out, out_lse);
     }
   }
 }
 
 // ------------------------------------------------------------------ backward: dq (and D)
-template <int D, bool PAIRED>
-__global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, int group, float scale, const bf16 *__restrict__ qkv,
+template <int D, bool PAIRED, bool EXACT>
+__global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, int head_dim, int group, float scale, const bf16 *__restrict__ qkv,
                                                          const bf16 *__restrict__ a, const float *__restrict__ lse,
                                                          const bf16 *__restrict__ da, bf16 *__restrict__ dqkv,
                                                          float *__restrict__ Dvec) {
@@ -518,32 +594,45 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
   const BackwardBlocks<PAIRED> bb(s, PAIRED ? hb.order : row_blocks(s) - 1 - hb.order, threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
-  const int64_t ld = (int64_t)n * 3 * D, pld = (int64_t)n * D;
-  const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * D;
+  const int d = EXACT ? head_dim : D;
+  const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
+  const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * d;
   const int qw = bb.block * 64 + ((threadIdx.x >> 6) & 3) * 16;
   const int k_half = PAIRED ? 0 : (wave >> 2) * 32;   // first key of a tile that this wave takes
-  const float c = scale * kLog2e;
+  const float f = EXACT ? scale : scale * kLog2e;
   typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
   const int q = qw + lr, qc = q < s ? q : s - 1;
   bf16x8 qf[KK], dof[KK];
   float dsum = 0.0f;
+  const bf16 *dah = da + (int64_t)bi * s * pld + (int64_t)j * d;
   {
-    const bf16 *dar = da + ((int64_t)bi * s + qc) * pld + (int64_t)j * D;
-    const bf16 *ar = a + ((int64_t)bi * s + qc) * pld + (int64_t)j * D;
+    const bf16 *ar = a + ((int64_t)bi * s + qc) * pld + (int64_t)j * d;
+    f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      qf[kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)qc * ld + 32 * kk + 8 * g);
-      dof[kk] = *reinterpret_cast<const bf16x8 *>(dar + 32 * kk + 8 * g);
-      const bf16x8 av = *reinterpret_cast<const bf16x8 *>(ar + 32 * kk + 8 * g);
+      const int col = 32 * kk + 8 * g;
+      qf[kk] = row_chunk<EXACT>(base + (int64_t)qc * ld, col, d);
+      dof[kk] = row_chunk<EXACT>(dah + (int64_t)qc * pld, col, d);
+      const bf16x8 av = row_chunk<EXACT>(ar, col, d);
+      if constexpr (EXACT) {   // D on the diagonal of a dO^T, by the same MFMAs as dP: where a row has one key (a = v) the two cancel exactly
+        t = MFMA16(av, dof[kk], t);
+      } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) dsum += (float)dof[kk][i] * (float)av[i];
+        for (int i = 0; i < 8; ++i) dsum += (float)dof[kk][i] * (float)av[i];
+      }
     }
-    dsum = quad_sum(dsum);
+    if constexpr (EXACT) {
+      const float mine = (lr & 2) ? ((lr & 1) ? t[3] : t[2]) : ((lr & 1) ? t[1] : t[0]);
+      dsum = __shfl(mine, 16 * (lr >> 2) + lr, 64);
+    } else {
+      dsum = quad_sum(dsum);
+    }
   }
-  float lse2 = lse[((int64_t)bi * n + j) * s + qc] * kLog2e;
-  if (q < s && g == 0 && (PAIRED ? !bb.idle : wave < 4)) Dvec[((int64_t)bi * n + j) * s + q] = -dsum;   // as the dk/dv kernel starts its accumulators
+  float lsf = lse[((int64_t)bi * n + j) * s + qc];
+  if constexpr (!EXACT) lsf *= kLog2e;
+  if (q < s && g == 0 && (PAIRED ? !bb.idle : wave < 4)) Dvec[((int64_t)bi * n + j) * s + q] = EXACT ? dsum : -dsum;   // as the dk/dv kernel starts its accumulators, or subtracts it
 
   f32x4 dq[DB];
 #pragma unroll
@@ -555,10 +644,10 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
   // tile DMAs as in the forward kernel
   constexpr int IPW = T::NI;   // DMA instructions per wave and tile
   const int quarter = wave & 3, half = wave >> 2;
-  TileStream kv(base + D + half * D, ((int64_t)s * ld - (j * 3 + 1 + half) * D) * 2, 64 * ld * 2);
+  TileStream kv(base + d + half * d, ((int64_t)s * ld - (j * 3 + 1 + half) * d) * 2, 64 * ld * 2);
   uint32_t dma_off[IPW];
 #pragma unroll
-  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(ld * 2), quarter, lane, i);
+  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(ld * 2), quarter, lane, i, d);
   auto issue_one = [&](auto tag, int st, int i) {   // instruction i of the stream's next tile into ring stage st
     constexpr int TAG = decltype(tag)::value;
     dma16<TAG>(kv.rsrc(), smem_addr + st * STAGE + half * T::BYTES + (quarter * IPW + i) * 1024, dma_off[i]);
@@ -582,7 +671,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
     arrive(qf[kk]);
     arrive(dof[kk]);
   }
-  arrive(lse2);
+  arrive(lsf);
   arrive(dsum);
   int cur = 0;
   for (int it = 0; it < ntiles; ++it) {
@@ -594,10 +683,11 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
     if (bb.idle || kv0 > qw + 15) {
       issue(nn);
     } else {
-      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D
+      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D (EXACT: dP)
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb) {
-        pc[kb] = f32x4{-dsum, -dsum, -dsum, -dsum};
+        const float start = EXACT ? 0.0f : -dsum;
+        pc[kb] = f32x4{start, start, start, start};
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[kb][e] = 0.0f;
       }
@@ -640,16 +730,16 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sc[kb][e] = fast_exp2(fmaf(sc[kb][e], c, -lse2)) * pc[kb][e];
-      bf16x8 df[NS];
+        for (int e = 0; e < 4; ++e) sc[kb][e] = weight<EXACT>(sc[kb][e], f, lsf) * (EXACT ? pc[kb][e] - dsum : pc[kb][e]);
+      Parts<EXACT ? 3 : 1> df[NS];
 #pragma unroll
-      for (int ks = 0; ks < NS; ++ks) df[ks] = pack2(sc[2 * ks], sc[2 * ks + 1]);
+      for (int ks = 0; ks < NS; ++ks) df[ks] = weights<EXACT>(sc[2 * ks], sc[2 * ks + 1]);
       pipelined_run<NS * HB, PT>(
           load,
           [&](int i) {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-              dq[2 * (i % HB) + h] = MFMA16(ktr[i % (PT + 1)][h], df[i / HB], dq[2 * (i % HB) + h]);
+              dq[2 * (i % HB) + h] = mma_weights(ktr[i % (PT + 1)][h], df[i / HB], dq[2 * (i % HB) + h]);
           },
           [&](int i) { issue_step(NS * KK + i, nn); });
     }
@@ -657,11 +747,18 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
     cur = cur == 2 ? 0 : cur + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  bf16 *out = dqkv + ((int64_t)bi * s + q) * ld + (int64_t)j * 3 * d;
+  float z = 0.0f;   // EXACT: NaN where a result is not finite
   auto store = [&](int db, const f32x4 &sum) {
+    if (EXACT && db * 16 + 4 * g >= d) return;
     bf16x4 v;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (bf16)(sum[e] * scale);
-    *reinterpret_cast<bf16x4 *>(dqkv + ((int64_t)bi * s + q) * ld + (int64_t)j * 3 * D + db * 16 + 4 * g) = v;
+    for (int e = 0; e < 4; ++e) {
+      const float x = sum[e] * scale;
+      if constexpr (EXACT) z = fmaf(x, 0.0f, z);
+      v[e] = (bf16)x;
+    }
+    *reinterpret_cast<bf16x4 *>(out + db * 16 + 4 * g) = v;
   };
   if constexpr (PAIRED) {
     if (q < s && !bb.idle) {
@@ -681,11 +778,15 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
 #pragma unroll
     for (int db = 0; db < DB; ++db) store(db, dq[db] + slots[db * 64]);
   }
+  if constexpr (EXACT) {
+    if (wave < 4 && !all_finite(z))
+      redo_dq<bf16, D>(base, ld, dah, pld, s, d, scale, q, qw + 15 < s ? qw + 15 : s - 1, lse[((int64_t)bi * n + j) * s + qc], dsum, g, out);
+  }
 }
 
 // ------------------------------------------------------------------ backward: dk, dv
-template <int D, bool PAIRED>
-__global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, int group, float scale, const bf16 *__restrict__ qkv,
+template <int D, bool PAIRED, bool EXACT>
+__global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, int head_dim, int group, float scale, const bf16 *__restrict__ qkv,
                                                            const float *__restrict__ lse,
                                                            const float *__restrict__ Dvec,
                                                            const bf16 *__restrict__ da, bf16 *__restrict__ dqkv) {
@@ -700,12 +801,13 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
   const BackwardBlocks<PAIRED> bb(s, hb.order, threadIdx.x >> 6);   // (from the thread number; head size 160: 194 registers instead of 230)
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
-  const int64_t ld = (int64_t)n * 3 * D, pld = (int64_t)n * D;
-  const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * D;
-  const bf16 *dab = da + (int64_t)bi * s * pld + (int64_t)j * D;
+  const int d = EXACT ? head_dim : D;
+  const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
+  const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * d;
+  const bf16 *dab = da + (int64_t)bi * s * pld + (int64_t)j * d;
   const int kw = bb.block * 64 + ((threadIdx.x >> 6) & 3) * 16;
   const int q_half = PAIRED ? 0 : (wave >> 2) * 32;   // first query of a tile that this wave takes
-  const float c = scale * kLog2e;
+  const float f = EXACT ? scale : scale * kLog2e;
   typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
@@ -713,8 +815,8 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
   bf16x8 kf[KK], vf[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
-    kf[kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)keyc * ld + D + 32 * kk + 8 * g);
-    vf[kk] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)keyc * ld + 2 * D + 32 * kk + 8 * g);
+    kf[kk] = row_chunk<EXACT>(base + (int64_t)keyc * ld + d, 32 * kk + 8 * g, d);
+    vf[kk] = row_chunk<EXACT>(base + (int64_t)keyc * ld + 2 * d, 32 * kk + 8 * g, d);
   }
   f32x4 dk[DB], dv[DB];
 #pragma unroll
@@ -729,11 +831,11 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
   constexpr int IPW = T::NI;
   const int quarter = wave & 3, half = wave >> 2;
   const int64_t pitch = half ? pld : ld, row0 = (int64_t)t_first * 64;
-  TileStream qo(half ? dab + row0 * pld : base + row0 * ld, ((s - row0) * pitch - (half ? j : 3 * j) * D) * 2, 64 * pitch * 2);
+  TileStream qo(half ? dab + row0 * pld : base + row0 * ld, ((s - row0) * pitch - (half ? j : 3 * j) * d) * 2, 64 * pitch * 2);
   TileStream stats(((wave & 1) ? Dvec : lse) + ((int64_t)bi * n + j) * s + row0, (s - row0) * 4, 256);
   uint32_t dma_off[IPW];
 #pragma unroll
-  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(pitch * 2), quarter, lane, i);
+  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(pitch * 2), quarter, lane, i, d);
   auto issue_one = [&](auto tag, int st, int i) {   // i == IPW: the statistics
     constexpr int TAG = decltype(tag)::value;
     const uint32_t stage = smem_addr + st * STAGE;
@@ -777,10 +879,11 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
     if (bb.idle || q0 + 16 * NB - 1 < kw) {  // wave-uniform: none of this wave's queries sees one of its keys
       issue(nn);
     } else {
-      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D
+      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D (EXACT: dP)
 #pragma unroll
       for (int qb = 0; qb < NB; ++qb) {
-        pc[qb] = *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
+        if constexpr (EXACT) pc[qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        else pc[qb] = *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[qb][e] = 0.0f;
       }
@@ -825,24 +928,25 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
 #pragma unroll
       for (int qb = 0; qb < NB; ++qb) {
         const f32x4 ls = *reinterpret_cast<const f32x4 *>(stat + 16 * qb + 4 * g);
+        if constexpr (EXACT) pc[qb] -= *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          sc[qb][e] = fast_exp2(fmaf(sc[qb][e], c, -ls[e] * kLog2e));
+          sc[qb][e] = weight<EXACT>(sc[qb][e], f, EXACT ? ls[e] : ls[e] * kLog2e);
           pc[qb][e] *= sc[qb][e];
         }
       }
-      bf16x8 pf[NS], df[NS];
+      Parts<EXACT ? 3 : 1> pf[NS], df[NS];
 #pragma unroll
       for (int ks = 0; ks < NS; ++ks) {
-        pf[ks] = pack2(sc[2 * ks], sc[2 * ks + 1]);
-        df[ks] = pack2(pc[2 * ks], pc[2 * ks + 1]);
+        pf[ks] = weights<EXACT>(sc[2 * ks], sc[2 * ks + 1]);
+        df[ks] = weights<EXACT>(pc[2 * ks], pc[2 * ks + 1]);
       }
       if constexpr (LATE) pipelined_start<NS * DB, PT>(load);
       pipelined_run<NS * DB, PT>(
           load,
           [&](int i) {
-            dv[i % DB] = MFMA16(otr[i % (PT + 1)], pf[i / DB], dv[i % DB]);
-            dk[i % DB] = MFMA16(qtr[i % (PT + 1)], df[i / DB], dk[i % DB]);
+            dv[i % DB] = mma_weights(otr[i % (PT + 1)], pf[i / DB], dv[i % DB]);
+            dk[i % DB] = mma_weights(qtr[i % (PT + 1)], df[i / DB], dk[i % DB]);
           },
           [&](int i) { issue_step(NS * KK + i, nn); });
     }
@@ -850,16 +954,20 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
     cur = cur == 2 ? 0 : cur + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  bf16 *out = dqkv + ((int64_t)bi * s + key) * ld + (int64_t)j * 3 * d;
+  float z = 0.0f;   // EXACT: NaN where a result is not finite
   auto store = [&](int db, const f32x4 &sk, const f32x4 &sv) {
-    bf16 *out = dqkv + ((int64_t)bi * s + key) * ld + (int64_t)j * 3 * D;
+    if (EXACT && db * 16 + 4 * g >= d) return;
     bf16x4 ok, ov;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      ok[e] = (bf16)(sk[e] * scale);
+      const float x = sk[e] * scale;
+      if constexpr (EXACT) z = fmaf(x, 0.0f, fmaf(sv[e], 0.0f, z));
+      ok[e] = (bf16)x;
       ov[e] = (bf16)sv[e];
     }
-    *reinterpret_cast<bf16x4 *>(out + D + db * 16 + 4 * g) = ok;
-    *reinterpret_cast<bf16x4 *>(out + 2 * D + db * 16 + 4 * g) = ov;
+    *reinterpret_cast<bf16x4 *>(out + d + db * 16 + 4 * g) = ok;
+    *reinterpret_cast<bf16x4 *>(out + 2 * d + db * 16 + 4 * g) = ov;
   };
   if constexpr (PAIRED) {
     if (key < s && !bb.idle) {
@@ -882,6 +990,10 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
 #pragma unroll
     for (int db = 0; db < DB; ++db) store(db, dk[db] + slots[db * 64], dv[db] + slots[(DB + db) * 64]);
   }
+  if constexpr (EXACT) {
+    const int64_t st = ((int64_t)bi * n + j) * s;
+    if (wave < 4 && !all_finite(z)) redo_dkv<bf16, D>(base, ld, dab, pld, s, d, scale, kw, key, lse + st, Dvec + st, g, out);
+  }
 }
 
 // Forward with 32 rows per wave on eight waves (256 rows per workgroup): every K / V fragment read from LDS feeds two
@@ -891,40 +1003,40 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
 // with 16 rows per wave) and the head size is 128 or 160 (at 64 the variant measures 17 % slower).  Measured with the
 // kernel as it was before the grid ran heads first: 1.3B-shaped layer (4 x 16 heads x 128) 168 with 16 rows, 123 us with 32,
 // slice at micro-batch 4 167 and 129 us, whole layer (128 heads) 326 and 250 us.
-template <int D, int G>
-int fwd_launch_g(int b, int s, int n, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
+template <int D, int G, bool EXACT = false>
+int fwd_launch_g(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
   constexpr int smem = 3 * 2 * 64 * D * 2;
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, G>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) !=
+    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, G, EXACT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) !=
         hipSuccess)
       return MTNLG_HIP_ERROR;
     attr_mark_set(attr_done, device);
   }
   const int count = PairedBlocks<G>::count(s), group = HeadBlock::group(b, n, count, 32, D >= 128 ? 511 : 768);   // (768: 3 a compute unit)
   LaunchScope scope(MTNLG_K_ATTN_FWD, st);
-  attn_fwd_kernel<D, G><<<HeadBlock::grid(b, n, group, count), 512, smem, st>>>(b, s, n, group, scale, (const bf16 *)qkv, (bf16 *)a, lse);
+  attn_fwd_kernel<D, G, EXACT><<<HeadBlock::grid(b, n, group, count), 512, smem, st>>>(b, s, n, d, group, scale, (const bf16 *)qkv, (bf16 *)a, lse);
   return check_launch();
 }
 
 template <int D>
 int fwd_launch(int b, int s, int n, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
-  if (D >= 128 && (int64_t)PairedBlocks<2>::count(s) * n * b >= 256) return fwd_launch_g<D, 2>(b, s, n, scale, qkv, a, lse, st);
-  return fwd_launch_g<D, 1>(b, s, n, scale, qkv, a, lse, st);
+  if (D >= 128 && (int64_t)PairedBlocks<2>::count(s) * n * b >= 256) return fwd_launch_g<D, 2>(b, s, n, D, scale, qkv, a, lse, st);
+  return fwd_launch_g<D, 1>(b, s, n, D, scale, qkv, a, lse, st);
 }
 
 // 16 rows per wave in both backward kernels: 32 do not fit the 256 registers a wave has at eight waves.
-template <int D, bool PAIRED>
-int bwd_launch_p(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
+template <int D, bool PAIRED, bool EXACT = false>
+int bwd_launch_p(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                  void *dqkv, void *ws, hipStream_t st) {
   constexpr int smem_dq = 3 * 2 * 64 * D * 2, smem_dkv = 3 * (2 * 64 * D * 2 + 512);
   static_assert(smem_dkv >= 4 * 2 * (D / 16) * 1024, "the merge of the two halves fits the rings");
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    if (hipFuncSetAttribute((const void *)attn_bwd_dq_kernel<D, PAIRED>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dq) != hipSuccess ||
-        hipFuncSetAttribute((const void *)attn_bwd_dkv_kernel<D, PAIRED>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dkv) != hipSuccess)
+    if (hipFuncSetAttribute((const void *)attn_bwd_dq_kernel<D, PAIRED, EXACT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dq) != hipSuccess ||
+        hipFuncSetAttribute((const void *)attn_bwd_dkv_kernel<D, PAIRED, EXACT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_dkv) != hipSuccess)
       return MTNLG_HIP_ERROR;
     attr_mark_set(attr_done, device);
   }
@@ -932,10 +1044,10 @@ int bwd_launch_p(int b, int s, int n, float scale, const void *qkv, const void *
   const int count = BackwardBlocks<PAIRED>::count(s), group = HeadBlock::group(b, n, count, PAIRED || D >= 128 ? 32 : 128, PAIRED ? 511 : 2047);
   const dim3 grid = HeadBlock::grid(b, n, group, count);
   LaunchScope scope(MTNLG_K_ATTN_BWD, st);
-  attn_bwd_dq_kernel<D, PAIRED><<<grid, 512, smem_dq, st>>>(b, s, n, group, scale, (const bf16 *)qkv, (const bf16 *)a, lse,
+  attn_bwd_dq_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dq, st>>>(b, s, n, d, group, scale, (const bf16 *)qkv, (const bf16 *)a, lse,
                                                            (const bf16 *)da, (bf16 *)dqkv, Dvec);
   MTNLG_TRY(check_launch());
-  attn_bwd_dkv_kernel<D, PAIRED><<<grid, 512, smem_dkv, st>>>(b, s, n, group, scale, (const bf16 *)qkv, lse, Dvec, (const bf16 *)da,
+  attn_bwd_dkv_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dkv, st>>>(b, s, n, d, group, scale, (const bf16 *)qkv, lse, Dvec, (const bf16 *)da,
                                                              (bf16 *)dqkv);
   return check_launch();
 }
@@ -970,12 +1082,24 @@ bool bwd_paired(int b, int s, int n) {
 template <int D>
 int bwd_launch(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                void *dqkv, void *ws, hipStream_t st) {
-  if (bwd_paired<D>(b, s, n)) return bwd_launch_p<D, true>(b, s, n, scale, qkv, a, lse, da, dqkv, ws, st);
-  return bwd_launch_p<D, false>(b, s, n, scale, qkv, a, lse, da, dqkv, ws, st);
+  if (bwd_paired<D>(b, s, n)) return bwd_launch_p<D, true>(b, s, n, D, scale, qkv, a, lse, da, dqkv, ws, st);
+  return bwd_launch_p<D, false>(b, s, n, D, scale, qkv, a, lse, da, dqkv, ws, st);
 }
 
 // The DMA addresses a sequence's rows with 32-bit byte offsets from its first row.
 bool fits(int s, int n, int d) { return (int64_t)s * n * 3 * d * 2 < ((int64_t)1 << 31); }
+
+// fn<D>, D: the head size rounded up to a multiple of 32
+#define BY_HEAD_SIZE(fn, ...)                                  \
+  switch ((d + 31) / 32) {                                     \
+    case 1: return fn(32)(__VA_ARGS__);                        \
+    case 2: return fn(64)(__VA_ARGS__);                        \
+    case 3: return fn(96)(__VA_ARGS__);                        \
+    case 4: return fn(128)(__VA_ARGS__);                       \
+    case 5: return fn(160)(__VA_ARGS__);                       \
+    case 6: return fn(192)(__VA_ARGS__);                       \
+    default: return MTNLG_UNSUPPORTED_SHAPE;                   \
+  }
 
 }  // namespace
 
@@ -1007,6 +1131,41 @@ int attention_bwd_mfma(int b, int s, int n, int d, float scale, const void *qkv,
     case 160: return bwd_launch<160>(b, s, n, scale, qkv, a, lse, da, dqkv, ws, stream);
     default: return MTNLG_UNSUPPORTED_SHAPE;
   }
+}
+
+// Rows are fetched in pieces of 16 bytes from addresses that have to be aligned to 4, and results leave in pieces of 8.
+static bool exact_takes(int dtype, int b, int s, int n, int d) {
+  return dtype == MTNLG_BF16 && d % 8 == 0 && d <= 192 && s <= ATTENTION_F32_MAX_SEQ && n <= 65535 && b <= 65535 && fits(s, n, d);
+}
+static int64_t groups_of_16(int b, int s, int n) { return (int64_t)b * n * ((s + 15) / 16); }
+
+// Against the kernels without LDS (attention_f32.hip), 444 sizes of 1 to 32 heads of 24 to 184, s 16 to 2048, and larger ones: faster
+// wherever those give a wave 16 rows of its own (more than 512 groups of 16 rows).  us, those / these, forward, then backward: 2 x 1024 x 16
+// heads of 96 103 / 21, 327 / 61; 4 x 2048 x 16 of 32 243 / 60, 641 / 163; 1024 x 16 of 192 104 / 31, 383 / 75; 32 x 64 x 16 of 80
+// 11.8 / 7.2, 31.6 / 24.3.  With fewer groups those split the streamed side over four waves, and these win by the longer sequences:
+// 512 x 16 of 96 14.9 / 11.6, 42.8 / 28.2, but 128 x 16 of 96 5.6 / 6.3, and at head size 24 512 x 4 6.8 / 8.4, 15.9 / 16.9; head size 56
+// forward 512 x 4 8.8 / 9.7, 512 x 16 11.3 / 10.1, backward 256 x 4 14.8 / 14.4, 128 x 4 10.2 / 10.8.
+bool attention_exact_fwd_takes(int dtype, int b, int s, int n, int d, const void *qkv, const void *a) {
+  if (!exact_takes(dtype, b, s, n, d) || (((uintptr_t)qkv | (uintptr_t)a) & 7)) return false;
+  const int64_t groups = groups_of_16(b, s, n);
+  return groups > 512 ? s > 32 : s > 256 && (d > 64 || (d > 32 && groups > 256));
+}
+bool attention_exact_bwd_takes(int dtype, int b, int s, int n, int d, const void *qkv, const void *a, const void *da, const void *dqkv) {
+  if (!exact_takes(dtype, b, s, n, d) || (((uintptr_t)qkv | (uintptr_t)a | (uintptr_t)da | (uintptr_t)dqkv) & 7)) return false;
+  return groups_of_16(b, s, n) > 512 ? s > 32 : s > 192 && d > 32;
+}
+
+int attention_fwd_exact(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream) {
+#define FWD(D) fwd_launch_g<D, 1, true>
+  BY_HEAD_SIZE(FWD, b, s, n, d, scale, qkv, a, lse, stream)
+#undef FWD
+}
+
+int attention_bwd_exact(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
+                        void *dqkv, void *ws, hipStream_t stream) {
+#define BWD(D) bwd_launch_p<D, false, true>
+  BY_HEAD_SIZE(BWD, b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream)
+#undef BWD
 }
 
 }  // namespace mtnlg

@@ -341,6 +341,14 @@ def test_attention_by_rows_of_a_workgroup(dtype, b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
 
 
+# bf16, P and dS in fp32, streamed side through LDS: the edges of its rule (513 groups of 16 rows, s 33; s 193 / 257 with fewer), of
+# the 64 rows of a block and of the head sizes that a tile of 32 k columns holds.
+@pytest.mark.parametrize("b,s,n,d", [(3, 33, 58, 8), (2, 64, 65, 32), (1, 65, 104, 40), (1, 129, 58, 88), (2, 127, 33, 96), (1, 191, 43, 104),
+                                     (1, 193, 3, 184), (1, 257, 2, 72), (1, 257, 17, 56), (1, 513, 1, 192), (1, 300, 2, 136)])
+def test_attention_with_exact_weights(b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
+
+
 # An infinity or NaN in one token reaches only what depends on that token.  K and V of token t0: outputs and dq of the rows before it
 # stay as they were; Q and dO of token t0: dk and dv of the keys after it.  t0 at the start, inside and at the end of a 16-row
 # block, and the last token, whose block hangs over the end of the sequence.
