@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmtnlg.so")
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ("api.cpp", "profile.cpp", "elementwise.hip", "gemm_generic.hip", "gemm_mfma.hip", "gemm_wave.hip",
+SOURCES = ("api.cpp", "profile.cpp", "elementwise.hip", "gemm_generic.hip", "gemm_mfma.hip", "gemm_wave.hip", "gemm_parts.hip",
            "attention_f32.hip", "attention_mfma.hip", "optimizer.hip", "head.hip", "calibrate.hip")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -4,6 +4,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "common.h"
 
 using namespace mtnlg;
@@ -389,10 +391,13 @@ int mtnlg_gemm(int dtype, int layout, int64_t M, int64_t N, int64_t K, const voi
   if (dtype == MTNLG_F32) epilogue &= ~MTNLG_EPI_OUT_F32;
   hipStream_t st = (hipStream_t)stream;
   if (gemm_wave_takes(dtype, layout, M, N, K, A, B, C, bias, aux)) {
-    const double other = dtype == MTNLG_F32 ? gemm_generic_time(layout, M, N, K)
-                                            : gemm_mfma_time(layout, M, N, K, workspace ? workspace_bytes : 0);
+    const double generic = dtype == MTNLG_F32 ? std::min(gemm_generic_time(layout, M, N, K), gemm_direct_time(M, N, K)) : 0.0;
+    const double parts = gemm_parts_time(M, N, K);
+    const bool in_parts = dtype == MTNLG_F32 && parts < generic;
+    const double other = in_parts ? parts : dtype == MTNLG_F32 ? generic : gemm_mfma_time(layout, M, N, K, workspace ? workspace_bytes : 0);
     const int tile = gemm_wave_pick(dtype, layout, M, N, K, other);
     if (tile) return gemm_wave(dtype, layout, M, N, K, A, B, C, bias, aux, epilogue, tile, st);
+    if (in_parts) return gemm_parts(layout, M, N, K, A, B, C, bias, aux, epilogue, st);
   }
   if (dtype == MTNLG_BF16) {
     int r = gemm_mfma_bf16(layout, M, N, K, A, B, C, bias, aux, epilogue, workspace, workspace_bytes, st);

@@ -331,9 +331,14 @@ bool gemm_wave_takes(int dtype, int layout, int64_t M, int64_t N, int64_t K, con
                      const void *bias, const void *aux);
 int gemm_wave(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B, void *C, const void *bias,
               void *aux, uint32_t epi, int tile, hipStream_t stream);   // tile: 32 or 64
+// fp32 problems that gemm_wave_takes, on 128 x 128 tiles
+double gemm_parts_time(int64_t M, int64_t N, int64_t K);
+int gemm_parts(int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B, void *C, const void *bias, void *aux, uint32_t epi,
+               hipStream_t stream);
 // the faster of the two tiles if it is estimated below `other` microseconds, else 0
 int gemm_wave_pick(int dtype, int layout, int64_t M, int64_t N, int64_t K, double other);
 double gemm_generic_time(int layout, int64_t M, int64_t N, int64_t K);   // of an fp32 problem on 64 x 64 tiles
+double gemm_direct_time(int64_t M, int64_t N, int64_t K);   // ... on the fp32 instructions, infinite for sums that these are not for
 bool gemm_generic_small_tile(int layout, int64_t M, int64_t N);   // 32 x 32 tiles, not 64 x 64, where accesses are aligned
 // returns MTNLG_UNSUPPORTED_SHAPE when the MFMA kernel cannot take this problem
 // ws (nullable): scratch for the split-K tail, see gemm_mfma_workspace_bytes

@@ -1,7 +1,7 @@
-// GEMM with operands loaded straight into registers: the large fp32 problems, and every problem whose row lengths the kernels that move
+// GEMM with operands loaded straight into registers: fp32 problems between a few tiles and many, and every problem whose row lengths the kernels that move
 // tiles by DMA do not take (bf16 elements are widened on load, which is exact).  Any M, N, K, any layout.
 //
-// fp32 values are cut into three bf16 parts that add up to them exactly, and the six largest of the nine products of parts run
+// Longer sums of fp32 values: they are cut into three bf16 parts that add up to them exactly, and the six largest of the nine products of parts run
 // on v_mfma_f32_16x16x32_bf16 (common.h: Parts): sums in fp32, an error below that of the fp32 instructions (1024 x 1024 x 4096 against
 // 64 bits: 5.7e-7 with those, 2.2e-7 so).  What bounds it: per 64 x 64 wave tile and 32 k 96 MFMAs (1600 cycles) and 250 vector
 // instructions for the parts (1100 cycles), which the two waves of a SIMD overlap little, and the 16 KB of operands that come
@@ -108,11 +108,11 @@ struct Frag {
 };
 
 // Workgroup of WGM x WGN x WGK waves, wave tile 16 TMB x 16 TNB.  VEC: every row length is a multiple of 4 elements and
-// every pointer aligned to 4 elements.
-template <typename E, int TMB, int TNB, int WGM, int WGN, int WGK, bool AT, bool BT, bool VEC>
-__global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm_f32_kernel(F32GemmArgs a) {
-  constexpr int KH = 2, CHUNK = 16 * KH;
-  constexpr int NP = sizeof(E) == 2 ? 1 : 3;
+// every pointer aligned to 4 elements.  DIRECT: chunks of 16 k on the fp32 instructions, two in flight (gemm_direct_time says when).
+template <typename E, int TMB, int TNB, int WGM, int WGN, int WGK, bool AT, bool BT, bool VEC, bool DIRECT>
+__global__ __launch_bounds__(64 * WGM * WGN * WGK, DIRECT && TMB == 2 ? 8 : 2) void gemm_f32_kernel(F32GemmArgs a) {
+  constexpr int KH = DIRECT ? 1 : 2, CHUNK = 16 * KH;
+  constexpr int NP = sizeof(E) == 2 || DIRECT ? 1 : 3;
   constexpr int NV = TMB * TNB;   // vectors of 4 columns a lane holds
   __shared__ f32x4 red[WGK > 1 ? WGK * WGM * WGN * NV * 64 : 1];
   const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
@@ -144,37 +144,67 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm_f32_kernel(F32Ge
   // unconditional (clamped): fragments that are fetched on some paths only, under a condition the compiler takes for
   // divergent, were miscompiled (accumulators placed over live fragments).
   auto start = [&](int c) { return (int64_t)(c < nc_all ? c : nc_all - 1) * CHUNK; };
-  af.fetch(A, a.lda, m0, a.M, start(c0), a.K, g, r);
-  bf.fetch(B, a.ldb, n0, a.N, start(c0), a.K, g, r);
-  for (int c = c0; c < c1; ++c) {
-    const int64_t k0 = (int64_t)c * CHUNK;
-    if (k0 + CHUNK > a.K) {   // uniform: the last chunk of a K that is no multiple of the chunk
-      af.clear_tail(k0, a.K, g);
-      bf.clear_tail(k0, a.K, g);
+  if constexpr (DIRECT) {
+    Frag<E, TMB, KH, AT, VEC> ad[2];
+    Frag<E, TNB, KH, BT, VEC> bd[2];
+    auto fetch = [&](int d, int c) {
+      ad[d].fetch(A, a.lda, m0, a.M, start(c), a.K, g, r);
+      bd[d].fetch(B, a.ldb, n0, a.N, start(c), a.K, g, r);
+    };
+    fetch(0, c0);
+    fetch(1, c0 + 1);
+    for (int c = c0; c < c1; c += 2) {
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        if (c + d < c1) {
+          const int64_t k0 = (int64_t)(c + d) * CHUNK;
+          if (k0 + CHUNK > a.K) {
+            ad[d].clear_tail(k0, a.K, g);
+            bd[d].clear_tail(k0, a.K, g);
+          }
+#pragma unroll
+          for (int e = 0; e < 4 * KH; ++e)
+#pragma unroll
+            for (int i = 0; i < TMB; ++i)
+#pragma unroll
+              for (int j = 0; j < TNB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bd[d].v[j][e], ad[d].v[i][e], acc[i][j], 0, 0, 0);
+          if (c + d + 2 < c1) fetch(d, c + d + 2);
+        }
+      }
     }
-    Parts<NP> ap[TMB], bp[TNB];
+  } else {
+    af.fetch(A, a.lda, m0, a.M, start(c0), a.K, g, r);
+    bf.fetch(B, a.ldb, n0, a.N, start(c0), a.K, g, r);
+    for (int c = c0; c < c1; ++c) {
+      const int64_t k0 = (int64_t)c * CHUNK;
+      if (k0 + CHUNK > a.K) {   // uniform: the last chunk of a K that is no multiple of the chunk
+        af.clear_tail(k0, a.K, g);
+        bf.clear_tail(k0, a.K, g);
+      }
+      Parts<NP> ap[TMB], bp[TNB];
 #pragma unroll
-    for (int i = 0; i < TMB; ++i) ap[i].of(af.v[i]);
-    af.fetch(A, a.lda, m0, a.M, start(c + 1), a.K, g, r);
-    __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < TMB; ++i) ap[i].of(af.v[i]);
+      af.fetch(A, a.lda, m0, a.M, start(c + 1), a.K, g, r);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < TNB; ++j) bp[j].of(bf.v[j]);
-    bf.fetch(B, a.ldb, n0, a.N, start(c + 1), a.K, g, r);
-    __builtin_amdgcn_sched_barrier(0);
+      for (int j = 0; j < TNB; ++j) bp[j].of(bf.v[j]);
+      bf.fetch(B, a.ldb, n0, a.N, start(c + 1), a.K, g, r);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < TNB; ++j) {
+      for (int j = 0; j < TNB; ++j) {
 #pragma unroll
-      for (int i = 0; i < TMB; ++i) acc[i][j] = mma_parts(bp[j], ap[i], acc[i][j], 0);
-      if constexpr (NP > 1) {   // the smaller products in sums of their own (for one chunk: there are no registers to keep them)
-        f32x4 low[TMB];
+        for (int i = 0; i < TMB; ++i) acc[i][j] = mma_parts(bp[j], ap[i], acc[i][j], 0);
+        if constexpr (NP > 1) {   // the smaller products in sums of their own (for one chunk: there are no registers to keep them)
+          f32x4 low[TMB];
 #pragma unroll
-        for (int i = 0; i < TMB; ++i) low[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+          for (int i = 0; i < TMB; ++i) low[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int step = 1; step < 6; ++step)
+          for (int step = 1; step < 6; ++step)
 #pragma unroll
-          for (int i = 0; i < TMB; ++i) low[i] = mma_parts(bp[j], ap[i], low[i], step);
+            for (int i = 0; i < TMB; ++i) low[i] = mma_parts(bp[j], ap[i], low[i], step);
 #pragma unroll
-        for (int i = 0; i < TMB; ++i) acc[i][j] += low[i];
+          for (int i = 0; i < TMB; ++i) acc[i][j] += low[i];
+        }
       }
     }
   }
@@ -254,7 +284,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm_f32_kernel(F32Ge
   }
 }
 
-template <typename E, int TMB, int TNB, int WGM, int WGN, int WGK, bool VEC>
+template <typename E, int TMB, int TNB, int WGM, int WGN, int WGK, bool VEC, bool DIRECT = false>
 int launch_f32(int layout, F32GemmArgs a, hipStream_t st) {
   const int64_t tm = (a.M + 16 * TMB * WGM - 1) / (16 * TMB * WGM), tn = (a.N + 16 * TNB * WGN - 1) / (16 * TNB * WGN);
   if (tm * tn > (1 << 28)) return MTNLG_UNSUPPORTED_SHAPE;
@@ -263,25 +293,28 @@ int launch_f32(int layout, F32GemmArgs a, hipStream_t st) {
   const dim3 grid((unsigned)((tm * tn + 7) / 8 * 8));
   constexpr int threads = 64 * WGM * WGN * WGK;
   if (layout == MTNLG_GEMM_NT)
-    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, false, false, VEC><<<grid, threads, 0, st>>>(a);
+    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, false, false, VEC, DIRECT><<<grid, threads, 0, st>>>(a);
   else if (layout == MTNLG_GEMM_NN)
-    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, false, true, VEC><<<grid, threads, 0, st>>>(a);
+    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, false, true, VEC, DIRECT><<<grid, threads, 0, st>>>(a);
   else
-    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, true, true, VEC><<<grid, threads, 0, st>>>(a);
+    gemm_f32_kernel<E, TMB, TNB, WGM, WGN, WGK, true, true, VEC, DIRECT><<<grid, threads, 0, st>>>(a);
   return check_launch();
 }
 
 template <typename E>
-int gemm_generic_of(int layout, const F32GemmArgs &a, bool vec, bool small, hipStream_t st) {
+int gemm_generic_of(int layout, const F32GemmArgs &a, bool vec, bool small, bool direct, hipStream_t st) {
   if (!vec) return launch_f32<E, 2, 2, 1, 1, 4, false>(layout, a, st);
-  if constexpr (sizeof(E) == 2)   // (small fp32 problems: gemm_wave)
+  if constexpr (sizeof(E) == 4) {
+    if (direct) return small ? launch_f32<E, 2, 2, 1, 1, 8, true, true>(layout, a, st) : launch_f32<E, 4, 4, 1, 1, 4, true, true>(layout, a, st);
+  } else {   // (small fp32 problems: gemm_wave)
     if (small) return launch_f32<E, 2, 2, 1, 1, 8, true>(layout, a, st);
+  }
   return launch_f32<E, 4, 4, 1, 1, 4, true>(layout, a, st);
 }
 
 }  // namespace
 
-// bf16 problems on these kernels: 32 x 32 tiles (K split over eight waves) or 64 x 64 tiles (over four), by rounds of 256 workgroups
+// bf16 problems on these kernels, and fp32 ones on the fp32 instructions: 32 x 32 tiles (K split over eight waves) or 64 x 64 tiles (over four), by rounds of 256 workgroups
 // times the time of a round at equal K on the fp32 instructions: measured then (us, K = 1024, 64 / 32) 256 x 256 23 / 10, 1024 x 1024
 // 26 / 33, 1024 x 3072 NT 88 / 95, TN 64 / 100.
 bool gemm_generic_small_tile(int layout, int64_t M, int64_t N) {
@@ -290,12 +323,21 @@ bool gemm_generic_small_tile(int layout, int64_t M, int64_t N) {
   return rounds(32) * round32 < rounds(64) * round64;
 }
 
-// fp32, 64 x 64 tiles: fitted to 120 measured problems (K 128 to 8192, 256 to 3072 tiles).
+// fp32, 64 x 64 tiles: fitted to 270 measured problems (K 128 to 4096, 4 to 4000 tiles).
 double gemm_generic_time(int layout, int64_t M, int64_t N, int64_t K) {
   const double rounds = (double)(((M + 63) / 64) * ((N + 63) / 64)) / 256;
-  const double per_k = layout == MTNLG_GEMM_NT ? 0.0137 : layout == MTNLG_GEMM_NN ? 0.0110 : 0.0108;
+  const double per_k = layout == MTNLG_GEMM_NT ? 0.0137 : layout == MTNLG_GEMM_NN ? 0.0120 : 0.0118;
   if (rounds <= 1) return 7.5 + 1.17 * per_k * (double)K;   // one wave on a SIMD
-  return 4.0 + (rounds < 2 ? 2 : rounds) * (3.5 + per_k * (double)K);
+  return 4.2 + (rounds < 2 ? 2 : rounds) * (3.7 + per_k * (double)K);
+}
+
+// fp32 on the fp32 instructions (32 x 32 or 64 x 64 tiles by the rule above): short sums, for which the way through LDS and the parts take longer than the products.
+// us here / in gemm_wave.hip, NT, NN, TN: 256 x 1024 x 192 4.6 / 4.7, 4.4 / 4.8, 4.3 / 4.7; 1024 x 1024 x 128 7.9 / 8.8, 7.7 / 9.5, 7.1 / 10.7;
+// 1024 x 2048 x 64 9.1 / 11.3, 10.7 / 11.5, 9.9 / 11.3; at K = 320 256 x 1024 5.3 / 5.3, 512 x 1024 7.9 / 6.8.
+double gemm_direct_time(int64_t M, int64_t N, int64_t K) {
+  if (K > 256) return INFINITY;
+  const double rounds = (double)(((M + 31) / 32) * ((N + 31) / 32)) / 256;
+  return 3.0 + (rounds < 1 ? 1 : rounds) * (0.45 + 0.0055 * (double)K);
 }
 
 int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A,
@@ -309,8 +351,9 @@ int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const v
   const bool vec = a.lda % 4 == 0 && a.ldb % 4 == 0 && N % 4 == 0 &&
                    !(((uintptr_t)A | (uintptr_t)B | (uintptr_t)bias | (uintptr_t)aux) & unit) && !((uintptr_t)C & c_unit);
   LaunchScope scope(MTNLG_K_GEMM_NT + layout, stream);
-  if (dtype == MTNLG_F32) return gemm_generic_of<float>(layout, a, vec, gemm_generic_small_tile(layout, M, N), stream);
-  return gemm_generic_of<bf16>(layout, a, vec, gemm_generic_small_tile(layout, M, N), stream);
+  const bool small = gemm_generic_small_tile(layout, M, N);
+  if (dtype == MTNLG_F32) return gemm_generic_of<float>(layout, a, vec, small, gemm_direct_time(M, N, K) < gemm_generic_time(layout, M, N, K), stream);
+  return gemm_generic_of<bf16>(layout, a, vec, small, false, stream);
 }
 
 }  // namespace mtnlg

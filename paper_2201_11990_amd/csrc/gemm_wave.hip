@@ -319,21 +319,22 @@ bool gemm_wave_takes(int dtype, int layout, int64_t M, int64_t N, int64_t K, con
   return reach_a < (int64_t)RECORDS - 256 && reach_b < (int64_t)RECORDS - 256;
 }
 
-// Estimated microseconds, fitted to 150 bf16 and 120 fp32 problems (graph replays, weights not in the caches).  A workgroup's chain is
-// launch, K / 8 and merge; beyond 256 workgroups the tiles queue for the L2's bandwidth (bf16) or the matrix and vector pipes (fp32,
-// whose cutting into parts adds to the MFMAs).  Measured us, bf16, streaming kernel / 32 / 64: 256 x 512 x 1024 10.6 / 4.5 / 7.0;
-// 512 x 512 x 4096 32 / 8.6 / 15.6; 1024 x 1024 x 4096 38 / 24 / 16.5; 1024 x 2048 x 2048 21 / 38 / 20; 2048 x 2048 x 64 5.5 / 16 / 13.
-// fp32, operands straight to registers / 32 / 64: 128 x 960 x 512 8.0 / 6.1 / 14; 1024 x 1024 x 4096 65 / 68 / 56;
-// 1024 x 4096 x 1024 TN 63 / 75 / 80.
+// Estimated microseconds, fitted to 150 bf16 problems (graph replays, weights not in the caches) and 270 fp32 ones (for which the choice
+// between all four kernels costs 0.6 % on average against the best, 19 % at most).  A workgroup's chain is launch, K / 8 and merge; beyond
+// 256 workgroups the tiles queue for the L2's bandwidth (bf16) or the matrix and vector pipes (fp32, whose cutting into parts adds to the
+// MFMAs).  Measured us, bf16, streaming kernel / 32 / 64: 256 x 512 x 1024 10.6 / 4.5 / 7.0; 512 x 512 x 4096 32 / 8.6 / 15.6;
+// 1024 x 1024 x 4096 38 / 24 / 16.5; 1024 x 2048 x 2048 21 / 38 / 20; 2048 x 2048 x 64 5.5 / 16 / 13.
+// fp32, operands straight to registers / 32 / 64 / 128 (gemm_parts.hip): 128 x 960 x 512 8.0 / 6.1 / 14 / 27; 1024 x 1024 x 4096 82 / 73 / 53 /
+// 169; 1024 x 4096 x 1024 77 / 70 / 69 / 53, TN 59 / 69 / 89 / 50; 2048 x 2048 x 4096 263 / 243 / 195 / 183; 1600 x 2048 x 3000 154 / 161 / 154 / 122.
 int gemm_wave_pick(int dtype, int layout, int64_t M, int64_t N, int64_t K, double other) {
   const double k = (double)K;
   const double t32 = (double)((M + 31) / 32) * (double)((N + 31) / 32) / 256, t64 = (double)((M + 63) / 64) * (double)((N + 63) / 64) / 256;
   const double r32 = t32 > 1 ? t32 : 1, r64 = t64 > 1 ? ceil(t64) : 1;
   double us32, us64;
   if (dtype == MTNLG_F32) {
-    const double pairs = t32 > 1 ? 2 * ceil(t32 / 2) : 1;   // two workgroups on a compute unit
-    us32 = 3.6 + pairs * 0.0036 * k + (pairs - 1) * 1.25;
-    us64 = r64 * (7.0 + 0.0116 * k);
+    const double halves = t32 > 1 ? ceil(2 * t32) / 2 : 1;   // rounds of two workgroups on a compute unit
+    us32 = 4.05 + halves * 0.0037 * k + (halves - 1) * 1.16 + 0.00028 * k;
+    us64 = r64 * (7.0 + 0.0116 * k) * (layout == MTNLG_GEMM_TN ? 1.17 : 1.0);
   } else {
     us32 = 2.7 + r32 * k * (layout == MTNLG_GEMM_NT ? 0.0014 : layout == MTNLG_GEMM_NN ? 0.0019 : 0.0023) + (r32 - 1) * 0.85;
     us64 = 1.0 + r64 * (3.2 + k * (layout == MTNLG_GEMM_TN ? 0.0034 : 0.0028));

@@ -230,36 +230,57 @@ def gemm_without_lds(layout, a, b, C):   # fp32, 64 x 64 tiles, operands straigh
               torch.cuda.current_stream().cuda_stream) == 0
 
 
+def gemm_in_parts(layout, a, b, C, epilogue=0, bias=None, aux=None):   # fp32, 128 x 128 tiles
+    fn = B.lib()._ZN5mtnlg10gemm_partsEilllPKvS1_PvS1_S2_jP12ihipStream_t
+    vp, i64 = ctypes.c_void_p, ctypes.c_int64
+    fn.argtypes = [ctypes.c_int, i64, i64, i64, vp, vp, vp, vp, vp, ctypes.c_uint32, vp]
+    ptr = lambda t: 0 if t is None else t.data_ptr()
+    K = a.shape[0] if layout == B.GEMM_TN else a.shape[1]
+    assert fn(layout, C.shape[0], C.shape[1], K, ptr(a), ptr(b), ptr(C), ptr(bias), ptr(aux), epilogue, torch.cuda.current_stream().cuda_stream) == 0
+
+
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
 @pytest.mark.parametrize("shape", WAVE_SHAPES)
 @pytest.mark.parametrize("tile", [32, 64])
 def test_gemm_with_k_split_over_waves(tile, shape, layout):
     Mm, N, K = shape
     check_bf16_gemm(layout, Mm, N, K - 5 if layout == B.GEMM_TN else K, lambda *a, **k: gemm_by_waves(tile, *a, **k))
-    K = K // 2 + 4   # fp32: slabs of 32
-    if layout == B.GEMM_TN:
-        K -= 3
+    K = K // 2 + 4   # slabs of 32
+    check_fp32_gemm(layout, Mm, N, K - 3 if layout == B.GEMM_TN else K, lambda *a, **k: gemm_by_waves(tile, *a, **k), f"waves {tile}")
+
+
+# fp32 on 128 x 128 tiles: less than a tile and a slab; 1 to 9 slabs through the ring of 4, with K tails; more row tiles than a group of 8,
+# ragged on every side, where a wave's whole half of the tile lies outside.
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("Mm,N,K", [(4, 4, 4), (128, 128, 32), (60, 260, 64), (132, 72, 100), (256, 128, 128), (200, 196, 156), (128, 256, 168),
+                                    (1100, 136, 200), (136, 1036, 256), (192, 64, 288)])
+def test_fp32_gemm_on_128_tiles(layout, Mm, N, K):
+    check_fp32_gemm(layout, Mm, N, K - 3 if layout == B.GEMM_TN else K, gemm_in_parts, "128 x 128")
+
+
+def check_fp32_gemm(layout, Mm, N, K, gemm, what):
+    shape = (Mm, N, K)
     A, Bm = operands(layout, Mm, N, K, "fp32")
     bias, aux = randn((N,), "fp32", 7), randn((Mm, N), "fp32", 8)
     want = gemm_oracle(layout, A, Bm)
     C = torch.full((Mm, N), float("nan"), device="cuda")
-    gemm_by_waves(tile, layout, dev(A), dev(Bm), C)
-    assert_close(C, want, TOL["fp32"], f"fp32 waves {tile} {layout} {shape}")
-    gemm_by_waves(tile, layout, dev(A), dev(Bm), C, epilogue=B.EPI_ACCUMULATE)
-    assert_close(C, 2 * want, TOL["fp32"], f"fp32 waves {tile} {layout} {shape} accumulate")
-    gemm_by_waves(tile, layout, dev(A), dev(Bm), C, bias=dev(bias), aux=dev(aux), epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
-    assert_close(C, want + to_np(bias) + to_np(aux), TOL["fp32"], f"fp32 waves {tile} {layout} {shape} bias + residual")
-    gemm_by_waves(tile, layout, dev(A), dev(Bm), C, aux=dev(aux), epilogue=B.EPI_GELU_GRAD)
-    assert_close(C, want * oracle.gelu_grad(to_np(aux)), TOL["fp32"], f"fp32 waves {tile} {layout} {shape} GeLU'")
+    gemm(layout, dev(A), dev(Bm), C)
+    assert_close(C, want, TOL["fp32"], f"fp32 {what} {layout} {shape}")
+    gemm(layout, dev(A), dev(Bm), C, epilogue=B.EPI_ACCUMULATE)
+    assert_close(C, 2 * want, TOL["fp32"], f"fp32 {what} {layout} {shape} accumulate")
+    gemm(layout, dev(A), dev(Bm), C, bias=dev(bias), aux=dev(aux), epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
+    assert_close(C, want + to_np(bias) + to_np(aux), TOL["fp32"], f"fp32 {what} {layout} {shape} bias + residual")
+    gemm(layout, dev(A), dev(Bm), C, aux=dev(aux), epilogue=B.EPI_GELU_GRAD)
+    assert_close(C, want * oracle.gelu_grad(to_np(aux)), TOL["fp32"], f"fp32 {what} {layout} {shape} GeLU'")
 
 
 # fp32 values in three bf16 parts: what the parts cannot say goes the way of the fp32 instructions.  Values whose third part or
-# whose rounded first part leaves bf16's range, an infinity, a NaN; 32 x 32, 64 x 64 and the 64 x 64 tiles without LDS.
+# whose rounded first part leaves bf16's range, an infinity, a NaN; 32 x 32, 64 x 64, 128 x 128 and the 64 x 64 tiles without LDS.
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
-@pytest.mark.parametrize("route", [32, 64, 0])
+@pytest.mark.parametrize("route", [32, 64, 128, 0])
 def test_fp32_gemm_at_the_ends_of_the_range(route, layout):
-    Mm, N, K = 96, 72, 136
-    gemm = (lambda *a: gemm_by_waves(route, *a)) if route else gemm_without_lds
+    Mm, N, K = 96, 72, 136 if route else 280   # (up to 256 the tiles without LDS multiply on the fp32 instructions)
+    gemm = {0: gemm_without_lds, 128: gemm_in_parts}.get(route, lambda *a: gemm_by_waves(route, *a))
     A, Bm = operands(layout, Mm, N, K, "fp32")
     for scale_a, scale_b in ((2.0 ** -118, 1.0), (2.0 ** -100, 2.0 ** -24), (2.0 ** 90, 2.0 ** 30)):
         C = torch.full((Mm, N), float("nan"), device="cuda")
