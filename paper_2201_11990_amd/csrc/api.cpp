@@ -79,6 +79,16 @@ void saved_layout(const Shape &S, mtnlg_saved_layout *L) {
   L->total = c.off;
 }
 
+// fp32 products with many tiles, rather than with operands straight to registers
+bool fp32_in_parts(int dtype, int layout, int64_t M, int64_t N, int64_t K) {
+  return dtype == MTNLG_F32 && gemm_parts_time(M, N, K) < std::min(gemm_generic_time(layout, M, N, K), gemm_direct_time(M, N, K));
+}
+// estimated microseconds of a product on the kernels that do not split K over waves
+double gemm_time(int dtype, int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+  if (dtype == MTNLG_BF16) return gemm_mfma_time(layout, M, N, K, ws_bytes);
+  return std::min(gemm_parts_time(M, N, K), std::min(gemm_generic_time(layout, M, N, K), gemm_direct_time(M, N, K)));
+}
+
 // Scratch carved from the caller's workspace.
 struct Work {
   size_t dgz, du, dx1, da, dqkv, red, attn, ping, pong, gemm, gemm_bytes, total;
@@ -182,6 +192,41 @@ int layer_fwd_impl(const Shape &S, const mtnlg_layer_weights *w, const void *x, 
   return MTNLG_OK;
 }
 
+// Backward of a linear layer Y = X W^T: dY [T, O] in; dX = dY W [T, I] (with its epilogue) and dW = dY^T X [O, I] out.
+struct LinearBwd {
+  const Shape &S;
+  GemmCall nn, tn;
+  void *ws;
+  size_t ws_bytes;
+  LinearBwd(const Shape &S_, const void *dY, int64_t O, const void *X, int64_t I, const void *W, void *dX, void *aux, uint32_t epi, void *dW,
+            void *ws_, size_t ws_bytes_)
+      : S(S_), nn{S_.T, I, O, dY, W, dX, aux, epi},
+        tn{O, I, S_.T, dY, X, dW, nullptr,
+           (S_.acc ? (uint32_t)MTNLG_EPI_ACCUMULATE : 0u) | ((S_.g32 && S_.dtype == MTNLG_BF16) ? (uint32_t)MTNLG_EPI_OUT_F32 : 0u)},
+        ws(ws_), ws_bytes(ws_bytes_) {}
+  // the tile on which both products and the column sums go out in one launch, 0: launches of their own
+  int group_tile(int sums, int64_t sum_rows, int64_t sum_cols) const {
+    auto separate = [&](int layout, const GemmCall &c) { return gemm_time(S.dtype, layout, c.M, c.N, c.K, ws ? ws_bytes : 0); };
+    return gemm_wave_group_tile(S.dtype, nn, tn, sums, sum_rows, sum_cols, separate(MTNLG_GEMM_NN, nn), separate(MTNLG_GEMM_TN, tn));
+  }
+  int products(hipStream_t st) const {
+    auto dx = [&] { return mtnlg_gemm(S.dtype, MTNLG_GEMM_NN, nn.M, nn.N, nn.K, nn.A, nn.B, nn.C, nullptr, nn.aux, nn.epi, ws, ws_bytes, st); };
+    auto dw = [&] { return mtnlg_gemm(S.dtype, MTNLG_GEMM_TN, tn.M, tn.N, tn.K, tn.A, tn.B, tn.C, nullptr, nullptr, tn.epi, ws, ws_bytes, st); };
+    const bool dx_last = nn.epi != 0;   // the product with the activation's backward is what the next kernels read
+    MTNLG_TRY(dx_last ? dw() : dx());
+    return dx_last ? dx() : dw();
+  }
+  // and db = sum_t dY
+  int with_bias(void *db, void *red, hipStream_t st) const {
+    if (const int tile = group_tile(1, S.T, nn.K)) {
+      const bool f32 = S.dtype == MTNLG_F32;
+      return gemm_wave_group(S.dtype, nn, tn, ColumnSums{1, S.T, nn.K, f32, S.g32 || f32, S.acc, {{nn.A, db}}}, tile, st);
+    }
+    MTNLG_TRY(mtnlg_colsum(S.dtype, S.T, nn.K, nn.A, db, S.g32 ? 1 : 0, S.acc ? 1 : 0, red, st));
+    return products(st);
+  }
+};
+
 int layer_bwd_impl(const Shape &S, const mtnlg_layer_weights *w, const void *x, const void *saved,
                    const void *dy, void *dx, const mtnlg_layer_grads *G, void *ws, mtnlg_reduce_fn reduce,
                    void *user, hipStream_t st) {
@@ -197,31 +242,32 @@ int layer_bwd_impl(const Shape &S, const mtnlg_layer_weights *w, const void *x, 
   void *dgz = at(ws, W.dgz), *du = at(ws, W.du), *dx1 = at(ws, W.dx1), *da = at(ws, W.da);
   void *dqkv = at(ws, W.dqkv), *red = at(ws, W.red), *attn_ws = at(ws, W.attn), *gws = at(ws, W.gemm);
   const int g32 = S.g32 ? 1 : 0, acc = S.acc ? 1 : 0;
-  const uint32_t wg_epi = (S.acc ? MTNLG_EPI_ACCUMULATE : 0u) | ((S.g32 && S.dtype == MTNLG_BF16) ? MTNLG_EPI_OUT_F32 : 0u);
 
   // y = x1 + M + b2:  db2 = sum_t dy ; dW2 = dy^T g ; dz = (dy W2) o GeLU'(z), the activation's backward in the
-  // epilogue of the product (dg itself is never stored) ; db1 = sum_t dz
-  MTNLG_TRY(mtnlg_colsum(S.dtype, S.T, S.h, dy, G->b_fc2, g32, acc, red, st));
-  MTNLG_TRY(mtnlg_gemm(S.dtype, MTNLG_GEMM_TN, S.h, S.F, S.T, dy, g, G->w_fc2, nullptr, nullptr, wg_epi, gws, W.gemm_bytes, st));
-  MTNLG_TRY(mtnlg_gemm(S.dtype, MTNLG_GEMM_NN, S.T, S.F, S.h, dy, w->w_fc2, dgz, nullptr, const_cast<void *>(z),
-                       MTNLG_EPI_GELU_GRAD | (S.gelu_erf ? MTNLG_EPI_GELU_ERF : 0u), gws, W.gemm_bytes, st));
-  MTNLG_TRY(mtnlg_colsum(S.dtype, S.T, S.F, dgz, G->b_fc1, g32, acc, red, st));
-  // du2_r = dz W1 ; dW1 = dz^T u2
-  MTNLG_TRY(mtnlg_gemm(S.dtype, MTNLG_GEMM_NN, S.T, S.h, S.F, dgz, w->w_fc1, du, nullptr, nullptr, 0, gws, W.gemm_bytes, st));
-  MTNLG_TRY(mtnlg_gemm(S.dtype, MTNLG_GEMM_TN, S.F, S.h, S.T, dgz, u2, G->w_fc1, nullptr, nullptr, wg_epi, gws, W.gemm_bytes, st));
+  // epilogue of the product (dg itself is never stored)
+  const uint32_t gelu_grad = MTNLG_EPI_GELU_GRAD | (S.gelu_erf ? MTNLG_EPI_GELU_ERF : 0u);
+  const LinearBwd fc2(S, dy, S.h, g, S.F, w->w_fc2, dgz, const_cast<void *>(z), gelu_grad, G->w_fc2, gws, W.gemm_bytes);
+  MTNLG_TRY(fc2.with_bias(G->b_fc2, red, st));
+  // db1 = sum_t dz ; du2_r = dz W1 ; dW1 = dz^T u2
+  const LinearBwd fc1(S, dgz, S.F, u2, S.h, w->w_fc1, du, nullptr, 0, G->w_fc1, gws, W.gemm_bytes);
+  MTNLG_TRY(fc1.with_bias(G->b_fc1, red, st));
   MTNLG_TRY(call_reduce(reduce, user, du, (size_t)(S.T * S.h), S.dtype, st));
-  // dx1 = dy + LN2^T(du2) ; dgamma2, dbeta2 ; dbo = sum_t dx1
-  MTNLG_TRY(mtnlg_layernorm_bwd(S.dtype, S.T, S.h, x1, w->ln2_g, mu2, rs2, du, dy, dx1, G->ln2_g, G->ln2_b,
-                                G->b_o, g32, acc, red, st));
-  // da = dx1 Wo ; dWo = dx1^T a
-  MTNLG_TRY(mtnlg_gemm(S.dtype, MTNLG_GEMM_NN, S.T, S.p, S.h, dx1, w->w_o, da, nullptr, nullptr, 0, gws, W.gemm_bytes, st));
-  MTNLG_TRY(mtnlg_gemm(S.dtype, MTNLG_GEMM_TN, S.h, S.p, S.T, dx1, a, G->w_o, nullptr, nullptr, wg_epi, gws, W.gemm_bytes, st));
+  // dx1 = dy + LN2^T(du2) ; dgamma2, dbeta2 ; dbo = sum_t dx1.  da = dx1 Wo ; dWo = dx1^T a
+  const LinearBwd out(S, dx1, S.h, a, S.p, w->w_o, da, nullptr, 0, G->w_o, gws, W.gemm_bytes);
+  if (const int tile = out.group_tile(3, layernorm_bwd_most_sums(S.T), S.h)) {
+    ColumnSums sums;
+    MTNLG_TRY(layernorm_bwd_rows(S.dtype, S.T, S.h, x1, w->ln2_g, mu2, rs2, du, dy, dx1, G->ln2_g, G->ln2_b, G->b_o, g32, acc, red, &sums, st));
+    MTNLG_TRY(gemm_wave_group(S.dtype, out.nn, out.tn, sums, tile, st));
+  } else {
+    MTNLG_TRY(mtnlg_layernorm_bwd(S.dtype, S.T, S.h, x1, w->ln2_g, mu2, rs2, du, dy, dx1, G->ln2_g, G->ln2_b,
+                                  G->b_o, g32, acc, red, st));
+    MTNLG_TRY(out.products(st));
+  }
   // attention backward
   MTNLG_TRY(mtnlg_attention_bwd(S.dtype, S.b, S.s, S.n, S.d, S.scale, qkv, a, lse, da, dqkv, attn_ws, st));
   // dbqkv = sum_t dqkv ; du1_r = dqkv Wqkv ; dWqkv = dqkv^T u1
-  MTNLG_TRY(mtnlg_colsum(S.dtype, S.T, 3 * S.p, dqkv, G->b_qkv, g32, acc, red, st));
-  MTNLG_TRY(mtnlg_gemm(S.dtype, MTNLG_GEMM_NN, S.T, S.h, 3 * S.p, dqkv, w->w_qkv, du, nullptr, nullptr, 0, gws, W.gemm_bytes, st));
-  MTNLG_TRY(mtnlg_gemm(S.dtype, MTNLG_GEMM_TN, 3 * S.p, S.h, S.T, dqkv, u1, G->w_qkv, nullptr, nullptr, wg_epi, gws, W.gemm_bytes, st));
+  const LinearBwd in(S, dqkv, 3 * S.p, u1, S.h, w->w_qkv, du, nullptr, 0, G->w_qkv, gws, W.gemm_bytes);
+  MTNLG_TRY(in.with_bias(G->b_qkv, red, st));
   MTNLG_TRY(call_reduce(reduce, user, du, (size_t)(S.T * S.h), S.dtype, st));
   // dx = dx1 + LN1^T(du1) ; dgamma1, dbeta1
   MTNLG_TRY(mtnlg_layernorm_bwd(S.dtype, S.T, S.h, x, w->ln1_g, mu1, rs1, du, dx1, dx, G->ln1_g, G->ln1_b,
@@ -391,13 +437,10 @@ int mtnlg_gemm(int dtype, int layout, int64_t M, int64_t N, int64_t K, const voi
   if (dtype == MTNLG_F32) epilogue &= ~MTNLG_EPI_OUT_F32;
   hipStream_t st = (hipStream_t)stream;
   if (gemm_wave_takes(dtype, layout, M, N, K, A, B, C, bias, aux)) {
-    const double generic = dtype == MTNLG_F32 ? std::min(gemm_generic_time(layout, M, N, K), gemm_direct_time(M, N, K)) : 0.0;
-    const double parts = gemm_parts_time(M, N, K);
-    const bool in_parts = dtype == MTNLG_F32 && parts < generic;
-    const double other = in_parts ? parts : dtype == MTNLG_F32 ? generic : gemm_mfma_time(layout, M, N, K, workspace ? workspace_bytes : 0);
+    const double other = gemm_time(dtype, layout, M, N, K, workspace ? workspace_bytes : 0);
     const int tile = gemm_wave_pick(dtype, layout, M, N, K, other);
     if (tile) return gemm_wave(dtype, layout, M, N, K, A, B, C, bias, aux, epilogue, tile, st);
-    if (in_parts) return gemm_parts(layout, M, N, K, A, B, C, bias, aux, epilogue, st);
+    if (fp32_in_parts(dtype, layout, M, N, K)) return gemm_parts(layout, M, N, K, A, B, C, bias, aux, epilogue, st);
   }
   if (dtype == MTNLG_BF16) {
     int r = gemm_mfma_bf16(layout, M, N, K, A, B, C, bias, aux, epilogue, workspace, workspace_bytes, st);

@@ -329,6 +329,34 @@ int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const v
 double gemm_mfma_time(int layout, int64_t M, int64_t N, int64_t K, size_t ws_bytes);   // estimated microseconds of that tile
 bool gemm_wave_takes(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B, const void *C,
                      const void *bias, const void *aux);
+// One product of a linear layer's backward pass, row lengths as of dense matrices; and sums over the rows of up to three dense [rows][C]
+// matrices, fp32 or bf16 in and out, up to 64 columns to a workgroup.
+struct GemmCall {
+  int64_t M, N, K;
+  const void *A, *B;
+  void *C, *aux;
+  uint32_t epi;
+};
+struct ColumnSum {
+  const void *in;
+  void *out;
+};
+struct ColumnSums {
+  int count;
+  int64_t rows, C;
+  bool in_f32, out_f32, accumulate;
+  ColumnSum of[3];
+};
+// One launch for both products and the sums: which tile it would take (32 or 64), 0 where separate launches are estimated to be faster or
+// have to be taken; sums: how many matrices, of how many rows and columns
+int gemm_wave_group_tile(int dtype, const GemmCall &nn, const GemmCall &tn, int sums, int64_t sum_rows, int64_t sum_cols, double separate_nn,
+                         double separate_tn);
+int gemm_wave_group(int dtype, const GemmCall &nn, const GemmCall &tn, const ColumnSums &sums, int tile, hipStream_t stream);
+// LayerNorm backward without the sums over rows; left: what is to be added up afterwards, over so many rows at most
+int layernorm_bwd_rows(int dtype, int64_t T, int64_t h, const void *x, const void *gamma, const float *mean, const float *rstd,
+                       const void *dout, const void *dres, void *dx, void *dgamma, void *dbeta, void *colsum_dx, int grad_f32,
+                       int accumulate, void *workspace, ColumnSums *left, hipStream_t stream);
+int layernorm_bwd_most_sums(int64_t T);
 int gemm_wave(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A, const void *B, void *C, const void *bias,
               void *aux, uint32_t epi, int tile, hipStream_t stream);   // tile: 32 or 64
 // fp32 problems that gemm_wave_takes, on 128 x 128 tiles

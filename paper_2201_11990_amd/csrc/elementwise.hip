@@ -394,10 +394,10 @@ static void stage2_launch(int64_t C, int nrb, const float *ws, int nout, void *o
 static int ln_bwd_workgroups(int64_t T) { return (int)(T < LNB_MAX_WGS ? T : LNB_MAX_WGS); }
 
 template <typename E>
-static int ln_bwd_launch(int64_t T, int64_t h, const void *x, const void *gamma, const float *mean,
+static int ln_bwd_rows_of(int64_t T, int64_t h, const void *x, const void *gamma, const float *mean,
                          const float *rstd, const void *dout, const void *dres, void *dx,
                          void *dgamma, void *dbeta, void *colsum_dx, int grad_f32, int accumulate,
-                         void *workspace, hipStream_t st) {
+                         void *workspace, ColumnSums *left, hipStream_t st) {
   const int nvec = (int)(h / 8);
   // waves to a row, and at least as many rows to a workgroup as it takes at a time: fewer partial sums to add
   const int gw = T * h < LNB_FEW ? 16 : nvec <= 64 ? 1 : nvec <= 128 ? 2 : nvec <= 256 ? 4 : nvec <= 512 ? 8 : 16;
@@ -421,14 +421,23 @@ static int ln_bwd_launch(int64_t T, int64_t h, const void *x, const void *gamma,
     else if (nvec <= 4096) LNB(4, 16, CS);       \
     else return MTNLG_UNSUPPORTED_SHAPE;         \
   } while (0)
-  LaunchScope scope(MTNLG_K_LN_BWD, st);
   if (colsum_dx) LNB_BY_WIDTH(true);
   else LNB_BY_WIDTH(false);
 #undef LNB_BY_WIDTH
 #undef LNB
   MTNLG_TRY(check_launch());
-  stage2_launch<E>(h, nwg, ws, colsum_dx ? 3 : 2, dgamma, dbeta, colsum_dx, grad_f32, accumulate, st);
-  return check_launch();
+  const int64_t stride = (int64_t)nwg * h;
+  *left = ColumnSums{colsum_dx ? 3 : 2, nwg, h, true, grad_f32 || sizeof(E) == 4, accumulate != 0,
+                     {{ws, dgamma}, {ws + stride, dbeta}, {ws + 2 * stride, colsum_dx}}};
+  return MTNLG_OK;
+}
+
+static int ln_bwd_rows(int dtype, int64_t T, int64_t h, const void *x, const void *gamma, const float *mean, const float *rstd,
+                       const void *dout, const void *dres, void *dx, void *dgamma, void *dbeta, void *colsum_dx, int grad_f32,
+                       int accumulate, void *workspace, ColumnSums *left, hipStream_t st) {
+  if (dtype == MTNLG_F32)
+    return ln_bwd_rows_of<float>(T, h, x, gamma, mean, rstd, dout, dres, dx, dgamma, dbeta, colsum_dx, 1, accumulate, workspace, left, st);
+  return ln_bwd_rows_of<bf16>(T, h, x, gamma, mean, rstd, dout, dres, dx, dgamma, dbeta, colsum_dx, grad_f32, accumulate, workspace, left, st);
 }
 
 template <typename E>
@@ -498,6 +507,14 @@ static unsigned ew_grid(int64_t nvec) {
   return (unsigned)g;
 }
 
+int layernorm_bwd_rows(int dtype, int64_t T, int64_t h, const void *x, const void *gamma, const float *mean, const float *rstd,
+                       const void *dout, const void *dres, void *dx, void *dgamma, void *dbeta, void *colsum_dx, int grad_f32,
+                       int accumulate, void *workspace, ColumnSums *left, hipStream_t st) {
+  LaunchScope scope(MTNLG_K_LN_BWD, st);
+  return ln_bwd_rows(dtype, T, h, x, gamma, mean, rstd, dout, dres, dx, dgamma, dbeta, colsum_dx, grad_f32, accumulate, workspace, left, st);
+}
+int layernorm_bwd_most_sums(int64_t T) { return ln_bwd_workgroups(T); }
+
 }  // namespace mtnlg
 
 using namespace mtnlg;
@@ -523,22 +540,27 @@ size_t mtnlg_layernorm_bwd_workspace(int64_t T, int64_t h) {
   return (size_t)3 * ln_bwd_workgroups(T) * (size_t)h * sizeof(float);
 }
 
+static int layernorm_bwd_check(int dtype, int64_t T, int64_t h) {
+  if (T <= 0 || h <= 0) return MTNLG_INVALID_ARG;
+  if (h % 8 || h > 32768) return MTNLG_UNSUPPORTED_SHAPE;
+  return dtype == MTNLG_F32 || dtype == MTNLG_BF16 ? MTNLG_OK : MTNLG_INVALID_ARG;
+}
+
 int mtnlg_layernorm_bwd(int dtype, int64_t T, int64_t h, const void *x, const void *gamma,
                         const float *mean, const float *rstd, const void *dout, const void *dres,
                         void *dx, void *dgamma, void *dbeta, void *colsum_dx, int grad_f32,
                         int accumulate, void *workspace, void *stream) {
   if (!x || !gamma || !mean || !rstd || !dout || !dx || !dgamma || !dbeta || !workspace)
     return MTNLG_NULL_POINTER;
-  if (T <= 0 || h <= 0) return MTNLG_INVALID_ARG;
-  if (h % 8 || h > 32768) return MTNLG_UNSUPPORTED_SHAPE;
+  MTNLG_TRY(layernorm_bwd_check(dtype, T, h));
   hipStream_t st = (hipStream_t)stream;
-  if (dtype == MTNLG_F32)
-    return ln_bwd_launch<float>(T, h, x, gamma, mean, rstd, dout, dres, dx, dgamma, dbeta, colsum_dx,
-                                1, accumulate, workspace, st);
-  if (dtype == MTNLG_BF16)
-    return ln_bwd_launch<bf16>(T, h, x, gamma, mean, rstd, dout, dres, dx, dgamma, dbeta, colsum_dx,
-                               grad_f32, accumulate, workspace, st);
-  return MTNLG_INVALID_ARG;
+  ColumnSums left;
+  LaunchScope scope(MTNLG_K_LN_BWD, st);
+  MTNLG_TRY(ln_bwd_rows(dtype, T, h, x, gamma, mean, rstd, dout, dres, dx, dgamma, dbeta, colsum_dx, grad_f32, accumulate, workspace, &left, st));
+  const float *ws = (const float *)workspace;
+  if (dtype == MTNLG_F32) stage2_launch<float>(h, (int)left.rows, ws, left.count, dgamma, dbeta, colsum_dx, 1, accumulate, st);
+  else stage2_launch<bf16>(h, (int)left.rows, ws, left.count, dgamma, dbeta, colsum_dx, grad_f32, accumulate, st);
+  return check_launch();
 }
 
 int mtnlg_gelu_fwd(int dtype, int gelu, int64_t count, const void *z, void *g, void *stream) {

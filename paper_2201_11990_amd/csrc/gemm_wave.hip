@@ -139,9 +139,9 @@ struct Frag32 {
   }
 };
 
+// The tile of workgroup `block` of a problem's grid.
 template <typename E, int TB, bool AT, bool BT>
-__global__ __launch_bounds__(64 * WAVES, 2) void gemm_wave_kernel(WaveGemmArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+__device__ __forceinline__ void wave_tile(const WaveGemmArgs &a, int block, char *smem) {
   using SA = Slab<E, TB, AT>;
   using SB = Slab<E, TB, BT>;
   constexpr int NB = TB / 16, NV = NB * NB, STAGE = SA::BYTES + SB::BYTES, SK = SA::SK;
@@ -151,8 +151,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_wave_kernel(WaveGemmArgs a
 
   // XCD x (workgroup id mod 8) takes a contiguous run of tiles, ordered in blocks of 8 row tiles
   const int tiles = a.tiles_m * a.tiles_n, per_xcd = (tiles + 7) / 8;
-  const int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per_xcd || pid >= tiles) return;
+  const int pid = (block & 7) * per_xcd + (block >> 3);
+  if (block >> 3 >= per_xcd || pid >= tiles) return;
   const int per_group = 8 * a.tiles_n, grp = pid / per_group, first_m = grp * 8;
   const int gsz = a.tiles_m - first_m < 8 ? a.tiles_m - first_m : 8;
   const int64_t m0 = (int64_t)(first_m + (pid % per_group) % gsz) * TB, n0 = (int64_t)((pid % per_group) / gsz) * TB;
@@ -281,6 +281,84 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_wave_kernel(WaveGemmArgs a
 }
 
 template <typename E, int TB, bool AT, bool BT>
+__global__ __launch_bounds__(64 * WAVES, 2) void gemm_wave_kernel(WaveGemmArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  wave_tile<E, TB, AT, BT>(a, blockIdx.x, smem);
+}
+
+// Sums over the rows of a matrix, 64 columns to a workgroup: eight lanes take a row's columns, so a wave has eight rows and a pass of
+// the workgroup 64, four passes in flight.  One pass over few rows where mtnlg_colsum takes two kernels.
+template <typename E>
+__device__ __forceinline__ void column_sums(const ColumnSum &s, int64_t rows, int64_t C, int block, bool out_f32, bool accumulate,
+                                            char *smem) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t c0 = (int64_t)block * 64 + (lane & 7) * 8;
+  const E *in = static_cast<const E *>(s.in) + c0;
+  constexpr int STEP = 8 * WAVES;
+  float acc[8] = {};
+  if (c0 < C) {
+    int64_t t = 8 * wave + (lane >> 3);
+    for (; t + 3 * STEP < rows; t += 4 * STEP) {
+      Raw8<E> v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i].load(in + (t + i * STEP) * C);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] += v[i][e];
+    }
+    for (; t < rows; t += STEP) {
+      Raw8<E> v;
+      v.load(in + t * C);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += v[e];
+    }
+  }
+  float *part = reinterpret_cast<float *>(smem);   // [wave][64]
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) acc[e] += __shfl_xor(acc[e], off, 64);
+  }
+  if (lane < 8) store8(part + wave * 64 + lane * 8, acc);
+  __syncthreads();
+  const int64_t c = (int64_t)block * 64 + threadIdx.x;
+  if (threadIdx.x >= 64 || c >= C) return;
+  float t = part[threadIdx.x];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) t += part[w * 64 + threadIdx.x];
+  if (out_f32) {
+    float *out = static_cast<float *>(s.out) + c;
+    *out = accumulate ? *out + t : t;
+  } else {
+    bf16 *out = static_cast<bf16 *>(s.out) + c;
+    *out = (bf16)(accumulate ? (float)*out + t : t);
+  }
+}
+
+// What the backward pass of a linear layer needs of dY, in one launch: dX = dY W (NN), dW = dY^T X (TN) and column sums (the bias gradient, or
+// partial sums that the kernel before left).  None needs another's result, and with few tiles each alone leaves most of the chip idle.
+struct GroupArgs {
+  WaveGemmArgs nn, tn;
+  int blocks_nn, blocks_tn;   // multiples of 8
+  ColumnSums sums;
+  int blocks_sum;             // for each of them
+};
+template <typename E, int TB>
+__global__ __launch_bounds__(64 * WAVES, 2) void gemm_wave_group_kernel(GroupArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  int block = blockIdx.x;
+  if (block < a.blocks_nn) return wave_tile<E, TB, false, true>(a.nn, block, smem);
+  block -= a.blocks_nn;
+  if (block < a.blocks_tn) return wave_tile<E, TB, true, true>(a.tn, block, smem);
+  block -= a.blocks_tn;
+  const ColumnSum s = a.sums.of[block / a.blocks_sum];
+  block %= a.blocks_sum;
+  if (a.sums.in_f32) column_sums<float>(s, a.sums.rows, a.sums.C, block, a.sums.out_f32, a.sums.accumulate, smem);
+  else column_sums<bf16>(s, a.sums.rows, a.sums.C, block, a.sums.out_f32, a.sums.accumulate, smem);
+}
+
+template <typename E, int TB, bool AT, bool BT>
 int launch(WaveGemmArgs a, hipStream_t st) {
   constexpr int smem = WAVES * 2 * TB * 128;
   static unsigned long long attr_done = 0;
@@ -305,6 +383,33 @@ int launch_layout(int layout, WaveGemmArgs a, hipStream_t st) {
   return launch<E, TB, true, true>(a, st);
 }
 
+template <typename E, int TB>
+int launch_group(GroupArgs a, hipStream_t st) {
+  auto blocks = [](WaveGemmArgs &p) {
+    p.tiles_m = (int)((p.M + TB - 1) / TB);
+    p.tiles_n = (int)((p.N + TB - 1) / TB);
+    return (p.tiles_m * p.tiles_n + 7) / 8 * 8;
+  };
+  a.blocks_nn = blocks(a.nn);
+  a.blocks_tn = blocks(a.tn);
+  constexpr int smem = WAVES * 2 * TB * 128;
+  static unsigned long long attr_done = 0;
+  int device;
+  if (!attr_is_set(attr_done, &device)) {
+    if (hipFuncSetAttribute((const void *)gemm_wave_group_kernel<E, TB>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
+      return MTNLG_HIP_ERROR;
+    attr_mark_set(attr_done, device);
+  }
+  gemm_wave_group_kernel<E, TB><<<dim3((unsigned)(a.blocks_nn + a.blocks_tn + a.sums.count * a.blocks_sum)), 64 * WAVES, smem, st>>>(a);
+  return check_launch();
+}
+
+// What a problem costs on tiles of TB rows: rounds of 256 workgroups, us of one workgroup's sum over K.
+struct Work {
+  double rounds, chain;
+  Work(int64_t tb, int64_t M, int64_t N, double chain_) : rounds((double)((M + tb - 1) / tb) * (double)((N + tb - 1) / tb) / 256), chain(chain_) {}
+};
+
 }  // namespace
 
 // Whether these kernels can take a problem: whole 16-byte units along every row, whole dwords, and slabs whose rows the 32-bit DMA
@@ -326,11 +431,10 @@ bool gemm_wave_takes(int dtype, int layout, int64_t M, int64_t N, int64_t K, con
 // 1024 x 1024 x 4096 38 / 24 / 16.5; 1024 x 2048 x 2048 21 / 38 / 20; 2048 x 2048 x 64 5.5 / 16 / 13.
 // fp32, operands straight to registers / 32 / 64 / 128 (gemm_parts.hip): 128 x 960 x 512 8.0 / 6.1 / 14 / 27; 1024 x 1024 x 4096 82 / 73 / 53 /
 // 169; 1024 x 4096 x 1024 77 / 70 / 69 / 53, TN 59 / 69 / 89 / 50; 2048 x 2048 x 4096 263 / 243 / 195 / 183; 1600 x 2048 x 3000 154 / 161 / 154 / 122.
-int gemm_wave_pick(int dtype, int layout, int64_t M, int64_t N, int64_t K, double other) {
+static void wave_times(int dtype, int layout, int64_t M, int64_t N, int64_t K, double &us32, double &us64) {
   const double k = (double)K;
-  const double t32 = (double)((M + 31) / 32) * (double)((N + 31) / 32) / 256, t64 = (double)((M + 63) / 64) * (double)((N + 63) / 64) / 256;
+  const double t32 = Work(32, M, N, 0).rounds, t64 = Work(64, M, N, 0).rounds;
   const double r32 = t32 > 1 ? t32 : 1, r64 = t64 > 1 ? ceil(t64) : 1;
-  double us32, us64;
   if (dtype == MTNLG_F32) {
     const double halves = t32 > 1 ? ceil(2 * t32) / 2 : 1;   // rounds of two workgroups on a compute unit
     us32 = 4.05 + halves * 0.0037 * k + (halves - 1) * 1.16 + 0.00028 * k;
@@ -339,7 +443,27 @@ int gemm_wave_pick(int dtype, int layout, int64_t M, int64_t N, int64_t K, doubl
     us32 = 2.7 + r32 * k * (layout == MTNLG_GEMM_NT ? 0.0014 : layout == MTNLG_GEMM_NN ? 0.0019 : 0.0023) + (r32 - 1) * 0.85;
     us64 = 1.0 + r64 * (3.2 + k * (layout == MTNLG_GEMM_TN ? 0.0034 : 0.0028));
   }
+}
+int gemm_wave_pick(int dtype, int layout, int64_t M, int64_t N, int64_t K, double other) {
+  double us32, us64;
+  wave_times(dtype, layout, M, N, K, us32, us64);
   if (us32 > other && us64 > other) return 0;
+  return us32 < us64 ? 32 : 64;
+}
+
+// The same for the two products of a group and its column sums: the longest chain where all workgroups run at once, else the chains
+// spread over the compute units.
+static int pick_group(int dtype, const GemmCall &nn, const GemmCall &tn, int64_t sum_rows, double separate) {
+  const bool f32 = dtype == MTNLG_F32;
+  auto time = [&](int tb, double launch, double tile, double c_nn, double c_tn) {
+    const Work a(tb, nn.M, nn.N, c_nn * (double)nn.K), b(tb, tn.M, tn.N, c_tn * (double)tn.K);
+    const double rounds = a.rounds + b.rounds, whole = tb == 64 ? ceil(rounds) : rounds > 1 ? rounds : 1;
+    const double longest = fmax(fmax(a.chain, b.chain), 0.5 + 0.004 * (double)sum_rows);
+    return launch + whole * tile + fmax(longest, (a.rounds * a.chain + b.rounds * b.chain) * whole / rounds);
+  };
+  const double us32 = f32 ? time(32, 2.9, 1.16, 0.0040, 0.0040) : time(32, 1.85, 0.85, 0.0019, 0.0023);
+  const double us64 = f32 ? INFINITY : time(64, 1.0, 3.2, 0.0028, 0.0034);   // (fp32 on 64 x 64 tiles: both layouts in one kernel spill)
+  if (us32 > separate && us64 > separate) return 0;
   return us32 < us64 ? 32 : 64;
 }
 
@@ -351,6 +475,40 @@ int gemm_wave(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void
   LaunchScope scope(MTNLG_K_GEMM_NT + layout, stream);
   if (dtype == MTNLG_F32) return tile == 32 ? launch_layout<float, 32>(layout, a, stream) : launch_layout<float, 64>(layout, a, stream);
   return tile == 32 ? launch_layout<bf16, 32>(layout, a, stream) : launch_layout<bf16, 64>(layout, a, stream);
+}
+
+// nn, tn: problems that mtnlg_gemm accepts; separate_nn, separate_tn: what a launch of its own is estimated to cost without these kernels.
+// Forward and backward of a layer, us with separate launches / so (one launch for 3 to 4): 128 tokens, h 512, FFN 2048, bf16 107 / 76, fp32
+// 144 / 110; 512 tokens 131 / 110, 231 / 197; 512 tokens, h 768, FFN 3072 180 / 145, 362 / 314.  By these estimates most larger ones stay
+// separate (1000 tokens, h 1024: 277 / 274): the streaming kernels are faster there than what the launches cost.
+int gemm_wave_group_tile(int dtype, const GemmCall &nn, const GemmCall &tn, int sums, int64_t sum_rows, int64_t sum_cols, double separate_nn,
+                         double separate_tn) {
+  if (!gemm_wave_takes(dtype, MTNLG_GEMM_NN, nn.M, nn.N, nn.K, nn.A, nn.B, nn.C, nullptr, nn.aux) ||
+      !gemm_wave_takes(dtype, MTNLG_GEMM_TN, tn.M, tn.N, tn.K, tn.A, tn.B, tn.C, nullptr, tn.aux) || sum_cols % 8 ||
+      Work(32, nn.M, nn.N, 0).rounds + Work(32, tn.M, tn.N, 0).rounds > 4096)
+    return 0;
+  double separate = sums == 0 ? 0.0 : sums > 1 ? 3.0 : 6.0;   // one kernel over partial sums, or two
+  double us32, us64;
+  wave_times(dtype, MTNLG_GEMM_NN, nn.M, nn.N, nn.K, us32, us64);
+  separate += fmin(separate_nn, fmin(us32, us64));
+  wave_times(dtype, MTNLG_GEMM_TN, tn.M, tn.N, tn.K, us32, us64);
+  separate += fmin(separate_tn, fmin(us32, us64));
+  return pick_group(dtype, nn, tn, sums ? sum_rows : 0, separate);
+}
+
+int gemm_wave_group(int dtype, const GemmCall &nn, const GemmCall &tn, const ColumnSums &sums, int tile, hipStream_t stream) {
+  if (tile != 32 && (tile != 64 || dtype == MTNLG_F32)) return MTNLG_INVALID_ARG;
+  const GroupArgs a{{nn.M, nn.N, nn.K, nn.K, nn.N, nn.A, nn.B, nn.C, EpiArgs{nullptr, nn.aux, nn.epi}, 0, 0},
+                    {tn.M, tn.N, tn.K, tn.M, tn.N, tn.A, tn.B, tn.C, EpiArgs{nullptr, tn.aux, tn.epi}, 0, 0},
+                    0, 0, sums, (int)((sums.C + 63) / 64)};
+  int status;
+  {   // timed as the input-gradient product; the others count with no time of their own
+    LaunchScope scope(MTNLG_K_GEMM_NN, stream);
+    if (dtype == MTNLG_F32) status = launch_group<float, 32>(a, stream);
+    else status = tile == 32 ? launch_group<bf16, 32>(a, stream) : launch_group<bf16, 64>(a, stream);
+  }
+  { LaunchScope scope(MTNLG_K_GEMM_TN, stream); }
+  return status;
 }
 
 }  // namespace mtnlg

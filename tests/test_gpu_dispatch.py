@@ -249,6 +249,46 @@ def test_gemm_with_k_split_over_waves(tile, shape, layout):
     check_fp32_gemm(layout, Mm, N, K - 3 if layout == B.GEMM_TN else K, lambda *a, **k: gemm_by_waves(tile, *a, **k), f"waves {tile}")
 
 
+class GemmCall(ctypes.Structure):
+    _fields_ = [("M", ctypes.c_int64), ("N", ctypes.c_int64), ("K", ctypes.c_int64), ("A", ctypes.c_void_p), ("B", ctypes.c_void_p),
+                ("C", ctypes.c_void_p), ("aux", ctypes.c_void_p), ("epi", ctypes.c_uint32)]
+
+
+class ColumnSums(ctypes.Structure):
+    _fields_ = [("count", ctypes.c_int), ("rows", ctypes.c_int64), ("C", ctypes.c_int64), ("in_f32", ctypes.c_bool), ("out_f32", ctypes.c_bool),
+                ("accumulate", ctypes.c_bool), ("of", ctypes.c_void_p * 6)]
+
+
+# A linear layer's backward in one launch: both products, and no column sums, the bias gradient, or three of fp32 partial sums.  Less than
+# a tile, ragged on every side, several tiles and slabs for every wave; 1 to 300 rows to sum.
+@pytest.mark.parametrize("dtype,tile", [("bf16", 32), ("bf16", 64), ("fp32", 32)])
+@pytest.mark.parametrize("T,I,O", [(8, 8, 8), (40, 72, 136), (136, 264, 72), (300, 128, 200)])
+@pytest.mark.parametrize("sums", [0, 1, 3])
+def test_linear_backward_in_one_launch(dtype, tile, T, I, O, sums):
+    dY, X, W, z = randn((T, O), dtype, 1), randn((T, I), dtype, 2), randn((O, I), dtype, 3), randn((T, I), dtype, 4)
+    code, td = (B.F32, torch.float32) if dtype == "fp32" else (B.BF16, torch.bfloat16)
+    accumulate = sums != 1
+    dX = torch.full((T, I), float("nan"), dtype=td, device="cuda")
+    dW = torch.full((O, I), 2.0, device="cuda")
+    a, x, w, zz = dev(dY), dev(X), dev(W), dev(z)
+    nn = GemmCall(T, I, O, a.data_ptr(), w.data_ptr(), dX.data_ptr(), zz.data_ptr(), B.EPI_GELU_GRAD)
+    tn = GemmCall(O, I, T, a.data_ptr(), x.data_ptr(), dW.data_ptr(), None, B.EPI_ACCUMULATE | (0 if dtype == "fp32" else B.EPI_OUT_F32))
+    rows = 1 if T == 8 else T
+    parts = [dY] if sums == 1 else [randn((rows, O), "fp32", 10 + i) for i in range(sums)]
+    ins, out_f32 = [dev(p) for p in parts], dtype == "fp32" or sums == 1
+    outs = [torch.full((O,), 3.0, dtype=torch.float32 if out_f32 else td, device="cuda") for _ in parts]
+    cs = ColumnSums(sums, T if sums == 1 else rows, O, sums != 1 or dtype == "fp32", out_f32, accumulate)
+    for i in range(sums):
+        cs.of[2 * i], cs.of[2 * i + 1] = ins[i].data_ptr(), outs[i].data_ptr()
+    fn = B.lib()._ZN5mtnlg15gemm_wave_groupEiRKNS_8GemmCallES2_RKNS_10ColumnSumsEiP12ihipStream_t
+    fn.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    assert fn(code, ctypes.byref(nn), ctypes.byref(tn), ctypes.byref(cs), tile, torch.cuda.current_stream().cuda_stream) == 0
+    assert_close(dX, gemm_oracle(B.GEMM_NN, dY, W) * oracle.gelu_grad(to_np(z)), TOL[dtype], f"dX {dtype} {tile} {T} {I} {O}")
+    assert_close(dW - 2.0, gemm_oracle(B.GEMM_TN, dY, X), TOL["fp32"], f"dW {dtype} {tile} {T} {I} {O}")
+    for part, out in zip(parts, outs):
+        assert_close(out, to_np(part).sum(0) + (3.0 if accumulate else 0.0), TOL["fp32"] if out_f32 else TOL[dtype], f"sums {dtype} {T} {O}")
+
+
 # fp32 on 128 x 128 tiles: less than a tile and a slab; 1 to 9 slabs through the ring of 4, with K tails; more row tiles than a group of 8,
 # ragged on every side, where a wave's whole half of the tile lies outside.
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
