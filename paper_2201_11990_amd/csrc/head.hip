@@ -67,16 +67,18 @@ __global__ __launch_bounds__(256) void add_positions_kernel(int64_t h, int seq, 
 }
 
 // dE[v] = sum over tokens t (in order) with tokens[t] == vocab_start + v of dx[t].
-// Workgroup (bx, by): the vocabulary rows bx + k 2^stride_log2, k < EB_ROWS, and columns 2048 by .. + 2047 (8 per thread).
+// Workgroup i of c = columns / 2048: the vocabulary rows i / c + k 2^stride_log2, k < EB_ROWS, and columns 2048 (i % c) .. + 2047 (8 per thread).
 // The token ids are searched 64 at a time by a wave: one ballot gives the tokens of any of the workgroup's rows as a bit
 // mask in LDS, a byte per token says which row.  The matching rows of dx are then fetched in token order, eight loads in flight
 // whatever rows they belong to, and each is added to its row.  Fixed order, no atomics.  A workgroup's rows lie far apart
 // because neighbouring ids tend to be about equally frequent: with 8 consecutive rows the workgroup of the 8 most
-// frequent ids was the whole kernel's tail.
+// frequent ids was the whole kernel's tail.  And the column chunks of a group of rows come one after the other, because the frequent ids
+// are the low ones: with the groups of a chunk one after the other the last chunk's longest workgroup started at nine tenths of the kernel
+// (2048 tokens, 6400 x 20480, lookup and gradients together: 194 us, now 159).
 // Bound by HBM once the search is parallel (dE written, dx read: 346 MB at 2048 tokens, 6400 x 20480); with every
 // workgroup walking the ids one by one for one row the search was 99 % of 9560 us.  With few tokens it is a chain of latencies, or of
 // workgroups that have next to nothing to do: masks and fetches row by row took 11.4 us for 32 tokens in 16 rows of 256 (7.3 now),
-// 40 us for one token in 51200 rows of 16 (under 15 now), and 219 us where the call takes 196 now (2048 tokens, 6400 x 20480).
+// 40 us for one token in 51200 rows of 16 (under 15 now), and 219 us where the call took 196 then (2048 tokens, 6400 x 20480).
 __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {   // v: the same in every lane
   return ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) |
          (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
@@ -89,8 +91,9 @@ __global__ __launch_bounds__(256) void embedding_bwd_kernel(int64_t T, int64_t h
   __shared__ unsigned long long mask[EB_GROUPS];
   __shared__ unsigned char row_of[64 * EB_GROUPS];   // of the tokens in the masks
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int v0 = blockIdx.x;
-  const int64_t c = (int64_t)blockIdx.y * 2048 + threadIdx.x * 8;
+  const unsigned chunks = (unsigned)((h + 2047) / 2048);
+  const int v0 = blockIdx.x / chunks;
+  const int64_t c = (int64_t)(blockIdx.x % chunks) * 2048 + threadIdx.x * 8;
   float acc[EB_ROWS][8];
 #pragma unroll
   for (int r = 0; r < EB_ROWS; ++r)
@@ -339,7 +342,9 @@ int mtnlg_embedding_bwd(const mtnlg_head_desc *desc, const int32_t *tokens, cons
   hipStream_t st = (hipStream_t)stream;
   int stride_log2 = 0;   // the least power of two that lets EB_ROWS strided rows per workgroup cover the vocabulary
   while (((int64_t)EB_ROWS << stride_log2) < desc->vocab_local) ++stride_log2;
-  const dim3 grid(1u << stride_log2, (unsigned)((h + 2047) / 2048));
+  const int64_t blocks = ((int64_t)1 << stride_log2) * ((h + 2047) / 2048);
+  if (blocks > 0x7FFFFFFF) return MTNLG_UNSUPPORTED_SHAPE;
+  const dim3 grid((unsigned)blocks);
   LaunchScope scope(MTNLG_K_ELEMENTWISE, st);
   if (desc->dtype == MTNLG_BF16) {
     embedding_bwd_kernel<bf16><<<grid, 256, 0, st>>>(T, h, desc->vocab_local, desc->vocab_start, stride_log2, tokens,
