@@ -373,6 +373,18 @@ def test_gelu_colsum_bias_residual(dtype):
 
 
 
+# The squared norm in one launch up to 16384 elements, else in parts of 8192 and, from 2048 parts on, longer ones.
+@pytest.mark.parametrize("count", [1, 3, 4097, 16384, 16385, 24579, 8192 * 2048, 8192 * 2048 + 5])
+def test_grad_sqnorm_by_size(count):
+    grad = torch.randn(count, generator=torch.Generator(device="cuda").manual_seed(count), device="cuda")
+    ws = torch.empty(M.mtnlg_grad_sqnorm_workspace(), dtype=torch.uint8, device="cuda")
+    sq = torch.full((1,), float("nan"), device="cuda")
+    want = oracle.grad_sqnorm([to_np(grad)])
+    for i in (1, 2):
+        M.mtnlg_grad_sqnorm(grad, ws, sq, accumulate=i > 1)
+        assert abs(float(sq) - i * want) <= 2e-7 * i * want   # 64-bit sums, each result rounded to fp32 (6e-8)
+
+
 # ---- optimizer step (Section 3.2: Adam, clipping, weight decay; Section 2.1: fp32 copies and states) ----------
 
 @pytest.mark.parametrize("count", [1, 1023, 4096 + 3, 3_000_001])
