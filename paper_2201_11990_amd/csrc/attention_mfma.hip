@@ -332,11 +332,11 @@ struct BackwardBlocks {
 struct HeadBlock {
   int head, batch, order;
   bool none;   // nothing left at this place of the last row
-  __device__ HeadBlock(int b, int n, int group, int count) {   // count: blocks of a head
+  __device__ HeadBlock(int b, int n, int group, int count, unsigned place) {   // count: blocks of a head; place: in the grid row
     const unsigned heads = (unsigned)b * (unsigned)n, first = blockIdx.y * (unsigned)group;
     const unsigned here = heads - first < (unsigned)group ? heads - first : (unsigned)group;
-    const unsigned hb = first + blockIdx.x % here;
-    order = blockIdx.x / here;
+    const unsigned hb = first + place % here;
+    order = place / here;
     head = hb % (unsigned)n;
     batch = hb / (unsigned)n;
     none = order >= count;
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES;
-  const HeadBlock hb(b, n, group, PairedBlocks<G>::count(s));
+  const HeadBlock hb(b, n, group, PairedBlocks<G>::count(s), blockIdx.x);
   const int j = hb.head, bi = hb.batch;
   if (hb.none) return;
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
@@ -578,16 +578,24 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
 }
 
 // ------------------------------------------------------------------ backward: dq (and D)
+struct BackwardArgs {
+  int b, s, n, head_dim, group;
+  float scale;
+  const bf16 *qkv, *a;
+  const float *lse;
+  const bf16 *da;
+  bf16 *dqkv;
+  float *Dvec;
+};
+
 template <int D, bool PAIRED, bool EXACT>
-__global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, int head_dim, int group, float scale, const bf16 *__restrict__ qkv,
-                                                         const bf16 *__restrict__ a, const float *__restrict__ lse,
-                                                         const bf16 *__restrict__ da, bf16 *__restrict__ dqkv,
-                                                         float *__restrict__ Dvec) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+__device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int s, int n, int head_dim, int group, float scale,
+                                         const bf16 *__restrict__ qkv, const bf16 *__restrict__ a, const float *__restrict__ lse,
+                                         const bf16 *__restrict__ da, bf16 *__restrict__ dqkv, float *__restrict__ Dvec) {
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES;
   constexpr int NB = PAIRED ? 4 : 2, NS = NB / 2;   // 16-row blocks and 32-row slots of a tile that a wave takes
-  const HeadBlock hb(b, n, group, BackwardBlocks<PAIRED>::count(s));
+  const HeadBlock hb(b, n, group, BackwardBlocks<PAIRED>::count(s), place);
   const int j = hb.head, bi = hb.batch;
   if (hb.none) return;
   // from the thread number: as in the forward kernel
@@ -785,17 +793,17 @@ __global__ __launch_bounds__(512) void attn_bwd_dq_kernel(int b, int s, int n, i
 }
 
 // ------------------------------------------------------------------ backward: dk, dv
-template <int D, bool PAIRED, bool EXACT>
-__global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, int head_dim, int group, float scale, const bf16 *__restrict__ qkv,
-                                                           const float *__restrict__ lse,
-                                                           const float *__restrict__ Dvec,
-                                                           const bf16 *__restrict__ da, bf16 *__restrict__ dqkv) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+// OWN_D: D is computed here (a: read then), not taken from the dq kernel.
+template <int D, bool PAIRED, bool EXACT, bool OWN_D>
+__device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int s, int n, int head_dim, int group, float scale,
+                                          const bf16 *__restrict__ qkv, const bf16 *__restrict__ a, const float *__restrict__ lse,
+                                          const float *__restrict__ Dvec, const bf16 *__restrict__ da, bf16 *__restrict__ dqkv) {
+  static_assert(!OWN_D || (!PAIRED && !EXACT), "as it is used");
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES + 512;   // Q tile, dO tile, lse[64], D[64]
   constexpr int NB = PAIRED ? 4 : 2, NS = NB / 2;   // as in the dq kernel
   constexpr bool LATE = PAIRED && D == 160;   // fewer fragments read ahead: no room in the registers
-  const HeadBlock hb(b, n, group, BackwardBlocks<PAIRED>::count(s));
+  const HeadBlock hb(b, n, group, BackwardBlocks<PAIRED>::count(s), place);
   const int j = hb.head, bi = hb.batch;
   if (hb.none) return;
   const BackwardBlocks<PAIRED> bb(s, hb.order, threadIdx.x >> 6);   // (from the thread number; head size 160: 194 registers instead of 230)
@@ -832,7 +840,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
   const int quarter = wave & 3, half = wave >> 2;
   const int64_t pitch = half ? pld : ld, row0 = (int64_t)t_first * 64;
   TileStream qo(half ? dab + row0 * pld : base + row0 * ld, ((s - row0) * pitch - (half ? j : 3 * j) * d) * 2, 64 * pitch * 2);
-  TileStream stats(((wave & 1) ? Dvec : lse) + ((int64_t)bi * n + j) * s + row0, (s - row0) * 4, 256);
+  TileStream stats(((wave & 1) && !OWN_D ? Dvec : lse) + ((int64_t)bi * n + j) * s + row0, (s - row0) * 4, 256);
   uint32_t dma_off[IPW];
 #pragma unroll
   for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(pitch * 2), quarter, lane, i, d);
@@ -868,6 +876,23 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
     arrive(kf[kk]);
     arrive(vf[kk]);
   }
+  float *const own_d = reinterpret_cast<float *>(smem + 3 * STAGE);   // -D of the rows from the first tile on
+  if constexpr (OWN_D) {
+    const bf16 *ah = a + (int64_t)bi * s * pld + (int64_t)j * d;
+    for (int row = (threadIdx.x >> 2); row < ntiles * 64; row += 128) {   // four lanes to a row
+      const int64_t at = (int64_t)(row0 + row < s ? row0 + row : s - 1) * pld + (threadIdx.x & 3) * 8;
+      float t = 0.0f;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const bf16x8 x = *reinterpret_cast<const bf16x8 *>(dab + at + 32 * kk), y = *reinterpret_cast<const bf16x8 *>(ah + at + 32 * kk);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t += (float)x[e] * (float)y[e];
+      }
+      t += __shfl_xor(t, 1, 64);
+      t += __shfl_xor(t, 2, 64);
+      if ((threadIdx.x & 3) == 0) own_d[row] = -t;
+    }
+  }
   int cur = 0;
   for (int it = 0; it < ntiles; ++it) {
     wait_and_barrier<IPW + 1>();
@@ -883,7 +908,7 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
 #pragma unroll
       for (int qb = 0; qb < NB; ++qb) {
         if constexpr (EXACT) pc[qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        else pc[qb] = *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
+        else pc[qb] = *reinterpret_cast<const f32x4 *>((OWN_D ? own_d + it * 64 + q_half : stat + 64) + 16 * qb + 4 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[qb][e] = 0.0f;
       }
@@ -996,6 +1021,27 @@ __global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(int b, int s, int n, 
   }
 }
 
+template <int D, bool PAIRED, bool EXACT>
+__global__ __launch_bounds__(512) void attn_bwd_dq_kernel(BackwardArgs w) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  dq_block<D, PAIRED, EXACT>(blockIdx.x, smem, w.b, w.s, w.n, w.head_dim, w.group, w.scale, w.qkv, w.a, w.lse, w.da, w.dqkv, w.Dvec);
+}
+template <int D, bool PAIRED, bool EXACT>
+__global__ __launch_bounds__(512) void attn_bwd_dkv_kernel(BackwardArgs w) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  dkv_block<D, PAIRED, EXACT, false>(blockIdx.x, smem, w.b, w.s, w.n, w.head_dim, w.group, w.scale, w.qkv, w.a, w.lse, w.Dvec, w.da, w.dqkv);
+}
+// Both in one launch (bwd_one_launch says when): the first half of a grid row's workgroups (dk / dv, the longer ones) compute D for themselves.
+template <int D>
+__global__ __launch_bounds__(512) void attn_bwd_kernel(BackwardArgs w) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const unsigned half = gridDim.x / 2;
+  if (blockIdx.x < half)
+    dkv_block<D, false, false, true>(blockIdx.x, smem, w.b, w.s, w.n, w.head_dim, w.group, w.scale, w.qkv, w.a, w.lse, nullptr, w.da, w.dqkv);
+  else
+    dq_block<D, false, false>(blockIdx.x - half, smem, w.b, w.s, w.n, w.head_dim, w.group, w.scale, w.qkv, w.a, w.lse, w.da, w.dqkv, w.Dvec);
+}
+
 // Forward with 32 rows per wave on eight waves (256 rows per workgroup): every K / V fragment read from LDS feeds two
 // MFMAs, which halves the kernel's LDS traffic -- its bound: each of the eight waves reads the whole K and V tile, the
 // V tile through half-rate transposing reads -- but halves the number of workgroups as well.  Taken when that still
@@ -1044,11 +1090,10 @@ int bwd_launch_p(int b, int s, int n, int d, float scale, const void *qkv, const
   const int count = BackwardBlocks<PAIRED>::count(s), group = HeadBlock::group(b, n, count, PAIRED || D >= 128 ? 32 : 128, PAIRED ? 511 : 2047);
   const dim3 grid = HeadBlock::grid(b, n, group, count);
   LaunchScope scope(MTNLG_K_ATTN_BWD, st);
-  attn_bwd_dq_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dq, st>>>(b, s, n, d, group, scale, (const bf16 *)qkv, (const bf16 *)a, lse,
-                                                           (const bf16 *)da, (bf16 *)dqkv, Dvec);
+  const BackwardArgs w{b, s, n, d, group, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da, (bf16 *)dqkv, Dvec};
+  attn_bwd_dq_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dq, st>>>(w);
   MTNLG_TRY(check_launch());
-  attn_bwd_dkv_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dkv, st>>>(b, s, n, d, group, scale, (const bf16 *)qkv, lse, Dvec, (const bf16 *)da,
-                                                             (bf16 *)dqkv);
+  attn_bwd_dkv_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dkv, st>>>(w);
   return check_launch();
 }
 
@@ -1079,9 +1124,42 @@ bool bwd_paired(int b, int s, int n) {
   return pairs.time(heads, nb, (nb + 1) / 2) < halves.time(heads, nb, nb);
 }
 
+constexpr int ONE_LAUNCH_ROWS = 4096;   // what their D has room for in LDS
+template <int D>
+int bwd_launch_one(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
+                   hipStream_t st) {
+  const int count = row_blocks(s), group = HeadBlock::group(b, n, count, 32, 2047);
+  const int smem = 3 * (2 * 64 * D * 2 + 512) + count * 64 * (int)sizeof(float);
+  static unsigned long long attr_done = 0;
+  int device;
+  if (!attr_is_set(attr_done, &device)) {
+    if (hipFuncSetAttribute((const void *)attn_bwd_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            3 * (2 * 64 * D * 2 + 512) + ONE_LAUNCH_ROWS * (int)sizeof(float)) != hipSuccess)
+      return MTNLG_HIP_ERROR;
+    attr_mark_set(attr_done, device);
+  }
+  dim3 grid = HeadBlock::grid(b, n, group, count);
+  grid.x *= 2;
+  LaunchScope scope(MTNLG_K_ATTN_BWD, st);
+  attn_bwd_kernel<D><<<grid, 512, smem, st>>>(
+      BackwardArgs{b, s, n, D, group, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da, (bf16 *)dqkv, (float *)ws});
+  return check_launch();
+}
+
+// One launch where all workgroups of either kernel run at once, so that both kernels' would leave units idle one after the other: a second
+// D for every tile costs less than that and the launch.  us, two launches / one: 1 x 256 x 2 heads of 160 21.9 / 13.7, 2 x 300 x 2 of 128
+// 20.8 / 13.4, 2 x 257 of 64 13.3 / 8.7; by blocks of all heads together (s 192 to 1024): up to 128 1.5 times as fast, 256 1.1 to 1.3; 384 1.0 to
+// 1.05 and 512 0.85 to 0.93 at head sizes 128 and 160, where one workgroup runs on a unit; at 64, where three do, 512 1.16 to 1.19, 768 1.11,
+// 1024 0.96.
+template <int D>
+bool bwd_one_launch(int b, int s, int n) {
+  return s <= ONE_LAUNCH_ROWS && (int64_t)b * n * row_blocks(s) <= (D >= 128 || s > 1024 ? 256 : 768);
+}
+
 template <int D>
 int bwd_launch(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                void *dqkv, void *ws, hipStream_t st) {
+  if (bwd_one_launch<D>(b, s, n)) return bwd_launch_one<D>(b, s, n, scale, qkv, a, lse, da, dqkv, ws, st);
   if (bwd_paired<D>(b, s, n)) return bwd_launch_p<D, true>(b, s, n, D, scale, qkv, a, lse, da, dqkv, ws, st);
   return bwd_launch_p<D, false>(b, s, n, D, scale, qkv, a, lse, da, dqkv, ws, st);
 }

@@ -410,6 +410,14 @@ def test_attention_with_exact_weights(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
+# Backward in one launch, dk / dv with a D of its own: two rows (with one dq is the rounding of dP - D), the edges of a 64-row block and of the 128 rows that a pass of D takes, and
+# either side of the rule (256 blocks; 768 at head size 64 up to s 1024).
+@pytest.mark.parametrize("b,s,n,d", [(1, 2, 1, 128), (2, 63, 3, 64), (1, 64, 2, 160), (1, 65, 1, 128), (1, 129, 2, 64), (3, 191, 1, 160), (1, 1030, 1, 64),
+                                     (4, 64, 64, 128), (1, 64, 257, 160), (3, 100, 128, 64), (1, 97, 385, 64)])
+def test_attention_backward_in_one_launch(b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
+
+
 # An infinity or NaN in one token reaches only what depends on that token.  K and V of token t0: outputs and dq of the rows before it
 # stay as they were; Q and dO of token t0: dk and dv of the keys after it.  t0 at the start, inside and at the end of a 16-row
 # block, and the last token, whose block hangs over the end of the sequence.
