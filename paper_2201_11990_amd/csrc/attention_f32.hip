@@ -204,11 +204,10 @@ __device__ __forceinline__ float quad_max(float v) {
 template <bool SPLIT>
 struct Where {
   int lane, g, r, row0, part, head, batch;
-  __device__ __forceinline__ Where(bool last_first) {
+  __device__ __forceinline__ Where(int blk) {   // blk: of the head's blocks of rows
     lane = threadIdx.x & 63;
     g = lane >> 4;
     r = lane & 15;
-    const int blk = last_first ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     row0 = SPLIT ? blk * 16 : blk * 64 + 16 * wave;
     part = SPLIT ? wave : 0;
@@ -234,7 +233,7 @@ struct Meeting {
 template <typename E, int DP, bool SPLIT>
 __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
                                                            E *__restrict__ a, float *__restrict__ lse) {
-  const Where<SPLIT> w(true);
+  const Where<SPLIT> w(gridDim.y - 1 - blockIdx.y);
   constexpr int STRIDE = SPLIT ? 128 : 32;
   const int first = 32 * w.part;
   if (w.row0 >= s) return;
@@ -327,15 +326,12 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(int s, int n, int d, 
   redo_fwd<E, DP>(base, ld, s, d, scale, q, last, w.g, out, out_lse);
 }
 
-// dq, and D for the kernel below
-// (fp32, small head sizes: two waves per SIMD are asked for, with which the compiler keeps the accumulators in ordinary registers
-// instead of copying them at every step; 2 x 512 x 16 heads of 64, dq: 3 us less, 1 x 1990 x 16 of 32: 9 us less.)
+// dq, and D for the kernel below.  meet: SPLIT only, like everywhere
 template <typename E, int DP, bool SPLIT>
-__global__ __launch_bounds__(256, sizeof(E) == 4 && DP <= 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
-                                                              const E *__restrict__ a, const float *__restrict__ lse,
-                                                              const E *__restrict__ da, E *__restrict__ dqkv,
-                                                              float *__restrict__ D) {
-  const Where<SPLIT> w(true);
+__device__ __forceinline__ void dq_rows(int blk, Meeting<DP> *meet, int s, int n, int d, float scale, const E *__restrict__ qkv,
+                                        const E *__restrict__ a, const float *__restrict__ lse, const E *__restrict__ da,
+                                        E *__restrict__ dqkv, float *__restrict__ D) {
+  const Where<SPLIT> w(blk);
   constexpr int STRIDE = SPLIT ? 64 : 16;
   const int first = 16 * w.part;
   if (w.row0 >= s) return;
@@ -378,8 +374,7 @@ __global__ __launch_bounds__(256, sizeof(E) == 4 && DP <= 64 ? 2 : 1) void attn_
   }
   if constexpr (PARTS) dq.flush(total);
   if constexpr (SPLIT) {
-    __shared__ Meeting<DP> meet;
-    meet.add(dq, w.part, w.lane);
+    meet->add(dq, w.part, w.lane);
     if (w.part > 0) return;
   }
   E *out = dqkv + ((int64_t)w.batch * s + q) * ld + (int64_t)w.head * 3 * d;
@@ -398,20 +393,21 @@ constexpr int dkv_waves(int most) {
   if (sizeof(E) == 2 && DP == 64) return most ? 2 : 1;
   return most ? 8 : 1;
 }
-template <typename E, int DP, bool SPLIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dkv_waves<E, DP>(0), dkv_waves<E, DP>(1)))) void attn_bwd_dkv_f32_kernel(int s, int n, int d, float scale, const E *__restrict__ qkv,
-                                                               const float *__restrict__ lse, const float *__restrict__ D,
-                                                               const E *__restrict__ da, E *__restrict__ dqkv) {
-  const Where<SPLIT> w(false);
+// OWN_D: D is not read; it is the diagonal of dO a^T by the MFMAs that give dP, as in the dq kernel.
+template <typename E, int DP, bool SPLIT, bool OWN_D>
+__device__ __forceinline__ void dkv_rows(int blk, Meeting<DP> *meet, int s, int n, int d, float scale, const E *__restrict__ qkv,
+                                         const E *__restrict__ a, const float *__restrict__ lse, const float *__restrict__ D,
+                                         const E *__restrict__ da, E *__restrict__ dqkv) {
+  const Where<SPLIT> w(blk);
   constexpr int STRIDE = SPLIT ? 64 : 16;
   const int first = w.row0 + 16 * w.part;
   if (w.row0 >= s) return;
   const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
   const E *base = qkv + (int64_t)w.batch * s * ld + (int64_t)w.head * 3 * d;
-  const E *dab = da + (int64_t)w.batch * s * pld + (int64_t)w.head * d;
+  const E *dab = da + (int64_t)w.batch * s * pld + (int64_t)w.head * d, *ab = a + (int64_t)w.batch * s * pld + (int64_t)w.head * d;
   const int64_t st = ((int64_t)w.batch * n + w.head) * s;
   const int key = w.row0 + w.r;
-  Rows<E, DP> kf, vf, qf, of;
+  Rows<E, DP> kf, vf, qf, of, af;
   kf.load(base + d, ld, w.row0, s, d, w.g, w.r);
   vf.load(base + 2 * d, ld, w.row0, s, d, w.g, w.r);
   constexpr bool PARTS = sizeof(E) == 4;
@@ -424,6 +420,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dkv_waves<E
   }
   qf.load(base, ld, first, s, d, w.g, w.r);
   of.load(dab, pld, first, s, d, w.g, w.r);
+  if constexpr (OWN_D) af.load(ab, pld, first, s, d, w.g, w.r);
   for (int q0 = first; q0 < s; q0 += STRIDE) {
     Cols<E, DP> oc, qcol;
     oc.load(dab, pld, q0, s, d, w.g, w.r);
@@ -433,7 +430,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dkv_waves<E
     for (int i = 0; i < 4; ++i) {
       const int q = q0 + 4 * w.g + i < s ? q0 + 4 * w.g + i : s - 1;
       ls[i] = lse[st + q];
-      dd[i] = D[st + q];
+      if constexpr (!OWN_D) dd[i] = D[st + q];
+    }
+    if constexpr (OWN_D) {
+      const f32x4 t = product(of, af);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dd[i] = __shfl(t[i], 20 * w.g + i, 64);
+      af.load(ab, pld, q0 + STRIDE, s, d, w.g, w.r);
     }
     const f32x4 sc = product(qf, kf) * scale, dp = product(of, vf);
     qf.load(base, ld, q0 + STRIDE, s, d, w.g, w.r);   // of the next step
@@ -458,17 +461,65 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dkv_waves<E
     dv.flush(tv);
   }
   if constexpr (SPLIT) {
-    __shared__ Meeting<DP> meet;
-    meet.add(dk, w.part, w.lane);
+    meet->add(dk, w.part, w.lane);
     __syncthreads();
-    meet.add(dv, w.part, w.lane);
+    meet->add(dv, w.part, w.lane);
     if (w.part > 0) return;
   }
   E *out = dqkv + ((int64_t)w.batch * s + key) * ld + (int64_t)w.head * 3 * d;
   float z = 0.0f;
   if (key < s) z = dk.store(out + d, d, scale, w.g) + dv.store(out + 2 * d, d, 1.0f, w.g);
   if (all_finite(z)) return;
-  redo_dkv<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, D + st, w.g, out);
+  if constexpr (OWN_D) redo_dkv<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, [&](int t) { return dot(dab + t * pld, ab + t * pld, d, w.g); }, w.g, out);
+  else redo_dkv<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, [&](int t) { return D[st + t]; }, w.g, out);
+}
+
+template <typename E>
+struct BackwardArgs {
+  int s, n, d;
+  float scale;
+  const E *qkv, *a;
+  const float *lse;
+  const E *da;
+  E *dqkv;
+  float *D;
+};
+template <int DP, bool SPLIT>
+__device__ __forceinline__ Meeting<DP> *meeting_place() {
+  if constexpr (SPLIT) {
+    __shared__ Meeting<DP> meet;
+    return &meet;
+  }
+  return nullptr;
+}
+// (fp32, small head sizes: two waves per SIMD are asked for, with which the compiler keeps the accumulators in ordinary registers
+// instead of copying them at every step; 2 x 512 x 16 heads of 64, dq: 3 us less, 1 x 1990 x 16 of 32: 9 us less.)
+template <typename E, int DP, bool SPLIT>
+__global__ __launch_bounds__(256, sizeof(E) == 4 && DP <= 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(BackwardArgs<E> x) {
+  dq_rows<E, DP, SPLIT>(gridDim.y - 1 - blockIdx.y, meeting_place<DP, SPLIT>(), x.s, x.n, x.d, x.scale, x.qkv, x.a, x.lse, x.da, x.dqkv, x.D);
+}
+template <typename E, int DP, bool SPLIT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dkv_waves<E, DP>(0), dkv_waves<E, DP>(1)))) void attn_bwd_dkv_f32_kernel(BackwardArgs<E> x) {
+  dkv_rows<E, DP, SPLIT, false>(blockIdx.y, meeting_place<DP, SPLIT>(), x.s, x.n, x.d, x.scale, x.qkv, x.a, x.lse, x.D, x.da, x.dqkv);
+}
+// Both in one launch, for calls that split the streamed side (one_launch_groups says which): the first half of the blocks are dk / dv, with a D of
+// their own.
+template <typename E, int DP>
+__global__ __launch_bounds__(256, DP <= (sizeof(E) == 4 ? 96 : 128) ? 2 : 1) void attn_bwd_f32_kernel(BackwardArgs<E> x) {
+  Meeting<DP> *meet = meeting_place<DP, true>();
+  const int half = gridDim.y / 2, blk = blockIdx.y;
+  if (blk < half) dkv_rows<E, DP, true, true>(blk, meet, x.s, x.n, x.d, x.scale, x.qkv, x.a, x.lse, nullptr, x.da, x.dqkv);
+  else dq_rows<E, DP, true>(2 * half - 1 - blk, meet, x.s, x.n, x.d, x.scale, x.qkv, x.a, x.lse, x.da, x.dqkv, x.D);
+}
+
+// Up to how many groups of 16 rows the backward kernels of a call that splits the streamed side go out in one launch.  us, two launches / one, fp32:
+// 1 x 257 x 2 heads of 64 22.0 / 15.3, 2 x 300 x 2 of 128 43.8 / 28.9; by groups: up to 128 1.2 to 1.8 times as fast, 256 1.06 to 1.3, and 512 1.07
+// to 1.19 up to head size 96, 0.91 at 128; at 160 1.0 for 256, 0.82 for 512; above 192 the registers run out (0.5 to 1.1).
+// bf16: 128 x 32 of 96 15.3 / 11.6, 128 x 16 of 184 24.9 / 16.4, 256 x 8 of 256 46 / 31; 512 x 16 of 232 (512 groups) 97.8 / 103.9.
+template <typename E, int DP>
+constexpr int one_launch_groups() {
+  if (sizeof(E) == 2) return DP <= 96 ? 256 : 128;
+  return DP <= 96 ? 512 : DP == 128 ? 256 : DP == 160 ? 128 : 0;
 }
 
 // Which calls split the streamed side over the waves of a workgroup: those with up to 512 groups of 16 rows, two workgroups
@@ -493,12 +544,19 @@ int fwd_launch(int b, int s, int n, int d, float scale, const void *qkv, void *a
 template <typename E, int DP, bool SPLIT>
 int bwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                  void *dqkv, void *ws, hipStream_t st) {
-  float *D = (float *)ws;
-  const dim3 grid(n, SPLIT ? (s + 15) / 16 : (s + 63) / 64, b);
+  const BackwardArgs<E> x{s, n, d, scale, (const E *)qkv, (const E *)a, lse, (const E *)da, (E *)dqkv, (float *)ws};
+  dim3 grid(n, SPLIT ? (s + 15) / 16 : (s + 63) / 64, b);
   LaunchScope scope(MTNLG_K_ATTN_BWD, st);
-  attn_bwd_dq_f32_kernel<E, DP, SPLIT><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, (const E *)a, lse, (const E *)da, (E *)dqkv, D);
+  if constexpr (SPLIT && one_launch_groups<E, DP>() > 0) {
+    if ((int64_t)b * n * ((s + 15) / 16) <= one_launch_groups<E, DP>()) {
+      grid.y *= 2;
+      attn_bwd_f32_kernel<E, DP><<<grid, 256, 0, st>>>(x);
+      return check_launch();
+    }
+  }
+  attn_bwd_dq_f32_kernel<E, DP, SPLIT><<<grid, 256, 0, st>>>(x);
   MTNLG_TRY(check_launch());
-  attn_bwd_dkv_f32_kernel<E, DP, SPLIT><<<grid, 256, 0, st>>>(s, n, d, scale, (const E *)qkv, lse, D, (const E *)da, (E *)dqkv);
+  attn_bwd_dkv_f32_kernel<E, DP, SPLIT><<<grid, 256, 0, st>>>(x);
   return check_launch();
 }
 template <typename E, int DP>

@@ -1017,7 +1017,7 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
   }
   if constexpr (EXACT) {
     const int64_t st = ((int64_t)bi * n + j) * s;
-    if (wave < 4 && !all_finite(z)) redo_dkv<bf16, D>(base, ld, dab, pld, s, d, scale, kw, key, lse + st, Dvec + st, g, out);
+    if (wave < 4 && !all_finite(z)) redo_dkv<bf16, D>(base, ld, dab, pld, s, d, scale, kw, key, lse + st, [&](int t) { return Dvec[st + t]; }, g, out);
   }
 }
 

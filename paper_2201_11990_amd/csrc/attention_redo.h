@@ -69,7 +69,7 @@ __device__ __forceinline__ float dot(const E *x, const E *y, int d, int g) {
   return quad_sum(t);
 }
 
-// 16 rows of the result, row q = first row + lane % 16 (rows q >= s: computed as row s - 1, not stored).  base, da, D, lse, out: of
+// 16 rows of the result, row q = first row + lane % 16 (rows q >= s: computed as row s - 1, not stored).  base, da, lse, out: of
 // the batch's sequence and the head, row 0; last: the last key any of the rows sees.
 template <typename E, int DP>
 __device__ __forceinline__ void redo_fwd(const E *base, int64_t ld, int s, int d, float scale, int q, int last, int g, E *out, float *out_lse) {
@@ -110,9 +110,9 @@ __device__ __forceinline__ void redo_dq(const E *base, int64_t ld, const E *da, 
   }
   if (q < s) sum.store(out, d, scale, g);
 }
-template <typename E, int DP>
+template <typename E, int DP, typename DOf>   // d_of(t): D of row t
 __device__ __forceinline__ void redo_dkv(const E *base, int64_t ld, const E *da, int64_t pld, int s, int d, float scale, int row0, int key,
-                                         const float *lse, const float *D, int g, E *out) {
+                                         const float *lse, DOf &&d_of, int g, E *out) {
   const E *krow = base + d + (key < s ? key : s - 1) * ld;
   auto prob = [&](int t) { return expf(dot(krow, base + t * ld, d, g) * scale - lse[t]); };
   Quarter<E, DP> sum;   // dv, then dk
@@ -126,8 +126,8 @@ __device__ __forceinline__ void redo_dkv(const E *base, int64_t ld, const E *da,
   sum.clear();
 #pragma unroll 1
   for (int t = row0; t < s; ++t) {
-    const float p = prob(t), dp = dot(krow + d, da + t * pld, d, g);
-    if (t >= key) sum.add(p * (dp - D[t]), base + t * ld, d, g);
+    const float p = prob(t), dp = dot(krow + d, da + t * pld, d, g), dt = d_of(t);
+    if (t >= key) sum.add(p * (dp - dt), base + t * ld, d, g);
   }
   if (key < s) sum.store(out + d, d, scale, g);
 }

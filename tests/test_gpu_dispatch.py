@@ -418,6 +418,15 @@ def test_attention_backward_in_one_launch(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
+# The same for the kernels without LDS: fp32 and small bf16 calls on either side of the rules (512, 256 and 128 groups of 16 rows), head sizes that have
+# no such launch, one row (dq is exactly zero).
+@pytest.mark.parametrize("dtype,b,s,n,d", [("fp32", 1, 1, 1, 64), ("fp32", 1, 64, 128, 96), ("fp32", 1, 64, 129, 96), ("fp32", 2, 127, 16, 128),
+                                           ("fp32", 1, 33, 42, 160), ("fp32", 1, 33, 43, 160), ("fp32", 1, 100, 2, 192), ("bf16", 1, 1, 2, 96),
+                                           ("bf16", 1, 128, 32, 72), ("bf16", 1, 49, 65, 24), ("bf16", 1, 99, 18, 184), ("bf16", 1, 113, 16, 256)])
+def test_attention_backward_in_one_launch_without_lds(dtype, b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
+
+
 # An infinity or NaN in one token reaches only what depends on that token.  K and V of token t0: outputs and dq of the rows before it
 # stay as they were; Q and dO of token t0: dk and dv of the keys after it.  t0 at the start, inside and at the end of a 16-row
 # block, and the last token, whose block hangs over the end of the sequence.
