@@ -29,7 +29,7 @@
 // No atomics: every output element has one owner, results are run-to-run identical.
 //
 // EXACT: any head size d that is a multiple of 8, in tiles of D = d rounded up to 32 columns (the DMA brings zeros past d).  P and dS are
-// not rounded to bf16: each goes into the second product as three bf16 parts that add up to it (common.h: Parts), three MFMAs
+// not rounded to bf16: each goes into the second product as three bf16 parts that add up to it (common.h: Parts; scaled, so of any size), three MFMAs
 // where the other kernels have one; 17 against 9 a tile in all, but the chain between barriers stays the bound.  2 x 1024 tokens, 16 heads of
 // 96, forward / backward: 103 / 327 us on the fp32 instructions without LDS (attention_f32.hip), 22 / 61 here.  Inputs that are not finite
 // take the slow path of attention_redo.h.
@@ -562,7 +562,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
         bf16x4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x = o[qg][db][e] * inv;
+          const float x = o[qg][db][e] * (EXACT ? inv * PARTS_UNSCALE : inv);
           if constexpr (EXACT) z = fmaf(x, 0.0f, z);
           v[e] = (bf16)x;
         }
@@ -762,7 +762,7 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int 
     bf16x4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float x = sum[e] * scale;
+      const float x = (EXACT ? sum[e] * PARTS_UNSCALE : sum[e]) * scale;
       if constexpr (EXACT) z = fmaf(x, 0.0f, z);
       v[e] = (bf16)x;
     }
@@ -986,10 +986,10 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
     bf16x4 ok, ov;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float x = sk[e] * scale;
-      if constexpr (EXACT) z = fmaf(x, 0.0f, fmaf(sv[e], 0.0f, z));
+      const float x = (EXACT ? sk[e] * PARTS_UNSCALE : sk[e]) * scale, y = EXACT ? sv[e] * PARTS_UNSCALE : sv[e];
+      if constexpr (EXACT) z = fmaf(x, 0.0f, fmaf(y, 0.0f, z));
       ok[e] = (bf16)x;
-      ov[e] = (bf16)sv[e];
+      ov[e] = (bf16)y;
     }
     *reinterpret_cast<bf16x4 *>(out + d + db * 16 + 4 * g) = ok;
     *reinterpret_cast<bf16x4 *>(out + 2 * d + db * 16 + 4 * g) = ov;

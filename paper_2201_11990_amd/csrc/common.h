@@ -248,7 +248,12 @@ __device__ __forceinline__ void epilogue4(const EpiArgs &ea, void *C, int64_t N,
 }
 
 // One operand of v_mfma_f32_16x16x32_bf16 in N parts that add up to the 8 values of a chunk: bf16 elements are one part, fp32
-// elements three, each the rounded rest of the ones before it (8 + 8 + 8 bits: the rest after three is zero).
+// elements three, each the rounded rest of the ones before it (8 + 8 + 8 bits: the rest after three is zero; fp32 products from bf16 ones in
+// this way: Henry, Tang, Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations", 2019).
+// Three parts are those of the value times PARTS_SCALE, with which the last bit of the smallest fp32 value, 2^-149, is a normal bf16
+// value: cut as they are, values lose digits from about 2^-110 down, which a sum does not show if the other factor is large (A about 2^-118,
+// B 2^60: results off by 9e-6).  Values of 2^104 and above have no such parts, their sums are not finite (parts_hold).
+constexpr float PARTS_SCALE = 0x1p24f, PARTS_UNSCALE = 0x1p-24f;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 template <int N>
 struct Parts {
@@ -259,7 +264,7 @@ struct Parts {
     asm("" : "+s"(first), "+s"(second));
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
-      float lo = x[e], hi = x[e + 1];
+      float lo = N > 1 ? x[e] * PARTS_SCALE : x[e], hi = N > 1 ? x[e + 1] * PARTS_SCALE : x[e + 1];
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const bf16x2 t = {(bf16)lo, (bf16)hi};
@@ -274,7 +279,7 @@ struct Parts {
   }
 };
 // The product of a block in parts: fp32 sums of products that are exact.  Of three parts each way the six largest products; what is
-// left out is below 2^-26 of the product of the two values.  The largest (step 0) and the other five (steps 1 .. 5) belong in separate
+// left out is at most 2^-24 of the product of the two values (second parts are up to 2^-8 of a value, third ones 2^-17).  The largest (step 0) and the other five (steps 1 .. 5) belong in separate
 // accumulators: the matrix instructions round a product down to the last bits of a much larger accumulator, and in one
 // accumulator the small products moved every result by -2e-8 to -1e-7 of the typical one (1024 x 1024 x 1024 to 4096), which a sum over
 // the rows of the result shows (7.6e-7 instead of 3.1e-7 with fp32 instructions, and 1.7e-7 so).
@@ -283,12 +288,10 @@ __device__ __forceinline__ f32x4 mma_parts(const Parts<N> &b, const Parts<N> &a,
   constexpr int PB[6] = {0, 2, 0, 1, 1, 0}, PA[6] = {0, 0, 2, 1, 0, 1};
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.p[N == 1 ? 0 : PB[step]], a.p[N == 1 ? 0 : PA[step]], acc, 0, 0, 0);
 }
-// Whether a sum of such products is what fp32 products would give: the parts cannot say an infinity, nor a value that rounds to one, nor
-// the last bits of a value below 2^-110.
-__device__ __forceinline__ bool parts_hold(float sum) {
-  const float t = fabsf(sum);
-  return t == 0.0f || (t > 0x1p-70f && t < INFINITY);
-}
+// Whether a sum of such products is what fp32 products would give: the parts cannot say an infinity, nor a value of 2^104 and above (the
+// rest of an infinite part is NaN), and scaled sums end at 2^80.  A sum that holds is taken back by parts_sum.
+__device__ __forceinline__ bool parts_hold(float sum) { return fabsf(sum) < INFINITY; }
+__device__ __forceinline__ f32x4 parts_sum(f32x4 scaled) { return scaled * (PARTS_UNSCALE * PARTS_UNSCALE); }
 
 // ---- host side -------------------------------------------------------------
 // Brackets a launch with HIP events when per-class timing is on (profile.cpp).

@@ -209,9 +209,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, DIRECT && TMB == 2 ? 8 : 2) v
     }
   }
   if constexpr (NP > 1) {
-    // The parts cannot say an infinity, nor a value that rounds to one, nor the last bits of a value below 2^-110.  Where
-    // a result is not finite or so small that such a value may be behind it, the wave takes its chunks once more on the fp32
-    // instructions.
+    // Where the parts cannot say a value (parts_hold), the wave takes its chunks once more on the fp32 instructions.
     bool odd = false;
 #pragma unroll
     for (int i = 0; i < TMB; ++i)
@@ -239,6 +237,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, DIRECT && TMB == 2 ? 8 : 2) v
             for (int j = 0; j < TNB; ++j)
               acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf.v[j][e], af.v[i][e], acc[i][j], 0, 0, 0);
       }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TMB; ++i)
+#pragma unroll
+        for (int j = 0; j < TNB; ++j) acc[i][j] = parts_sum(acc[i][j]);
     }
   }
 

@@ -1,7 +1,7 @@
 // fp32 GEMM for problems with many output tiles: values in three bf16 parts (common.h: Parts), 128 x 128 tiles, parts shared through LDS.
 //
 // Eight waves of 64 x 32, slabs of 32 k.  Every value is cut into parts once a workgroup: a wave loads two of the tile's sixteen 16-row
-// blocks into registers, two slabs ahead, cuts them (56 vector instructions a slab) and writes the fragments to LDS as the matrix
+// blocks into registers, two slabs ahead, cuts them (72 vector instructions a slab) and writes the fragments to LDS as the matrix
 // instructions read them, lane by lane (a ring of three stages of 48 KB, one barrier a slab).  us,
 // operands straight to registers (gemm_generic.hip) / K split over waves (gemm_wave.hip) / here: 1024 x 4096 x 1024 NT 77 / 69 / 53, NN 62 / 73 / 55,
 // TN 59 / 89 / 50; 2048 x 2048 x 4096 NT 263 / 195 / 183.  Those two cut a value once a wave, two to eight times a workgroup, and with the
@@ -168,8 +168,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_parts_kernel(PartsArgs a) 
     else run(Num<BT>{});
   }
 
-  // The parts cannot say an infinity, nor a value that rounds to one, nor the last bits of a value below 2^-110.  Where a result is
-  // not finite, or so small that such a value may be behind it, the tile is taken once more on the fp32 instructions.
+  // Where the parts cannot say a value (parts_hold), the tile is taken once more on the fp32 instructions.
   bool odd = false;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -215,6 +214,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_parts_kernel(PartsArgs a) 
             for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[j][e], x[i][e], acc[i][j], 0, 0, 0);
       }
     }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = parts_sum(acc[i][j]);
   }
 
 #pragma unroll

@@ -218,9 +218,7 @@ __device__ __forceinline__ void wave_tile(const WaveGemmArgs &a, int block, char
     }
   }
   if constexpr (sizeof(E) == 4) {
-    // The parts cannot say an infinity, nor a value that rounds to one, nor the last bits of a value below 2^-110.  Where a
-    // result is not finite, or so small that such a value may be behind it, the wave takes its slabs once more on the fp32
-    // instructions.
+    // Where the parts cannot say a value (parts_hold), the wave takes its slabs once more on the fp32 instructions.
     bool odd = false;
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -249,6 +247,11 @@ __device__ __forceinline__ void wave_tile(const WaveGemmArgs &a, int block, char
 #pragma unroll
             for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf.v[j][e], af.v[i][e], acc[i][j], 0, 0, 0);
       }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = parts_sum(acc[i][j]);
     }
   }
 

@@ -346,6 +346,33 @@ def test_fp32_gemm_at_the_ends_of_the_range(route, layout):
             assert torch.equal(torch.isnan(C[5].cpu()), torch.isnan(want[5])) and torch.equal(torch.isinf(C[5].cpu()), torch.isinf(want[5]))
 
 
+# ... and small values whose products with large ones are ordinary numbers: every digit of an fp32 value down to the smallest one has to be
+# in its parts, whatever the size of the sum.  Both operands either way, and one such term among ordinary ones (in the second case
+# of it the large values are beyond what the parts can say).
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("route", [32, 64, 128, 0])
+def test_fp32_gemm_of_small_values_times_large_ones(route, layout):
+    Mm, N, K = 96, 72, 136 if route else 280
+    gemm = {0: gemm_without_lds, 128: gemm_in_parts}.get(route, lambda *a: gemm_by_waves(route, *a))
+    A, Bm = operands(layout, Mm, N, K, "fp32")
+
+    def check(X, Y, what):
+        C = torch.full((Mm, N), float("nan"), device="cuda")
+        gemm(layout, dev(X), dev(Y), C)
+        assert_close(C, gemm_oracle(layout, X, Y), TOL["fp32"], f"fp32 gemm {route} {layout} {what}")
+
+    for small, large in ((-112, 60), (-118, 60), (-130, 90), (-136, 30), (-140, 125)):
+        check(A * 2.0 ** small, Bm * 2.0 ** large, f"2^{small} x 2^{large}")
+        check(A * 2.0 ** large, Bm * 2.0 ** small, f"2^{large} x 2^{small}")
+    for small, large in ((-126, 100), (-124, 124)):
+        X, Y = A * 2.0 ** (small + large), Bm.clone()
+        col, row = (X[7], Y[7]) if layout == B.GEMM_TN else (X[:, 7], Y[:, 7] if layout == B.GEMM_NT else Y[7])
+        col.zero_()
+        col[5] = 1.37 * 2.0 ** small
+        row *= 2.0 ** large
+        check(X, Y, f"one term 2^{small} x 2^{large}")
+
+
 def check_bf16_gemm(layout, Mm, N, K, gemm):
     A, Bm = operands(layout, Mm, N, K, "bf16")
     what = f"bf16 gemm {layout} {Mm} {N} {K}"
@@ -408,6 +435,30 @@ def test_attention_by_rows_of_a_workgroup(dtype, b, s, n, d):
                                      (1, 193, 3, 184), (1, 257, 2, 72), (1, 257, 17, 56), (1, 513, 1, 192), (1, 300, 2, 136)])
 def test_attention_with_exact_weights(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
+
+
+# ... and dS of any size: one key takes all but 2^-20 of the weight and the gradient is small, so dS is about 2^-135 and every digit of it that
+# fp32 holds has to be in its parts.  dq where the keys are large, dk where the queries are; without the dominating key and the column
+# of its score, in which dP - D has no digits left.
+@pytest.mark.parametrize("part", [0, 1])
+@pytest.mark.parametrize("b,s,n,d", [(1, 257, 2, 96), (1, 100, 80, 40), (1, 257, 3, 184)])
+def test_attention_with_small_score_gradients(b, s, n, d, part):
+    dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
+    x, da = randn((b, s, n, 3, d), "fp32", 31), randn((b, s, n, d), "fp32", 32) * 2.0 ** -114
+    x[..., 0, 0], x[..., 1, 0] = 32.0, 0.0
+    x[:, 0, :, 1] = 0.0
+    x[:, 0, :, 1, 0] = 16.0 * math.sqrt(d) / 32.0
+    x[..., part, :] *= 2.0 ** -50
+    x[..., 1 - part, :] *= 2.0 ** 50
+    qkv, da = x.reshape(b * s, -1).to(torch.bfloat16), da.reshape(b * s, -1).to(torch.bfloat16)
+    a, dqkv = torch.empty_like(da, device="cuda"), torch.empty_like(qkv, device="cuda")
+    lse = torch.empty((b, n, s), device="cuda")
+    ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+    M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), dev(qkv), a, lse)
+    M.mtnlg_attention_bwd(b, s, n, d, 1.0 / math.sqrt(d), dev(qkv), a, lse, dev(da), dqkv, ws)
+    want = oracle.attention_bwd(dims, to_np(qkv), to_np(da)).reshape(b, s, n, 3, d)
+    got = dqkv.reshape(b, s, n, 3, d)
+    assert_close(got[:, 1:, :, part, 1:], want[:, 1:, :, part, 1:], TOL["bf16"], "dq" if part == 0 else "dk")
 
 
 # Backward in one launch, dk / dv with a D of its own: two rows (with one dq is the rounding of dP - D), the edges of a 64-row block and of the 128 rows that a pass of D takes, and
