@@ -461,6 +461,33 @@ def test_attention_with_small_score_gradients(b, s, n, d, part):
     assert_close(got[:, 1:, :, part, 1:], want[:, 1:, :, part, 1:], TOL["bf16"], "dq" if part == 0 else "dk")
 
 
+# ... and weights of any size that fp32 has: one key scores 90 (natural units) above the others, whose weights are about 2^-130.  What they
+# weigh is large and what the dominating key weighs is 0, so they are all of the result: V in a, dO in dv.  The key at the start, and in the
+# third tile, where the sums of the tiles before it are scaled down by as much.
+@pytest.mark.parametrize("at", [0, 150])
+@pytest.mark.parametrize("b,s,n,d", [(1, 257, 17, 56), (1, 200, 40, 96), (1, 257, 3, 184)])
+def test_attention_with_small_weights(b, s, n, d, at):
+    dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
+    x, da = randn((b, s, n, 3, d), "fp32", 33), randn((b, s, n, d), "fp32", 34) * 2.0 ** 40
+    x[..., 0, 0], x[..., 1, 0] = 32.0, 0.0
+    x[:, at, :, 1] = 0.0
+    x[:, at, :, 1, 0] = 90.0 * math.sqrt(d) / 32.0
+    x[..., 2, :] *= 2.0 ** 60
+    x[:, at, :, 2] = 0.0
+    qkv, da = x.reshape(b * s, -1).to(torch.bfloat16), da.reshape(b * s, -1).to(torch.bfloat16)
+    a, dqkv = torch.empty_like(da, device="cuda"), torch.empty_like(qkv, device="cuda")
+    lse = torch.empty((b, n, s), device="cuda")
+    ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+    M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), dev(qkv), a, lse)
+    M.mtnlg_attention_bwd(b, s, n, d, 1.0 / math.sqrt(d), dev(qkv), a, lse, dev(da), dqkv, ws)
+    want = oracle.attention_fwd(dims, to_np(qkv)).reshape(b, s, n, d)
+    # rows that see the dominating key: of such a row the others' weights are left
+    first = max(at, 1)
+    assert_close(a.reshape(b, s, n, d)[:, first:], want[:, first:], TOL["bf16"], "a")
+    want = oracle.attention_bwd(dims, to_np(qkv), to_np(da)).reshape(b, s, n, 3, d)
+    assert_close(dqkv.reshape(b, s, n, 3, d)[:, at + 1:, :, 2], want[:, at + 1:, :, 2], TOL["bf16"], "dv")
+
+
 # Backward in one launch, dk / dv with a D of its own: two rows (with one dq is the rounding of dP - D), the edges of a 64-row block and of the 128 rows that a pass of D takes, and
 # either side of the rule (256 blocks; 768 at head size 64 up to s 1024).
 @pytest.mark.parametrize("b,s,n,d", [(1, 2, 1, 128), (2, 63, 3, 64), (1, 64, 2, 160), (1, 65, 1, 128), (1, 129, 2, 64), (3, 191, 1, 160), (1, 1030, 1, 64),
