@@ -370,7 +370,8 @@ int gemm_parts(int layout, int64_t M, int64_t N, int64_t K, const void *A, const
 int gemm_wave_pick(int dtype, int layout, int64_t M, int64_t N, int64_t K, double other);
 double gemm_generic_time(int layout, int64_t M, int64_t N, int64_t K);   // of an fp32 problem on 64 x 64 tiles
 double gemm_direct_time(int64_t M, int64_t N, int64_t K);   // ... on the fp32 instructions, infinite for sums that these are not for
-bool gemm_generic_small_tile(int layout, int64_t M, int64_t N);   // 32 x 32 tiles, not 64 x 64, where accesses are aligned
+bool gemm_generic_small_tile(int layout, int64_t M, int64_t N);   // 32 x 32 tiles, not 64 x 64, where accesses are aligned: fp32
+bool gemm_generic_small_tile_bf16(int layout, int64_t M, int64_t N);
 // returns MTNLG_UNSUPPORTED_SHAPE when the MFMA kernel cannot take this problem
 // ws (nullable): scratch for the split-K tail, see gemm_mfma_workspace_bytes
 // prof_class: kernel class the launch is timed under (-1: MTNLG_K_GEMM_NT + layout)

@@ -1,5 +1,6 @@
 // GEMM with operands loaded straight into registers: fp32 problems between a few tiles and many, and every problem whose row lengths the kernels that move
-// tiles by DMA do not take (bf16 elements are widened on load, which is exact).  Any M, N, K, any layout.
+// tiles by DMA do not take (bf16 elements are widened on load and go to the bf16 instructions as the one part that they are).  Any M, N, K,
+// any layout.
 //
 // Longer sums of fp32 values: they are cut into three bf16 parts that add up to them exactly, and the six largest of the nine products of parts run
 // on v_mfma_f32_16x16x32_bf16 (common.h: Parts): sums in fp32, an error below that of the fp32 instructions (1024 x 1024 x 4096 against
@@ -317,13 +318,21 @@ int gemm_generic_of(int layout, const F32GemmArgs &a, bool vec, bool small, bool
 
 }  // namespace
 
-// bf16 problems on these kernels, and fp32 ones on the fp32 instructions: 32 x 32 tiles (K split over eight waves) or 64 x 64 tiles (over four), by rounds of 256 workgroups
-// times the time of a round at equal K on the fp32 instructions: measured then (us, K = 1024, 64 / 32) 256 x 256 23 / 10, 1024 x 1024
-// 26 / 33, 1024 x 3072 NT 88 / 95, TN 64 / 100.
-bool gemm_generic_small_tile(int layout, int64_t M, int64_t N) {
-  const double round64 = layout == MTNLG_GEMM_NT ? 25 : layout == MTNLG_GEMM_NN ? 22 : 20, round32 = 8.5;
+// 32 x 32 tiles (K split over eight waves) or 64 x 64 tiles (over four): rounds of 256 workgroups times the time of a round at equal K.
+static bool small_tile(int64_t M, int64_t N, double round64, double round32) {
   auto rounds = [&](int64_t t) { return (double)((((M + t - 1) / t) * ((N + t - 1) / t) + 255) / 256); };
   return rounds(32) * round32 < rounds(64) * round64;
+}
+// fp32 problems on the fp32 instructions: measured (us, K = 1024, 64 / 32) 256 x 256 23 / 10, 1024 x 1024 26 / 33, 1024 x 3072 NT 88 / 95,
+// TN 64 / 100.
+bool gemm_generic_small_tile(int layout, int64_t M, int64_t N) {
+  return small_tile(M, N, layout == MTNLG_GEMM_NT ? 25 : layout == MTNLG_GEMM_NN ? 22 : 20, 8.5);
+}
+// bf16 problems, one part on the bf16 instructions: 228 sizes (60 to 4100 rows and columns, K 132 to 4100), 0.2 % off the better tile on
+// average, 7 % at most; by the line above 1.3 % and 29 %.  us, 64 / 32: 252 x 1020 x 1020 NT 12.3 / 7.8; 508 x 516 x 1028 NT 12.8 / 12.0,
+// TN 9.8 / 10.4; 1020 x 1028 x 1028 NT 20.8 / 24.8; 2044 x 2052 x 1028 NT 44 / 78.
+bool gemm_generic_small_tile_bf16(int layout, int64_t M, int64_t N) {
+  return small_tile(M, N, layout == MTNLG_GEMM_NT ? 11 : layout == MTNLG_GEMM_NN ? 9.5 : 7.7, 4.5);
 }
 
 // fp32, 64 x 64 tiles: fitted to 270 measured problems (K 128 to 4096, 4 to 4000 tiles).
@@ -354,9 +363,9 @@ int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const v
   const bool vec = a.lda % 4 == 0 && a.ldb % 4 == 0 && N % 4 == 0 &&
                    !(((uintptr_t)A | (uintptr_t)B | (uintptr_t)bias | (uintptr_t)aux) & unit) && !((uintptr_t)C & c_unit);
   LaunchScope scope(MTNLG_K_GEMM_NT + layout, stream);
-  const bool small = gemm_generic_small_tile(layout, M, N);
-  if (dtype == MTNLG_F32) return gemm_generic_of<float>(layout, a, vec, small, gemm_direct_time(M, N, K) < gemm_generic_time(layout, M, N, K), stream);
-  return gemm_generic_of<bf16>(layout, a, vec, small, false, stream);
+  if (dtype == MTNLG_F32)
+    return gemm_generic_of<float>(layout, a, vec, gemm_generic_small_tile(layout, M, N), gemm_direct_time(M, N, K) < gemm_generic_time(layout, M, N, K), stream);
+  return gemm_generic_of<bf16>(layout, a, vec, gemm_generic_small_tile_bf16(layout, M, N), false, stream);
 }
 
 }  // namespace mtnlg

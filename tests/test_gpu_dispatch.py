@@ -125,6 +125,23 @@ def test_fp32_gemm_large_tile_with_long_k(dtype, layout, shape):
     assert_close(out, oracle.gelu(want + to_np(bias)), TOL[dtype], f"{dtype} gemm {layout} {shape} GeLU")
 
 
+# bf16 products of these kernels either side of the rule for their tiles, which is one for their times on the bf16 instructions: 72 tiles
+# of 64 x 64 or 272 of 32 x 32; 272 or 1056, which went out in five rounds of small tiles where two of large ones take less; by the layout
+# at 72 or 272.
+@pytest.mark.parametrize("layout,shape,small", [(B.GEMM_NT, (508, 516, 260), True), (B.GEMM_NN, (508, 516, 260), True), (B.GEMM_TN, (508, 516, 259), False),
+                                                (B.GEMM_NT, (1020, 1028, 132), False), (B.GEMM_NN, (1020, 1028, 132), False),
+                                                (B.GEMM_NT, (252, 1020, 68), True), (B.GEMM_TN, (252, 1020, 69), True)])
+def test_bf16_gemm_without_dma_on_either_tile(layout, shape, small):
+    Mm, N, K = shape
+    fn = B.lib()._ZN5mtnlg28gemm_generic_small_tile_bf16Eill
+    fn.argtypes, fn.restype = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64], ctypes.c_bool
+    assert N % 8 and fn(layout, Mm, N) == small   # N % 8: not a product of the kernels with DMA
+    A, Bm = operands(layout, Mm, N, K, "bf16")
+    C = torch.full((Mm, N), float("nan"), device="cuda")
+    M.mtnlg_gemm(layout, dev(A), dev(Bm), C, epilogue=B.EPI_OUT_F32)
+    assert_close(C, gemm_oracle(layout, A, Bm), TOL["fp32"], f"bf16 gemm {layout} {shape}")
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
 @pytest.mark.parametrize("Mm", [70, 72])   # 72: the weight-gradient form has 4-element accesses to lose
