@@ -436,6 +436,8 @@ int mtnlg_gemm(int dtype, int layout, int64_t M, int64_t N, int64_t K, const voi
     return MTNLG_INVALID_ARG;
   if (dtype == MTNLG_F32) epilogue &= ~MTNLG_EPI_OUT_F32;
   hipStream_t st = (hipStream_t)stream;
+  // fp32: the same limit whichever kernel an estimate of time picks
+  if (dtype == MTNLG_F32 && M > GEMM_GENERIC_MAX_ROWS) return MTNLG_UNSUPPORTED_SHAPE;
   if (gemm_wave_takes(dtype, layout, M, N, K, A, B, C, bias, aux)) {
     const double other = gemm_time(dtype, layout, M, N, K, workspace ? workspace_bytes : 0);
     const int tile = gemm_wave_pick(dtype, layout, M, N, K, other);

@@ -326,6 +326,7 @@ inline void attr_mark_set(unsigned long long &done, int device) {
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // internal launchers shared between translation units
+constexpr int64_t GEMM_GENERIC_MAX_ROWS = 65535 * 64;
 int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const void *A,
                  const void *B, void *C, const void *bias, void *aux, uint32_t epi,
                  hipStream_t stream);

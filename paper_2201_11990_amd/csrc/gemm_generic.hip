@@ -356,7 +356,7 @@ int gemm_generic(int dtype, int layout, int64_t M, int64_t N, int64_t K, const v
                  const void *B, void *C, const void *bias, void *aux, uint32_t epi,
                  hipStream_t stream) {
   if (layout < 0 || layout > 2) return MTNLG_INVALID_ARG;
-  if ((M + 63) / 64 > 65535) return MTNLG_UNSUPPORTED_SHAPE;
+  if (M > GEMM_GENERIC_MAX_ROWS) return MTNLG_UNSUPPORTED_SHAPE;
   F32GemmArgs a{M, N, K, layout == MTNLG_GEMM_TN ? M : K, layout == MTNLG_GEMM_NT ? K : N, A, B, C, EpiArgs{bias, aux, epi}, 0, 0};
   const size_t es = dtype == MTNLG_F32 ? 4 : 2;
   const uintptr_t unit = 4 * es - 1, c_unit = (epi & MTNLG_EPI_OUT_F32) ? 15 : unit;

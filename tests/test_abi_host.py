@@ -124,3 +124,12 @@ def test_empty_problems_are_rejected_before_any_gpu_work():
     head = B.head_desc(64, 0, 0, 8, 1, "fp32")
     assert L.mtnlg_lm_head_workspace(ctypes.byref(head)) == 0
     assert L.mtnlg_embedding_fwd(ctypes.byref(head), one, one, one, two, ctypes.cast(None, B.REDUCE_OP_FN), None, None) == -1
+
+
+# fp32 products have one limit of rows, 64 x 65535, whichever kernel their sizes pick: few columns (32 x 32 tiles), many (128 x 128), short sums,
+# and a row length that leaves the kernels without DMA only.
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("N,K", [(32, 260), (256, 260), (2048, 4096), (64, 64), (30, 260)])
+def test_fp32_products_beyond_the_row_limit_are_refused(layout, N, K):
+    one = ctypes.c_void_p(256)   # never dereferenced
+    assert B.lib().mtnlg_gemm(B.F32, layout, 64 * 65536, N, K, one, one, one, None, None, 0, None, 0, None) == -3
