@@ -367,8 +367,9 @@ int mtnlg_adam_step(const mtnlg_adam_desc *desc, int64_t count, float *master, f
  * caller enqueues between two library launches counts for the second.
  * mtnlg_profile_read synchronises those events and returns, per class, the number
  * of launches and their summed duration in milliseconds, then clears the record.
- * A launch that does the work of several classes (small calls: both gradient products
- * of a linear layer and column sums) counts for each product, with its time in the first.
+ * A launch that does both gradient products of a linear layer and column sums (small
+ * calls) counts as a launch of either product's class, with half of its time; the sums
+ * are not counted apart.
  * Event objects are host-side resources created on demand and destroyed by
  * mtnlg_profile_enable(0).  Not thread-safe. */
 enum mtnlg_kernel_class {

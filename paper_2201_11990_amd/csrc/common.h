@@ -299,7 +299,7 @@ struct LaunchScope {
   int cls;
   hipStream_t stream;
   long idx;  // slot in the record list, -1 when timing is off
-  LaunchScope(int cls_, hipStream_t s);
+  LaunchScope(int cls_, hipStream_t s, int also = -1);   // also: a second class that does as much of the launch's work
   ~LaunchScope();
 };
 

@@ -504,14 +504,9 @@ int gemm_wave_group(int dtype, const GemmCall &nn, const GemmCall &tn, const Col
   const GroupArgs a{{nn.M, nn.N, nn.K, nn.K, nn.N, nn.A, nn.B, nn.C, EpiArgs{nullptr, nn.aux, nn.epi}, 0, 0},
                     {tn.M, tn.N, tn.K, tn.M, tn.N, tn.A, tn.B, tn.C, EpiArgs{nullptr, tn.aux, tn.epi}, 0, 0},
                     0, 0, sums, (int)((sums.C + 63) / 64)};
-  int status;
-  {   // timed as the input-gradient product; the others count with no time of their own
-    LaunchScope scope(MTNLG_K_GEMM_NN, stream);
-    if (dtype == MTNLG_F32) status = launch_group<float, 32>(a, stream);
-    else status = tile == 32 ? launch_group<bf16, 32>(a, stream) : launch_group<bf16, 64>(a, stream);
-  }
-  { LaunchScope scope(MTNLG_K_GEMM_TN, stream); }
-  return status;
+  LaunchScope scope(MTNLG_K_GEMM_NN, stream, MTNLG_K_GEMM_TN);   // the two products have the same number of operations
+  if (dtype == MTNLG_F32) return launch_group<float, 32>(a, stream);
+  return tile == 32 ? launch_group<bf16, 32>(a, stream) : launch_group<bf16, 64>(a, stream);
 }
 
 }  // namespace mtnlg

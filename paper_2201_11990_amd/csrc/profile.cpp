@@ -13,7 +13,7 @@
 namespace mtnlg {
 
 struct Record {
-  int cls;
+  int cls, also;   // also: -1, or the class that half of the time is for
   hipEvent_t begin, end;
 };
 
@@ -36,9 +36,9 @@ static hipEvent_t take_event() {
   return e;
 }
 
-LaunchScope::LaunchScope(int cls_, hipStream_t s) : cls(cls_), stream(s), idx(-1) {
+LaunchScope::LaunchScope(int cls_, hipStream_t s, int also) : cls(cls_), stream(s), idx(-1) {
   if (!g_enabled) return;
-  Record r{cls, nullptr, nullptr};
+  Record r{cls, also, nullptr, nullptr};
   if (g_chain_end && g_chain_stream == stream) {
     r.begin = g_chain_end;
   } else {
@@ -99,6 +99,12 @@ extern "C" int mtnlg_profile_read(int32_t *launches, float *ms) {
     if (hipEventSynchronize(r.end) != hipSuccess || hipEventElapsedTime(&t, r.begin, r.end) != hipSuccess) {
       status = MTNLG_HIP_ERROR;
     } else if (r.cls >= 0 && r.cls < MTNLG_K_CLASSES) {
+      const bool shared = r.also >= 0 && r.also < MTNLG_K_CLASSES;
+      if (shared) {
+        t *= 0.5f;
+        launches[r.also] += 1;
+        ms[r.also] += t;
+      }
       launches[r.cls] += 1;
       ms[r.cls] += t;
     }

@@ -290,6 +290,23 @@ def test_profile_counts_every_kernel_class():
     torch.cuda.synchronize()
 
 
+# Both gradient products of a linear layer in one launch: each class gets its share of the time (they have the same operations).
+def test_profile_shares_the_time_of_a_launch_of_two_classes():
+    wl = SMALL_BF16
+    run = LayerRunner(wl, to_dev(make_layer_params(wl, 0)))
+    x, dy = (t.cuda() for t in make_activations(wl))
+    for _ in range(2):   # the first pass sets attributes
+        M.mtnlg_profile_enable(True)
+        try:
+            run.forward(x)
+            run.backward(x, dy)
+            prof = M.mtnlg_profile_read()
+        finally:
+            M.mtnlg_profile_enable(False)
+    assert prof["colsum"][0] == 0   # all of them ride along
+    assert prof["gemm_nn"] == prof["gemm_tn"] and prof["gemm_nn"][0] == 4 and prof["gemm_nn"][1] > 0
+
+
 # ---- first / last stage extras ------------------------------------------------------------------------------
 
 def _head_inputs(dtype, T, h, V, seed):
