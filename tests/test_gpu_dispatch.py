@@ -238,12 +238,13 @@ def gemm_by_waves(tile, layout, a, b, C, epilogue=0, bias=None, aux=None):
               epilogue, tile, torch.cuda.current_stream().cuda_stream) == 0
 
 
-def gemm_without_lds(layout, a, b, C):   # fp32, 64 x 64 tiles, operands straight to registers
+def gemm_without_lds(layout, a, b, C, epilogue=0, bias=None, aux=None):   # fp32, 64 x 64 tiles, operands straight to registers
     fn = B.lib()._ZN5mtnlg12gemm_genericEiilllPKvS1_PvS1_S2_jP12ihipStream_t
     vp, i64 = ctypes.c_void_p, ctypes.c_int64
     fn.argtypes = [ctypes.c_int, ctypes.c_int, i64, i64, i64, vp, vp, vp, vp, vp, ctypes.c_uint32, vp]
+    ptr = lambda t: 0 if t is None else t.data_ptr()
     K = a.shape[0] if layout == B.GEMM_TN else a.shape[1]
-    assert fn(B.F32, layout, C.shape[0], C.shape[1], K, a.data_ptr(), b.data_ptr(), C.data_ptr(), 0, 0, 0,
+    assert fn(B.F32, layout, C.shape[0], C.shape[1], K, ptr(a), ptr(b), ptr(C), ptr(bias), ptr(aux), epilogue,
               torch.cuda.current_stream().cuda_stream) == 0
 
 
@@ -306,13 +307,35 @@ def test_linear_backward_in_one_launch(dtype, tile, T, I, O, sums):
         assert_close(out, to_np(part).sum(0) + (3.0 if accumulate else 0.0), TOL["fp32"] if out_f32 else TOL[dtype], f"sums {dtype} {T} {O}")
 
 
-# fp32 on 128 x 128 tiles: less than a tile and a slab; 1 to 9 slabs through the ring of 4, with K tails; more row tiles than a group of 8,
+# fp32 on 128 x 128 tiles: less than a tile and a slab; 1 to 9 slabs through the ring of 3, with K tails; more row tiles than a group of 8,
 # ragged on every side, where a wave's whole half of the tile lies outside.
 @pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
 @pytest.mark.parametrize("Mm,N,K", [(4, 4, 4), (128, 128, 32), (60, 260, 64), (132, 72, 100), (256, 128, 128), (200, 196, 156), (128, 256, 168),
                                     (1100, 136, 200), (136, 1036, 256), (192, 64, 288)])
 def test_fp32_gemm_on_128_tiles(layout, Mm, N, K):
     check_fp32_gemm(layout, Mm, N, K - 3 if layout == B.GEMM_TN else K, gemm_in_parts, "128 x 128")
+
+
+# fp32 on the 64 x 64 tiles without LDS in bf16 parts (sums of more than 256): less than a tile; one chunk of 32 for some of the four waves, and
+# several with a tail; widths that are no multiple of 4 (scalar accesses).
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("Mm,N,K", [(4, 4, 260), (60, 72, 264), (132, 196, 612), (66, 130, 301)])
+def test_fp32_gemm_without_lds(layout, Mm, N, K):
+    check_fp32_gemm(layout, Mm, N, K - 3 if layout == B.GEMM_TN else K, gemm_without_lds, "without LDS")
+
+
+# Pointers aligned to 4 bytes only, which the kernels with DMA take: every operand and result 4 bytes past an allocation.
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("route", [32, 64, 128])
+def test_gemm_with_pointers_aligned_to_four_bytes(route, layout):
+    Mm, N, K = 72, 136, 104
+    for dtype in ("fp32", "bf16") if route < 128 else ("fp32",):
+        by = 1 if dtype == "fp32" else 2
+        gemm = gemm_in_parts if route == 128 else lambda *a, **k: gemm_by_waves(route, *a, **k)
+        A, Bm = operands(layout, Mm, N, K, dtype)
+        bias, aux, C = randn((N,), dtype, 7), randn((Mm, N), dtype, 8), shifted(torch.zeros((Mm, N), dtype=DT[dtype]), by)
+        gemm(layout, shifted(A, by), shifted(Bm, by), C, bias=shifted(bias, by), aux=shifted(aux, by), epilogue=B.EPI_BIAS | B.EPI_RESIDUAL)
+        assert_close(C, gemm_oracle(layout, A, Bm) + to_np(bias) + to_np(aux), TOL[dtype], f"{dtype} {route} {layout} aligned to 4 bytes")
 
 
 def check_fp32_gemm(layout, Mm, N, K, gemm, what):
@@ -446,6 +469,36 @@ def test_attention_by_rows_of_a_workgroup(dtype, b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
 
 
+def attention_fwd_without_lds(b, s, n, d, scale, qkv, a, lse):
+    fn = B.lib()._ZN5mtnlg17attention_fwd_f32EiiiiifPKvPvPfP12ihipStream_t
+    fn.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float] + [ctypes.c_void_p] * 4
+    assert fn(B.F32 if qkv.dtype == torch.float32 else B.BF16, b, s, n, d, scale, qkv.data_ptr(), a.data_ptr(), lse.data_ptr(),
+              torch.cuda.current_stream().cuda_stream) == 0
+
+
+def attention_bwd_without_lds(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws):
+    fn = B.lib()._ZN5mtnlg17attention_bwd_f32EiiiiifPKvS1_PKfS1_PvS4_P12ihipStream_t
+    fn.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float] + [ctypes.c_void_p] * 7
+    assert fn(B.F32 if qkv.dtype == torch.float32 else B.BF16, b, s, n, d, scale, qkv.data_ptr(), a.data_ptr(), lse.data_ptr(),
+              da.data_ptr(), dqkv.data_ptr(), ws.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+
+
+# bf16 with 64 rows to a workgroup and no LDS, at every compiled head size: what calls take whose sequences the DMA's 32-bit offsets do not reach.
+@pytest.mark.parametrize("d", [24, 64, 72, 96, 104, 136, 160, 184])
+def test_bf16_attention_without_lds(d):
+    b, s, n = 3, 100, 25
+    qkv, da = randn((b * s, 3 * n * d), "bf16", 21), randn((b * s, n * d), "bf16", 22)
+    dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
+    a, dqkv = torch.full_like(da, float("nan"), device="cuda"), torch.full_like(qkv, float("nan"), device="cuda")
+    lse = torch.full((b, n, s), float("nan"), device="cuda")
+    ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+    x, g = dev(qkv), dev(da)
+    attention_fwd_without_lds(b, s, n, d, 1.0 / math.sqrt(d), x, a, lse)
+    attention_bwd_without_lds(b, s, n, d, 1.0 / math.sqrt(d), x, a, lse, g, dqkv, ws)
+    assert_close(a, oracle.attention_fwd(dims, to_np(qkv)), TOL["bf16"], "attention out")
+    assert_close(dqkv, oracle.attention_bwd(dims, to_np(qkv), to_np(da)), TOL["bf16"], "attention dqkv")
+
+
 # bf16, P and dS in fp32, streamed side through LDS: the edges of its rule (513 groups of 16 rows, s 33; s 193 / 257 with fewer), of
 # the 64 rows of a block and of the head sizes that a tile of 32 k columns holds.
 @pytest.mark.parametrize("b,s,n,d", [(3, 33, 58, 8), (2, 64, 65, 32), (1, 65, 104, 40), (1, 129, 58, 88), (2, 127, 33, 96), (1, 191, 43, 104),
@@ -527,9 +580,22 @@ def test_attention_backward_in_one_launch_without_lds(dtype, b, s, n, d):
 # block, and the last token, whose block hangs over the end of the sequence.
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 @pytest.mark.parametrize("t0", [0, 32, 37, 63, 89])
-@pytest.mark.parametrize("dtype,n,d", [("fp32", 2, 24), ("fp32", 2, 64), ("fp32", 2, 96), ("bf16", 2, 40), ("bf16", 2, 96),
-                                       ("fp32", 44, 24), ("fp32", 44, 96), ("bf16", 44, 96)])   # 44 heads: 64 rows to a workgroup, else 16
+# 2 heads: 16 rows to a workgroup (head size 224: the backward kernels in two launches); 44 heads: 64 rows, and bf16 up to head size 192
+# through LDS, in tiles of as many columns, of an even number of 32, and with columns past the head size.
+@pytest.mark.parametrize("dtype,n,d", [("fp32", 2, 24), ("fp32", 2, 64), ("fp32", 2, 96), ("fp32", 2, 224), ("bf16", 2, 40), ("bf16", 2, 96),
+                                       ("fp32", 44, 24), ("fp32", 44, 96), ("bf16", 44, 96), ("bf16", 44, 40), ("bf16", 44, 184), ("bf16", 44, 200)])
 def test_attention_non_finite_token_stays_where_it_belongs(dtype, n, d, t0, bad):
+    check_non_finite_token(dtype, n, d, t0, bad, M.mtnlg_attention_fwd, M.mtnlg_attention_bwd)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("t0", [0, 37, 63, 89])
+@pytest.mark.parametrize("d", [40, 96])   # bf16, 64 rows to a workgroup without LDS
+def test_attention_without_lds_non_finite_token_stays_where_it_belongs(d, t0, bad):
+    check_non_finite_token("bf16", 44, d, t0, bad, attention_fwd_without_lds, attention_bwd_without_lds)
+
+
+def check_non_finite_token(dtype, n, d, t0, bad, attention_fwd, attention_bwd):
     b, s, col = 2, 90, 5
     dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
     qkv, da = randn((b, s, n, 3, d), dtype, 51), randn((b, s, n, d), dtype, 52)
@@ -539,8 +605,9 @@ def test_attention_non_finite_token_stays_where_it_belongs(dtype, n, d, t0, bad)
         a, dx = torch.full_like(g, 7.0, device="cuda").reshape(b * s, -1), torch.full_like(x, 7.0, device="cuda").reshape(b * s, -1)
         lse = torch.full((b, n, s), 7.0, device="cuda")
         ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
-        M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), flat(x), a, lse)
-        M.mtnlg_attention_bwd(b, s, n, d, 1.0 / math.sqrt(d), flat(x), a, lse, flat(g), dx, ws)
+        fx, fg = flat(x), flat(g)
+        attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), fx, a, lse)
+        attention_bwd(b, s, n, d, 1.0 / math.sqrt(d), fx, a, lse, fg, dx, ws)
         return a.reshape(b, s, n, d), lse, dx.reshape(b, s, n, 3, d)
 
     want_a = oracle.attention_fwd(dims, to_np(qkv).reshape(b * s, -1)).reshape(b, s, n, d)
@@ -598,10 +665,10 @@ def test_attention_batches_of_several_grid_rows():
         assert torch.equal(whole, torch.cat([first, second]))
 
 
-# Many heads: the backward kernels with two blocks of a head to a workgroup (all but the last case; an even and an odd number of
-# blocks), every kernel with the heads in several grid rows, the last one shorter and no multiple of 8 (forward: the last three;
-# backward: all but the first two).
-@pytest.mark.parametrize("b,s,n,d", [(5, 192, 20, 128), (12, 100, 25, 64), (12, 130, 25, 128), (12, 130, 25, 160), (24, 128, 25, 64),
+# Many heads: the backward kernels with two blocks of a head to a workgroup (all but the second case, which goes out in one launch, and the
+# last; an even and an odd number of blocks), every kernel with the heads in several grid rows, the last one shorter and no multiple of 8
+# (forward: the last three; backward: all but the first three).
+@pytest.mark.parametrize("b,s,n,d", [(5, 192, 20, 128), (12, 100, 25, 64), (16, 100, 25, 64), (12, 130, 25, 128), (12, 130, 25, 160), (24, 128, 25, 64),
                                      (12, 260, 25, 128), (12, 260, 25, 160), (20, 449, 13, 64)])
 def test_attention_of_many_heads(b, s, n, d):
     qkv, da = randn((b * s, 3 * n * d), "bf16", 21), randn((b * s, n * d), "bf16", 22)
