@@ -1134,13 +1134,13 @@ struct BackwardCost {
 // Two blocks of a head in each workgroup?  At head size 128 and 160, where one workgroup at a time runs on a compute unit, whichever
 // the estimate says; its constants were fitted to 207 and 201 measured sizes (8 to 1024 heads, s 80 to 4096, both kernels), for
 // which the choice costs 0.4 % on average against the better of the two (10 % at most: 160, 96 heads, s = 384).  At head size 64, with three workgroups on a compute unit to
-// cover each other, only for sequences of two blocks that are more than one a unit: 512 heads, s = 80 26.0 us by halves, 23.3 paired;
-// 192, s = 128 17.0, 14.9; but 300, s = 192 31.2, 36.7 and 64, s = 128 11.3 against 13.3.
+// cover each other, only for sequences of two blocks, of which those that come here have more than 384 heads (bwd_one_launch takes the others):
+// 512 heads, s = 80 26.0 us by halves, 23.3 paired; but 300, s = 192 31.2, 36.7.
 template <int D>
 bool bwd_paired(int b, int s, int n) {
   const int64_t heads = (int64_t)b * n;
   const int nb = row_blocks(s);
-  if (D < 128) return nb == 2 && heads > 128;
+  if (D < 128) return nb == 2;
   constexpr BackwardCost halves = D == 128 ? BackwardCost{1.95, 12.0, 0.5} : BackwardCost{2.1, 14.5, 0.63};
   constexpr BackwardCost pairs = D == 128 ? BackwardCost{2.6, 13.0, 0.75} : BackwardCost{3.2, 16.5, 0.67};
   return pairs.time(heads, nb, (nb + 1) / 2) < halves.time(heads, nb, nb);
@@ -1172,7 +1172,9 @@ int bwd_launch_one(int b, int s, int n, float scale, const void *qkv, const void
 // D for every tile costs less than that and the launch.  us, two launches / one: 1 x 256 x 2 heads of 160 21.9 / 13.7, 2 x 300 x 2 of 128
 // 20.8 / 13.4, 2 x 257 of 64 13.3 / 8.7; by blocks of all heads together (s 192 to 1024): up to 128 1.5 times as fast, 256 1.1 to 1.3; 384 1.0 to
 // 1.05 and 512 0.85 to 0.93 at head sizes 128 and 160, where one workgroup runs on a unit; at 64, where three do, 512 1.16 to 1.19, 768 1.11,
-// 1024 0.96.
+// 1024 0.96 (two blocks of 70 to 128 rows: 256 1.22 to 1.35, 384 0.92 to 1.10, 512 0.92 to 1.01, 768 1.13 to 1.20).  At 64 beyond s 960 D takes
+// the LDS of the third workgroup: up to 256 blocks 1.19 to 1.44 times as fast from s 1030 to 4096, 384 1.11 to
+// 1.33, 512 0.92 to 1.17, 768 0.94 to 1.06.
 template <int D>
 bool bwd_one_launch(int b, int s, int n) {
   return s <= ONE_LAUNCH_ROWS && (int64_t)b * n * row_blocks(s) <= (D >= 128 || s > 1024 ? 256 : 768);
