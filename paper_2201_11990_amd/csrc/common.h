@@ -205,16 +205,17 @@ __device__ __forceinline__ void epilogue_store(const EpiArgs &ea, void *C, int64
   }
 }
 
-template <typename E> __device__ __forceinline__ float gelu_of(float z, bool erf_form) {
-  if constexpr (sizeof(E) == 2) { if (!erf_form) return gelu_tanh_fast_f(z); }
+template <bool FAST> __device__ __forceinline__ float gelu_of(float z, bool erf_form) {
+  if constexpr (FAST) { if (!erf_form) return gelu_tanh_fast_f(z); }
   return gelu_f(z, erf_form);
 }
-template <typename E> __device__ __forceinline__ float gelu_grad_of(float z, bool erf_form) {
-  if constexpr (sizeof(E) == 2) { if (!erf_form) return gelu_tanh_grad_fast_f(z); }
+template <bool FAST> __device__ __forceinline__ float gelu_grad_of(float z, bool erf_form) {
+  if constexpr (FAST) { if (!erf_form) return gelu_tanh_grad_fast_f(z); }
   return gelu_grad_f(z, erf_form);
 }
-// 4 consecutive outputs of row m at column n (n + 3 < N and everything aligned for 4-element accesses)
-template <typename E>
+// 4 consecutive outputs of row m at column n (n + 3 < N and everything aligned for 4-element accesses).  FAST: the forms of the streaming
+// bf16 kernels, for problems that those take too; they do not reach the limits for |z| of 10^13 and above, which the library's tanhf does.
+template <typename E, bool FAST = sizeof(E) == 2>
 __device__ __forceinline__ void epilogue4(const EpiArgs &ea, void *C, int64_t N, int64_t m, int64_t n, f32x4 v) {
   const int64_t off = m * N + n;
   if (ea.flags & MTNLG_EPI_BIAS) v += load4(static_cast<const E *>(ea.bias) + n);
@@ -225,7 +226,7 @@ __device__ __forceinline__ void epilogue4(const EpiArgs &ea, void *C, int64_t N,
   if (ea.flags & MTNLG_EPI_GELU) {
     put(static_cast<E *>(ea.aux) + off, v);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = gelu_of<E>(v[e], (ea.flags & MTNLG_EPI_GELU_ERF) != 0);
+    for (int e = 0; e < 4; ++e) v[e] = gelu_of<FAST>(v[e], (ea.flags & MTNLG_EPI_GELU_ERF) != 0);
   }
   if (ea.flags & (MTNLG_EPI_RESIDUAL | MTNLG_EPI_GELU_GRAD)) {
     const f32x4 t = load4(static_cast<const E *>(ea.aux) + off);
@@ -233,7 +234,7 @@ __device__ __forceinline__ void epilogue4(const EpiArgs &ea, void *C, int64_t N,
       v += t;
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_of<E>(t[e], (ea.flags & MTNLG_EPI_GELU_ERF) != 0);
+      for (int e = 0; e < 4; ++e) v[e] *= gelu_grad_of<FAST>(t[e], (ea.flags & MTNLG_EPI_GELU_ERF) != 0);
     }
   }
   if (ea.flags & MTNLG_EPI_OUT_F32) {

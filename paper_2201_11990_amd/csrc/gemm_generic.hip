@@ -259,7 +259,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, DIRECT && TMB == 2 ? 8 : 2) v
     const int64_t n = n0 + (BT ? 4 * TNB * g + 4 * v : 16 * v + 4 * g);
     if (m >= a.M) return;
     if constexpr (VEC) {
-      if (n < a.N) epilogue4<E>(a.ea, a.C, a.N, m, n, x);
+      if (n < a.N) epilogue4<E, false>(a.ea, a.C, a.N, m, n, x);
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)

@@ -125,6 +125,23 @@ def test_fp32_gemm_large_tile_with_long_k(dtype, layout, shape):
     assert_close(out, oracle.gelu(want + to_np(bias)), TOL[dtype], f"{dtype} gemm {layout} {shape} GeLU")
 
 
+# The limits of GeLU and GeLU' on these kernels, whose epilogues are the same for aligned rows and for others: z or 0, and 1 or 0.
+@pytest.mark.parametrize("layout", [B.GEMM_NT, B.GEMM_NN, B.GEMM_TN])
+@pytest.mark.parametrize("N", [68, 70])
+def test_bf16_gemm_without_dma_at_the_limits_of_gelu(layout, N):
+    Mm, K = 36, 44
+    A, Bm = operands(layout, Mm, N, K, "bf16")
+    acc = gemm_oracle(layout, A, Bm)
+    z = torch.tensor([1e14, -1e14, 1e18, -1e18])[torch.arange(N) % 4].to(torch.bfloat16)
+    aux, C = (torch.full((Mm, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    M.mtnlg_gemm(layout, dev(A), dev(Bm), C, bias=dev(z), aux=aux, epilogue=B.EPI_BIAS | B.EPI_GELU)
+    rows = z.expand(Mm, N)
+    assert torch.equal(aux.cpu(), rows) and torch.equal(C.cpu(), rows.clamp(min=0.0))
+    out = torch.full((Mm, N), float("nan"), device="cuda")
+    M.mtnlg_gemm(layout, dev(A), dev(Bm), out, aux=dev(rows.contiguous()), epilogue=B.EPI_GELU_GRAD | B.EPI_OUT_F32)
+    assert_close(out, acc * (to_np(rows) > 0), TOL["fp32"], f"bf16 gemm {layout} {N} GeLU' at its limits")
+
+
 # bf16 products of these kernels either side of the rule for their tiles, which is one for their times on the bf16 instructions: 72 tiles
 # of 64 x 64 or 272 of 32 x 32; 272 or 1056, which went out in five rounds of small tiles where two of large ones take less; by the layout
 # at 72 or 272.
