@@ -53,35 +53,18 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 // 2^x on the transcendental unit (v_exp_f32): no denormal fix-up, 2^-inf = 0.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-// s becomes e^(s f - shift).  EXACT: f is the scale, whose rounding after a multiplication by log2 e would move every exponent the same
-// way; else f and shift have the factor log2 e.  EXACT weights below 2^-126, which the instruction takes for 0, keep the digits that fp32 has
-// for them: four more vector instructions an element, for the lanes of a tile that have such a weight or a masked one (2 x 1024 x 16 heads of
-// 96: 81.4 us without, 83.8 so, 86.1 with them in every tile).
+// e^x down to the least weight that fp32 has.  The instruction takes results below 2^-126 for 0, so it is given half the exponent: one
+// multiplication more (2 x 1024 x 16 heads of 96, forward and backward: 81.4 us without, 82.1 so; 83.8 with a branch for such weights).
 __device__ __forceinline__ float exact_exp(float x) {
-  const bool low = x < -80.0f;
-  return fast_exp2(fmaf(x, kLog2e, low ? 64.0f : 0.0f)) * (low ? 0x1p-64f : 1.0f);
+  const float half = fast_exp2(x * (0.5f * kLog2e));
+  return half * half;
 }
-template <bool EXACT, int N, typename Shift>
-__device__ __forceinline__ void to_weights(f32x4 (&s)[N], float f, Shift &&shift) {
-  float lowest = 0.0f;
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      s[i][e] = fmaf(s[i][e], f, -shift(i, e));
-      if constexpr (EXACT) lowest = fminf(lowest, s[i][e]);
-    }
-  if (EXACT && lowest < -80.0f) {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[i][e] = exact_exp(s[i][e]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[i][e] = fast_exp2(EXACT ? s[i][e] * kLog2e : s[i][e]);
-  }
+// e^(s f - shift).  EXACT: f is the scale, whose rounding after a multiplication by log2 e would move every exponent the same way; else
+// f and shift have the factor log2 e.
+template <bool EXACT>
+__device__ __forceinline__ float weight(float s, float f, float shift) {
+  const float x = fmaf(s, f, -shift);
+  return EXACT ? exact_exp(x) : fast_exp2(x);
 }
 // m + log(l), rounded about once: the reference maximum may lie up to 2^8 below the largest weight, and log(l) of such a sum is large
 // enough for its own rounding to show (2048 keys, 4 heads of 96: log-sum-exp 3.4e-7 off, rms, with m + logf(l), 1.8e-7 so; 3.0e-7 with a maximum that always follows).
@@ -519,11 +502,14 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int 
         const float m_new = mx * c > m[qg] * c + 8.0f ? mx : m[qg];
         const float mc = EXACT ? product_of(m_new, scale) : m_new * c;
         float rs = 0.0f;
-        to_weights<EXACT>(sc[qg], f, [&](int, int) { return mc; });
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) rs += sc[qg][kb][e];
+          for (int e = 0; e < 4; ++e) {
+            const float p = weight<EXACT>(sc[qg][kb][e], f, mc);
+            sc[qg][kb][e] = p;
+            rs += p;
+          }
         alpha[qg] = EXACT ? exact_exp((m[qg] - m_new) * scale) : fast_exp2((m[qg] - m_new) * c);
         l[qg] = l[qg] * alpha[qg] + rs;
         m[qg] = m_new;
@@ -755,11 +741,10 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int 
           for (int e = 0; e < 4; ++e)
             if (kv0 + 16 * kb + 4 * g + e > qc) sc[kb][e] = -INFINITY;
       }
-      to_weights<EXACT>(sc, f, [&](int, int) { return lsf; });
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sc[kb][e] *= EXACT ? pc[kb][e] - dsum : pc[kb][e];
+        for (int e = 0; e < 4; ++e) sc[kb][e] = weight<EXACT>(sc[kb][e], f, lsf) * (EXACT ? pc[kb][e] - dsum : pc[kb][e]);
       Parts<EXACT ? 3 : 1> df[NS];
 #pragma unroll
       for (int ks = 0; ks < NS; ++ks) df[ks] = weights<EXACT>(sc[2 * ks], sc[2 * ks + 1]);
@@ -971,17 +956,16 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
             if (qq < key || qq >= s) sc[qb][e] = -INFINITY;
           }
       }
-      f32x4 ls[NB];
 #pragma unroll
       for (int qb = 0; qb < NB; ++qb) {
-        ls[qb] = *reinterpret_cast<const f32x4 *>(stat + 16 * qb + 4 * g);
+        const f32x4 ls = *reinterpret_cast<const f32x4 *>(stat + 16 * qb + 4 * g);
         if constexpr (EXACT) pc[qb] -= *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sc[qb][e] = weight<EXACT>(sc[qb][e], f, EXACT ? ls[e] : ls[e] * kLog2e);
+          pc[qb][e] *= sc[qb][e];
+        }
       }
-      to_weights<EXACT>(sc, f, [&](int qb, int e) { return EXACT ? ls[qb][e] : ls[qb][e] * kLog2e; });
-#pragma unroll
-      for (int qb = 0; qb < NB; ++qb)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) pc[qb][e] *= sc[qb][e];
       Parts<EXACT ? 3 : 1> pf[NS], df[NS];
 #pragma unroll
       for (int ks = 0; ks < NS; ++ks) {
