@@ -4,10 +4,10 @@
 //
 // Longer sums of fp32 values: they are cut into three bf16 parts that add up to them exactly, and the six largest of the nine products of parts run
 // on v_mfma_f32_16x16x32_bf16 (common.h: Parts): sums in fp32, an error below that of the fp32 instructions (1024 x 1024 x 4096 against
-// 64 bits: 5.7e-7 with those, 2.2e-7 so).  What bounds it: per 64 x 64 wave tile and 32 k 96 MFMAs (1600 cycles) and 250 vector
-// instructions for the parts (1100 cycles), which the two waves of a SIMD overlap little, and the 16 KB of operands that come
-// from L2 for them (9 TB/s over the chip).  On v_mfma_f32_16x16x4_f32 before: 1024 x 4096 x 1024 109 / 96 / 91 us (NT / NN / TN), now 76 / 64 /
-// 63; 2048^3 199 / 174 / 157, now 139 / 117 / 114.
+// 64 bits: 5.7e-7 with those, 2.2e-7 so).  What bounds it: per 64 x 64 wave tile and 32 k 96 MFMAs (1600 cycles) and 310 vector
+// instructions for the parts (1300 cycles), which the two waves of a SIMD overlap little, and the 16 KB of operands that come
+// from L2 for them (9 TB/s over the chip).  On v_mfma_f32_16x16x4_f32 before: 1024 x 4096 x 1024 109 / 96 / 91 us (NT / NN / TN), now 71 / 61 /
+// 58; 2048^3 199 / 174 / 157, now 129 / 112 / 110.
 // The K axis of a workgroup's tile is split over its waves (WGK); their partial tiles are added through LDS in a fixed
 // order, so a small M x N still fills the chip and a long K is a short chain.
 //   Chunk of 32 k: lane l = 16 g + r supplies k = 16 h + 4 g + e as element 4 h + e of its operand (the k order inside a chunk is

@@ -3,8 +3,8 @@
 // Eight waves of 64 x 32, slabs of 32 k.  Every value is cut into parts once a workgroup: a wave loads two of the tile's sixteen 16-row
 // blocks into registers, two slabs ahead, cuts them (72 vector instructions a slab) and writes the fragments to LDS as the matrix
 // instructions read them, lane by lane (a ring of three stages of 48 KB, one barrier a slab).  us,
-// operands straight to registers (gemm_generic.hip) / K split over waves (gemm_wave.hip) / here: 1024 x 4096 x 1024 NT 77 / 69 / 53, NN 62 / 73 / 55,
-// TN 59 / 89 / 50; 2048 x 2048 x 4096 NT 263 / 195 / 183.  Those two cut a value once a wave, two to eight times a workgroup, and with the
+// operands straight to registers (gemm_generic.hip) / K split over waves (gemm_wave.hip) / here: 1024 x 4096 x 1024 NT 71 / 65 / 51, NN 61 / 68 / 52,
+// TN 58 / 65 / 50; 2048 x 2048 x 4096 NT 242 / 208 / 179.  Those two cut a value once a wave, two to eight times a workgroup, and with the
 // operands in LDS as fp32 values and the cutting behind the reads the same tiles took 66 us at 1024 x 4096 x 1024 NT; leaving the cutting out
 // altogether, 45.  What bounds it now: the MFMAs (0.97 to 1.2 PFLOP/s of products of parts), then LDS: 147 KB read and 48 KB written a slab.
 #include "common.h"

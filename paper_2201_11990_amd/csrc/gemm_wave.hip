@@ -427,13 +427,13 @@ bool gemm_wave_takes(int dtype, int layout, int64_t M, int64_t N, int64_t K, con
   return reach_a < (int64_t)RECORDS - 256 && reach_b < (int64_t)RECORDS - 256;
 }
 
-// Estimated microseconds, fitted to 150 bf16 problems (graph replays, weights not in the caches) and 270 fp32 ones (for which the choice
-// between all four kernels costs 0.6 % on average against the best, 19 % at most).  A workgroup's chain is launch, K / 8 and merge; beyond
+// Estimated microseconds, fitted to 150 bf16 problems (graph replays, weights not in the caches) and 270 fp32 ones (the choice between all
+// four kernels then cost 0.6 % on average against the best, 19 % at most; 600 others since: 1.4 %, 28 % at most, 768 x 3072 x 2048).  A workgroup's chain is launch, K / 8 and merge; beyond
 // 256 workgroups the tiles queue for the L2's bandwidth (bf16) or the matrix and vector pipes (fp32, whose cutting into parts adds to the
 // MFMAs).  Measured us, bf16, streaming kernel / 32 / 64: 256 x 512 x 1024 10.6 / 4.5 / 7.0; 512 x 512 x 4096 32 / 8.6 / 15.6;
 // 1024 x 1024 x 4096 38 / 24 / 16.5; 1024 x 2048 x 2048 21 / 38 / 20; 2048 x 2048 x 64 5.5 / 16 / 13.
-// fp32, operands straight to registers / 32 / 64 / 128 (gemm_parts.hip): 128 x 960 x 512 8.0 / 6.1 / 14 / 27; 1024 x 1024 x 4096 82 / 73 / 53 /
-// 169; 1024 x 4096 x 1024 77 / 70 / 69 / 53, TN 59 / 69 / 89 / 50; 2048 x 2048 x 4096 263 / 243 / 195 / 183; 1600 x 2048 x 3000 154 / 161 / 154 / 122.
+// fp32, operands straight to registers / 32 / 64 / 128 (gemm_parts.hip): 128 x 960 x 512 13 / 5.6 / 11 / 26; 1024 x 1024 x 4096 69 / 71 / 60 /
+// 160; 1024 x 4096 x 1024 71 / 72 / 65 / 51, TN 58 / 71 / 65 / 50; 2048 x 2048 x 4096 242 / 268 / 208 / 179; 1600 x 2048 x 3000 147 / 169 / 152 / 120.
 static void wave_times(int dtype, int layout, int64_t M, int64_t N, int64_t K, double &us32, double &us64) {
   const double k = (double)K;
   const double t32 = Work(32, M, N, 0).rounds, t64 = Work(64, M, N, 0).rounds;
@@ -441,7 +441,7 @@ static void wave_times(int dtype, int layout, int64_t M, int64_t N, int64_t K, d
   if (dtype == MTNLG_F32) {
     const double halves = t32 > 1 ? ceil(2 * t32) / 2 : 1;   // rounds of two workgroups on a compute unit
     us32 = 4.05 + halves * 0.0037 * k + (halves - 1) * 1.16 + 0.00028 * k;
-    us64 = r64 * (7.0 + 0.0116 * k) * (layout == MTNLG_GEMM_TN ? 1.17 : 1.0);
+    us64 = r64 * (7.0 + 0.0116 * k);   // (TN took 1.17 times as long while it spilled)
   } else {
     us32 = 2.7 + r32 * k * (layout == MTNLG_GEMM_NT ? 0.0014 : layout == MTNLG_GEMM_NN ? 0.0019 : 0.0023) + (r32 - 1) * 0.85;
     us64 = 1.0 + r64 * (3.2 + k * (layout == MTNLG_GEMM_TN ? 0.0034 : 0.0028));
