@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void add_positions_kernel(int64_t h, int seq, 
 }
 
 // dE[v] = sum over tokens t (in order) with tokens[t] == vocab_start + v of dx[t].
-// Workgroup i of c = columns / 2048: the vocabulary rows i / c + k 2^stride_log2, k < EB_ROWS, and columns 2048 (i % c) .. + 2047 (8 per thread).
+// Workgroup (x, y, z): the vocabulary rows v0 + k 2^stride_log2, k < EB_ROWS, v0 = y + z gridDim.y, and columns 2048 x .. + 2047 (8 per thread).
 // The token ids are searched 64 at a time by a wave: one ballot gives the tokens of any of the workgroup's rows as a bit
 // mask in LDS, a byte per token says which row.  The matching rows of dx are then fetched in token order, eight loads in flight
 // whatever rows they belong to, and each is added to its row.  Fixed order, no atomics.  A workgroup's rows lie far apart
@@ -91,9 +91,8 @@ __global__ __launch_bounds__(256) void embedding_bwd_kernel(int64_t T, int64_t h
   __shared__ unsigned long long mask[EB_GROUPS];
   __shared__ unsigned char row_of[64 * EB_GROUPS];   // of the tokens in the masks
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const unsigned chunks = (unsigned)((h + 2047) / 2048);
-  const int v0 = blockIdx.x / chunks;
-  const int64_t c = (int64_t)(blockIdx.x % chunks) * 2048 + threadIdx.x * 8;
+  const int v0 = (int)(blockIdx.y + blockIdx.z * gridDim.y);
+  const int64_t c = (int64_t)blockIdx.x * 2048 + threadIdx.x * 8;
   float acc[EB_ROWS][8];
 #pragma unroll
   for (int r = 0; r < EB_ROWS; ++r)
@@ -295,6 +294,17 @@ int call_hook(mtnlg_reduce_op_fn reduce, void *user, void *buf, size_t count, in
 
 }  // namespace
 
+// Workgroups of the embedding's gradient: chunks of columns, groups of vocabulary rows (2^stride_log2 of them) in one dimension or, as
+// that one ends at 65535, two.
+void embedding_bwd_grid(int64_t vocab, int64_t h, int *stride_log2, uint32_t (*grid)[3]) {
+  *stride_log2 = 0;   // the least power of two that lets EB_ROWS strided rows per workgroup cover the vocabulary
+  while (((int64_t)EB_ROWS << *stride_log2) < vocab) ++*stride_log2;
+  const int y = *stride_log2 < 15 ? *stride_log2 : 15;
+  (*grid)[0] = (uint32_t)((h + 2047) / 2048);
+  (*grid)[1] = 1u << y;
+  (*grid)[2] = 1u << (*stride_log2 - y);
+}
+
 }  // namespace mtnlg
 
 using namespace mtnlg;
@@ -340,11 +350,10 @@ int mtnlg_embedding_bwd(const mtnlg_head_desc *desc, const int32_t *tokens, cons
   if (desc->vocab_local > 65535 * 32) return MTNLG_UNSUPPORTED_SHAPE;
   const int64_t T = (int64_t)desc->micro_batch * desc->seq, h = desc->hidden;
   hipStream_t st = (hipStream_t)stream;
-  int stride_log2 = 0;   // the least power of two that lets EB_ROWS strided rows per workgroup cover the vocabulary
-  while (((int64_t)EB_ROWS << stride_log2) < desc->vocab_local) ++stride_log2;
-  const int64_t blocks = ((int64_t)1 << stride_log2) * ((h + 2047) / 2048);
-  if (blocks > 0x7FFFFFFF) return MTNLG_UNSUPPORTED_SHAPE;
-  const dim3 grid((unsigned)blocks);
+  int stride_log2;
+  uint32_t g[3];
+  embedding_bwd_grid(desc->vocab_local, h, &stride_log2, &g);
+  const dim3 grid(g[0], g[1], g[2]);
   LaunchScope scope(MTNLG_K_ELEMENTWISE, st);
   if (desc->dtype == MTNLG_BF16) {
     embedding_bwd_kernel<bf16><<<grid, 256, 0, st>>>(T, h, desc->vocab_local, desc->vocab_start, stride_log2, tokens,

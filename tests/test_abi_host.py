@@ -133,3 +133,17 @@ def test_empty_problems_are_rejected_before_any_gpu_work():
 def test_fp32_products_beyond_the_row_limit_are_refused(layout, N, K):
     one = ctypes.c_void_p(256)   # never dereferenced
     assert B.lib().mtnlg_gemm(B.F32, layout, 64 * 65536, N, K, one, one, one, None, None, 0, None, 0, None) == -3
+
+
+# The embedding's gradient goes out for any vocabulary and width that its entry point takes: every dimension of the grid within what a launch can
+# have (2^32 threads along x, 65535 workgroups along y and z), and a workgroup for every row and column.
+@pytest.mark.parametrize("vocab", [1, 8, 9, 6400, 262144, 262145, 1048577, 65535 * 32])
+@pytest.mark.parametrize("h", [8, 2048, 2056, 20480, 131080, 2 ** 31 - 8])
+def test_embedding_gradient_grid(vocab, h):
+    fn = B.lib()._ZN5mtnlg18embedding_bwd_gridEllPiPA3_j
+    fn.argtypes, fn.restype = [ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p], None
+    log2, grid = ctypes.c_int(), (ctypes.c_uint32 * 3)()
+    fn(vocab, h, ctypes.byref(log2), ctypes.byref(grid))
+    assert grid[0] * 256 < 2 ** 32 and 1 <= grid[1] <= 65535 and 1 <= grid[2] <= 65535
+    assert grid[0] * 2048 >= h > (grid[0] - 1) * 2048 and grid[1] * grid[2] == 1 << log2.value
+    assert 8 << log2.value >= vocab and (log2.value == 0 or 8 << (log2.value - 1) < vocab)
