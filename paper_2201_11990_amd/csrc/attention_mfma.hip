@@ -31,7 +31,7 @@
 // EXACT: any head size d that is a multiple of 8, in tiles of D = d rounded up to 32 columns (the DMA brings zeros past d).  P and dS are
 // not rounded to bf16: each goes into the second product as three bf16 parts that add up to it (common.h: Parts; scaled, so of any size), three MFMAs
 // where the other kernels have one; 17 against 9 a tile in all, but the chain between barriers stays the bound.  2 x 1024 tokens, 16 heads of
-// 96, forward / backward: 103 / 327 us on the fp32 instructions without LDS (attention_f32.hip), 22 / 61 here.  Inputs that are not finite
+// 96, forward / backward: 103 / 327 us on the fp32 instructions without LDS (attention_f32.hip), 24 / 61 here.  Inputs that are not finite
 // take the slow path of attention_redo.h.
 #include <math.h>
 
@@ -66,7 +66,7 @@ __device__ __forceinline__ float weight(float s, float f, float shift) {
   const float x = fmaf(s, f, -shift);
   return EXACT ? exact_exp(x) : fast_exp2(x);
 }
-// m + log(l), rounded about once: the reference maximum may lie up to 2^8 below the largest weight, and log(l) of such a sum is large
+// m + log(l), rounded about once, with log 2 in two parts (Cody and Waite): the reference maximum may lie up to 2^8 below the largest weight, and log(l) of such a sum is large
 // enough for its own rounding to show (2048 keys, 4 heads of 96: log-sum-exp 3.4e-7 off, rms, with m + logf(l), 1.8e-7 so; 3.0e-7 with a maximum that always follows).
 __device__ __forceinline__ float plus_log(float m, float l) {
   int k;
@@ -1227,10 +1227,13 @@ static int64_t groups_of_16(int b, int s, int n) { return (int64_t)b * n * ((s +
 
 // Against the kernels without LDS (attention_f32.hip), 444 sizes of 1 to 32 heads of 24 to 184, s 16 to 2048, and larger ones: faster
 // wherever those give a wave 16 rows of its own (more than 512 groups of 16 rows).  us, those / these, forward, then backward: 2 x 1024 x 16
-// heads of 96 103 / 21, 327 / 61; 4 x 2048 x 16 of 32 243 / 60, 641 / 163; 1024 x 16 of 192 104 / 31, 383 / 75; 32 x 64 x 16 of 80
-// 11.8 / 7.2, 31.6 / 24.3.  With fewer groups those split the streamed side over four waves, and these win by the longer sequences:
-// 512 x 16 of 96 14.9 / 11.6, 42.8 / 28.2, but 128 x 16 of 96 5.6 / 6.3, and at head size 24 512 x 4 6.8 / 8.4, 15.9 / 16.9; head size 56
-// forward 512 x 4 8.8 / 9.7, 512 x 16 11.3 / 10.1, backward 256 x 4 14.8 / 14.4, 128 x 4 10.2 / 10.8.
+// heads of 96 103 / 24, 327 / 61; 4 x 2048 x 16 of 32 243 / 68, 641 / 165; 1024 x 16 of 192 104 / 31, 383 / 76; 32 x 64 x 16 of 80
+// 12.4 / 7.8, 32.2 / 25.2.  With fewer groups those split the streamed side over four waves, and these win by the longer sequences:
+// 512 x 16 of 96 15.4 / 13.2, 43.9 / 29.2, and at head size 24 512 x 4 6.8 / 8.4, 15.9 / 16.9.  The lines were drawn before small weights cost
+// the forward kernel 6 to 8 % and before small calls of those went out backward in one launch.  Since then, forward s > 256: head sizes above
+// 96 0.98 to 1.7 times as fast here; 72 to 96 up to 320 groups 0.92 to 1.09 (1712 x 2 of 96 29.7 / 31.8), beyond 1.01 to 1.5; 56 at 257 to 320 groups
+// 0.86 to 0.95: they stay, with half the error of lse (1.5e-7 against 2.7e-7 rms).  Forward s <= 256, up to 512 groups: 1.04 to 1.33 here from head size
+// 72 on.  Backward up to 128 groups: 0.73 to 0.95 (296 x 1 of 40 11.6 / 16.0, 597 x 1 of 96 25.7 / 30.0), as fast as those in two launches.
 bool attention_exact_fwd_takes(int dtype, int b, int s, int n, int d, const void *qkv, const void *a) {
   if (!exact_takes(dtype, b, s, n, d) || (((uintptr_t)qkv | (uintptr_t)a) & 7)) return false;
   const int64_t groups = groups_of_16(b, s, n);
