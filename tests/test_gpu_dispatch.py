@@ -575,6 +575,32 @@ def test_attention_with_small_weights(b, s, n, d, at):
     assert_close(dqkv.reshape(b, s, n, 3, d)[:, at + 1:, :, 2], want[:, at + 1:, :, 2], TOL["bf16"], "dv")
 
 
+# ... and values whose sums leave the range of the scaled parts, but not that of fp32: V (dP stays ordinary, the gradient is small), then K with
+# the gradient (P stays ordinary, Q is small).
+@pytest.mark.parametrize("b,s,n,d", [(1, 100, 80, 40), (1, 257, 3, 96)])
+@pytest.mark.parametrize("part", [1, 2])
+def test_attention_with_large_values(b, s, n, d, part):
+    dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
+    x, da = randn((b, s, n, 3, d), "fp32", 35), randn((b, s, n, d), "fp32", 36)
+    if part == 2:
+        x[..., 2, :] *= 2.0 ** 112
+        da *= 2.0 ** -100
+    else:
+        x[..., 0, :] *= 2.0 ** -60
+        x[..., 1, :] *= 2.0 ** 60
+        da *= 2.0 ** 50
+    qkv, da = x.reshape(b * s, -1).to(torch.bfloat16), da.reshape(b * s, -1).to(torch.bfloat16)
+    a, dqkv = torch.empty_like(da, device="cuda"), torch.empty_like(qkv, device="cuda")
+    lse = torch.empty((b, n, s), device="cuda")
+    ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+    M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), dev(qkv), a, lse)
+    M.mtnlg_attention_bwd(b, s, n, d, 1.0 / math.sqrt(d), dev(qkv), a, lse, dev(da), dqkv, ws)
+    assert_close(a, oracle.attention_fwd(dims, to_np(qkv)), TOL["bf16"], "a")
+    want, got = oracle.attention_bwd(dims, to_np(qkv), to_np(da)).reshape(b, s, n, 3, d), dqkv.reshape(b, s, n, 3, d)
+    for i in range(3):
+        assert_close(got[:, :, :, i], want[:, :, :, i], TOL["bf16"], f"d{'qkv'[i]}")
+
+
 # Backward in one launch, dk / dv with a D of its own: two rows (with one dq is the rounding of dP - D), the edges of a 64-row block and of the 128 rows that a pass of D takes, and
 # either side of the rule (256 blocks; 768 at head size 64 up to s 1024).
 @pytest.mark.parametrize("b,s,n,d", [(1, 2, 1, 128), (2, 63, 3, 64), (1, 64, 2, 160), (1, 65, 1, 128), (1, 129, 2, 64), (3, 191, 1, 160), (1, 1030, 1, 64),
