@@ -470,8 +470,9 @@ __device__ __forceinline__ void dkv_rows(int blk, Meeting<DP> *meet, int s, int 
   float z = 0.0f;
   if (key < s) z = dk.store(out + d, d, scale, w.g) + dv.store(out + 2 * d, d, 1.0f, w.g);
   if (all_finite(z)) return;
-  if constexpr (OWN_D) redo_dkv<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, [&](int t) { return dot(dab + t * pld, ab + t * pld, d, w.g); }, w.g, out);
-  else redo_dkv<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, [&](int t) { return D[st + t]; }, w.g, out);
+  redo_dv<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, w.g, out);
+  if constexpr (OWN_D) redo_dk<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, [&](int t) { return dot(dab + t * pld, ab + t * pld, d, w.g); }, w.g, out);
+  else redo_dk<E, DP>(base, ld, dab, pld, s, d, scale, w.row0, key, lse + st, [&](int t) { return D[st + t]; }, w.g, out);
 }
 
 template <typename E>

@@ -110,23 +110,28 @@ __device__ __forceinline__ void redo_dq(const E *base, int64_t ld, const E *da, 
   }
   if (q < s) sum.store(out, d, scale, g);
 }
-template <typename E, int DP, typename DOf>   // d_of(t): D of row t
-__device__ __forceinline__ void redo_dkv(const E *base, int64_t ld, const E *da, int64_t pld, int s, int d, float scale, int row0, int key,
-                                         const float *lse, DOf &&d_of, int g, E *out) {
+template <typename E, int DP>
+__device__ __forceinline__ void redo_dv(const E *base, int64_t ld, const E *da, int64_t pld, int s, int d, float scale, int row0, int key,
+                                        const float *lse, int g, E *out) {
   const E *krow = base + d + (key < s ? key : s - 1) * ld;
-  auto prob = [&](int t) { return expf(dot(krow, base + t * ld, d, g) * scale - lse[t]); };
-  Quarter<E, DP> sum;   // dv, then dk
+  Quarter<E, DP> sum;
   sum.clear();
 #pragma unroll 1
   for (int t = row0; t < s; ++t) {
-    const float p = prob(t);
+    const float p = expf(dot(krow, base + t * ld, d, g) * scale - lse[t]);
     if (t >= key) sum.add(p, da + t * pld, d, g);
   }
   if (key < s) sum.store(out + 2 * d, d, 1.0f, g);
+}
+template <typename E, int DP, typename DOf>   // d_of(t): D of row t
+__device__ __forceinline__ void redo_dk(const E *base, int64_t ld, const E *da, int64_t pld, int s, int d, float scale, int row0, int key,
+                                        const float *lse, DOf &&d_of, int g, E *out) {
+  const E *krow = base + d + (key < s ? key : s - 1) * ld;
+  Quarter<E, DP> sum;
   sum.clear();
 #pragma unroll 1
   for (int t = row0; t < s; ++t) {
-    const float p = prob(t), dp = dot(krow + d, da + t * pld, d, g), dt = d_of(t);
+    const float p = expf(dot(krow, base + t * ld, d, g) * scale - lse[t]), dp = dot(krow + d, da + t * pld, d, g), dt = d_of(t);
     if (t >= key) sum.add(p * (dp - dt), base + t * ld, d, g);
   }
   if (key < s) sum.store(out + d, d, scale, g);

@@ -609,6 +609,14 @@ def test_attention_backward_in_one_launch(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
+# Backward in two launches at head sizes 128 and 160, workgroups of 64 own rows (from 321 blocks of 64 rows on) and of 128 rows with tiles of 32 (from 768 on): either side of
+# the rules, ends of sequences at the edges of a 32-row part, of a tile and of the own rows.
+@pytest.mark.parametrize("b,s,n,d", [(1, 64, 320, 128), (1, 33, 321, 128), (1, 96, 161, 160), (3, 127, 64, 128), (1, 97, 192, 160), (1, 191, 255, 128),
+                                     (1, 95, 384, 128), (3, 129, 85, 160), (2, 129, 128, 160), (1, 32, 768, 128), (2, 161, 128, 128), (1, 257, 154, 160)])
+def test_attention_backward_by_rows_of_a_workgroup(b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
+
+
 # The same for the kernels without LDS: fp32 and small bf16 calls on either side of the rules (512, 256 and 128 groups of 16 rows), head sizes that have
 # no such launch, one row (dq is exactly zero).
 @pytest.mark.parametrize("dtype,b,s,n,d", [("fp32", 1, 1, 1, 64), ("fp32", 1, 64, 128, 96), ("fp32", 1, 64, 129, 96), ("fp32", 2, 127, 16, 128),
