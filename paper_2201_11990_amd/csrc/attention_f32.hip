@@ -523,11 +523,31 @@ constexpr int one_launch_groups() {
   return DP <= 96 ? 512 : DP == 128 ? 256 : DP == 160 ? 128 : 0;
 }
 
-// Which calls split the streamed side over the waves of a workgroup: those with up to 512 groups of 16 rows, two workgroups
-// for each compute unit, which leave most of the chip idle with 64 rows to a workgroup, so that a wave's chain of steps is the time.
-// us with 64 rows / 16 rows, forward, then backward: 1 head of 256, s = 256 81.9 / 28.1, 247 / 87; 4 of 64, s = 512 72 / 26,
-// 198 / 65; 16 of 64, s = 512 81 / 39, 214 / 103.  At 1024 groups it is between 0.5 and 1.2 of the time; at s <= 32 there is nothing to share.
-inline bool splits(int b, int s, int n) { return s > 32 && (int64_t)b * n * ((s + 15) / 16) <= 512; }
+// Up to how many groups of 16 rows a call splits the streamed side over the waves of a workgroup.  With 64 rows to a workgroup, 16 to a wave, the
+// time is the longest wave's chain of steps until there are several waves to a SIMD, and it grows with s; with 16 rows to a workgroup a chain is a quarter of that, but
+// the waves no longer share what they load, and the time grows with the work.  So the line lies higher for longer sequences and smaller head sizes.  fp32,
+// times as fast with 16 rows to a workgroup, forward / backward, at head size 32, 64, 128, 224: 20 heads, s = 512 (640 groups) 1.9 / 2.1, 1.9 / 2.1, 1.5 / 1.9, 1.6 / 1.6;
+// 48, 256 (768) 1.4 / 1.7, 1.2 / 1.4, 1.05 / 1.3, 1.1 / 1.2; 72, 224 (1008) 1.3 / 1.4, 1.1 / 1.2, 0.7 / 0.9, 0.7 / 0.9; 128, 128 (1024) 1.05 / 1.2, 0.9 / 1.06, 0.6 / 0.8, 0.7 / 0.8; 32,
+// 512 (1024) 1.6 / 1.7, 1.35 / 1.4, 1.1 / 1.3, -; 16, 1024 (1024) 1.8 / 1.9, 1.6 / 1.7, 1.3 / 1.6, -; 48, 512 (1536) 1.3 / 1.4, 1.2 / 1.3, 0.75 / 0.9, 0.8 / 0.9; 12, 2048 (1536) 1.6 / 1.8, 1.5 / 1.6,
+// 1.03 / 1.2, 1.07 / 1.1; 40, 1024 (2560) 1.2 / 1.3, 1.03 / 1.1, 0.9 / 1.0, 0.9 / 0.9; 64, 1024 (4096) 1.1 / 1.1, 0.9 / 1.01, 0.8 / 0.9, 0.8 / 0.8.  Up to 512 groups at any s above 32 (1 head of
+// 256, s = 256 81.9 -> 28.1 us, 247 -> 87); at s <= 32 there is nothing to share.  bf16 comes here with more groups only above head size 192 and in calls that the
+// tiled kernels refuse.  2 x 512 tokens, 16 heads of 64, fp32: 35.5 -> 29.4 us, 118 -> 85.
+template <typename E, int DP, bool BACKWARD>
+constexpr int64_t most_split_groups(int s) {
+  if (s <= 32) return 0;
+  if (sizeof(E) == 2) return 512;
+  if (!BACKWARD) {
+    if (DP == 32) return s >= 512 ? 4096 : s >= 192 ? 1024 : 512;
+    if (DP <= 96) return s >= 1024 ? 2560 : s >= 512 ? 1536 : s >= 256 ? 1024 : s >= 192 ? 768 : 512;
+    return s >= 2048 ? 1536 : s >= 512 ? 1024 : s >= 256 ? 768 : 512;
+  }
+  if (DP <= 64) return s >= 512 ? 4096 : s >= 128 ? 1024 : 512;
+  if (DP == 96) return s >= 1024 ? 2048 : s >= 512 ? 1536 : s >= 192 ? 1024 : 512;
+  if (DP <= 160) return s >= 1024 ? 1536 : s >= 256 ? 1024 : s >= 192 ? 768 : 512;
+  return s >= 512 ? 1024 : s >= 256 ? 768 : 512;
+}
+template <typename E, int DP, bool BACKWARD>
+bool splits(int b, int s, int n) { return (int64_t)b * n * ((s + 15) / 16) <= most_split_groups<E, DP, BACKWARD>(s); }
 
 template <typename E, int DP, bool SPLIT>
 int fwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
@@ -538,7 +558,7 @@ int fwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, void 
 }
 template <typename E, int DP>
 int fwd_launch(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
-  if (splits(b, s, n)) return fwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, st);
+  if (splits<E, DP, false>(b, s, n)) return fwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, st);
   return fwd_launch_s<E, DP, false>(b, s, n, d, scale, qkv, a, lse, st);
 }
 
@@ -563,7 +583,7 @@ int bwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, const
 template <typename E, int DP>
 int bwd_launch(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                void *dqkv, void *ws, hipStream_t st) {
-  if (splits(b, s, n)) return bwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
+  if (splits<E, DP, true>(b, s, n)) return bwd_launch_s<E, DP, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
   return bwd_launch_s<E, DP, false>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
 }
 

@@ -486,6 +486,14 @@ def test_attention_by_rows_of_a_workgroup(dtype, b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
 
 
+# fp32 at the edges of the rule for 16 or 64 rows to a workgroup, which depends on the sequence, the head size and the direction: above 512 groups of 16
+# rows (groups in comments), on both sides of a limit.
+@pytest.mark.parametrize("b,s,n,d", [(1, 192, 64, 32), (1, 192, 86, 32), (2, 192, 32, 64), (1, 256, 64, 88), (1, 257, 61, 64),   # 768, 1032, 768, 1024, 1037
+                                     (1, 256, 48, 128), (1, 256, 64, 160), (1, 272, 31, 232), (1, 520, 47, 64), (1, 512, 49, 96)])  # 768, 1024, 527, 1551, 1568
+def test_fp32_attention_by_groups_of_rows(b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd("fp32", b, s, n, d)
+
+
 def attention_fwd_without_lds(b, s, n, d, scale, qkv, a, lse):
     fn = B.lib()._ZN5mtnlg17attention_fwd_f32EiiiiifPKvPvPfP12ihipStream_t
     fn.argtypes = [ctypes.c_int] * 5 + [ctypes.c_float] + [ctypes.c_void_p] * 4
