@@ -12,13 +12,13 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmtnlg.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ("api.cpp", "profile.cpp", "elementwise.hip", "gemm_generic.hip", "gemm_mfma.hip", "gemm_wave.hip", "gemm_parts.hip",
-           "attention_f32.hip", "attention_mfma.hip", "attention_bwd.hip", "attention_bwd64.hip", "optimizer.hip", "head.hip", "calibrate.hip")
+           "attention_f32.hip", "attention_mfma.hip", "attention_fwd16.hip", "attention_bwd.hip", "attention_bwd64.hip", "optimizer.hip", "head.hip", "calibrate.hip")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes"]
 # Kernels of four waves may have more than 256 registers, of which the vector unit reads 256.  By default the compiler then puts the results of all matrix
 # instructions into the others and copies scores back element by element.
-SOURCE_FLAGS = {"attention_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+SOURCE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("attention_mfma.hip", "attention_bwd.hip")}
 
 
 def _compile(src):

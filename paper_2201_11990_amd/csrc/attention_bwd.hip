@@ -28,7 +28,6 @@ namespace {
 //
 // A step is one fragment and its MFMA (EXACT: three in the second product).  Fragments are read PF steps ahead across the end of a tile, and a tile's barrier
 // stands PF steps before its end.
-__host__ __device__ inline int own_blocks(int s, int owned) { return (s + owned - 1) / owned; }   // workgroups to a head
 struct BackwardArgs {
   int b, s, n, head_dim, group;
   float scale;
@@ -72,18 +71,6 @@ struct Head {
   }
 };
 
-// EXACT with SPLIT 2, where waves `wave` and wave ^ 2 have stored half of a result's columns each: the slow path computes whole rows, so the wave of part 0
-// takes it if either has found a result that is not finite (z: NaN), after what both have stored.
-__device__ __forceinline__ float either_part(float z, char *smem, int wave, int part, int lane) {
-  __syncthreads();   // LDS is free
-  int *bad = reinterpret_cast<int *>(smem);
-  const bool any = __builtin_amdgcn_ballot_w64(z != 0.0f) != 0;
-  if (lane == 0) bad[wave] = any;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  return part == 0 && (bad[wave] | bad[wave ^ 2]) ? NAN : 0.0f;
-}
-
 // ------------------------------------------------------------------ backward: dq (and D)
 // Four waves, and two workgroups to a compute unit where registers and LDS allow: they cover each other's start, end and barriers.
 constexpr int DQ_THREADS = 256;
@@ -102,9 +89,8 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
   const Head<EXACT, D> at(w, hb.batch, hb.head);
   const int half = wave >> 1;   // waves 0, 1 bring 32 rows each of K (of Q, the own rows), waves 2, 3 of V (dO)
   const int s = at.s, d = at.d, lane = at.lane, g = lane >> 4, lr = lane & 15, h = lane >> 5;
-  // Falling work.  Where all workgroups run at once, two to a compute unit, place 256 + i joins place i there: those go out in rising order.
-  const int heads = w.b * w.n, count = own_blocks(s, OWNED), first = (255 + heads) / heads;
-  const int block = RING == 2 && heads * count <= 512 && hb.order >= first ? hb.order - first : count - 1 - hb.order;
+  const int heads = w.b * w.n, count = own_blocks(s, OWNED);   // falling work
+  const int block = count - 1 - (RING == 2 && heads * count <= 512 ? in_turns(hb.order, count, heads) : hb.order);
   const int rows_of = SPLIT == 2 ? (threadIdx.x >> 6) & 1 : threadIdx.x >> 6;   // (from the thread number: see the forward kernel)
   const int block0 = block * OWNED, own0 = block0 + rows_of * 32, mine = own0 + (lane & 31);
   const int part = SPLIT == 2 ? wave >> 1 : 0;
@@ -292,7 +278,7 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
     }
   }
   if constexpr (EXACT) {
-    if constexpr (SPLIT == 2) z = either_part(z, smem, wave, part, lane);
+    if constexpr (SPLIT == 2) z = either_part(z, smem, wave, wave ^ 2, part, lane);
     if (!all_finite(z)) {
 #pragma unroll 1
       for (int c = 0; c < 2; ++c) {
@@ -635,7 +621,7 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, const Back
     }
   }
   if constexpr (EXACT) {
-    if constexpr (L::PARTS == 2) z = either_part(z, smem, wave, part, lane);
+    if constexpr (L::PARTS == 2) z = either_part(z, smem, wave, wave ^ 2, part, lane);
     if (!all_finite(z)) {
       auto d_of = [&](int t) { return at.Dvec[t]; };
 #pragma unroll 1

@@ -3,300 +3,277 @@
 //
 //   S = scale * q k^T (causal),  P = rowsoftmax(S),  a = P v,  lse = log sum exp(S)
 //
-// Eight waves.  A workgroup owns 128 or 256 queries, 16 or 32 per wave, held in registers as MFMA B operands (groups of 16, one row per lane
-// column); K and V stream through LDS in tiles of 64 rows, brought in by LDS DMA (buffer_load ... lds, no staging
-// registers) three tiles deep, one workgroup barrier per tile.  What bounds it: no single unit.  Between two barriers a
-// wave runs LDS reads, MFMAs, the softmax and the DMA issue in one chain, and the waves of a workgroup run it in step, so
-// the times of the four add up; taking any one out shortened a tile by no more than that one's own time.
+// A workgroup owns 64 or 128 queries, 32 to a wave, held in registers as MFMA B operands (one row to a lane column); K and V stream through LDS in tiles of 64 rows, brought in by LDS
+// DMA (buffer_load ... lds, no staging registers), one workgroup barrier per tile.  All products are v_mfma_f32_32x32x16_bf16 with the streamed tile as the A operand, so a product
+// block comes out as C[tile row 8 (i / 4) + 4 (lane / 32) + i % 4][own row lane % 32], i < 16: S^T = K Q^T, with the softmax statistics of a query in the two lanes that share lane % 32, and P^T packed
+// to bf16 is directly the B operand of O^T += V^T P^T.  That product contracts over the tile's rows: its A operand is read from the same natural [row][D] tile with the transposing LDS read
+// (ds_read_b64_tr_b16: a 16-lane group reads 4 tile rows x 16 columns, each lane receives the 4 row values of its column), its k slots ordered as the first product leaves the rows, so P never leaves
+// the registers and nothing is transposed in software.  No atomics: every output element has one owner, results are run-to-run identical.
 //
-// All products are v_mfma_f32_16x16x32_bf16 with the streamed tile as the A operand, so a product block comes out as
-// C[tile row 4 (lane/16) + i][own row lane%16], i = 0..3: S^T = K Q^T; the softmax statistics of a query live in the four lanes that
-// share lane%16; P^T packed to bf16 is directly the B operand of O^T += V^T P^T.  That product contracts over the tile's rows.  Its A operand is read
-// from the same natural [row][D] tile with the transposing LDS read (ds_read_b64_tr_b16: a
-// 16-lane group reads 4 tile rows x 16 columns, each lane receives the 4 row values of its
-// column); the k slots of that MFMA are ordered to match the accumulator layout of the
-// first product (slot (g, e) of a 32-row step = tile row 4g + e for e < 4, 16 + 4g + e - 4
-// otherwise), so P never leaves the registers and nothing is transposed in software.
-// No atomics: every output element has one owner, results are run-to-run identical.
+// What bounds it: in a tile the softmax (some 75 vector instructions and 16 exponentials for 16 MFMAs at head size 128), which hides behind the MFMAs of the other workgroup on the
+// unit only; in small calls the 3 to 4 us of a launch and the first trips to memory.  us against eight waves of 16 or 32 queries on 16x16x32 MFMAs, one workgroup to a unit: 16 heads, s = 2048, head
+// size 64 24.6 -> 22.3, 128 36.0 -> 30.3, 160 38.8 -> 35.6; 20 heads of 128 51.9 -> 33.1; 128 of 128, s = 768 46.8 -> 36.9; 2 of 160, s = 256 9.3 -> 7.5; 64 of 128, s = 1024 32.2 -> 29.8.
 //
-// EXACT: any head size d that is a multiple of 8, in tiles of D = d rounded up to 32 columns (the DMA brings zeros past d).  P is
-// not rounded to bf16: it goes into the second product as three bf16 parts that add up to it (common.h: Parts; scaled, so of any size), three MFMAs
-// where the other kernels have one.  2 x 1024 tokens, 16 heads of 96: 103 us on the fp32 instructions without LDS (attention_f32.hip), 24 here.  Inputs that are
-// not finite take the slow path of attention_redo.h.
+// EXACT: any head size d that is a multiple of 8, in tiles of D = d rounded up to 32 columns (the DMA brings zeros past d).  P is not rounded to bf16: it goes into the second product as
+// three bf16 parts that add up to it (common.h: Parts; scaled, so of any size), three MFMAs where the other kernels have one.  Inputs that are not finite take the slow path of attention_redo.h.
 #include "attention_tiles.h"
 
 namespace mtnlg {
 
 namespace {
 
-// Which rows a wave of the forward kernel owns.
-// Under the causal mask a 64-row block b works on b + 1 of the 64-row tiles the workgroup streams, so blocks taken in order
-// would leave the workgroups of a head with 1 .. s/64 tiles of work.  The two halves of a workgroup therefore take
-// blocks p and nb - 1 - p (nb blocks of 64 G rows in the sequence): every workgroup then computes nb + 1 wave-halves
-// of tiles, and while only one half has work in a tile it has the compute unit to itself.  With an
-// odd nb the middle block is alone in its workgroup and the other half only helps to move tiles.
-template <int G>
-struct PairedBlocks {
-  int row0;        // first row of this wave
-  int last_tile;   // highest 64-row block of the workgroup: it streams tiles 0 .. last
-  bool idle;       // wave-uniform: this wave owns no rows
-  __device__ PairedBlocks(int s, int pair, int wave) {
-    const int nb = (s + 63) / 64, nblk = (nb + G - 1) / G;
-    const int lo = pair, hi = nblk - 1 - pair, half = wave >> 2;
-    row0 = (half ? hi : lo) * (64 * G) + (wave & 3) * (16 * G);
-    last_tile = hi * G + G - 1 < nb ? hi * G + G - 1 : nb - 1;
-    idle = half && hi == lo;
-  }
-  static __host__ __device__ int count(int s) { return (((s + 63) / 64 + G - 1) / G + 1) / 2; }
+// Waves of 32 queries; tiles, fragments, blocks and steps as in the dq kernel of attention_bwd.hip (why 32 rows and 32x32x16 is said there).  Four to a workgroup, and two workgroups
+// to a compute unit (four at head size 64): they cover each other's softmax, barriers, start and end.  SPLIT 2: a workgroup owns 64 queries, waves 0, 1 take the first 32 keys of every
+// tile, waves 2, 3 the last 32, each with a maximum and a sum of its own; the results are merged through LDS at the end.  SPLIT 1: 128 queries.
+constexpr int FWD_RING = 2;   // tiles of K and V in LDS: with a third one workgroup less fits a unit
+struct ForwardArgs {
+  int b, s, n, head_dim, group;
+  bool turns;
+  float scale;
+  const bf16 *qkv;
+  bf16 *a;
+  float *lse;
 };
-
-// ------------------------------------------------------------------ forward
-template <int D, int G, bool EXACT>
-__global__ __launch_bounds__(512) void attn_fwd_kernel(int b, int s, int n, int head_dim, int group, float scale, const bf16 *__restrict__ qkv,
-                                                      bf16 *__restrict__ a, float *__restrict__ lse) {
+constexpr int FWD_WAVES = 4;
+template <int D, int SPLIT, bool EXACT>
+__global__ __launch_bounds__(64 * FWD_WAVES, 2) void attn_fwd_kernel(ForwardArgs w) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  using T = Tile<D>;
-  constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES;
-  const HeadBlock hb(b, n, group, PairedBlocks<G>::count(s), blockIdx.x);
-  const int j = hb.head, bi = hb.batch;
+  using T = Tile<D, true>;
+  constexpr int ROWS = FWD_WAVES / SPLIT, OWNED = 32 * ROWS;   // waves with rows of their own
+  constexpr int K1 = D / 16, CB = D / 32, STAGE = 2 * T::BYTES, NP = EXACT ? 3 : 1;
+  constexpr int SUBS = SPLIT == 2 ? 1 : 2;                // 32-key parts of a tile that a wave takes
+  constexpr int N1 = 2 * K1, N = SUBS * N1, NF = D == 160 ? 5 : D == 96 || D == 192 ? 6 : 4, PF = NF - 1;   // steps of a part: K1 for S, K1 for O
+  static_assert(N1 % NF == 0, "fragment buffers");
+  const int s = w.s, n = w.n, d = EXACT ? w.head_dim : D;
+  const int count = own_blocks(s, OWNED);
+  const HeadBlock hb(w.b, n, w.group, count, blockIdx.x);
   if (hb.none) return;
-  const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
+  const int lane = threadIdx.x & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
-  const int d = EXACT ? head_dim : D;
   const int64_t ld = (int64_t)n * 3 * d;
-  const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * d;
-  // From the thread number and not the scalar: with a scalar condition for masked tiles the compiler lays the tile's code
-  // out per path and holds 60 registers more (head size 160, 32 rows per wave: 256 and 27 spilled, 163 us; now 208, 105).
-  const PairedBlocks<G> rb(s, hb.order, threadIdx.x >> 6);
-  const int qw = rb.row0;
-  const float c = scale * kLog2e, f = EXACT ? scale : c;
-  typename T::Lane ln(lane);
+  const bf16 *base = w.qkv + (int64_t)hb.batch * s * ld + (int64_t)hb.head * 3 * d;
+  const int64_t left = (int64_t)s * ld - 3 * (int64_t)hb.head * d;   // elements from base to the end of the sequence
+  const int block = count - 1 - (w.turns ? in_turns(hb.order, count, w.b * n) : hb.order);   // falling work
+  // From the thread number and not the scalar: with a scalar condition for masked tiles the compiler lays the tile's code out per path and holds more registers.
+  const int rows_of = (threadIdx.x >> 6) % ROWS;
+  const int block0 = block * OWNED, own0 = block0 + rows_of * 32, mine = own0 + (lane & 31);
+  const int part = SPLIT == 2 ? wave / ROWS : 0, other = SPLIT == 2 ? wave ^ ROWS : wave;   // the wave with the same rows
+  const float c = w.scale * kLog2e, f = EXACT ? w.scale : c;
+  typename T::Lane32 ln(lane);
   const uint32_t smem_addr = lds_address(smem);
+  const int ntiles = (block + 1) * (OWNED / 64) < row_blocks(s) ? (block + 1) * (OWNED / 64) : row_blocks(s);
 
-  int qc[G];
-  bf16x8 qf[G][KK];
+  // waves 0, 1 bring 32 rows each of K (SPLIT 2: and 16 of Q, the own rows, which two waves need, into the last stage), waves 2, 3 of V (Q)
+  constexpr int BANDS = 8 / FWD_WAVES, IPW = BANDS * T::NI;   // bands of 16 rows
+  const int half = wave / (FWD_WAVES / 2), band = BANDS * (wave % (FWD_WAVES / 2));
+  const uint32_t dst0 = smem_addr + half * T::BYTES + band * (T::NI * 1024);
+  bf16x8 qf[K1];   // own rows: columns 16 kk + 8 h .. + 7
+  if constexpr (SPLIT == 2) {
+    const TileStream own(base + block0 * ld, (left - block0 * ld) * 2, OWNED * ld * 2);
 #pragma unroll
-  for (int qg = 0; qg < G; ++qg) {
-    const int q = qw + 16 * qg + lr;
-    qc[qg] = q < s ? q : s - 1;
+    for (int i = 0; i < T::NI; ++i)
+      dma16<Burst::value>(own.rsrc(), smem_addr + STAGE + (wave * T::NI + i) * 1024, T::dma_offset((uint32_t)(ld * 2), wave, lane, i, d));
+  } else {
+    const int qc = mine < s ? mine : s - 1;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-      qf[qg][kk] = row_chunk<EXACT>(base + (int64_t)qc[qg] * ld, 32 * kk + 8 * g, d);
+    for (int kk = 0; kk < K1; ++kk) qf[kk] = row_chunk<EXACT>(base + (int64_t)qc * ld, 16 * kk + 8 * h, d);
   }
-  f32x4 o[G][DB];
-#pragma unroll
-  for (int qg = 0; qg < G; ++qg)
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[qg][db][e] = 0.0f;
-  float m[G], l[G];   // l: this lane's share of the row sum
-#pragma unroll
-  for (int qg = 0; qg < G; ++qg) {
-    m[qg] = -INFINITY;
-    l[qg] = 0.0f;
-  }
-
-  const int ntiles = rb.last_tile + 1;
-  // Waves 0-3 bring the K tile, waves 4-7 the V tile, 16 rows each.  The DMAs of tile it + 2 are spread over
-  // the MFMA steps of tile it (dma_by).
-  constexpr int IPW = T::NI;   // DMA instructions per wave and tile
-  const int quarter = wave & 3, half = wave >> 2;
-  TileStream kv(base + d + half * d, ((int64_t)s * ld - (j * 3 + 1 + half) * d) * 2, 64 * ld * 2);
+  TileStream stream(base + (1 + half) * d, (left - (1 + half) * d) * 2, 64 * ld * 2);
   uint32_t dma_off[IPW];
 #pragma unroll
-  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(ld * 2), quarter, lane, i, d);
-  auto issue_one = [&](auto tag, int st, int i) {   // instruction i of the stream's next tile into ring stage st
-    constexpr int TAG = decltype(tag)::value;
-    dma16<TAG>(kv.rsrc(), smem_addr + st * STAGE + half * T::BYTES + (quarter * IPW + i) * 1024, dma_off[i]);
-  };
-  constexpr int STEPS = 2 * KK + DB;   // MFMA steps of a tile
+  for (int i = 0; i < IPW; ++i) dma_off[i] = T::dma_offset((uint32_t)(ld * 2), band + i / T::NI, lane, i % T::NI, d);
+  constexpr int ISSUE_STEPS = IPW / 2;   // (one tile ahead: it is waited for in the same iteration)
   auto issue_step = [&](int step, int st) {
 #pragma unroll
     for (int i = 0; i < IPW; ++i)
-      if (i >= (step ? dma_by<IPW, STEPS>(step - 1) : 0) && i < dma_by<IPW, STEPS>(step)) issue_one(Spread{}, st, i);
+      if (i >= (step ? dma_by<IPW, ISSUE_STEPS>(step - 1) : 0) && i < dma_by<IPW, ISSUE_STEPS>(step))
+        dma16<Spread::value>(stream.rsrc(), dst0 + st * STAGE + i * 1024, dma_off[i]);
   };
-  auto issue = [&](int st) {
 #pragma unroll
-    for (int i = 0; i < IPW; ++i) issue_one(Burst{}, st, i);
+  for (int i = 0; i < IPW; ++i) dma16<Burst::value>(stream.rsrc(), dst0 + i * 1024, dma_off[i]);
+  stream.advance();
+  if constexpr (SPLIT == 2) {
+    wait_and_barrier<IPW>();
+#pragma unroll
+    for (int kk = 0; kk < K1; ++kk) qf[kk] = T::nat32(smem + STAGE + rows_of * T::ROWS32, ln, kk);
+  }
+#pragma unroll
+  for (int kk = 0; kk < K1; ++kk) arrive(qf[kk]);
+  f32x16 o[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) o[cb] = f32x16{};
+  float m = -INFINITY, l = 0.0f;   // l: this lane's share of the row sum
+  wait_and_barrier<0>();   // tile 0 landed everywhere, the own rows have been read
+
+  bf16x8 fr[NF];
+  f32x16 sc;
+  Parts<NP> x[2];
+  const char *Kt = smem;   // stage of the tile whose fragments are being read
+  auto load = [&](int i) {   // the fragment of step i
+    const int sub = i / N1, r = i % N1;
+    const char *k = Kt + (part + sub) * T::ROWS32;
+    if (r < K1) fr[i % NF] = T::nat32(k, ln, r);
+    else fr[i % NF] = T::tr32(k + T::BYTES, ln, (r - K1) / 2, r % 2);
   };
-  issue(0);
-  kv.advance();
-  issue(1);
-  kv.advance();
 #pragma unroll
-  for (int qg = 0; qg < G; ++qg)
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) arrive(qf[qg][kk]);
+  for (int i = 0; i < PF; ++i) load(i);
+  __builtin_amdgcn_sched_barrier(0);
+
   int cur = 0;
   for (int it = 0; it < ntiles; ++it) {
-    wait_and_barrier<IPW>();   // tile it landed everywhere, tile it-1 no longer read
     ln.here();
-    const int nn = cur == 0 ? 2 : cur - 1;   // stage of tile it + 2
-    const char *Kt = smem + cur * STAGE, *Vt = Kt + T::BYTES;
-    const int kv0 = it * 64;
-    if (rb.idle || kv0 > qw + (16 * G - 1)) {  // wave-uniform: every (query, key) pair of this wave is masked
-      issue(nn);
-    } else {
-      f32x4 sc[G][4];
+    const int next = cur ^ 1;   // stage of tile it + 1
+    auto step = [&](auto I) __attribute__((always_inline)) {
+      constexpr int i = decltype(I)::value, sub = i / N1, r = i % N1;
+      const int row = it * 64 + 32 * (part + sub);
+      if (r == 0) sc = f32x16{};
+      if (r == K1) {
+        // element e: key row + 8 (e / 4) + 4 h + e % 4, query `mine`
+        if (row + 31 > own0) {  // wave-uniform: diagonal (or past-the-end keys) among these keys
 #pragma unroll
-      for (int qg = 0; qg < G; ++qg)
+          for (int e = 0; e < 16; ++e)
+            if (row + 8 * (e / 4) + 4 * h + e % 4 > mine) sc[e] = -INFINITY;
+        }
+        // m tracks the running maximum of the raw scores; exponents are taken in base 2 with the scale folded in: p = 2^(s c - m c).  The reference maximum only
+        // follows when the row maximum has outgrown it by more than 2^8 in the exponent's units (any reference gives the same sums; this one keeps p <= 256
+        // and makes rescaling O rare).  -inf until a part has seen a key of the row.
+        float mx = sc[0];
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) sc[qg][kb][e] = 0.0f;
-      {  // step i: k-step i / 2, key blocks 2 (i % 2) and 2 (i % 2) + 1
-        bf16x8 kfr[4][2];
-        pipelined<2 * KK, 3>(
-            [&](int i) {
-#pragma unroll
-              for (int h = 0; h < 2; ++h) kfr[i & 3][h] = T::nat(Kt, ln, 2 * (i & 1) + h, i >> 1);
-            },
-            [&](int i) {
-#pragma unroll
-              for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int qg = 0; qg < G; ++qg)
-                  sc[qg][2 * (i & 1) + h] = MFMA16(kfr[i & 3][h], qf[qg][i >> 1], sc[qg][2 * (i & 1) + h]);
-            },
-            [&](int i) { issue_step(i, nn); });
-      }
-      // element (qg, kb, e): key kv0 + 16 kb + 4 g + e, query qc[qg]
-      if (kv0 + 63 > qw) {  // wave-uniform: this tile crosses the diagonal for some row
-#pragma unroll
-        for (int qg = 0; qg < G; ++qg)
-#pragma unroll
-          for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (kv0 + 16 * kb + 4 * g + e > qc[qg]) sc[qg][kb][e] = -INFINITY;
-      }
-      // m tracks the running maximum of the raw scores; exponents are taken in base 2 with the
-      // scale folded in: p = 2^(s c - m c).
-      float alpha[G];
-#pragma unroll
-      for (int qg = 0; qg < G; ++qg) {
-        float mx = -INFINITY;
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) mx = fmaxf(mx, sc[qg][kb][e]);
-        mx = quad_max(mx);
-        // The reference maximum only follows when the row maximum has outgrown it by more than
-        // 2^8 in the exponent's units (any reference gives the same sums; this one keeps p <= 256
-        // and makes rescaling O rare).  Finite from the first tile on: key 0 is never masked.
-        const float m_new = mx * c > m[qg] * c + 8.0f ? mx : m[qg];
-        const float mc = EXACT ? product_of(m_new, scale) : m_new * c;
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
+        mx = pair_max(mx);
+        const float m_new = mx * c > m * c + 8.0f ? mx : m;
+        const float ref = m_new == -INFINITY ? 0.0f : m_new;
+        const float mc = EXACT ? product_of(ref, w.scale) : ref * c;
         float rs = 0.0f;
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float p = weight<EXACT>(sc[qg][kb][e], f, mc);
-            sc[qg][kb][e] = p;
-            rs += p;
-          }
-        alpha[qg] = EXACT ? exact_exp((m[qg] - m_new) * scale) : fast_exp2((m[qg] - m_new) * c);
-        l[qg] = l[qg] * alpha[qg] + rs;
-        m[qg] = m_new;
-      }
-      bool moved = false;
-#pragma unroll
-      for (int qg = 0; qg < G; ++qg) moved = moved || alpha[qg] != 1.0f;
-      if (__builtin_amdgcn_ballot_w64(moved) != 0) {  // a reference maximum moved: rescale O
-#pragma unroll
-        for (int qg = 0; qg < G; ++qg)
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[qg][db][e] *= alpha[qg];
-      }
-      {  // step i: key half i / (DB / 2), output blocks 2 (i % (DB / 2)) and + 1
-        Parts<EXACT ? 3 : 1> pf[2][G];
-        bf16x8 vfr[4][2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int qg = 0; qg < G; ++qg) pf[ks][qg] = weights<EXACT>(sc[qg][2 * ks], sc[qg][2 * ks + 1]);
-        constexpr int HB = DB / 2;
-        pipelined<2 * HB, 3>(
-            [&](int i) {
-#pragma unroll
-              for (int h = 0; h < 2; ++h) vfr[i & 3][h] = T::tr(Vt, ln, 2 * (i % HB) + h, i / HB);
-            },
-            [&](int i) {
-#pragma unroll
-              for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int qg = 0; qg < G; ++qg)
-                  o[qg][2 * (i % HB) + h] = mma_weights(vfr[i & 3][h], pf[i / HB][qg], o[qg][2 * (i % HB) + h]);
-            },
-            [&](int i) { issue_step(2 * KK + i, nn); });
-      }
-    }
-    kv.advance();
-    cur = cur == 2 ? 0 : cur + 1;
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the look-ahead tiles, which nobody reads
-
-#pragma unroll
-  for (int qg = 0; qg < G; ++qg) {
-    const int q = qw + 16 * qg + lr;
-    const float lsum = quad_sum(l[qg]);
-    bf16 *out = a + ((int64_t)bi * s + q) * ((int64_t)n * d) + (int64_t)j * d;
-    float *out_lse = lse + ((int64_t)bi * n + j) * s + q;
-    float z = 0.0f;   // EXACT: NaN where a result is not finite
-    if (q < s && !rb.idle) {
-      const float inv = 1.0f / lsum;
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        if (EXACT && db * 16 + 4 * g >= d) continue;
-        bf16x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x = o[qg][db][e] * (EXACT ? inv * PARTS_UNSCALE : inv);
-          if constexpr (EXACT) z = fmaf(x, 0.0f, z);
-          v[e] = (bf16)x;
+        for (int e = 0; e < 16; ++e) {
+          sc[e] = weight<EXACT>(sc[e], f, mc);
+          rs += sc[e];
         }
-        *reinterpret_cast<bf16x4 *>(out + db * 16 + 4 * g) = v;
+        const float alpha = m == m_new ? 1.0f : EXACT ? exact_exp((m - m_new) * w.scale) : fast_exp2((m - m_new) * c);
+        l = l * alpha + rs;
+        m = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // a reference maximum moved: rescale O
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) o[cb] *= alpha;
+        }
+        x[0] = weights16<EXACT>(sc, 0);
+        x[1] = weights16<EXACT>(sc, 1);
       }
-      if (g == 0) *out_lse = EXACT ? plus_log(product_of(m[qg], scale), lsum) : (m[qg] * c + log2f(lsum)) * kLn2;
+      if (i == N - PF) {   // all of tile `it` has been read; tile it + 1 landed everywhere
+        wait_and_barrier<0>();
+        Kt = smem + next * STAGE;
+      }
+      load((i + PF) % N);
+      if (i < ISSUE_STEPS) issue_step(i, next);
+      const bf16x8 &v = fr[i % NF];
+      if constexpr (r < K1) sc = MFMA32(v, qf[r], sc);
+      else o[(r - K1) / 2] = mma_weights32(v, x[r % 2], o[(r - K1) / 2]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for_each_step(step, std::make_integer_sequence<int, N>{});
+    stream.advance();
+    cur = next;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the look-ahead tiles, which nobody uses
+
+  l += __shfl_xor(l, 32, 64);
+  f32x4 *slots = reinterpret_cast<f32x4 *>(smem) + lane;
+  float *const stat = reinterpret_cast<float *>(smem + 2 * FWD_WAVES * CB * 1024);   // maximum and sum of each wave
+  if constexpr (SPLIT == 2) {   // the part's results relative to the larger of the two maxima
+    __syncthreads();   // the rings are no longer read
+    stat[wave * 128 + lane] = m;
+    stat[wave * 128 + 64 + lane] = l;
+    __syncthreads();
+    const float mo = stat[other * 128 + lane], lo = stat[other * 128 + 64 + lane], both = fmaxf(m, mo);   // finite: key 0 is never masked
+    auto relative = [&](float x) { return EXACT ? exact_exp((x - both) * w.scale) : fast_exp2((x - both) * c); };
+    const float mul = relative(m);
+    l = part ? fmaf(l, mul, lo * relative(mo)) : fmaf(lo, relative(mo), l * mul);
+    m = both;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) o[cb] *= mul;
+    // the two waves with the same rows each hand over half of their column blocks' elements (q 0, 1 or 2, 3) and finish the other half
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) slots[((wave * CB + cb) * 2 + q) * 64] = part ? quarter_of(o[cb], q) : quarter_of(o[cb], 2 + q);
+    __syncthreads();
+  }
+  float z = 0.0f;   // EXACT: NaN where a result is not finite
+  bf16 *const out = w.a + ((int64_t)hb.batch * s + mine) * ((int64_t)n * d) + (int64_t)hb.head * d;
+  float *const out_lse = w.lse + ((int64_t)hb.batch * n + hb.head) * s + mine;
+  const float inv = EXACT ? 1.0f / l * PARTS_UNSCALE : 1.0f / l;
+  auto put = [&](int cb, int q, f32x4 sum) {   // columns 32 cb + 8 q + 4 h .. + 3
+    const int col = 32 * cb + 8 * q + 4 * h;
+    if (EXACT && col >= d) return;
+    bf16x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float r = sum[e] * inv;
+      if constexpr (EXACT) z = fmaf(r, 0.0f, z);
+      v[e] = (bf16)r;
     }
-    if constexpr (EXACT) {
-      const int first = qw + 16 * qg, last = first + 15 < s ? first + 15 : s - 1;
-      if (!all_finite(z)) redo_fwd<bf16, D>(base, ld, s, d, scale, q, last, g, out, out_lse);
+    *reinterpret_cast<bf16x4 *>(out + col) = v;
+  };
+  if (mine < s) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      if constexpr (SPLIT == 2) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const f32x4 rest = slots[((other * CB + cb) * 2 + q) * 64];
+          if (part) put(cb, 2 + q, quarter_of(o[cb], 2 + q) + rest);
+          else put(cb, q, quarter_of(o[cb], q) + rest);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) put(cb, q, quarter_of(o[cb], q));
+      }
+    }
+    if (h == 0 && part == 0) *out_lse = EXACT ? plus_log(product_of(m, w.scale), l) : (m * c + log2f(l)) * kLn2;
+  }
+  if constexpr (EXACT) {
+    if constexpr (SPLIT == 2) z = either_part(z, smem, wave, other, part, lane);
+    if (!all_finite(z)) {
+      const int lr = lane & 15, g = lane >> 4;
+#pragma unroll 1
+      for (int k = 0; k < 2; ++k) {
+        const int q = own0 + 16 * k + lr, last = own0 + 16 * k + 15;
+        redo_fwd<bf16, D>(base, ld, s, d, w.scale, q, last < s ? last : s - 1, g, w.a + ((int64_t)hb.batch * s + q) * ((int64_t)n * d) + (int64_t)hb.head * d,
+                          w.lse + ((int64_t)hb.batch * n + hb.head) * s + q);
+      }
     }
   }
 }
 
-// Forward with 32 rows per wave on eight waves (256 rows per workgroup): every K / V fragment read from LDS feeds two
-// MFMAs, which halves the kernel's LDS traffic -- its bound: each of the eight waves reads the whole K and V tile, the
-// V tile through half-rate transposing reads -- but halves the number of workgroups as well.  Taken when that still
-// leaves at least one workgroup per compute unit (the MT-NLG slice at micro-batch 1 has 16 heads x 8 = 128: it stays
-// with 16 rows per wave) and the head size is 128 or 160 (at 64 the variant measures 17 % slower).  Measured with the
-// kernel as it was before the grid ran heads first: 1.3B-shaped layer (4 x 16 heads x 128) 168 with 16 rows, 123 us with 32,
-// slice at micro-batch 4 167 and 129 us, whole layer (128 heads) 326 and 250 us.
-template <int D, int G, bool EXACT = false>
-int fwd_launch_g(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
-  constexpr int smem = 3 * 2 * 64 * D * 2;
+template <int D, int SPLIT, bool EXACT = false>
+int fwd_launch_rows(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
+  constexpr int merge = SPLIT == 2 ? FWD_WAVES * (2 * (D / 32) * 1024 + 512) : 0, ring = FWD_RING * 2 * Tile<D>::BYTES, smem = ring > merge ? ring : merge;
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    if (hipFuncSetAttribute((const void *)attn_fwd_kernel<D, G, EXACT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) !=
-        hipSuccess)
-      return MTNLG_HIP_ERROR;
+    MTNLG_TRY(set_lds(attn_fwd_kernel<D, SPLIT, EXACT>, smem));
     attr_mark_set(attr_done, device);
   }
-  const int count = PairedBlocks<G>::count(s), group = HeadBlock::group(b, n, count, 32, D >= 128 ? 511 : 768);   // (768: 3 a compute unit)
+  constexpr int EACH = D <= 64 ? 4 : 2, ALL = 256 * EACH;   // workgroups to a compute unit, and on the chip at once
+  const int count = own_blocks(s, 32 * FWD_WAVES / SPLIT), group = HeadBlock::group(b, n, count, 32, ALL);
   LaunchScope scope(MTNLG_K_ATTN_FWD, st);
-  attn_fwd_kernel<D, G, EXACT><<<HeadBlock::grid(b, n, group, count), 512, smem, st>>>(b, s, n, d, group, scale, (const bf16 *)qkv, (bf16 *)a, lse);
+  attn_fwd_kernel<D, SPLIT, EXACT><<<HeadBlock::grid(b, n, group, count), 64 * FWD_WAVES, smem, st>>>(
+      ForwardArgs{b, s, n, d, group, (int64_t)b * n * count <= ALL, scale, (const bf16 *)qkv, (bf16 *)a, lse});
   return check_launch();
 }
 
+// Workgroups of 128 queries halve the tiles' way into LDS and what a workgroup costs besides its tiles; those of 64 even out better, and where all run at once a full
+// round of either does better than a part of one.  By workgroups of 128; us with 64 / 128 queries: head size 128: 64 heads, s = 1024 (512) 30.4 / 29.8; 128, 768 (768) 36.9 /
+// 42.1; 48, 2048 (768) 70.1 / 70.4; 256, 512 (1024) 39.1 / 37.8; 128, 2048 (2048) 174 / 165; 512, 768 (3072) 155 / 134; 160: 64, 1024 (512) 37.6 / 35.0; 128, 768 (768) 45.0 / 49.8; 64, 2048
+// (1024) 108 / 101; 512, 768 (3072) 194 / 166.  Head size 64, four workgroups to a unit: 64, 2048 (1024) 60.4 / 50.6; 128, 1024 (1024) 33.6 / 30.6; 256, 512 (1024) 23.1 / 22.3; but 512, 256
+// (1024) 17.8 / 18.7; 48, 2048 (768) 39.0 / 50.1; 512, 768 (3072) 72.4 / 75.8.
 template <int D>
 int fwd_launch(int b, int s, int n, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
-  if (D >= 128 && (int64_t)PairedBlocks<2>::count(s) * n * b >= 256) return fwd_launch_g<D, 2>(b, s, n, D, scale, qkv, a, lse, st);
-  return fwd_launch_g<D, 1>(b, s, n, D, scale, qkv, a, lse, st);
+  const int64_t large = (int64_t)b * n * own_blocks(s, 128);
+  const bool rows128 = D == 64 ? large > 896 && large <= 1024 && s >= 512 : large >= 1024 || (large > 448 && large <= 512);
+  if (rows128) return fwd_launch_rows<D, 1>(b, s, n, D, scale, qkv, a, lse, st);
+  return fwd_launch_rows<D, 2>(b, s, n, D, scale, qkv, a, lse, st);
 }
 
 }  // namespace
@@ -346,9 +323,14 @@ bool attention_exact_bwd_takes(int dtype, int b, int s, int n, int d, const void
 }
 
 int attention_fwd_exact(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream) {
-#define FWD(D) fwd_launch_g<D, 1, true>
-  BY_HEAD_SIZE(FWD, b, s, n, d, scale, qkv, a, lse, stream)
-#undef FWD
+  // 16 rows to a wave where that is as fast or faster: up to head size 32, above 160, and from 65 to 96 with many blocks of 64 rows.  us, those / these: 64 heads, s = 1536, of 32
+  // 42 / 47; 16, 2048 of 192 62 / 76; of 96 32, 1024 (512 blocks) 24.3 / 22.3; 48, 1024 (768) 32.8 / 31.7; 96, 512 (768) 20.8 / 24.1; 64, 1024 (1024) 34.4 / 38.7; 64, 2048
+  // (2048) 108 / 118.  The others: 64, 1024 of 48 29.6 / 26.9; 4, 2048 of 104 42.2 / 36.3; 64, 2048 of 120 161 / 140, of 144 181 / 164.
+  if (d <= 32 || d > 160 || (d > 64 && d <= 96 && (int64_t)b * n * row_blocks(s) >= 704)) return attention_fwd_exact16(b, s, n, d, scale, qkv, a, lse, stream);
+  if (d <= 64) return fwd_launch_rows<64, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);
+  if (d <= 96) return fwd_launch_rows<96, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);
+  if (d <= 128) return fwd_launch_rows<128, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);
+  return fwd_launch_rows<160, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);
 }
 
 }  // namespace mtnlg

@@ -309,12 +309,41 @@ __device__ __forceinline__ float quad_max(float v) {
   return fmaxf(__builtin_bit_cast(float, q0), __builtin_bit_cast(float, q1));
 }
 
+// maximum over the two lanes that share lane % 32
+__device__ __forceinline__ float pair_max(float v) {
+  typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+  const unsigned a = __builtin_bit_cast(unsigned, v);
+  const u32x2 p = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(a, a, false, false));
+  const unsigned p0 = p[0], p1 = p[1];
+  return fmaxf(__builtin_bit_cast(float, p0), __builtin_bit_cast(float, p1));
+}
+
+// EXACT with SPLIT 2, where waves `wave` and wave ^ 2 have stored half of a result's columns each: the slow path computes whole rows, so the wave of part 0
+// takes it if either has found a result that is not finite (z: NaN), after what both have stored.
+__device__ __forceinline__ float either_part(float z, char *smem, int wave, int other, int part, int lane) {
+  __syncthreads();   // LDS is free
+  int *bad = reinterpret_cast<int *>(smem);
+  const bool any = __builtin_amdgcn_ballot_w64(z != 0.0f) != 0;
+  if (lane == 0) bad[wave] = any;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  return part == 0 && (bad[wave] | bad[other]) ? NAN : 0.0f;
+}
+
 // Number of a wave's IPW DMA instructions that go out by step `step` of the STEPS MFMA steps of a tile (both runs counted):
 // spread evenly, because the texture path takes 16 cycles for each and a wave that meets a full queue waits.
 template <int IPW, int STEPS>
 constexpr int dma_by(int step) { return ((step + 1) * IPW + STEPS - 1) / STEPS; }
 
 __host__ __device__ inline int row_blocks(int s) { return (s + 63) / 64; }
+__host__ __device__ inline int own_blocks(int s, int owned) { return (s + owned - 1) / owned; }   // workgroups to a head
+
+// Where all workgroups run at once, several to a compute unit, places i, 256 + i, 512 + i share one: every other 256 go out in the opposite order, so that
+// the units' work comes out even.
+__device__ __forceinline__ int in_turns(int order, int count, int heads) {
+  const int each = (255 + heads) / heads, turn = order / each, first = turn * each, end = first + each < count ? first + each : count;
+  return turn & 1 ? end - 1 - (order - first) : order;
+}
 
 // Which head a workgroup works on, and at which place of the head's order of blocks.  The heads of all sequences are numbered
 // through and a grid row takes `group` of them, heads fastest: with a multiple of 8 all workgroups of a head run on one XCD (they

@@ -401,13 +401,15 @@ int attention_fwd_mfma(int b, int s, int n, int d, float scale, const void *qkv,
                        hipStream_t stream);
 int attention_bwd_mfma(int b, int s, int n, int d, float scale, const void *qkv, const void *a,
                        const float *lse, const void *da, void *dqkv, void *ws, hipStream_t stream);
-int attention_bwd64(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
-                    hipStream_t stream);   // of head size 64
 // ... with P and dS in fp32, for the other head sizes (bf16): whether these kernels are the faster ones, and can take the call
 bool attention_exact_fwd_takes(int dtype, int b, int s, int n, int d, const void *qkv, const void *a);
 bool attention_exact_bwd_takes(int dtype, int b, int s, int n, int d, const void *qkv, const void *a, const void *da, const void *dqkv);
 int attention_fwd_exact(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream);
 int attention_bwd_exact(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                         void *dqkv, void *ws, hipStream_t stream);
+// 16 rows to a wave (attention_fwd16.hip, attention_bwd64.hip), called by those above where that is the faster
+int attention_fwd_exact16(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream);
+int attention_bwd64(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
+                    hipStream_t stream);   // of head size 64
 
 }  // namespace mtnlg

@@ -625,6 +625,26 @@ def test_attention_backward_by_rows_of_a_workgroup(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
+# Forward by workgroups of 64 and of 128 own rows: either side of the rules (by workgroups of 128 rows: 448, 512 and 1024; head size 64: 896 and 1024, s from 512 on), sequences
+# that end at the edges of a 32-row part, of a tile and of the own rows, two rows (with one dq is the rounding of dP - D) and one head.
+@pytest.mark.parametrize("b,s,n,d", [(1, 2, 1, 128), (2, 31, 3, 160), (1, 33, 2, 64), (1, 64, 448, 128), (3, 65, 150, 160), (1, 97, 512, 128), (1, 96, 513, 160),
+                                     (1, 129, 511, 128), (4, 127, 256, 160), (1, 161, 256, 128), (1, 257, 342, 128), (1, 513, 180, 64), (2, 545, 102, 64), (1, 640, 205, 64)])
+def test_attention_forward_by_rows_of_a_workgroup(b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
+
+
+# With fp32 weights, on 16 or 32 rows to a wave: either side of the rule (704 blocks of 64 rows).
+@pytest.mark.parametrize("b,s,n,d", [(3, 100, 30, 24), (1, 65, 383, 40), (2, 96, 192, 56), (1, 127, 351, 72), (1, 97, 352, 88), (1, 33, 2047, 96), (1, 95, 1024, 104),
+                                     (1, 129, 683, 152), (2, 161, 342, 80), (1, 513, 17, 112), (1, 35, 2048, 184)])
+def test_attention_with_exact_weights_by_rows(b, s, n, d):
+    test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
+
+
+@pytest.mark.parametrize("n,d", [(44, 24), (352, 88), (384, 40), (1024, 120)])
+def test_attention_with_exact_weights_by_rows_non_finite_token(n, d):
+    check_non_finite_token("bf16", n, d, 37, float("inf"), M.mtnlg_attention_fwd, M.mtnlg_attention_bwd)
+
+
 # The same for the kernels without LDS: fp32 and small bf16 calls on either side of the rules (512, 256 and 128 groups of 16 rows), head sizes that have
 # no such launch, one row (dq is exactly zero).
 @pytest.mark.parametrize("dtype,b,s,n,d", [("fp32", 1, 1, 1, 64), ("fp32", 1, 64, 128, 96), ("fp32", 1, 64, 129, 96), ("fp32", 2, 127, 16, 128),
