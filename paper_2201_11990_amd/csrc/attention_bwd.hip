@@ -714,6 +714,15 @@ int bwd_launch(int b, int s, int n, float scale, const void *qkv, const void *a,
   return bwd_launch_p<D, 2>(b, s, n, D, scale, qkv, a, lse, da, dqkv, ws, st);
 }
 
+// EXACT: 128 own rows to a workgroup from 2048 blocks of 64 rows on.  us, 64 / 128 rows: of 96 64 heads, s = 1024 (1024) 109 / 123, 64, 2048 (2048) 359 / 350, 512, 512 309 /
+// 270; of 144 48, 2048 (1536) 411 / 401, 96, 1024 (1536) 249 / 257, 64, 2048 (2048) 561 / 526; of 104 1024, 256 279 / 265.
+template <int D>
+int exact_launch(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
+                 hipStream_t st) {
+  if ((int64_t)b * n * row_blocks(s) >= 2048) return bwd_launch_p<D, 1, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
+  return bwd_launch_p<D, 2, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
+}
+
 }  // namespace
 
 int attention_bwd_mfma(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse,
@@ -729,9 +738,15 @@ int attention_bwd_mfma(int b, int s, int n, int d, float scale, const void *qkv,
 
 int attention_bwd_exact(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                         void *dqkv, void *ws, hipStream_t stream) {
-#define BWD(D) bwd_launch_p<D, 2, true>
-  BY_HEAD_SIZE(BWD, b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream)
-#undef BWD
+  // 16 rows to a wave up to head size 32, and to 64 from 768 blocks of 64 rows on: us, those / these, 16 heads of 32, s = 2 x 1024 39.4 / 42.3; of 48 32, 1024 (512 blocks)
+  // 47.9 / 45.7, 48, 1024 (768) 60.9 / 68.3, 64, 2048 (2048) 240 / 267.
+  const int64_t blocks = (int64_t)b * n * row_blocks(s);
+  if (d <= 32 || (d <= 64 && blocks >= 768)) return attention_bwd_exact64(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
+  if (d <= 64) return bwd_launch_p<64, 2, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
+  if (d <= 96) return exact_launch<96>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
+  if (d <= 128) return exact_launch<128>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
+  if (d <= 160) return exact_launch<160>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
+  return bwd_launch_p<192, 2, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
 }
 
 }  // namespace mtnlg

@@ -1,4 +1,5 @@
-// Backward of the fused causal attention for bf16 head size 64 (the others: attention_bwd.hip), tiles and fragments as in the forward kernel (attention_mfma.hip).
+// Backward of the fused causal attention for bf16 head size 64 and, with P and dS in fp32 (EXACT), for the smaller ones (the others: attention_bwd.hip), with the tiles and fragments of
+// attention_fwd16.hip.
 //
 // dP = da v^T,  dS = P o (dP - D) with D_t = da_t . a_t,  dq = scale dS k,  dk = scale dS^T q,  dv = P^T da, on 16x16x32 MFMAs with 16 own rows to a wave:
 //   dq      : S^T and dP^T = V dO^T with the query on the lane column, dQ^T += K^T dS^T.
@@ -11,8 +12,6 @@
 namespace mtnlg {
 
 namespace {
-
-constexpr int D = 64;
 
 // The backward kernels: a workgroup owns one 64-row block (queries for dq, keys for dk / dv), 16 rows to each of waves 0-3
 // and again to waves 4-7: the two halves of the workgroup take the first and the last 32 rows of every streamed
@@ -45,7 +44,7 @@ __device__ __forceinline__ f32x4 *merge_slots(char *smem, int wave, int lane, in
 
 // ------------------------------------------------------------------ backward: dq (and D)
 struct BackwardArgs {
-  int b, s, n, group;
+  int b, s, n, head_dim, group;
   float scale;
   const bf16 *qkv, *a;
   const float *lse;
@@ -54,8 +53,8 @@ struct BackwardArgs {
   float *Dvec;
 };
 
-template <bool PAIRED>
-__device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int s, int n, int group, float scale,
+template <int D, bool PAIRED, bool EXACT>
+__device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int s, int n, int head_dim, int group, float scale,
                                          const bf16 *__restrict__ qkv, const bf16 *__restrict__ a, const float *__restrict__ lse,
                                          const bf16 *__restrict__ da, bf16 *__restrict__ dqkv, float *__restrict__ Dvec) {
   using T = Tile<D>;
@@ -68,35 +67,45 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int 
   const BackwardBlocks<PAIRED> bb(s, PAIRED ? hb.order : row_blocks(s) - 1 - hb.order, threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
-  const int d = D;
+  const int d = EXACT ? head_dim : D;
   const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
   const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * d;
   const int qw = bb.block * 64 + ((threadIdx.x >> 6) & 3) * 16;
   const int k_half = PAIRED ? 0 : (wave >> 2) * 32;   // first key of a tile that this wave takes
-  const float f = scale * kLog2e;
+  const float f = EXACT ? scale : scale * kLog2e;
   typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
   const int q = qw + lr, qc = q < s ? q : s - 1;
   bf16x8 qf[KK], dof[KK];
   float dsum = 0.0f;
+  f32x4 diag = {0.0f, 0.0f, 0.0f, 0.0f};
   const bf16 *dah = da + (int64_t)bi * s * pld + (int64_t)j * d;
   {
     const bf16 *ar = a + ((int64_t)bi * s + qc) * pld + (int64_t)j * d;
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       const int col = 32 * kk + 8 * g;
-      qf[kk] = row_chunk<false>(base + (int64_t)qc * ld, col, d);
-      dof[kk] = row_chunk<false>(dah + (int64_t)qc * pld, col, d);
-      const bf16x8 av = row_chunk<false>(ar, col, d);
+      qf[kk] = row_chunk<EXACT>(base + (int64_t)qc * ld, col, d);
+      dof[kk] = row_chunk<EXACT>(dah + (int64_t)qc * pld, col, d);
+      const bf16x8 av = row_chunk<EXACT>(ar, col, d);
+      if constexpr (EXACT) {   // D on the diagonal of a dO^T, by the same MFMAs as dP: where a row has one key (a = v) the two cancel exactly
+        diag = MFMA16(av, dof[kk], diag);
+      } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) dsum += (float)dof[kk][i] * (float)av[i];
+        for (int i = 0; i < 8; ++i) dsum += (float)dof[kk][i] * (float)av[i];
+      }
     }
-    dsum = quad_sum(dsum);
+    if constexpr (EXACT) {
+      const float mine = (lr & 2) ? ((lr & 1) ? diag[3] : diag[2]) : ((lr & 1) ? diag[1] : diag[0]);
+      dsum = __shfl(mine, 16 * (lr >> 2) + lr, 64);
+    } else {
+      dsum = quad_sum(dsum);
+    }
   }
   float lsf = lse[((int64_t)bi * n + j) * s + qc];
-  lsf *= kLog2e;
-  if (q < s && g == 0 && (PAIRED ? !bb.idle : wave < 4)) Dvec[((int64_t)bi * n + j) * s + q] = -dsum;   // as the dk/dv kernel starts its accumulators
+  if constexpr (!EXACT) lsf *= kLog2e;
+  if (q < s && g == 0 && (PAIRED ? !bb.idle : wave < 4)) Dvec[((int64_t)bi * n + j) * s + q] = EXACT ? dsum : -dsum;   // as the dk/dv kernel starts its accumulators, or subtracts it
 
   f32x4 dq[DB];
 #pragma unroll
@@ -147,10 +156,10 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int 
     if (bb.idle || kv0 > qw + 15) {
       issue(nn);
     } else {
-      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D
+      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D (EXACT: dP)
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb) {
-        const float start = -dsum;
+        const float start = EXACT ? 0.0f : -dsum;
         pc[kb] = f32x4{start, start, start, start};
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[kb][e] = 0.0f;
@@ -194,10 +203,10 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int 
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sc[kb][e] = weight<false>(sc[kb][e], f, lsf) * pc[kb][e];
-      Parts<1> df[NS];
+        for (int e = 0; e < 4; ++e) sc[kb][e] = weight<EXACT>(sc[kb][e], f, lsf) * (EXACT ? pc[kb][e] - dsum : pc[kb][e]);
+      Parts<EXACT ? 3 : 1> df[NS];
 #pragma unroll
-      for (int ks = 0; ks < NS; ++ks) df[ks] = weights<false>(sc[2 * ks], sc[2 * ks + 1]);
+      for (int ks = 0; ks < NS; ++ks) df[ks] = weights<EXACT>(sc[2 * ks], sc[2 * ks + 1]);
       pipelined_run<NS * HB, PT>(
           load,
           [&](int i) {
@@ -212,11 +221,14 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int 
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   bf16 *out = dqkv + ((int64_t)bi * s + q) * ld + (int64_t)j * 3 * d;
+  float z = 0.0f;   // EXACT: NaN where a result is not finite
   auto store = [&](int db, const f32x4 &sum) {
+    if (EXACT && db * 16 + 4 * g >= d) return;
     bf16x4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float x = sum[e] * scale;
+      const float x = (EXACT ? sum[e] * PARTS_UNSCALE : sum[e]) * scale;
+      if constexpr (EXACT) z = fmaf(x, 0.0f, z);
       v[e] = (bf16)x;
     }
     *reinterpret_cast<bf16x4 *>(out + db * 16 + 4 * g) = v;
@@ -239,15 +251,19 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int 
 #pragma unroll
     for (int db = 0; db < DB; ++db) store(db, dq[db] + slots[db * 64]);
   }
+  if constexpr (EXACT) {
+    if (wave < 4 && !all_finite(z))
+      redo_dq<bf16, D>(base, ld, dah, pld, s, d, scale, q, qw + 15 < s ? qw + 15 : s - 1, lse[((int64_t)bi * n + j) * s + qc], dsum, g, out);
+  }
 }
 
 // ------------------------------------------------------------------ backward: dk, dv
 // OWN_D: D is computed here (a: read then), not taken from the dq kernel.
-template <bool PAIRED, bool OWN_D>
-__device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int s, int n, int group, float scale,
+template <int D, bool PAIRED, bool EXACT, bool OWN_D>
+__device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int s, int n, int head_dim, int group, float scale,
                                           const bf16 *__restrict__ qkv, const bf16 *__restrict__ a, const float *__restrict__ lse,
                                           const float *__restrict__ Dvec, const bf16 *__restrict__ da, bf16 *__restrict__ dqkv) {
-  static_assert(!OWN_D || !PAIRED, "as it is used");
+  static_assert(!OWN_D || (!PAIRED && !EXACT), "as it is used");
   using T = Tile<D>;
   constexpr int KK = D / 32, DB = D / 16, STAGE = 2 * T::BYTES + 512;   // Q tile, dO tile, lse[64], D[64]
   constexpr int NB = PAIRED ? 4 : 2, NS = NB / 2;   // as in the dq kernel
@@ -257,13 +273,13 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
   const BackwardBlocks<PAIRED> bb(s, hb.order, threadIdx.x >> 6);   // (from the thread number; head size 160: 194 registers instead of 230)
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
-  const int d = D;
+  const int d = EXACT ? head_dim : D;
   const int64_t ld = (int64_t)n * 3 * d, pld = (int64_t)n * d;
   const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * d;
   const bf16 *dab = da + (int64_t)bi * s * pld + (int64_t)j * d;
   const int kw = bb.block * 64 + ((threadIdx.x >> 6) & 3) * 16;
   const int q_half = PAIRED ? 0 : (wave >> 2) * 32;   // first query of a tile that this wave takes
-  const float f = scale * kLog2e;
+  const float f = EXACT ? scale : scale * kLog2e;
   typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
@@ -271,8 +287,8 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
   bf16x8 kf[KK], vf[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
-    kf[kk] = row_chunk<false>(base + (int64_t)keyc * ld + d, 32 * kk + 8 * g, d);
-    vf[kk] = row_chunk<false>(base + (int64_t)keyc * ld + 2 * d, 32 * kk + 8 * g, d);
+    kf[kk] = row_chunk<EXACT>(base + (int64_t)keyc * ld + d, 32 * kk + 8 * g, d);
+    vf[kk] = row_chunk<EXACT>(base + (int64_t)keyc * ld + 2 * d, 32 * kk + 8 * g, d);
   }
   f32x4 dk[DB], dv[DB];
 #pragma unroll
@@ -352,10 +368,11 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
     if (bb.idle || q0 + 16 * NB - 1 < kw) {  // wave-uniform: none of this wave's queries sees one of its keys
       issue(nn);
     } else {
-      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D
+      f32x4 sc[NB], pc[NB];   // pc accumulates dP - D (EXACT: dP)
 #pragma unroll
       for (int qb = 0; qb < NB; ++qb) {
-        pc[qb] = *reinterpret_cast<const f32x4 *>((OWN_D ? own_d + it * 64 + q_half : stat + 64) + 16 * qb + 4 * g);
+        if constexpr (EXACT) pc[qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        else pc[qb] = *reinterpret_cast<const f32x4 *>((OWN_D ? own_d + it * 64 + q_half : stat + 64) + 16 * qb + 4 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc[qb][e] = 0.0f;
       }
@@ -399,18 +416,19 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
       }
 #pragma unroll
       for (int qb = 0; qb < NB; ++qb) {
+        if constexpr (EXACT) pc[qb] -= *reinterpret_cast<const f32x4 *>(stat + 64 + 16 * qb + 4 * g);
         const f32x4 ls = *reinterpret_cast<const f32x4 *>(stat + 16 * qb + 4 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          sc[qb][e] = weight<false>(sc[qb][e], f, ls[e] * kLog2e);
+          sc[qb][e] = weight<EXACT>(sc[qb][e], f, EXACT ? ls[e] : ls[e] * kLog2e);
           pc[qb][e] *= sc[qb][e];
         }
       }
-      Parts<1> pf[NS], df[NS];
+      Parts<EXACT ? 3 : 1> pf[NS], df[NS];
 #pragma unroll
       for (int ks = 0; ks < NS; ++ks) {
-        pf[ks] = weights<false>(sc[2 * ks], sc[2 * ks + 1]);
-        df[ks] = weights<false>(pc[2 * ks], pc[2 * ks + 1]);
+        pf[ks] = weights<EXACT>(sc[2 * ks], sc[2 * ks + 1]);
+        df[ks] = weights<EXACT>(pc[2 * ks], pc[2 * ks + 1]);
       }
       pipelined_run<NS * DB, PT>(
           load,
@@ -425,12 +443,16 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   bf16 *out = dqkv + ((int64_t)bi * s + key) * ld + (int64_t)j * 3 * d;
+  float z = 0.0f;   // EXACT: NaN where a result is not finite
   auto store = [&](int db, const f32x4 &sk, const f32x4 &sv) {
+    if (EXACT && db * 16 + 4 * g >= d) return;
     bf16x4 ok, ov;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      ok[e] = (bf16)(sk[e] * scale);
-      ov[e] = (bf16)sv[e];
+      const float x = (EXACT ? sk[e] * PARTS_UNSCALE : sk[e]) * scale, y = EXACT ? sv[e] * PARTS_UNSCALE : sv[e];
+      if constexpr (EXACT) z = fmaf(x, 0.0f, fmaf(y, 0.0f, z));
+      ok[e] = (bf16)x;
+      ov[e] = (bf16)y;
     }
     *reinterpret_cast<bf16x4 *>(out + d + db * 16 + 4 * g) = ok;
     *reinterpret_cast<bf16x4 *>(out + 2 * d + db * 16 + 4 * g) = ov;
@@ -456,37 +478,44 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
 #pragma unroll
     for (int db = 0; db < DB; ++db) store(db, dk[db] + slots[db * 64], dv[db] + slots[(DB + db) * 64]);
   }
+  if constexpr (EXACT) {
+    if (wave < 4 && !all_finite(z)) {
+      const int64_t st = ((int64_t)bi * n + j) * s;
+      redo_dk<bf16, D>(base, ld, dab, pld, s, d, scale, kw, key, lse + st, [&](int t) { return Dvec[st + t]; }, g, out);
+      redo_dv<bf16, D>(base, ld, dab, pld, s, d, scale, kw, key, lse + st, g, out);
+    }
+  }
 }
 
-template <bool PAIRED>
+template <int D, bool PAIRED, bool EXACT>
 __global__ __launch_bounds__(512) void attn_bwd64_dq_kernel(BackwardArgs w) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  dq_block<PAIRED>(blockIdx.x, smem, w.b, w.s, w.n, w.group, w.scale, w.qkv, w.a, w.lse, w.da, w.dqkv, w.Dvec);
+  dq_block<D, PAIRED, EXACT>(blockIdx.x, smem, w.b, w.s, w.n, w.head_dim, w.group, w.scale, w.qkv, w.a, w.lse, w.da, w.dqkv, w.Dvec);
 }
-template <bool PAIRED>
+template <int D, bool PAIRED, bool EXACT>
 __global__ __launch_bounds__(512) void attn_bwd64_dkv_kernel(BackwardArgs w) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  dkv_block<PAIRED, false>(blockIdx.x, smem, w.b, w.s, w.n, w.group, w.scale, w.qkv, w.a, w.lse, w.Dvec, w.da, w.dqkv);
+  dkv_block<D, PAIRED, EXACT, false>(blockIdx.x, smem, w.b, w.s, w.n, w.head_dim, w.group, w.scale, w.qkv, w.a, w.lse, w.Dvec, w.da, w.dqkv);
 }
 // Both in one launch (attention_bwd64 says when): the first half of a grid row's workgroups (dk / dv, the longer ones) compute D for themselves.
 __global__ __launch_bounds__(512) void attn_bwd64_kernel(BackwardArgs w) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const unsigned half = gridDim.x / 2;
   if (blockIdx.x < half)
-    dkv_block<false, true>(blockIdx.x, smem, w.b, w.s, w.n, w.group, w.scale, w.qkv, w.a, w.lse, nullptr, w.da, w.dqkv);
+    dkv_block<64, false, false, true>(blockIdx.x, smem, w.b, w.s, w.n, w.head_dim, w.group, w.scale, w.qkv, w.a, w.lse, nullptr, w.da, w.dqkv);
   else
-    dq_block<false>(blockIdx.x - half, smem, w.b, w.s, w.n, w.group, w.scale, w.qkv, w.a, w.lse, w.da, w.dqkv, w.Dvec);
+    dq_block<64, false, false>(blockIdx.x - half, smem, w.b, w.s, w.n, w.head_dim, w.group, w.scale, w.qkv, w.a, w.lse, w.da, w.dqkv, w.Dvec);
 }
 
-template <bool PAIRED>
+template <int D, bool PAIRED, bool EXACT>
 int launch_two(const BackwardArgs &in, hipStream_t st) {
-  constexpr int smem_dq = 3 * 2 * 64 * D * 2, smem_dkv = 3 * (2 * 64 * D * 2 + 512);
+  constexpr int smem_dq = 3 * 2 * Tile<D>::BYTES, smem_dkv = smem_dq + 3 * 512;
   static_assert(smem_dkv >= 4 * 2 * (D / 16) * 1024, "the merge of the two halves fits the rings");
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    MTNLG_TRY(set_lds(attn_bwd64_dq_kernel<PAIRED>, smem_dq));
-    MTNLG_TRY(set_lds(attn_bwd64_dkv_kernel<PAIRED>, smem_dkv));
+    MTNLG_TRY(set_lds(attn_bwd64_dq_kernel<D, PAIRED, EXACT>, smem_dq));
+    MTNLG_TRY(set_lds(attn_bwd64_dkv_kernel<D, PAIRED, EXACT>, smem_dkv));
     attr_mark_set(attr_done, device);
   }
   BackwardArgs w = in;
@@ -494,9 +523,9 @@ int launch_two(const BackwardArgs &in, hipStream_t st) {
   w.group = HeadBlock::group(w.b, w.n, count, PAIRED ? 32 : 128, PAIRED ? 511 : 2047);
   const dim3 grid = HeadBlock::grid(w.b, w.n, w.group, count);
   LaunchScope scope(MTNLG_K_ATTN_BWD, st);
-  attn_bwd64_dq_kernel<PAIRED><<<grid, 512, smem_dq, st>>>(w);
+  attn_bwd64_dq_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dq, st>>>(w);
   MTNLG_TRY(check_launch());
-  attn_bwd64_dkv_kernel<PAIRED><<<grid, 512, smem_dkv, st>>>(w);
+  attn_bwd64_dkv_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dkv, st>>>(w);
   return check_launch();
 }
 
@@ -505,7 +534,7 @@ int launch_one(const BackwardArgs &in, hipStream_t st) {
   BackwardArgs w = in;
   const int count = row_blocks(w.s);
   w.group = HeadBlock::group(w.b, w.n, count, 32, 2047);
-  constexpr int rings = 3 * (2 * 64 * D * 2 + 512);
+  constexpr int rings = 3 * (2 * Tile<64>::BYTES + 512);
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
@@ -528,9 +557,15 @@ int launch_one(const BackwardArgs &in, hipStream_t st) {
 // 1.19 times as fast, 768 1.11, 1024 0.96 (two blocks of 70 to 128 rows: 256 1.22 to 1.35, 384 0.92 to 1.10, 512 0.92 to 1.01, 768 1.13 to 1.20).  Beyond s 960 D takes the LDS of
 // the third workgroup: up to 256 blocks 1.19 to 1.44 times as fast from s 1030 to 4096, 384 1.11 to 1.33, 512 0.92 to 1.17, 768 0.94 to 1.06.
 int attention_bwd64(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws, hipStream_t st) {
-  const BackwardArgs w{b, s, n, 0, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da, (bf16 *)dqkv, (float *)ws};
+  const BackwardArgs w{b, s, n, 64, 0, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da, (bf16 *)dqkv, (float *)ws};
   if (s <= ONE_LAUNCH_ROWS && (int64_t)b * n * row_blocks(s) <= (s > 1024 ? 256 : 768)) return launch_one(w, st);
-  return row_blocks(s) == 2 ? launch_two<true>(w, st) : launch_two<false>(w, st);
+  return row_blocks(s) == 2 ? launch_two<64, true, false>(w, st) : launch_two<64, false, false>(w, st);
+}
+
+int attention_bwd_exact64(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
+                          hipStream_t st) {
+  const BackwardArgs w{b, s, n, d, 0, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da, (bf16 *)dqkv, (float *)ws};
+  return d <= 32 ? launch_two<32, false, true>(w, st) : launch_two<64, false, true>(w, st);
 }
 
 }  // namespace mtnlg

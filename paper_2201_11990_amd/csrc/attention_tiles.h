@@ -387,18 +387,6 @@ int set_lds(K kernel, int bytes) {
   return hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess ? MTNLG_OK : MTNLG_HIP_ERROR;
 }
 
-// fn<D>, D: the head size rounded up to a multiple of 32
-#define BY_HEAD_SIZE(fn, ...)                                  \
-  switch ((d + 31) / 32) {                                     \
-    case 1: return fn(32)(__VA_ARGS__);                        \
-    case 2: return fn(64)(__VA_ARGS__);                        \
-    case 3: return fn(96)(__VA_ARGS__);                        \
-    case 4: return fn(128)(__VA_ARGS__);                       \
-    case 5: return fn(160)(__VA_ARGS__);                       \
-    case 6: return fn(192)(__VA_ARGS__);                       \
-    default: return MTNLG_UNSUPPORTED_SHAPE;                   \
-  }
-
 }  // namespace
 
 }  // namespace mtnlg

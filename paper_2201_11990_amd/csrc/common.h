@@ -411,5 +411,7 @@ int attention_bwd_exact(int b, int s, int n, int d, float scale, const void *qkv
 int attention_fwd_exact16(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream);
 int attention_bwd64(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
                     hipStream_t stream);   // of head size 64
+int attention_bwd_exact64(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv,
+                          void *ws, hipStream_t stream);   // up to 64
 
 }  // namespace mtnlg

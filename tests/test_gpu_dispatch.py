@@ -633,7 +633,7 @@ def test_attention_forward_by_rows_of_a_workgroup(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
-# With fp32 weights, on 16 or 32 rows to a wave: either side of the rule (704 blocks of 64 rows).
+# With fp32 weights, forward and backward on 16 or 32 rows to a wave and 64 or 128 to a workgroup: either side of the rules (704, 768 and 2048 blocks of 64 rows).
 @pytest.mark.parametrize("b,s,n,d", [(3, 100, 30, 24), (1, 65, 383, 40), (2, 96, 192, 56), (1, 127, 351, 72), (1, 97, 352, 88), (1, 33, 2047, 96), (1, 95, 1024, 104),
                                      (1, 129, 683, 152), (2, 161, 342, 80), (1, 513, 17, 112), (1, 35, 2048, 184)])
 def test_attention_with_exact_weights_by_rows(b, s, n, d):
