@@ -318,7 +318,7 @@ __device__ __forceinline__ float pair_max(float v) {
   return fmaxf(__builtin_bit_cast(float, p0), __builtin_bit_cast(float, p1));
 }
 
-// EXACT with SPLIT 2, where waves `wave` and wave ^ 2 have stored half of a result's columns each: the slow path computes whole rows, so the wave of part 0
+// EXACT with SPLIT 2, where waves `wave` and `other` have stored half of a result's columns each: the slow path computes whole rows, so the wave of part 0
 // takes it if either has found a result that is not finite (z: NaN), after what both have stored.
 __device__ __forceinline__ float either_part(float z, char *smem, int wave, int other, int part, int lane) {
   __syncthreads();   // LDS is free
