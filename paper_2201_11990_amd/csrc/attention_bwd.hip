@@ -1,4 +1,5 @@
-// Backward of the fused causal attention (attention_mfma.hip: forward), for bf16 head sizes 128 and 160 and, with P and dS in fp32 (EXACT), the others up to 192.
+// Backward of the fused causal attention (attention_mfma.hip: forward), for bf16 head sizes 128 and 160 and, with P and dS in fp32 (EXACT), most of
+// the others up to 192 (attention_bwd64.hip: the small ones).
 //
 //   D_t = da_t . a_t:  dP = da v^T,  dS = P o (dP - D),  dq = scale dS k,  dk = scale dS^T q,  dv = P^T da.
 //

@@ -1,5 +1,5 @@
-// What the tiled attention kernels share (attention_mfma.hip: forward; attention_bwd.hip, attention_bwd64.hip: backward): tiles in LDS and the streams that fill
-// them, fragments, weights, the order of the grid.
+// What the tiled attention kernels share (attention_mfma.hip, attention_fwd16.hip: forward; attention_bwd.hip, attention_bwd64.hip: backward): tiles in LDS and the
+// streams that fill them, fragments, weights, the order of the grid.
 #pragma once
 #include <math.h>
 
