@@ -461,6 +461,11 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, const Back
         for (int e = 0; e < 4; ++e) p[4 * q + e] = v[e];
       }
     };
+    // LAG: the first tile has none before it.  Its products are with zeros, P among them: LDS holds what was there before
+    if constexpr (LAG && me == 1) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xchg[(odd ^ 1) * (L::XCHG / 16) + q * 64] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
     f32x16 dn_all;   // EXACT: D of this tile's rows, and of the one before
     f32x16 dn_prev = {};
     auto gradient = [&](float p, float dp, float dd) { return (EXACT ? dp - dd : dp) * p; };

@@ -723,6 +723,30 @@ def check_non_finite_token(dtype, n, d, t0, bad, attention_fwd, attention_bwd):
                 assert not bool(torch.isfinite(dx[0, :t0 + 1, 1, 2, col].float()).any())
 
 
+# Backward at head sizes 128 and 160, one launch and two, 64 and 128 own rows: an infinity in V of one key, with a and lse from before it, enters dP of that key only;
+# so dk of the other keys, and all of dv, keep every bit (dk / dv hands P on through LDS that V of its own rows came through).
+@pytest.mark.parametrize("b,s,n,d", [(1, 64, 6, 128), (1, 64, 330, 128), (1, 128, 400, 128), (1, 64, 330, 160), (1, 128, 400, 160)])
+def test_attention_backward_infinity_in_one_key(b, s, n, d):
+    qkv, da = randn((b * s, n, 3, d), "bf16", 53), dev(randn((b * s, n * d), "bf16", 54))
+    x, a, lse = dev(qkv.reshape(b * s, -1)), torch.empty_like(da), torch.empty((b, n, s), device="cuda")
+    ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+    M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), x, a, lse)
+
+    def backward(x):
+        dx = torch.full_like(x, 7.0)
+        M.mtnlg_attention_bwd(b, s, n, d, 1.0 / math.sqrt(d), x, a, lse, da, dx, ws)
+        return dx.reshape(s, n, 3, d)
+
+    want = backward(x)
+    for key in (3, s - 28):
+        bad = x.clone()
+        bad.reshape(s, n, 3, d)[key, 1, 2, 5] = float("inf")
+        got = backward(bad)
+        others = [t for t in range(s) if t != key]
+        assert torch.equal(got[others][:, :, 1], want[others][:, :, 1]), f"dk of the keys besides {key}"
+        assert torch.equal(got[:, :, 2], want[:, :, 2]), "dv"
+
+
 # Matrix-core attention over very many heads, whose workgroups are dealt out in rows of a few heads each, in the backward kernels
 # of others than in the forward kernel: sequences do not depend on each other, so two calls on parts give the same bytes.
 def test_attention_batches_of_several_grid_rows():
