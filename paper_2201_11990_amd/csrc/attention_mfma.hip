@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 2) void attn_fwd_kernel(ForwardArgs
   constexpr int ROWS = FWD_WAVES / SPLIT, OWNED = 32 * ROWS;   // waves with rows of their own
   constexpr int K1 = D / 16, CB = D / 32, STAGE = 2 * T::BYTES, NP = EXACT ? 3 : 1;
   constexpr int SUBS = SPLIT == 2 ? 1 : 2;                // 32-key parts of a tile that a wave takes
-  constexpr int N1 = 2 * K1, N = SUBS * N1, NF = D == 160 ? 5 : D == 96 || D == 192 ? 6 : 4, PF = NF - 1;   // steps of a part: K1 for S, K1 for O
+  constexpr int N1 = 2 * K1, NF = D == 160 ? 5 : D == 96 || D == 192 ? 6 : 4, PF = NF - 1;   // steps of a part: K1 for S, K1 for O
   static_assert(N1 % NF == 0, "fragment buffers");
   const int s = w.s, n = w.n, d = EXACT ? w.head_dim : D;
   const int count = own_blocks(s, OWNED);
@@ -120,7 +120,8 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 2) void attn_fwd_kernel(ForwardArgs
   __builtin_amdgcn_sched_barrier(0);
 
   int cur = 0;
-  for (int it = 0; it < ntiles; ++it) {
+  auto tile = [&](auto TAKEN, int it) __attribute__((always_inline)) {   // TAKEN: parts, SUBS or the first only
+    constexpr int N = decltype(TAKEN)::value * N1;
     ln.here();
     const int next = cur ^ 1;   // stage of tile it + 1
     auto step = [&](auto I) __attribute__((always_inline)) {
@@ -174,6 +175,22 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 2) void attn_fwd_kernel(ForwardArgs
     for_each_step(step, std::make_integer_sequence<int, N>{});
     stream.advance();
     cur = next;
+  };
+  // How many 32-key parts this wave takes: those with a key that one of its queries sees.  The rest, at the end, it passes over: an infinity or NaN there would reach its rows (0 x inf).
+  const int visible = visible_parts(block0 / 32 + wave % ROWS, part, SUBS, ntiles);
+  int it = 0;
+  // Where the loop lies in 32-byte pieces of code counts for a wave that is alone on its SIMD (2 heads of 64, s = 3749: 31.1 to 33.2 us from place to place; 20 and more workgroups to a unit: nothing).
+  asm volatile(".p2align 6");
+  for (; it < visible / SUBS; ++it) tile(std::integral_constant<int, SUBS>{}, it);
+  if constexpr (SUBS == 2) {
+    if (visible % 2) tile(std::integral_constant<int, 1>{}, it++);
+  }
+  for (; it < ntiles; ++it) {   // passed over: its share of the next tile, and the barrier
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) dma16<Burst::value>(stream.rsrc(), dst0 + (cur ^ 1) * STAGE + i * 1024, dma_off[i]);
+    wait_and_barrier<0>();
+    stream.advance();
+    cur ^= 1;
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the look-ahead tiles, which nobody uses
 

@@ -176,7 +176,9 @@ struct TileStream {
   __device__ __forceinline__ dma_rsrc_t rsrc() const { return dma_rsrc((const void *)base, (uint32_t)left); }
   __device__ __forceinline__ void advance() {
     base += (uint32_t)tile_bytes;
-    left = left > tile_bytes ? left - tile_bytes : 0;
+    // left = max(left - tile_bytes, 0) in scalar registers: left to itself the compiler makes a saturating subtraction of it, which only the vector unit has,
+    // and a descriptor in vector registers
+    asm("s_sub_i32 %0, %0, %1\n\ts_max_i32 %0, %0, 0" : "+s"(left) : "s"(tile_bytes) : "scc");
   }
 };
 
@@ -336,6 +338,12 @@ template <int IPW, int STEPS>
 constexpr int dma_by(int step) { return ((step + 1) * IPW + STEPS - 1) / STEPS; }
 
 __host__ __device__ inline int row_blocks(int s) { return (s + 63) / 64; }
+// How many of the 32-row parts of a workgroup's ntiles tiles hold a row that the own rows 32 own .. + 31 see under the causal mask, from the first on: by a wave that takes part `part` of every
+// tile (subs 1) or both (2).
+__device__ __forceinline__ int visible_parts(int own, int part, int subs, int ntiles) {
+  const int seen = subs == 1 ? (own + 2 - part) / 2 : own + 1;
+  return seen < subs * ntiles ? seen : subs * ntiles;
+}
 __host__ __device__ inline int own_blocks(int s, int owned) { return (s + owned - 1) / owned; }   // workgroups to a head
 
 // Where all workgroups run at once, several to a compute unit, places i, 256 + i, 512 + i share one: every other 256 go out in the opposite order, so that

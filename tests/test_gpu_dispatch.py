@@ -747,6 +747,35 @@ def test_attention_backward_infinity_in_one_key(b, s, n, d):
         assert torch.equal(got[:, :, 2], want[:, :, 2]), "dv"
 
 
+# Head sizes 64, 128 and 160 without the slow path: an infinity or NaN in K or V of one token reaches outputs of the token's 64-row tile and of later rows,
+# whatever the number of rows of a workgroup (forward: 64, and 128 from 449 to 512 and from 1024 workgroups of 128 rows on; head size 64 from 897 to 1024).  The rows
+# before, the other heads and the other sequence keep every bit.
+REACH_CASES = [(2, 200, 3, 64), (2, 520, 100, 64), (2, 200, 3, 128), (2, 200, 120, 128), (2, 200, 260, 128), (2, 200, 3, 160), (2, 200, 120, 160)]
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("t0", [70, 127, 199])
+@pytest.mark.parametrize("b,s,n,d", REACH_CASES)
+def test_attention_forward_non_finite_token_reach(b, s, n, d, t0, bad):
+    qkv = dev(randn((b * s, 3 * n * d), "bf16", 55))
+
+    def forward(x):
+        a, lse = torch.full((b, s, n, d), 7.0, device="cuda", dtype=torch.bfloat16), torch.full((b, n, s), 7.0, device="cuda")
+        M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), x, a.view(b * s, -1), lse)
+        return a, lse
+
+    a0, lse0 = forward(qkv)
+    first = t0 // 64 * 64
+    for part in (1, 2):   # K, V of token t0 in head 1 of sequence 0
+        x = qkv.clone()
+        x.view(b, s, n, 3, d)[0, t0, 1, part, 5] = bad
+        a, lse = forward(x)
+        assert torch.equal(a[1], a0[1]) and torch.equal(lse[1], lse0[1]), "the other sequence"
+        others = [j for j in range(n) if j != 1]
+        assert torch.equal(a[0][:, others], a0[0][:, others]) and torch.equal(lse[0][others], lse0[0][others]), "the other heads"
+        assert torch.equal(a[0, :first, 1], a0[0, :first, 1]) and torch.equal(lse[0, 1, :first], lse0[0, 1, :first]), f"rows before {first}"
+
+
 # Matrix-core attention over very many heads, whose workgroups are dealt out in rows of a few heads each, in the backward kernels
 # of others than in the forward kernel: sequences do not depend on each other, so two calls on parts give the same bytes.
 def test_attention_batches_of_several_grid_rows():
