@@ -82,7 +82,7 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
   constexpr int OWNED = SPLIT == 2 ? 64 : 128;
   constexpr int K1 = D / 16, STAGE = 2 * T::BYTES, RING = dq_ring(D, EXACT), NP = EXACT ? 3 : 1;
   constexpr int SUBS = SPLIT == 2 ? 1 : 2;                // 32-row parts of a tile that a wave takes
-  constexpr int N1 = 3 * K1, N = SUBS * N1, NF = D == 160 ? 5 : D == 64 ? 4 : 6, PF = NF - 1;   // steps of a part: K1 for S, K1 for dP, K1 for dq
+  constexpr int N1 = 3 * K1, NF = D == 160 ? 5 : D == 64 ? 4 : 6, PF = NF - 1;   // steps of a part: K1 for S, K1 for dP, K1 for dq
   static_assert(N1 % NF == 0, "fragment buffers");
   const HeadBlock hb(w.b, w.n, w.group, own_blocks(w.s, OWNED), place);
   if (hb.none) return;
@@ -99,6 +99,7 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
   typename T::Lane32 ln(lane);
   const uint32_t smem_addr = lds_address(smem);
   const int ntiles = (block + 1) * (OWNED / 64) < row_blocks(s) ? (block + 1) * (OWNED / 64) : row_blocks(s);
+  const int visible = visible_parts(block0 / 32 + (SPLIT == 2 ? wave & 1 : wave), part, SUBS, ntiles);   // the rest of the 32-key parts is passed over (as in the forward kernel)
 
   constexpr int IPW = 2 * T::NI;
   auto offset = [&](bool queries, int i) {
@@ -126,11 +127,11 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
   uint32_t dma_off[IPW];
 #pragma unroll
   for (int i = 0; i < IPW; ++i) dma_off[i] = offset(false, i);
-  constexpr int ISSUE_STEPS = RING == 2 ? IPW / 2 : N - PF;   // (one tile ahead: it is waited for in the same iteration)
-  auto issue_step = [&](int step, int st) {
+  auto issue_step = [&](auto STEPS, int step, int st) {   // over the first STEPS steps of a tile
+    constexpr int steps = decltype(STEPS)::value;
 #pragma unroll
     for (int i = 0; i < IPW; ++i)
-      if (i >= (step ? dma_by<IPW, ISSUE_STEPS>(step - 1) : 0) && i < dma_by<IPW, ISSUE_STEPS>(step))
+      if (i >= (step ? dma_by<IPW, steps>(step - 1) : 0) && i < dma_by<IPW, steps>(step))
         dma16<Spread::value>(stream.rsrc(), dst0 + st * STAGE + i * 1024, dma_off[i]);
   };
 #pragma unroll
@@ -156,10 +157,10 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
     float v = t[0];
 #pragma unroll
     for (int e = 1; e < 16; ++e) v = i == e ? t[e] : v;
-    dsum = __shfl(v, row + 32 * (row >> 2 & 1), 64);
+    dsum = __shfl(EXACT ? v : -v, row + 32 * (row >> 2 & 1), 64);   // D, or -D, as dP's accumulators start
     if constexpr (!EXACT) lsf *= kLog2e;
   }
-  if (mine < s && h == 0 && part == 0) at.Dvec[mine] = EXACT ? dsum : -dsum;   // as the dk / dv workgroups start their accumulators, or subtract it
+  if (mine < s && h == 0 && part == 0) at.Dvec[mine] = dsum;
 #pragma unroll
   for (int kk = 0; kk < K1; ++kk) {
     arrive(of0[kk]);
@@ -189,14 +190,18 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
   __builtin_amdgcn_sched_barrier(0);
 
   int cur = 0;
-  for (int it = 0; it < ntiles; ++it) {
+  auto next_of = [](int cur) { return cur == RING - 1 ? 0 : cur + 1; };                         // stages of tiles it + 1
+  auto ahead_of = [&](int cur) { return RING == 2 ? next_of(cur) : cur == 0 ? 2 : cur - 1; };   // and it + RING - 1
+  auto tile = [&](auto TAKEN, int it) __attribute__((always_inline)) {   // TAKEN: parts, SUBS or the first only
+    constexpr int N = decltype(TAKEN)::value * N1;
+    constexpr int ISSUE_STEPS = RING == 2 ? IPW / 2 : N - PF;   // (one tile ahead: it is waited for in the same iteration)
     ln.here();
-    const int next = cur == RING - 1 ? 0 : cur + 1, nn = RING == 2 ? next : cur == 0 ? 2 : cur - 1;   // stages of tiles it + 1 and it + RING - 1
+    const int next = next_of(cur), nn = ahead_of(cur);
     auto step = [&](auto I) __attribute__((always_inline)) {
       constexpr int i = decltype(I)::value, sub = i / N1, r = i % N1;
       const int row = it * 64 + 32 * (part + sub);
       if (r == 0) {
-        const float start = EXACT ? 0.0f : -dsum;
+        const float start = EXACT ? 0.0f : dsum;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           sc[e] = 0.0f;
@@ -204,9 +209,10 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
         }
       }
       if (r == K1 && row + 31 > own0) {   // wave-uniform: diagonal (or past-the-end keys) among these keys
+        const int h4 = (lane_here() >> 5) * 4;
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int key = row + 8 * (e / 4) + 4 * h + e % 4;
+          const int key = row + 8 * (e / 4) + h4 + e % 4;
           if (key > mine || key >= s) sc[e] = -INFINITY;
         }
       }
@@ -225,7 +231,7 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
         Kt = smem + next * STAGE;
       }
       load((i + PF) % N);
-      if (i < ISSUE_STEPS) issue_step(i, nn);
+      if (i < ISSUE_STEPS) issue_step(std::integral_constant<int, ISSUE_STEPS>{}, i, nn);
       const bf16x8 &v = fr[i % NF];
       if constexpr (r < K1) sc = MFMA32(v, of0[r], sc);
       else if constexpr (r < 2 * K1) pc = MFMA32(v, of1[r - K1], pc);
@@ -235,13 +241,27 @@ __device__ __forceinline__ void dq_block(unsigned place, char *smem, const Backw
     for_each_step(step, std::make_integer_sequence<int, N>{});
     stream.advance();
     cur = next;
+  };
+  int it = 0;
+  for (; it < visible / SUBS; ++it) tile(std::integral_constant<int, SUBS>{}, it);
+  if constexpr (SUBS == 2) {
+    if (visible % 2) tile(std::integral_constant<int, 1>{}, it++);
+  }
+  for (; it < ntiles; ++it) {   // passed over: its share of a later tile, and the barrier
+    const int nn = ahead_of(cur);
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) dma16<Burst::value>(stream.rsrc(), dst0 + nn * STAGE + i * 1024, dma_off[i]);
+    wait_and_barrier<(RING - 2) * IPW>();
+    stream.advance();
+    cur = next_of(cur);
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the look-ahead tiles, which nobody uses
 
   float z = 0.0f;   // EXACT: NaN where a result is not finite
   bf16 *out = at.out + (int64_t)mine * at.ld;
+  const int h4 = (lane_here() >> 5) * 4;
   auto put = [&](int cb, int q, f32x4 sum) {   // elements 4 q .. + 3 of column block cb: columns 32 cb + 8 q + 4 h .. + 3
-    const int col = 32 * cb + 8 * q + 4 * h;
+    const int col = 32 * cb + 8 * q + h4;
     if (EXACT && col >= d) return;
     bf16x4 o;
 #pragma unroll
@@ -338,6 +358,8 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, const Back
   typename T::Lane32 ln(lane);
   const uint32_t smem_addr = lds_address(smem);
   const int ntiles = (s + ROWS - 1) / ROWS - block0 / ROWS;
+  // Tiles whose rows, those that this pair takes, none of its keys is seen by: the first ones, passed over (as in the forward kernel).
+  const int before_own = ((wave & (L::GROUPS - 1)) - part + ROWS / 32 - 1) / (ROWS / 32), hidden = before_own < ntiles ? before_own : ntiles;
 
   // Tiles of 64 rows: waves 0-3 bring the Q tile, waves 4-7 the dO tile, 16 rows each; of 32 rows: waves 0, 1 and waves 2, 3.  Every wave that brings any brings the
   // tile's lse values (even waves) or -D values (odd waves) too; those arrive several times over, so that every wave issues the same number of memory
@@ -436,6 +458,16 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, const Back
   const char *now = smem, *before = smem;   // stages of the tile whose first product, and whose second, are next to be read
   f32x4 *const xchg = reinterpret_cast<f32x4 *>(smem + RING * STAGE) + (wave & 3) * 256 + lane;   // 4 x 64 of the pair
   int cur = 0, odd = 0;
+  auto next_of = [](int cur) { return cur == RING - 1 ? 0 : cur + 1; };   // stages of tiles it + 1
+  auto ahead_of = [&](int cur) { return AHEAD == 1 ? next_of(cur) : cur + AHEAD >= RING ? cur + AHEAD - RING : cur + AHEAD; };   // and it + AHEAD
+  for (int it = 0; it < hidden; ++it) {   // its share of a later tile, and the barriers
+    if constexpr (!LAG) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    issue_tile(ahead_of(cur));
+    wait_and_barrier<(AHEAD - 1) * OPS>();
+    cur = next_of(cur);
+    odd ^= 1;
+  }
+  now = before = smem + cur * STAGE;   // (LAG: the first second product, of zeros, is with rows that the pair takes)
   auto run = [&](auto ROLE) __attribute__((always_inline)) {
     constexpr int me = decltype(ROLE)::value;
     const int part_rows = part * T::ROWS32;
@@ -472,10 +504,9 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, const Back
 #pragma unroll
     for (int i = 0; i < PF; ++i) load(i);
     __builtin_amdgcn_sched_barrier(0);
-    for (int it = 0; it < ntiles; ++it) {
+    for (int it = hidden; it < ntiles; ++it) {
       ln.here();
-      const int next = cur == RING - 1 ? 0 : cur + 1;
-      const int nn = AHEAD == 1 ? next : cur + AHEAD >= RING ? cur + AHEAD - RING : cur + AHEAD;   // stage of tile it + AHEAD
+      const int next = next_of(cur), nn = ahead_of(cur);
       const float *stat = reinterpret_cast<const float *>(smem + cur * STAGE + 2 * L::MATRIX) + 32 * part + 4 * h;
       const float *dneg = OWN_D ? rows_d + it * ROWS + 32 * part + 4 * h : stat + 64;
       const int row = block0 + it * ROWS + 32 * part;   // element e: row + 8 (e / 4) + 4 h + e % 4
@@ -567,7 +598,7 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, const Back
       cur = next;
       odd ^= 1;
     }
-    if constexpr (!LAG) return;
+    if (!LAG || hidden == ntiles) return;
     // the second product of the last tile
     if constexpr (me == 1) {
       f32x16 p;

@@ -294,6 +294,12 @@ template <typename V>
 __device__ __forceinline__ void arrive(V &v) {
   asm volatile("" : "+v"(v));
 }
+// The lane's number, worked out where it stands: a register less across a loop that needs them all.
+__device__ __forceinline__ int lane_here() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
+}
 // maximum over the four lanes that share lane % 16:
 // v_permlane{16,32}_swap of a value with itself leaves the two halves of every pair side by side; unlike a shuffle
 // through LDS it costs a vector instruction's latency, which the forward kernel pays twice in every tile's chain.

@@ -776,6 +776,34 @@ def test_attention_forward_non_finite_token_reach(b, s, n, d, t0, bad):
         assert torch.equal(a[0, :first, 1], a0[0, :first, 1]) and torch.equal(lse[0, 1, :first], lse0[0, 1, :first]), f"rows before {first}"
 
 
+# Backward: K or V of the token reach dq of its tile and of later rows; Q or dO of it dk and dv of the keys up to the end of its tile.  (One launch; two, with 64 rows to a workgroup; with 128.)
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("t0", [70, 127, 199])
+@pytest.mark.parametrize("b,s,n,d", [(2, 200, 3, 64), (2, 200, 3, 128), (2, 200, 60, 128), (2, 200, 120, 128), (2, 200, 3, 160), (2, 200, 60, 160), (2, 230, 120, 160)])
+def test_attention_backward_non_finite_token_reach(b, s, n, d, t0, bad):
+    qkv, da = dev(randn((b * s, 3 * n * d), "bf16", 55)), dev(randn((b * s, n * d), "bf16", 56))
+
+    def step(x, g):
+        a, dx, lse = torch.empty_like(g), torch.full_like(x, 7.0), torch.empty((b, n, s), device="cuda")
+        ws = torch.empty(M.mtnlg_attention_bwd_workspace(b, s, n, d), dtype=torch.uint8, device="cuda")
+        M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), x, a, lse)
+        M.mtnlg_attention_bwd(b, s, n, d, 1.0 / math.sqrt(d), x, a, lse, g, dx, ws)
+        return dx.view(b, s, n, 3, d)
+
+    want = step(qkv, da)
+    first, end = t0 // 64 * 64, t0 // 64 * 64 + 64
+    for part in range(4):   # Q, K, V, dO of token t0 in head 1 of sequence 0
+        x, g = qkv.clone(), da.clone()
+        (g.view(b, s, n, 1, d) if part == 3 else x.view(b, s, n, 3, d))[0, t0, 1, part % 3, 5] = bad
+        got = step(x, g)
+        others = [j for j in range(n) if j != 1]
+        assert torch.equal(got[1], want[1]) and torch.equal(got[0][:, others], want[0][:, others]), "the other sequence and heads"
+        if part in (1, 2):
+            assert torch.equal(got[0, :first, 1, 0], want[0, :first, 1, 0]), f"dq of the rows before {first}"
+        else:
+            assert torch.equal(got[0, end:, 1, 1:], want[0, end:, 1, 1:]), f"dk, dv of the keys from {end} on"
+
+
 # Matrix-core attention over very many heads, whose workgroups are dealt out in rows of a few heads each, in the backward kernels
 # of others than in the forward kernel: sequences do not depend on each other, so two calls on parts give the same bytes.
 def test_attention_batches_of_several_grid_rows():
