@@ -525,29 +525,32 @@ constexpr int one_launch_groups() {
 
 // Up to how many groups of 16 rows a call splits the streamed side over the waves of a workgroup.  With 64 rows to a workgroup, 16 to a wave, the
 // time is the longest wave's chain of steps until there are several waves to a SIMD, and it grows with s; with 16 rows to a workgroup a chain is a quarter of that, but
-// the waves no longer share what they load, and the time grows with the work.  So the line lies higher for longer sequences and smaller head sizes.  fp32,
-// times as fast with 16 rows to a workgroup, forward / backward, at head size 32, 64, 128, 224: 20 heads, s = 512 (640 groups) 1.9 / 2.1, 1.9 / 2.1, 1.5 / 1.9, 1.6 / 1.6;
-// 48, 256 (768) 1.4 / 1.7, 1.2 / 1.4, 1.05 / 1.3, 1.1 / 1.2; 72, 224 (1008) 1.3 / 1.4, 1.1 / 1.2, 0.7 / 0.9, 0.7 / 0.9; 128, 128 (1024) 1.05 / 1.2, 0.9 / 1.06, 0.6 / 0.8, 0.7 / 0.8; 32,
-// 512 (1024) 1.6 / 1.7, 1.35 / 1.4, 1.1 / 1.3, -; 16, 1024 (1024) 1.8 / 1.9, 1.6 / 1.7, 1.3 / 1.6, -; 48, 512 (1536) 1.3 / 1.4, 1.2 / 1.3, 0.75 / 0.9, 0.8 / 0.9; 12, 2048 (1536) 1.6 / 1.8, 1.5 / 1.6,
-// 1.03 / 1.2, 1.07 / 1.1; 40, 1024 (2560) 1.2 / 1.3, 1.03 / 1.1, 0.9 / 1.0, 0.9 / 0.9; 64, 1024 (4096) 1.1 / 1.1, 0.9 / 1.01, 0.8 / 0.9, 0.8 / 0.8.  Up to 512 groups at any s above 32 (1 head of
-// 256, s = 256 81.9 -> 28.1 us, 247 -> 87); at s <= 32 there is nothing to share.  bf16 comes here with more groups only above head size 192 and in calls that the
-// tiled kernels refuse.  2 x 512 tokens, 16 heads of 64, fp32: 35.5 -> 29.4 us, 118 -> 85.
+// the waves no longer share what they load, and the time grows with the work.  So the line lies higher for longer sequences and smaller head sizes; and lower for one
+// sequence, whose workgroups start in the order of falling work (of several, the last one's longest wait for all of the others), least of all with a number of heads that is
+// no multiple of 8.  Lines by 3789 sizes (head size 16 to 256, s 48 to 4096, 512 to 4600 groups, 1 to 4 sequences, even and odd numbers of heads).  fp32, times as
+// fast with 16 rows to a workgroup, before a line and beyond it, one sequence: forward, head size 32, s = 768, 2560 groups 1.13, 4080 0.85; 64, s = 320, 760 1.33, 1020 0.97 to
+// 1.07; s = 1024, 1536 1.39, 2496 0.84; 128, s = 512, 768 1.33, 1024 0.92 to 1.08; 256, s = 2048, 1280 1.12, 1536 0.94 to 0.98; backward, 64, s = 512, 2048 1.12, 4064 0.87;
+// 256, s = 553, 720 1.5, 1015 0.95.  Several: 4 x 728 tokens, 20 heads of 32 (3680) 1.60, backward 1.53; 2 x 1336, 14 of 64 (2352) 1.36; 4 x 1309, 11 of 48 (3608) backward
+// 1.39.  Up to 512 groups at any s above 32 (1 head of 256, s = 256 81.9 -> 28.1 us, 247 -> 87); at s <= 32 there is nothing to share.  bf16 comes here with more groups
+// only above head size 192 and in calls that the tiled kernels refuse.  2 x 512 tokens, 16 heads of 64, fp32: 35.5 -> 29.4 us, 118 -> 85.
 template <typename E, int DP, bool BACKWARD>
-constexpr int64_t most_split_groups(int s) {
+constexpr int64_t most_split_groups(int b, int s) {
   if (s <= 32) return 0;
   if (sizeof(E) == 2) return 512;
+  const bool one = b == 1;
   if (!BACKWARD) {
-    if (DP == 32) return s >= 512 ? 4096 : s >= 192 ? 1024 : 512;
-    if (DP <= 96) return s >= 1024 ? 2560 : s >= 512 ? 1536 : s >= 256 ? 1024 : s >= 192 ? 768 : 512;
-    return s >= 2048 ? 1536 : s >= 512 ? 1024 : s >= 256 ? 768 : 512;
+    if (DP == 32) return s >= (one ? 2048 : 512) ? 4096 : s >= 768 ? 3584 : s >= 512 ? 3072 : s >= 192 ? 1024 : 512;
+    if (DP <= 96) return s >= (one ? 1536 : 1024) ? 2560 : s >= 1024 ? 2048 : s >= 512 ? 1536 : s >= (one ? 384 : 256) ? 1024 : s >= 256 ? 960 : s >= 192 ? 768 : 512;
+    return s >= 2048 ? (one && DP > 224 ? 1280 : 1536) : s >= (one ? 768 : 512) ? 1024 : s >= 512 ? 960 : s >= 256 ? 768 : 512;
   }
-  if (DP <= 64) return s >= 512 ? 4096 : s >= 128 ? 1024 : 512;
+  if (DP == 32) return s >= (one ? 768 : 512) ? 4096 : s >= 512 ? 3584 : s >= 128 ? 1024 : 512;
+  if (DP == 64) return s >= (one ? 1536 : 512) ? 4096 : s >= 1024 ? 3584 : s >= 768 ? 3072 : s >= 512 ? 2560 : s >= 128 ? 1024 : 512;
   if (DP == 96) return s >= 1024 ? 2048 : s >= 512 ? 1536 : s >= 192 ? 1024 : 512;
   if (DP <= 160) return s >= 1024 ? 1536 : s >= 256 ? 1024 : s >= 192 ? 768 : 512;
-  return s >= 512 ? 1024 : s >= 256 ? 768 : 512;
+  return s >= (one ? 768 : 512) ? 1024 : s >= 512 ? 960 : s >= 256 ? 768 : 512;
 }
 template <typename E, int DP, bool BACKWARD>
-bool splits(int b, int s, int n) { return (int64_t)b * n * ((s + 15) / 16) <= most_split_groups<E, DP, BACKWARD>(s); }
+bool splits(int b, int s, int n) { return (int64_t)b * n * ((s + 15) / 16) <= most_split_groups<E, DP, BACKWARD>(b, s); }
 
 template <typename E, int DP, bool SPLIT>
 int fwd_launch_s(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {

@@ -486,10 +486,11 @@ def test_attention_by_rows_of_a_workgroup(dtype, b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd(dtype, b, s, n, d)
 
 
-# fp32 at the edges of the rule for 16 or 64 rows to a workgroup, which depends on the sequence, the head size and the direction: above 512 groups of 16
-# rows (groups in comments), on both sides of a limit.
-@pytest.mark.parametrize("b,s,n,d", [(1, 192, 64, 32), (1, 192, 86, 32), (2, 192, 32, 64), (1, 256, 64, 88), (1, 257, 61, 64),   # 768, 1032, 768, 1024, 1037
-                                     (1, 256, 48, 128), (1, 256, 64, 160), (1, 272, 31, 232), (1, 520, 47, 64), (1, 512, 49, 96)])  # 768, 1024, 527, 1551, 1568
+# fp32 at the edges of the rule for 16 or 64 rows to a workgroup, which depends on the sequence, the head size, the direction and whether there are several sequences: above
+# 512 groups of 16 rows, on both sides of a limit (groups, then 1 where forward and backward take 16 rows).
+@pytest.mark.parametrize("b,s,n,d", [(1, 192, 64, 32), (1, 192, 86, 32), (2, 192, 32, 64), (1, 256, 64, 88), (1, 257, 61, 64),      # 768 11, 1032 00, 768 11, 1024 01, 1037 00
+                                     (1, 256, 48, 128), (1, 256, 64, 160), (1, 272, 31, 232), (1, 520, 47, 64), (1, 512, 49, 96),   # 768 11, 1024 01, 527 11, 1551 01, 1568 00
+                                     (2, 256, 32, 88), (1, 513, 31, 128), (1, 513, 30, 248), (3, 513, 10, 248)])                    # 1024 11, 1023 01, 990 00, 990 11
 def test_fp32_attention_by_groups_of_rows(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("fp32", b, s, n, d)
 
