@@ -1,5 +1,5 @@
-// Fused causal softmax attention on the gfx950 matrix cores, forward, with P in fp32: the head sizes where rows of 16 to a wave beat those of attention_mfma.hip
-// (EXACT there: what is computed, and how).
+// Fused causal softmax attention on the gfx950 matrix cores, forward: the calls where rows of 16 to a wave beat those of attention_mfma.hip (which says what is computed, and
+// how, and which calls these are): with P in fp32 (EXACT) some head sizes, short sequences and a few others, else short sequences.
 //
 // Eight waves.  A workgroup owns 128 queries, 16 per wave, held in registers as MFMA B operands; K and V stream through LDS in tiles of 64 rows, brought in by LDS DMA three
 // tiles deep, one workgroup barrier per tile.  What bounds it: no single unit.  Between two barriers a wave runs LDS reads, MFMAs, the softmax and the
@@ -31,8 +31,8 @@ struct PairedBlocks {
   static __host__ __device__ int count(int s) { return (row_blocks(s) + 1) / 2; }
 };
 
-template <int D>
-__global__ __launch_bounds__(512) void attn_fwd16_kernel(int b, int s, int n, int d, int group, float scale, const bf16 *__restrict__ qkv,
+template <int D, bool EXACT>
+__global__ __launch_bounds__(512) void attn_fwd16_kernel(int b, int s, int n, int head_dim, int group, float scale, const bf16 *__restrict__ qkv,
                                                         bf16 *__restrict__ a, float *__restrict__ lse) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   using T = Tile<D>;
@@ -42,12 +42,13 @@ __global__ __launch_bounds__(512) void attn_fwd16_kernel(int b, int s, int n, in
   if (hb.none) return;
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
+  const int d = EXACT ? head_dim : D;
   const int64_t ld = (int64_t)n * 3 * d;
   const bf16 *base = qkv + (int64_t)bi * s * ld + (int64_t)j * 3 * d;
   // From the thread number and not the scalar: with a scalar condition for masked tiles the compiler lays the tile's code out per path and holds more registers.
   const PairedBlocks rb(s, hb.order, threadIdx.x >> 6);
   const int qw = rb.row0;
-  const float c = scale * kLog2e;
+  const float c = scale * kLog2e, f = EXACT ? scale : c;
   typename T::Lane ln(lane);
   const uint32_t smem_addr = lds_address(smem);
 
@@ -55,7 +56,7 @@ __global__ __launch_bounds__(512) void attn_fwd16_kernel(int b, int s, int n, in
   const int q = qw + lr, qc = q < s ? q : s - 1;
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk)
-    qf[kk] = row_chunk<true>(base + (int64_t)qc * ld, 32 * kk + 8 * g, d);
+    qf[kk] = row_chunk<EXACT>(base + (int64_t)qc * ld, 32 * kk + 8 * g, d);
   f32x4 o[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -141,17 +142,17 @@ __global__ __launch_bounds__(512) void attn_fwd16_kernel(int b, int s, int n, in
       // 2^8 in the exponent's units (any reference gives the same sums; this one keeps p <= 256
       // and makes rescaling O rare).  Finite from the first tile on: key 0 is never masked.
       const float m_new = mx * c > m * c + 8.0f ? mx : m;
-      const float mc = product_of(m_new, scale);
+      const float mc = EXACT ? product_of(m_new, scale) : m_new * c;
       float rs = 0.0f;
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float p = weight<true>(sc[kb][e], scale, mc);
+          const float p = weight<EXACT>(sc[kb][e], f, mc);
           sc[kb][e] = p;
           rs += p;
         }
-      const float alpha = exact_exp((m - m_new) * scale);
+      const float alpha = EXACT ? exact_exp((m - m_new) * scale) : fast_exp2((m - m_new) * c);
       l = l * alpha + rs;
       m = m_new;
       if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {  // a reference maximum moved: rescale O
@@ -161,10 +162,10 @@ __global__ __launch_bounds__(512) void attn_fwd16_kernel(int b, int s, int n, in
           for (int e = 0; e < 4; ++e) o[db][e] *= alpha;
       }
       {  // step i: key half i / (DB / 2), output blocks 2 (i % (DB / 2)) and + 1
-        Parts<3> pf[2];
+        Parts<EXACT ? 3 : 1> pf[2];
         bf16x8 vfr[4][2];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) pf[ks] = weights<true>(sc[2 * ks], sc[2 * ks + 1]);
+        for (int ks = 0; ks < 2; ++ks) pf[ks] = weights<EXACT>(sc[2 * ks], sc[2 * ks + 1]);
         constexpr int HB = DB / 2;
         pipelined<2 * HB, 3>(
             [&](int i) {
@@ -187,47 +188,64 @@ __global__ __launch_bounds__(512) void attn_fwd16_kernel(int b, int s, int n, in
   const float lsum = quad_sum(l);
   bf16 *out = a + ((int64_t)bi * s + q) * ((int64_t)n * d) + (int64_t)j * d;
   float *out_lse = lse + ((int64_t)bi * n + j) * s + q;
-  float z = 0.0f;   // NaN where a result is not finite
+  float z = 0.0f;   // EXACT: NaN where a result is not finite
   if (q < s && !rb.idle) {
-    const float inv = 1.0f / lsum * PARTS_UNSCALE;
+    const float inv = EXACT ? 1.0f / lsum * PARTS_UNSCALE : 1.0f / lsum;
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
-      if (db * 16 + 4 * g >= d) continue;
+      if (EXACT && db * 16 + 4 * g >= d) continue;
       bf16x4 v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float x = o[db][e] * inv;
-        z = fmaf(x, 0.0f, z);
+        if constexpr (EXACT) z = fmaf(x, 0.0f, z);
         v[e] = (bf16)x;
       }
       *reinterpret_cast<bf16x4 *>(out + db * 16 + 4 * g) = v;
     }
-    if (g == 0) *out_lse = plus_log(product_of(m, scale), lsum);
+    if (g == 0) *out_lse = EXACT ? plus_log(product_of(m, scale), lsum) : (m * c + log2f(lsum)) * kLn2;
   }
-  if (!all_finite(z)) redo_fwd<bf16, D>(base, ld, s, d, scale, q, qw + 15 < s ? qw + 15 : s - 1, g, out, out_lse);
+  if constexpr (EXACT) {
+    if (!all_finite(z)) redo_fwd<bf16, D>(base, ld, s, d, scale, q, qw + 15 < s ? qw + 15 : s - 1, g, out, out_lse);
+  }
 }
 
-template <int D>
+template <int D, bool EXACT>
 int fwd16_launch(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
   constexpr int smem = 3 * 2 * Tile<D>::BYTES;
   static unsigned long long attr_done = 0;
   int device;
   if (!attr_is_set(attr_done, &device)) {
-    MTNLG_TRY(set_lds(attn_fwd16_kernel<D>, smem));
+    MTNLG_TRY(set_lds(attn_fwd16_kernel<D, EXACT>, smem));
     attr_mark_set(attr_done, device);
   }
   const int count = PairedBlocks::count(s), group = HeadBlock::group(b, n, count, 32, D >= 128 ? 511 : 768);   // (768: 3 a compute unit)
   LaunchScope scope(MTNLG_K_ATTN_FWD, st);
-  attn_fwd16_kernel<D><<<HeadBlock::grid(b, n, group, count), 512, smem, st>>>(b, s, n, d, group, scale, (const bf16 *)qkv, (bf16 *)a, lse);
+  attn_fwd16_kernel<D, EXACT><<<HeadBlock::grid(b, n, group, count), 512, smem, st>>>(b, s, n, d, group, scale, (const bf16 *)qkv, (bf16 *)a, lse);
   return check_launch();
 }
 
 }  // namespace
 
+int attention_fwd_mfma16(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream) {
+  switch (d) {
+    case 64: return fwd16_launch<64, false>(b, s, n, d, scale, qkv, a, lse, stream);
+    case 128: return fwd16_launch<128, false>(b, s, n, d, scale, qkv, a, lse, stream);
+    case 160: return fwd16_launch<160, false>(b, s, n, d, scale, qkv, a, lse, stream);
+    default: return MTNLG_UNSUPPORTED_SHAPE;
+  }
+}
+
 int attention_fwd_exact16(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream) {
-  if (d <= 32) return fwd16_launch<32>(b, s, n, d, scale, qkv, a, lse, stream);
-  if (d <= 96) return fwd16_launch<96>(b, s, n, d, scale, qkv, a, lse, stream);
-  return fwd16_launch<192>(b, s, n, d, scale, qkv, a, lse, stream);
+  switch ((d + 31) / 32) {
+    case 1: return fwd16_launch<32, true>(b, s, n, d, scale, qkv, a, lse, stream);
+    case 2: return fwd16_launch<64, true>(b, s, n, d, scale, qkv, a, lse, stream);
+    case 3: return fwd16_launch<96, true>(b, s, n, d, scale, qkv, a, lse, stream);
+    case 4: return fwd16_launch<128, true>(b, s, n, d, scale, qkv, a, lse, stream);
+    case 5: return fwd16_launch<160, true>(b, s, n, d, scale, qkv, a, lse, stream);
+    case 6: return fwd16_launch<192, true>(b, s, n, d, scale, qkv, a, lse, stream);
+    default: return MTNLG_UNSUPPORTED_SHAPE;
+  }
 }
 
 }  // namespace mtnlg

@@ -280,15 +280,33 @@ int fwd_launch_rows(int b, int s, int n, int d, float scale, const void *qkv, vo
   return check_launch();
 }
 
+// Sequences of one or two blocks of 64 rows: 16 rows to a wave (attention_fwd16.hip) while few workgroups share a unit.  Eight waves to a block and no merge make a shorter chain there.  Times as fast
+// as these, one block (up to `few` of them), then two (257 to 512): head size 64 1.01 to 1.15, 1.02 to 1.12; 33 to 64 with P in fp32 1.02 to 1.15, 1.02 to 1.05; 65 to 96 1.00 to
+// 1.16, 1.05 to 1.11; 97 to 128 1.1 to 1.18, 1.05 to 1.2; 129 to 160 1.1 to 1.2, 1.1 to 1.28.  (700 and 1800 sizes; d 64 3.3 / 3.7 us, 8 x 80 x 32 4.6 / 5.1.)  Head sizes 128 and 160 only up to 32
+// tokens and 255 blocks, 1.02 to 1.1.
+bool short_on_rows16(int s, int64_t blocks, int few) { return s <= 64 ? blocks <= few : s <= 128 && blocks > 256 && blocks <= 512; }
+
+// Workgroups of 64 queries that take part of the chip twice over, of a number of heads that is no multiple of 4: the workgroups of a head lie on all XCDs and most of its K and V comes into several
+// L2s.  Half as many workgroups of 128 queries do better, or, with P in fp32, the pairs of blocks of attention_fwd16.hip.  us, these / those: 384 tokens x 85 heads of 160 21.3 / 17.2, of 120 18.9 /
+// 16.8; 197 x 102 of 160 14.0 / 11.4; but 350 x 68 of 160 12.9 / 14.7.
+bool heads_scattered(int b, int n, int s, int64_t blocks) { return (int64_t)b * n % 4 && s <= 384 && blocks > 320 && blocks <= 512; }
+
 // Workgroups of 128 queries halve the tiles' way into LDS and what a workgroup costs besides its tiles; those of 64 even out better, and where all run at once a full
 // round of either does better than a part of one.  By workgroups of 128; us with 64 / 128 queries: head size 128: 64 heads, s = 1024 (512) 30.4 / 29.8; 128, 768 (768) 36.9 /
 // 42.1; 48, 2048 (768) 70.1 / 70.4; 256, 512 (1024) 39.1 / 37.8; 128, 2048 (2048) 174 / 165; 512, 768 (3072) 155 / 134; 160: 64, 1024 (512) 37.6 / 35.0; 128, 768 (768) 45.0 / 49.8; 64, 2048
 // (1024) 108 / 101; 512, 768 (3072) 194 / 166.  Head size 64, four workgroups to a unit: 64, 2048 (1024) 60.4 / 50.6; 128, 1024 (1024) 33.6 / 30.6; 256, 512 (1024) 23.1 / 22.3; but 512, 256
 // (1024) 17.8 / 18.7; 48, 2048 (768) 39.0 / 50.1; 512, 768 (3072) 72.4 / 75.8.
+// Head size 64 besides: where 128 queries hold the whole sequence, beyond 896 blocks of 64 (s 65 to 128: 1.02 to 1.2 times as fast), and of sequences up to 384 those whose workgroups of 64 just fill
+// the chip (897 to 1024: 384 tokens x 170 heads 15.0 / 13.5).
 template <int D>
 int fwd_launch(int b, int s, int n, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
-  const int64_t large = (int64_t)b * n * own_blocks(s, 128);
-  const bool rows128 = D == 64 ? large > 896 && large <= 1024 && s >= 512 : large >= 1024 || (large > 448 && large <= 512);
+  const int64_t large = (int64_t)b * n * own_blocks(s, 128), blocks = (int64_t)b * n * row_blocks(s);
+  bool rows128 = large >= 1024 || (large > 448 && large <= 512);
+  if (D == 64 ? short_on_rows16(s, blocks, 512) : s <= 32 && blocks < 256) return attention_fwd_mfma16(b, s, n, D, scale, qkv, a, lse, st);
+  if (D > 64 && s > 128 && heads_scattered(b, n, s, blocks)) rows128 = true;
+  if constexpr (D == 64) {
+    rows128 = (s >= 512 && large > 896 && large <= 1024) || (s > 64 && s <= 384 && blocks > 896 && (s <= 128 || (s > 192 && blocks <= 1024)));
+  }
   if (rows128) return fwd_launch_rows<D, 1>(b, s, n, D, scale, qkv, a, lse, st);
   return fwd_launch_rows<D, 2>(b, s, n, D, scale, qkv, a, lse, st);
 }
@@ -340,10 +358,15 @@ bool attention_exact_bwd_takes(int dtype, int b, int s, int n, int d, const void
 }
 
 int attention_fwd_exact(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream) {
-  // 16 rows to a wave where that is as fast or faster: up to head size 32, above 160, and from 65 to 96 with many blocks of 64 rows.  us, those / these: 64 heads, s = 1536, of 32
+  // 16 rows to a wave where that is as fast or faster: up to head size 32, above 160, short sequences, and from 65 to 96 with many blocks of 64 rows.  us, those / these: 64 heads, s = 1536, of 32
   // 42 / 47; 16, 2048 of 192 62 / 76; of 96 32, 1024 (512 blocks) 24.3 / 22.3; 48, 1024 (768) 32.8 / 31.7; 96, 512 (768) 20.8 / 24.1; 64, 1024 (1024) 34.4 / 38.7; 64, 2048
-  // (2048) 108 / 118.  The others: 64, 1024 of 48 29.6 / 26.9; 4, 2048 of 104 42.2 / 36.3; 64, 2048 of 120 161 / 140, of 144 181 / 164.
-  if (d <= 32 || d > 160 || (d > 64 && d <= 96 && (int64_t)b * n * row_blocks(s) >= 704)) return attention_fwd_exact16(b, s, n, d, scale, qkv, a, lse, stream);
+  // (2048) 108 / 118.  The others: 64, 1024 of 48 29.6 / 26.9; 4, 2048 of 104 42.2 / 36.3; 64, 2048 of 120 161 / 140, of 144 181 / 164.  65 to 96 at s 65 to 96 those 1.01 to 1.2 times as fast throughout, at
+  // s 97 to 128 beyond 256 blocks up to 1.18; at s 129 to 192 1.08 from 513 to 768, 0.93 beyond.
+  const int64_t blocks = (int64_t)b * n * row_blocks(s);
+  bool rows16 = d <= 32 || d > 160 || short_on_rows16(s, blocks, d <= 64 ? 512 : d <= 96 ? 384 : 256);
+  if (d > 64 && d <= 96 && s > 64) rows16 = s <= 96 || (s <= 128 ? blocks > 256 : s <= 192 ? blocks > 512 && blocks <= 768 : blocks >= 704);
+  if (d > 64 && s > 192 && heads_scattered(b, n, s, blocks)) rows16 = true;
+  if (rows16) return attention_fwd_exact16(b, s, n, d, scale, qkv, a, lse, stream);
   if (d <= 64) return fwd_launch_rows<64, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);
   if (d <= 96) return fwd_launch_rows<96, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);
   if (d <= 128) return fwd_launch_rows<128, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);

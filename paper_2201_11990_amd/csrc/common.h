@@ -408,10 +408,11 @@ int attention_fwd_exact(int b, int s, int n, int d, float scale, const void *qkv
 int attention_bwd_exact(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                         void *dqkv, void *ws, hipStream_t stream);
 // 16 rows to a wave (attention_fwd16.hip, attention_bwd64.hip), called by those above where that is the faster
+int attention_fwd_mfma16(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream);   // of head sizes 64, 128, 160
 int attention_fwd_exact16(int b, int s, int n, int d, float scale, const void *qkv, void *a, float *lse, hipStream_t stream);
 int attention_bwd64(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
                     hipStream_t stream);   // of head size 64
 int attention_bwd_exact64(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv,
-                          void *ws, hipStream_t stream);   // up to 64
+                          void *ws, hipStream_t stream);
 
 }  // namespace mtnlg
