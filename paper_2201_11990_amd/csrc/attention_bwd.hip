@@ -738,25 +738,34 @@ int bwd_launch_one(int b, int s, int n, float scale, const void *qkv, const void
 
 // By blocks of 64 rows of all heads together.  One launch where (nearly) all workgroups of either kernel run at once, so that both kernels' would leave units idle
 // one after the other: a second D for every tile costs less than that and the launch.  us, two launches / one, head size 128: 2 heads, s = 256 (8
-// blocks) 17.1 / 10.5; 16, 1024 (256) 38.9 / 32.9; 75, 256 (300) 27.4 / 26.4; 40, 512 (320) 29.2 / 28.1; 20, 1024 (320) 40.4 / 41.7; 24, 1024 (384) 45.7 / 51.6; at 160 the same.
+// blocks) 17.1 / 10.5; 16, 1024 (256) 38.9 / 32.9; 75, 256 (300) 27.4 / 26.4; 40, 512 (320) 29.2 / 28.1; 20, 1024 (320) 40.4 / 41.7; 24, 1024 (384) 45.7 / 51.6; at 160 the same.  Over 27 sizes of
+// 257 to 320 blocks one is 0.96 to 1.21 times as fast, 1.05 on average (s 65 to 96 from 297 blocks on 0.94 to 0.99, against 128 rows), over 25 of 321 to 384 0.81 to 1.18, 0.97.
 // Workgroups of 128 rows where there are enough of them to even out: half of what a workgroup costs besides its tiles, and of the tiles' way into LDS.
 // us, 64 / 128 rows, head size 128, then 160: 20 heads, s = 2048 (640 blocks) 102 / 115, 118 / 129; 80, 512 (640) 49.2 / 49.6, 61.1 / 58.8; 24, 2048 (768) 114 / 116, 136 / 134; 48,
 // 1024 (768) 74.2 / 72.9, 91.5 / 86.1; 200, 256 (800) 52.7 / 48.1, 67.0 / 58.8; 28, 2048 (896) 133 / 129, 162 / 151; 64, 2048 (2048) 291 / 275, 358 / 321; 512, 768 542 / 466, 634 / 541.
+// Shorter sequences (1600 sizes, times as fast with 128 rows): s 65 to 128, one round of 128 rows (257 to 512 blocks) 1.0 to 1.24 (80 x 200 heads of 128 21.4 / 18.8), 513 to 767 0.93 to 1.02; s 129 to
+// 512, 513 blocks and more 0.98 to 1.18, to 1024, 577 and more 0.99 to 1.27; s 33 to 64, of whose 128 rows half are empty, 0.92 to 1.0; scattered heads (s 129 to 384, at head size 128 from 385 blocks on) 1.0 to 1.17.
 template <int D>
 int bwd_launch(int b, int s, int n, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                void *dqkv, void *ws, hipStream_t st) {
   const int64_t blocks = (int64_t)b * n * row_blocks(s);
-  if (s <= ONE_LAUNCH_ROWS && blocks <= 320) return bwd_launch_one<D>(b, s, n, scale, qkv, a, lse, da, dqkv, ws, st);
-  if (blocks >= 768) return bwd_launch_p<D, 1>(b, s, n, D, scale, qkv, a, lse, da, dqkv, ws, st);
+  const bool two_blocks = s > 64 && s <= 128;
+  if (s <= ONE_LAUNCH_ROWS && blocks <= (two_blocks && s <= 96 ? 296 : 320)) return bwd_launch_one<D>(b, s, n, scale, qkv, a, lse, da, dqkv, ws, st);
+  bool rows128 = blocks >= 768 && (s <= 32 || s > 64);
+  if (two_blocks) rows128 = blocks <= 512 || blocks >= 768;
+  else if (s > 128 && s <= 1024) rows128 = blocks > (s <= 512 ? 512 : 576) || (s <= 384 && blocks > (D == 128 ? 384 : 320) && heads_scattered(b, n, s, D));
+  if (rows128) return bwd_launch_p<D, 1>(b, s, n, D, scale, qkv, a, lse, da, dqkv, ws, st);
   return bwd_launch_p<D, 2>(b, s, n, D, scale, qkv, a, lse, da, dqkv, ws, st);
 }
 
-// EXACT: 128 own rows to a workgroup from 2048 blocks of 64 rows on.  us, 64 / 128 rows: of 96 64 heads, s = 1024 (1024) 109 / 123, 64, 2048 (2048) 359 / 350, 512, 512 309 /
-// 270; of 144 48, 2048 (1536) 411 / 401, 96, 1024 (1536) 249 / 257, 64, 2048 (2048) 561 / 526; of 104 1024, 256 279 / 265.
+// EXACT: 128 own rows to a workgroup from 2048 blocks of 64 rows on, and for shorter sequences before.  us, 64 / 128 rows: of 96 64 heads, s = 1024 (1024) 109 / 123, 64, 2048 (2048) 359 / 350, 512, 512
+// 309 / 270; of 144 48, 2048 (1536) 411 / 401, 96, 1024 (1536) 249 / 257, 64, 2048 (2048) 561 / 526; of 104 1024, 256 279 / 265.  s 65 to 128, more than 256 blocks: 128 rows 1.05 to 1.4 times as
+// fast; s 129 to 512, more than 768: 1.0 to 1.25.
 template <int D>
 int exact_launch(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
                  hipStream_t st) {
-  if ((int64_t)b * n * row_blocks(s) >= 2048) return bwd_launch_p<D, 1, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
+  const int64_t blocks = (int64_t)b * n * row_blocks(s);
+  if (s > 64 && blocks > (s <= 128 ? 256 : s <= 512 ? 768 : 2047)) return bwd_launch_p<D, 1, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
   return bwd_launch_p<D, 2, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, st);
 }
 
@@ -775,10 +784,19 @@ int attention_bwd_mfma(int b, int s, int n, int d, float scale, const void *qkv,
 
 int attention_bwd_exact(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da,
                         void *dqkv, void *ws, hipStream_t stream) {
-  // 16 rows to a wave up to head size 32, and to 64 from 768 blocks of 64 rows on: us, those / these, 16 heads of 32, s = 2 x 1024 39.4 / 42.3; of 48 32, 1024 (512 blocks)
-  // 47.9 / 45.7, 48, 1024 (768) 60.9 / 68.3, 64, 2048 (2048) 240 / 267.
+  // 16 rows to a wave (attention_bwd64.hip) up to head size 32, to 64 but for few blocks of long sequences, and for short sequences of the others: there the chain of these kernels' prologue, exchange
+  // and merge is most of the time.  Times as fast as these (2300 sizes): 33 to 64, s up to 128 1.1 to 1.45, 385 to 768 1.0 to 1.05 (more than 512 blocks 1.1 to 1.25), beyond 0.95 to 1.0 (1.1 to
+  // 1.2); 65 to 96, s up to 64 1.06 to 1.25, 129 to 192 1.05 to 1.1, 193 to 384 1.02 to 1.1, 385 and more 0.93 to 1.0; 97 to 128, s up to 64 1.05 to 1.1 up to 256 blocks, else 0.96 to 1.0; 129 to
+  // 160, s up to 64 1.03 to 1.16; 161 to 192, s up to 96 1.02 to 1.13 beyond 384 blocks.  us: 2 x 87 tokens x 169 heads of 48 22.6 / 27.6, 80 x 774 of 144 114 / 124.
   const int64_t blocks = (int64_t)b * n * row_blocks(s);
-  if (d <= 32 || (d <= 64 && blocks >= 768)) return attention_bwd_exact64(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
+  bool rows16;
+  if (d <= 32) rows16 = true;
+  else if (d <= 64) rows16 = s <= 768 || blocks > 512;
+  else if (d <= 96) rows16 = s <= 64 || (s <= 96 ? blocks <= 256 : s <= 192 || (s <= 384 && blocks <= 768));
+  else if (d <= 128) rows16 = s <= 64 && blocks <= 256;
+  else if (d <= 160) rows16 = s <= 64;
+  else rows16 = s <= 96 && blocks > 384;
+  if (rows16) return attention_bwd_exact64(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
   if (d <= 64) return bwd_launch_p<64, 2, true>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
   if (d <= 96) return exact_launch<96>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);
   if (d <= 128) return exact_launch<128>(b, s, n, d, scale, qkv, a, lse, da, dqkv, ws, stream);

@@ -520,7 +520,7 @@ int launch_two(const BackwardArgs &in, hipStream_t st) {
   }
   BackwardArgs w = in;
   const int count = BackwardBlocks<PAIRED>::count(w.s);
-  w.group = HeadBlock::group(w.b, w.n, count, PAIRED ? 32 : 128, PAIRED ? 511 : 2047);
+  w.group = HeadBlock::group(w.b, w.n, count, PAIRED || D >= 128 ? 32 : 128, PAIRED ? 511 : 2047);
   const dim3 grid = HeadBlock::grid(w.b, w.n, w.group, count);
   LaunchScope scope(MTNLG_K_ATTN_BWD, st);
   attn_bwd64_dq_kernel<D, PAIRED, EXACT><<<grid, 512, smem_dq, st>>>(w);
@@ -565,7 +565,15 @@ int attention_bwd64(int b, int s, int n, float scale, const void *qkv, const voi
 int attention_bwd_exact64(int b, int s, int n, int d, float scale, const void *qkv, const void *a, const float *lse, const void *da, void *dqkv, void *ws,
                           hipStream_t st) {
   const BackwardArgs w{b, s, n, d, 0, scale, (const bf16 *)qkv, (const bf16 *)a, lse, (const bf16 *)da, (bf16 *)dqkv, (float *)ws};
-  return d <= 32 ? launch_two<32, false, true>(w, st) : launch_two<64, false, true>(w, st);
+  switch ((d + 31) / 32) {
+    case 1: return launch_two<32, false, true>(w, st);
+    case 2: return launch_two<64, false, true>(w, st);
+    case 3: return launch_two<96, false, true>(w, st);
+    case 4: return launch_two<128, false, true>(w, st);
+    case 5: return launch_two<160, false, true>(w, st);
+    case 6: return launch_two<192, false, true>(w, st);
+    default: return MTNLG_UNSUPPORTED_SHAPE;
+  }
 }
 
 }  // namespace mtnlg

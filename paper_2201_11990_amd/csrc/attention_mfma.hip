@@ -286,11 +286,6 @@ int fwd_launch_rows(int b, int s, int n, int d, float scale, const void *qkv, vo
 // tokens and 255 blocks, 1.02 to 1.1.
 bool short_on_rows16(int s, int64_t blocks, int few) { return s <= 64 ? blocks <= few : s <= 128 && blocks > 256 && blocks <= 512; }
 
-// Workgroups of 64 queries that take part of the chip twice over, of a number of heads that is no multiple of 4: the workgroups of a head lie on all XCDs and most of its K and V comes into several
-// L2s.  Half as many workgroups of 128 queries do better, or, with P in fp32, the pairs of blocks of attention_fwd16.hip.  us, these / those: 384 tokens x 85 heads of 160 21.3 / 17.2, of 120 18.9 /
-// 16.8; 197 x 102 of 160 14.0 / 11.4; but 350 x 68 of 160 12.9 / 14.7.
-bool heads_scattered(int b, int n, int s, int64_t blocks) { return (int64_t)b * n % 4 && s <= 384 && blocks > 320 && blocks <= 512; }
-
 // Workgroups of 128 queries halve the tiles' way into LDS and what a workgroup costs besides its tiles; those of 64 even out better, and where all run at once a full
 // round of either does better than a part of one.  By workgroups of 128; us with 64 / 128 queries: head size 128: 64 heads, s = 1024 (512) 30.4 / 29.8; 128, 768 (768) 36.9 /
 // 42.1; 48, 2048 (768) 70.1 / 70.4; 256, 512 (1024) 39.1 / 37.8; 128, 2048 (2048) 174 / 165; 512, 768 (3072) 155 / 134; 160: 64, 1024 (512) 37.6 / 35.0; 128, 768 (768) 45.0 / 49.8; 64, 2048
@@ -302,8 +297,8 @@ template <int D>
 int fwd_launch(int b, int s, int n, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
   const int64_t large = (int64_t)b * n * own_blocks(s, 128), blocks = (int64_t)b * n * row_blocks(s);
   bool rows128 = large >= 1024 || (large > 448 && large <= 512);
-  if (D == 64 ? short_on_rows16(s, blocks, 512) : s <= 32 && blocks < 256) return attention_fwd_mfma16(b, s, n, D, scale, qkv, a, lse, st);
-  if (D > 64 && s > 128 && heads_scattered(b, n, s, blocks)) rows128 = true;
+  const bool rows16 = D == 64 ? short_on_rows16(s, blocks, 512) : (s <= 32 && blocks < 256) || heads_scattered(b, n, s, D);
+  if (rows16) return attention_fwd_mfma16(b, s, n, D, scale, qkv, a, lse, st);
   if constexpr (D == 64) {
     rows128 = (s >= 512 && large > 896 && large <= 1024) || (s > 64 && s <= 384 && blocks > 896 && (s <= 128 || (s > 192 && blocks <= 1024)));
   }
@@ -365,7 +360,7 @@ int attention_fwd_exact(int b, int s, int n, int d, float scale, const void *qkv
   const int64_t blocks = (int64_t)b * n * row_blocks(s);
   bool rows16 = d <= 32 || d > 160 || short_on_rows16(s, blocks, d <= 64 ? 512 : d <= 96 ? 384 : 256);
   if (d > 64 && d <= 96 && s > 64) rows16 = s <= 96 || (s <= 128 ? blocks > 256 : s <= 192 ? blocks > 512 && blocks <= 768 : blocks >= 704);
-  if (d > 64 && s > 192 && heads_scattered(b, n, s, blocks)) rows16 = true;
+  if (d > 64 && s > 192 && s <= (d > 128 ? 768 : 384) && heads_scattered(b, n, s, d)) rows16 = true;
   if (rows16) return attention_fwd_exact16(b, s, n, d, scale, qkv, a, lse, stream);
   if (d <= 64) return fwd_launch_rows<64, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);
   if (d <= 96) return fwd_launch_rows<96, 2, true>(b, s, n, d, scale, qkv, a, lse, stream);

@@ -393,6 +393,20 @@ struct HeadBlock {
   }
 };
 
+// Calls of more workgroups of 64 rows than there are units, and no more of 128, whose heads are scattered: with heads running fastest the workgroups of a head lie on one XCD if the number of heads is a
+// multiple of 8, else on 2, 4 or 8, and what it streams comes into as many L2s.  The fewer and larger workgroups (pairs of blocks with 16 rows to a wave, attention_fwd16.hip, or 128 rows) do better, on
+// more XCDs up to longer sequences.  Times as fast as workgroups of 64 rows with 32 to a wave, forward at head size 160 by number of heads (900 sizes): multiples of 8 0.83 to 1.04; of 4 s 65 to 128 1.04 to 1.18, then 0.9
+// to 1.03; of 2 up to 384 1.03 to 1.27, 385 to 512 0.99 to 1.02, then 0.9 to 0.99; odd 1.05 to 1.37 up to 768; at 128 0.95 to 1.13, 1.02 to 1.2, 1.03 to 1.28.  us: 384 tokens x 85 heads of 160 21.3 / 17.6, 123 x 225
+// 12.2 / 9.2, 197 x 102 14.0 / 11.6; but 350 x 68 12.9 / 13.6.  At 128 only from 321 blocks on, and not from s 129 to 192 (142 x 120 7.1 / 7.6); an odd number of heads of more than 256 tokens from 64 blocks
+// less on (358 x 51 of 128 12.5 / 10.9, 251 x 63 of 160 10.8 / 10.0).
+inline bool heads_scattered(int b, int n, int s, int d) {
+  const int64_t heads = (int64_t)b * n;
+  const int longest = heads % 8 == 0 ? 0 : heads % 4 == 0 ? 128 : heads % 2 == 0 ? 384 : 768;
+  if (d <= 128 && s > 128 && s <= 192) return false;
+  const int fewest = (d <= 128 ? 320 : 256) - (heads % 2 && s > 256 ? 64 : 0);
+  return s <= longest && heads * row_blocks(s) > fewest && heads * own_blocks(s, 128) <= 256;
+}
+
 // The DMA addresses a sequence's rows with 32-bit byte offsets from its first row.
 inline bool fits(int s, int n, int d) { return (int64_t)s * n * 3 * d * 2 < ((int64_t)1 << 31); }
 

@@ -618,35 +618,38 @@ def test_attention_backward_in_one_launch(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
-# Backward in two launches at head sizes 128 and 160, workgroups of 64 own rows (from 321 blocks of 64 rows on) and of 128 rows with tiles of 32 (from 768 on): either side of
-# the rules, ends of sequences at the edges of a 32-row part, of a tile and of the own rows.
-@pytest.mark.parametrize("b,s,n,d", [(1, 64, 320, 128), (1, 33, 321, 128), (1, 96, 161, 160), (3, 127, 64, 128), (1, 97, 192, 160), (1, 191, 255, 128),
-                                     (1, 95, 384, 128), (3, 129, 85, 160), (2, 129, 128, 160), (1, 32, 768, 128), (2, 161, 128, 128), (1, 257, 154, 160)])
+# Backward in two launches at head sizes 128 and 160 (from 321 blocks of 64 rows on), workgroups of 64 own rows and of 128 rows with tiles of 32 (s 65 to 128; s 129 to 1024 from 513 blocks on; others
+# from 768 on, but s 33 to 64 never): either side of the rules, ends of sequences at the edges of a 32-row part, of a tile and of the own rows.
+@pytest.mark.parametrize("b,s,n,d", [(1, 64, 321, 128), (1, 33, 321, 128), (1, 96, 161, 160), (3, 127, 64, 128), (1, 97, 192, 160), (1, 191, 170, 128), (1, 191, 255, 128),
+                                     (1, 95, 384, 128), (3, 129, 85, 160), (2, 129, 128, 160), (1, 32, 768, 128), (1, 64, 768, 160), (2, 161, 128, 128), (1, 257, 154, 160),
+                                     (1, 200, 81, 160)])
 def test_attention_backward_by_rows_of_a_workgroup(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
 # Forward by workgroups of 64 and of 128 own rows: either side of the rules (by workgroups of 128 rows: 448, 512 and 1024; head size 64: 896 and 1024, s from 512 on, and 896 blocks of 64 rows below),
 # sequences that end at the edges of a 32-row part, of a tile and of the own rows, two rows (with one dq is the rounding of dP - D) and one head; and the short
-# sequences that have 16 rows to a wave (head size 64 up to 512 blocks, others up to 32 tokens); a number of heads that is no multiple of 4 (321 to 512 blocks).
+# sequences that have 16 rows to a wave (head size 64 up to 512 blocks, others up to 32 tokens); a number of heads that is no multiple of 4 (257 to 512 blocks).
 @pytest.mark.parametrize("b,s,n,d", [(1, 2, 1, 128), (2, 31, 3, 160), (1, 33, 2, 64), (1, 64, 448, 128), (3, 65, 150, 160), (1, 97, 512, 128), (1, 96, 513, 160),
                                      (1, 129, 511, 128), (4, 127, 256, 160), (1, 161, 256, 128), (1, 257, 342, 128), (1, 513, 180, 64), (2, 545, 102, 64), (1, 640, 205, 64),
                                      (1, 64, 512, 64), (1, 49, 513, 64), (2, 65, 65, 64), (1, 128, 256, 64), (1, 95, 257, 64), (1, 127, 449, 64), (1, 205, 225, 64),
-                                     (1, 32, 9, 128), (1, 17, 255, 160), (1, 200, 81, 128), (1, 385, 47, 160)])
+                                     (1, 32, 9, 128), (1, 17, 255, 160), (1, 200, 81, 128), (1, 385, 47, 160), (1, 100, 129, 160), (1, 769, 21, 128), (1, 384, 86, 160), (1, 768, 23, 128), (1, 120, 140, 160)])
 def test_attention_forward_by_rows_of_a_workgroup(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
 # With fp32 weights, forward and backward on 16 or 32 rows to a wave and 64 or 128 to a workgroup: either side of the rules (704, 768 and 2048 blocks of 64 rows; short sequences up to 512,
-# 384 and 256 blocks by head size).
+# 384 and 256 blocks by head size; backward by head size, sequence and blocks).
 @pytest.mark.parametrize("b,s,n,d", [(3, 100, 30, 24), (1, 65, 383, 40), (2, 96, 192, 56), (1, 127, 351, 72), (1, 97, 352, 88), (1, 33, 2047, 96), (1, 95, 1024, 104),
                                      (1, 129, 683, 152), (2, 161, 342, 80), (1, 513, 17, 112), (1, 35, 2048, 184),
-                                     (1, 64, 384, 72), (1, 63, 256, 104), (1, 49, 257, 120), (1, 128, 256, 112), (1, 65, 129, 152), (1, 48, 200, 144), (1, 66, 129, 40), (1, 200, 81, 144), (1, 270, 90, 72)])
+                                     (1, 64, 384, 72), (1, 63, 256, 104), (1, 49, 257, 120), (1, 128, 256, 112), (1, 65, 129, 152), (1, 48, 200, 144), (1, 66, 129, 40), (1, 200, 81, 144), (1, 270, 90, 72),
+                                     (1, 33, 513, 88), (1, 96, 129, 96), (1, 95, 128, 96), (1, 191, 257, 80), (1, 193, 193, 72), (1, 385, 30, 72), (1, 100, 129, 128), (1, 520, 80, 56),
+                                     (1, 780, 40, 48), (1, 50, 257, 136), (1, 129, 257, 136), (1, 65, 200, 168), (1, 97, 200, 192)])
 def test_attention_with_exact_weights_by_rows(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
 
-@pytest.mark.parametrize("n,d", [(44, 24), (70, 56), (352, 88), (384, 40), (70, 104), (1024, 120), (70, 152)])
+@pytest.mark.parametrize("n,d", [(44, 24), (70, 56), (352, 88), (384, 40), (70, 104), (1024, 120), (70, 152), (250, 192)])
 def test_attention_with_exact_weights_by_rows_non_finite_token(n, d):
     check_non_finite_token("bf16", n, d, 37, float("inf"), M.mtnlg_attention_fwd, M.mtnlg_attention_bwd)
 
