@@ -151,7 +151,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 2) void attn_fwd_kernel(ForwardArgs
           sc[e] = weight<EXACT>(sc[e], f, mc);
           rs += sc[e];
         }
-        const float alpha = m == m_new ? 1.0f : EXACT ? exact_exp((m - m_new) * w.scale) : fast_exp2((m - m_new) * c);
+        const float alpha = m == m_new ? 1.0f : EXACT ? exact_exp(product_of(m, w.scale) - mc) : fast_exp2((m - m_new) * c);   // EXACT: by what the weights are relative to, rounded as it is
         l = l * alpha + rs;
         m = m_new;
         if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // a reference maximum moved: rescale O
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 2) void attn_fwd_kernel(ForwardArgs
     stat[wave * 128 + 64 + lane] = l;
     __syncthreads();
     const float mo = stat[other * 128 + lane], lo = stat[other * 128 + 64 + lane], both = fmaxf(m, mo);   // finite: key 0 is never masked
-    auto relative = [&](float x) { return EXACT ? exact_exp((x - both) * w.scale) : fast_exp2((x - both) * c); };
+    auto relative = [&](float x) { return EXACT ? exact_exp(product_of(x, w.scale) - product_of(both, w.scale)) : fast_exp2((x - both) * c); };
     const float mul = relative(m);
     l = part ? fmaf(l, mul, lo * relative(mo)) : fmaf(lo, relative(mo), l * mul);
     m = both;

@@ -813,6 +813,25 @@ def test_attention_backward_non_finite_token_reach(b, s, n, d, t0, bad):
             assert torch.equal(got[0, end:, 1, 1:], want[0, end:, 1, 1:]), f"dk, dv of the keys from {end} on"
 
 
+# Weights in fp32 with each half of the keys under a maximum of its own: lse of scores around 160, which are whole numbers times the scale, so that only the softmax rounds.  What is left is the rounding of
+# the result, half a unit in its last place, and the error of a logarithm and a sum of fp32 weights, below 1e-6 where that unit is 1.5e-5: 0.57 of it in all.
+@pytest.mark.parametrize("s,n,d", [(512, 16, 96), (330, 8, 120), (300, 4, 152)])
+def test_attention_with_exact_weights_lse_of_large_scores(s, n, d):
+    g = torch.Generator().manual_seed(57)
+    qkv = torch.randint(-3, 4, (s, n, 3, d), generator=g).float()
+    qkv[:, :, 0, 0] = 16.0
+    qkv[:, :, 1, 0] = 100.0
+    scale = float(np.float32(0.0971))
+    x = dev(qkv.reshape(s, -1).bfloat16())
+    a, lse = torch.empty((s, n * d), device="cuda", dtype=torch.bfloat16), torch.empty((1, n, s), device="cuda")
+    M.mtnlg_attention_fwd(1, s, n, d, scale, x, a, lse)
+    S = np.einsum("snd,tnd->nst", qkv[:, :, 0].double().numpy(), qkv[:, :, 1].double().numpy()) * scale
+    S = np.where(np.tril(np.ones((s, s), bool)), S, -np.inf)
+    want = np.log(np.exp(S - S.max(-1, keepdims=True)).sum(-1)) + S.max(-1)
+    ulps = np.abs(lse[0].double().cpu().numpy() - want) / np.spacing(want.astype(np.float32)).astype(np.float64)
+    assert ulps.max() <= 0.57, ulps.max()
+
+
 # Matrix-core attention over very many heads, whose workgroups are dealt out in rows of a few heads each, in the backward kernels
 # of others than in the forward kernel: sequences do not depend on each other, so two calls on parts give the same bytes.
 def test_attention_batches_of_several_grid_rows():
