@@ -832,6 +832,32 @@ def test_attention_with_exact_weights_lse_of_large_scores(s, n, d):
     assert ulps.max() <= 0.57, ulps.max()
 
 
+# The weights of head sizes 64, 128 and 160 are rounded to bf16 relative to a running maximum, whose own weight rounds to itself.  The error of a is no larger than with the maximum of the first 64 keys, moved
+# when a later one is 2^8 beyond it (the bound: 0.5 %, twice what draws of the inputs differ by); workgroups of 128 queries, and of 64.
+@pytest.mark.parametrize("b,s,n,d", [(2, 512, 60, 128), (1, 900, 64, 160), (1, 640, 200, 64), (1, 600, 8, 128)])
+def test_attention_forward_error_of_rounded_weights(b, s, n, d):
+    g = torch.Generator(device="cuda").manual_seed(58)
+    qkv = torch.randn((b, s, n, 3, d), generator=g, device="cuda").bfloat16()
+    a, lse = torch.empty((b * s, n * d), device="cuda", dtype=torch.bfloat16), torch.empty((b, n, s), device="cuda")
+    M.mtnlg_attention_fwd(b, s, n, d, 1.0 / math.sqrt(d), qkv.view(b * s, -1), a, lse)
+    got, mask = a.view(b, s, n, d).double(), torch.ones(s, s, dtype=torch.bool, device="cuda").triu(1)
+    ours = theirs = 0.0
+    for i in range(b):
+        for j in range(n):
+            q, k, v = (qkv[i, :, j, c].double().contiguous() for c in range(3))
+            x = (q @ k.t().contiguous() / math.sqrt(d) * math.log2(math.e)).masked_fill(mask, -math.inf)
+            p = torch.softmax(x * math.log(2), -1)
+            want, m, num, den = p @ v, torch.full((s,), -math.inf, device="cuda", dtype=torch.float64), 0.0, 0.0
+            for u in range(0, s, 64):
+                top = x[:, u:u + 64].amax(-1)
+                m_new = torch.where(top > m + 8, top, m)
+                w, alpha = torch.exp2(x[:, u:u + 64] - m_new[:, None]), torch.exp2(m - m_new)[:, None]
+                num, den, m = num * alpha + w.bfloat16().double() @ v[u:u + 64], den * alpha + w.sum(-1, keepdim=True), m_new
+            ours += ((got[i, :, j] - want) ** 2).sum().item()
+            theirs += (((num / den).bfloat16().double() - want) ** 2).sum().item()
+    assert math.sqrt(ours / theirs) <= 1.005, math.sqrt(ours / theirs)
+
+
 # Matrix-core attention over very many heads, whose workgroups are dealt out in rows of a few heads each, in the backward kernels
 # of others than in the forward kernel: sequences do not depend on each other, so two calls on parts give the same bytes.
 def test_attention_batches_of_several_grid_rows():
