@@ -292,12 +292,15 @@ bool short_on_rows16(int s, int64_t blocks, int few) { return s <= 64 ? blocks <
 // 42.1; 48, 2048 (768) 70.1 / 70.4; 256, 512 (1024) 39.1 / 37.8; 128, 2048 (2048) 174 / 165; 512, 768 (3072) 155 / 134; 160: 64, 1024 (512) 37.6 / 35.0; 128, 768 (768) 45.0 / 49.8; 64, 2048
 // (1024) 108 / 101; 512, 768 (3072) 194 / 166.  Head size 64, four workgroups to a unit: 64, 2048 (1024) 60.4 / 50.6; 128, 1024 (1024) 33.6 / 30.6; 256, 512 (1024) 23.1 / 22.3; but 512, 256
 // (1024) 17.8 / 18.7; 48, 2048 (768) 39.0 / 50.1; 512, 768 (3072) 72.4 / 75.8.
+// Head sizes 128 and 160, 800 sizes: from 513 workgroups of 128 on they are 1.0 to 1.1 times as fast as those of 64 beyond 1024 tokens, 1.2 to 1.7 if the number of heads is odd and every workgroup's K and V come
+// from another XCD's L2 (47 heads, s = 2048 of 128 114 / 73, of 160 148 / 91; 1486 of 160 89 / 60); s 577 to 1024 and odd 0.93 to 1.4 (at 160 from 385 on).
 // Head size 64 besides: where 128 queries hold the whole sequence, beyond 896 blocks of 64 (s 65 to 128: 1.02 to 1.2 times as fast), and of sequences up to 384 those whose workgroups of 64 just fill
 // the chip (897 to 1024: 384 tokens x 170 heads 15.0 / 13.5).
 template <int D>
 int fwd_launch(int b, int s, int n, float scale, const void *qkv, void *a, float *lse, hipStream_t st) {
   const int64_t large = (int64_t)b * n * own_blocks(s, 128), blocks = (int64_t)b * n * row_blocks(s);
-  bool rows128 = large >= 1024 || (large > 448 && large <= 512);
+  const bool odd = (int64_t)b * n % 2 != 0;
+  bool rows128 = large >= 1024 || (large > 448 && large <= 512) || (s > 1024 && large > 512) || (odd && s > 576 && large > (D == 128 ? 448 : 384));
   const bool rows16 = D == 64 ? short_on_rows16(s, blocks, 512) : (s <= 32 && blocks < 256) || heads_scattered(b, n, s, D);
   if (rows16) return attention_fwd_mfma16(b, s, n, D, scale, qkv, a, lse, st);
   if constexpr (D == 64) {

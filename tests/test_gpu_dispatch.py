@@ -633,7 +633,7 @@ def test_attention_backward_by_rows_of_a_workgroup(b, s, n, d):
 @pytest.mark.parametrize("b,s,n,d", [(1, 2, 1, 128), (2, 31, 3, 160), (1, 33, 2, 64), (1, 64, 448, 128), (3, 65, 150, 160), (1, 97, 512, 128), (1, 96, 513, 160),
                                      (1, 129, 511, 128), (4, 127, 256, 160), (1, 161, 256, 128), (1, 257, 342, 128), (1, 513, 180, 64), (2, 545, 102, 64), (1, 640, 205, 64),
                                      (1, 64, 512, 64), (1, 49, 513, 64), (2, 65, 65, 64), (1, 128, 256, 64), (1, 95, 257, 64), (1, 127, 449, 64), (1, 205, 225, 64),
-                                     (1, 32, 9, 128), (1, 17, 255, 160), (1, 200, 81, 128), (1, 385, 47, 160), (1, 100, 129, 160), (1, 769, 21, 128), (1, 384, 86, 160), (1, 768, 23, 128), (1, 120, 140, 160)])
+                                     (1, 32, 9, 128), (1, 17, 255, 160), (1, 200, 81, 128), (1, 385, 47, 160), (1, 100, 129, 160), (1, 769, 21, 128), (1, 384, 86, 160), (1, 768, 23, 128), (1, 120, 140, 160), (1, 600, 91, 128), (1, 1030, 57, 160)])
 def test_attention_forward_by_rows_of_a_workgroup(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
