@@ -29,16 +29,6 @@ namespace {
 //
 // A step is one fragment and its MFMA (EXACT: three in the second product).  Fragments are read PF steps ahead across the end of a tile, and a tile's barrier
 // stands PF steps before its end.
-struct BackwardArgs {
-  int b, s, n, head_dim, group;
-  float scale;
-  const bf16 *qkv, *a;
-  const float *lse;
-  const bf16 *da;
-  bf16 *dqkv;
-  float *Dvec;
-};
-
 // what both kernels know of the head that a workgroup works on
 template <bool EXACT, int D>
 struct Head {
@@ -343,9 +333,9 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, const Back
   using L = DkvLds<D, OWNED, ROWS, EXACT, OWN_D>;
   constexpr int K1 = D / 16, CB = D / 32, STAGE = L::STAGE, RING = L::RING, AHEAD = L::AHEAD, NP = EXACT ? 3 : 1;
   constexpr bool LAG = L::LAG;
-  constexpr int N = 2 * K1, NF = D == 32 ? 2 : D == 128 ? 8 : D == 160 ? 10 : 4, PF = D == 128 ? 5 : D == 160 ? 6 : NF - 1;   // steps of a tile: K1 for the first product, K1 for the second (LAG: of the tile before)
+  constexpr int N = 2 * K1, NF = D == 128 ? 8 : D == 160 ? 10 : 4, PF = D == 128 ? 5 : D == 160 ? 6 : NF - 1;   // steps of a tile: K1 for the first product, K1 for the second (LAG: of the tile before)
   constexpr int HAND_OVER = LAG ? N - PF : K1;
-  static_assert(N % NF == 0 && HAND_OVER >= K1, "");
+  static_assert(D >= 64 && D <= 192 && N % NF == 0 && HAND_OVER >= K1, "");
   const HeadBlock hb(w.b, w.n, w.group, own_blocks(w.s, OWNED), place);
   if (hb.none) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
@@ -565,7 +555,7 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, const Back
           }
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            if (LAG && r == (K1 > 2 ? 2 + e * (K1 - 2) / 16 : 1)) prev[e] = gradient(p[e], prev[e], dn_prev[e]);
+            if (LAG && r == 2 + e * (K1 - 2) / 16) prev[e] = gradient(p[e], prev[e], dn_prev[e]);
             if (!LAG && r == K1) prev[e] = gradient(p[e], sc[e], dn_all[e]);
           }
           if (r == K1)

@@ -43,16 +43,6 @@ __device__ __forceinline__ f32x4 *merge_slots(char *smem, int wave, int lane, in
 }
 
 // ------------------------------------------------------------------ backward: dq (and D)
-struct BackwardArgs {
-  int b, s, n, head_dim, group;
-  float scale;
-  const bf16 *qkv, *a;
-  const float *lse;
-  const bf16 *da;
-  bf16 *dqkv;
-  float *Dvec;
-};
-
 template <int D, bool PAIRED, bool EXACT>
 __device__ __forceinline__ void dq_block(unsigned place, char *smem, int b, int s, int n, int head_dim, int group, float scale,
                                          const bf16 *__restrict__ qkv, const bf16 *__restrict__ a, const float *__restrict__ lse,
@@ -270,7 +260,7 @@ __device__ __forceinline__ void dkv_block(unsigned place, char *smem, int b, int
   const HeadBlock hb(b, n, group, BackwardBlocks<PAIRED>::count(s), place);
   const int j = hb.head, bi = hb.batch;
   if (hb.none) return;
-  const BackwardBlocks<PAIRED> bb(s, hb.order, threadIdx.x >> 6);   // (from the thread number; head size 160: 194 registers instead of 230)
+  const BackwardBlocks<PAIRED> bb(s, hb.order, threadIdx.x >> 6);   // (from the thread number: as in the forward kernels)
   const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // a scalar
   const int d = EXACT ? head_dim : D;

@@ -42,8 +42,8 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 2) void attn_fwd_kernel(ForwardArgs
   constexpr int ROWS = FWD_WAVES / SPLIT, OWNED = 32 * ROWS;   // waves with rows of their own
   constexpr int K1 = D / 16, CB = D / 32, STAGE = 2 * T::BYTES, NP = EXACT ? 3 : 1;
   constexpr int SUBS = SPLIT == 2 ? 1 : 2;                // 32-key parts of a tile that a wave takes
-  constexpr int N1 = 2 * K1, NF = D == 160 ? 5 : D == 96 || D == 192 ? 6 : 4, PF = NF - 1;   // steps of a part: K1 for S, K1 for O
-  static_assert(N1 % NF == 0, "fragment buffers");
+  constexpr int N1 = 2 * K1, NF = D == 160 ? 5 : D == 96 ? 6 : 4, PF = NF - 1;   // steps of a part: K1 for S, K1 for O
+  static_assert(D >= 64 && D <= 160 && N1 % NF == 0, "fragment buffers");
   const int s = w.s, n = w.n, d = EXACT ? w.head_dim : D;
   const int count = own_blocks(s, OWNED);
   const HeadBlock hb(w.b, n, w.group, count, blockIdx.x);

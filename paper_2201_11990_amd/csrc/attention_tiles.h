@@ -317,6 +317,17 @@ __device__ __forceinline__ float quad_max(float v) {
   return fmaxf(__builtin_bit_cast(float, q0), __builtin_bit_cast(float, q1));
 }
 
+// what the backward kernels take
+struct BackwardArgs {
+  int b, s, n, head_dim, group;
+  float scale;
+  const bf16 *qkv, *a;
+  const float *lse;
+  const bf16 *da;
+  bf16 *dqkv;
+  float *Dvec;
+};
+
 // maximum over the two lanes that share lane % 32
 __device__ __forceinline__ float pair_max(float v) {
   typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
