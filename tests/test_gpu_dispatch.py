@@ -611,9 +611,10 @@ def test_attention_with_large_values(b, s, n, d, part):
 
 
 # Backward in one launch, dk / dv with a D of its own: two rows (with one dq is the rounding of dP - D), the edges of a 64-row block and of the 128 rows that a pass of D takes, and
-# either side of the rule (256 blocks; 768 at head size 64 up to s 1024).
+# either side of the rule (up to 320 blocks, 296 for s 65 to 96; head size 64 up to 768, 256 beyond s 1024).
 @pytest.mark.parametrize("b,s,n,d", [(1, 2, 1, 128), (2, 63, 3, 64), (1, 64, 2, 160), (1, 65, 1, 128), (1, 129, 2, 64), (3, 191, 1, 160), (1, 1030, 1, 64),
-                                     (4, 64, 64, 128), (1, 64, 257, 160), (3, 100, 128, 64), (1, 97, 385, 64)])
+                                     (4, 64, 64, 128), (1, 64, 257, 160), (3, 100, 128, 64), (1, 97, 385, 64), (1, 64, 320, 128), (1, 64, 321, 160), (1, 70, 148, 160), (1, 70, 149, 128),
+                                     (1, 1030, 16, 64)])
 def test_attention_backward_in_one_launch(b, s, n, d):
     test_gpu_ops.test_attention_fwd_bwd("bf16", b, s, n, d)
 
@@ -879,11 +880,10 @@ def test_attention_batches_of_several_grid_rows():
         assert torch.equal(whole, torch.cat([first, second]))
 
 
-# Many heads: the backward kernels with two blocks of a head to a workgroup (all but the second case, which goes out in one launch, and the
-# last; an even and an odd number of blocks), every kernel with the heads in several grid rows, the last one shorter and no multiple of 8
-# (forward: the last three; backward: all but the first three).
+# Many heads.  Backward: one launch (the first two cases), two blocks of a head to a workgroup (head size 64, s 65 to 128), 128 rows and 64 (the last case but one) to a workgroup.  Forward: 64 queries to a workgroup,
+# and 128 (24 x 128 and the last case).  The heads in several grid rows, the last one shorter and no multiple of 8: forward all but the first three cases and 24 x 128, backward all but the first three.
 @pytest.mark.parametrize("b,s,n,d", [(5, 192, 20, 128), (12, 100, 25, 64), (16, 100, 25, 64), (12, 130, 25, 128), (12, 130, 25, 160), (24, 128, 25, 64),
-                                     (12, 260, 25, 128), (12, 260, 25, 160), (20, 449, 13, 64)])
+                                     (12, 260, 25, 128), (12, 260, 25, 160), (20, 449, 13, 64), (12, 130, 43, 160)])
 def test_attention_of_many_heads(b, s, n, d):
     qkv, da = randn((b * s, 3 * n * d), "bf16", 21), randn((b * s, n * d), "bf16", 22)
     dims = oracle.Dims(hidden=8, heads=n, head_dim=d, ffn=8, seq=s, batch=b)
@@ -900,9 +900,9 @@ def test_attention_of_many_heads(b, s, n, d):
 
 # One key that scores 100 (natural units) above all others, head by head at every position modulo 16 and, by sequence, in the
 # first tile, a middle one and the last: exponents taken from any but the maximum over all keys overflow.  208 rows: 16 heads x 3
-# sequences stay with 16 rows per wave in the forward kernel, x 18 take 32 at head sizes 128 and 160.
+# and x 18 sequences go to workgroups of 64 queries, whose halves of the keys have a maximum each, x 32 to workgroups of 128 at head sizes 128 and 160.
 @pytest.mark.parametrize("d", [64, 128, 160])
-@pytest.mark.parametrize("b", [3, 18])
+@pytest.mark.parametrize("b", [3, 18, 32])
 def test_attention_with_one_dominating_key(b, d):
     s, n = 208, 16
     g = torch.Generator().manual_seed(17)

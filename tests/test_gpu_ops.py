@@ -269,10 +269,9 @@ def test_attention_fwd_bwd(dtype, b, s, n, d):
         assert rel_fro(got[:, :, :, i], want[:, :, :, i]) <= tol, f"d{nm}"
 
 
-# Enough (sequence block, head, batch) workgroups for the forward kernel to take its 256-rows-per-workgroup shape
-# (32 rows per wave) at head sizes 128 and 160: an odd number of 64-row tiles whose last block hangs over the end
-# (s 150), an odd number of 128-row blocks, i.e. a middle block alone in its workgroup (s 257, 700 -> 3 and 6 blocks),
-# one block only (s 64, s 1), several tiles per block with a ragged end (s 1000).
+# Head sizes 128 and 160, 32 rows per wave, forward and backward with 128 own rows to a workgroup (s 150 forward and backward, s 1000 forward, s 257 to 1000 backward) and with 64: an odd number of 64-row
+# tiles whose last block hangs over the end (s 150), an odd number of 128-row blocks (s 257, 700 -> 3 and 6 blocks), one block only (s 64, s 1), several tiles per block with a
+# ragged end (s 1000).
 ATT_WIDE_CASES = [(8, 150, 64, 128), (4, 257, 64, 160), (2, 700, 64, 128), (16, 64, 16, 160), (8, 1, 32, 128),
                   (2, 1000, 32, 160)]
 
