@@ -1,5 +1,5 @@
-// Backward of the fused causal attention (attention_mfma.hip: forward), for bf16 head sizes 128 and 160 and, with P and dS in fp32 (EXACT), most of
-// the others up to 192 (attention_bwd64.hip: the small ones).
+// Backward of the fused causal attention (attention_mfma.hip: forward), for bf16 head sizes 128 and 160 and, with P and dS in fp32 (EXACT), for the longer sequences of
+// the others up to 192 (the rest: attention_bwd64.hip; attention_bwd_exact says which).
 //
 //   D_t = da_t . a_t:  dP = da v^T,  dS = P o (dP - D),  dq = scale dS k,  dk = scale dS^T q,  dv = P^T da.
 //
@@ -7,8 +7,8 @@
 // LDS as in the forward kernel.  No atomics: every output element has one owner, results are run-to-run identical.  Both form S and dP: writing dS
 // instead would move 2 bytes a score, four times what is read and written otherwise.
 //
-// What bounds them: in the loop the MFMAs, 60 to 80 % of the time at head size 160 and 50 to 70 % at 128 (the rest: barriers, the start of a tile, vector work that does not hide), under a clock of
-// 1.8 to 2.0 GHz; besides, the 3 to 6 us that a workgroup costs at its start and end.  us against the kernels before, 16 own rows a wave on 16x16x32 MFMAs: 1990 tokens
+// What bounds them: the MFMAs and the vector work that does not hide behind them.  The matrix pipes work 44 to 57 % of the time of a busy unit in dq and 42 to 49 % in dk / dv (head sizes 128 and 160, one
+// to four sequences of 2048, 16 heads; EXACT 34 to 48 %), LDS 24 to 38 %, without bank conflicts; the rest are exponentials, dS, packing, barriers, and the 3 to 6 us that a workgroup costs at its start and end.  us against the kernels before, 16 own rows a wave on 16x16x32 MFMAs: 1990 tokens
 // x 16 heads of 160 112 -> 97, 2048 x 16 of 128 98 -> 81, 4 x 2048 x 16 of 128 325 -> 270, 2048 x 20 of 128 137 -> 102, 384 x 256 of 160 126 -> 105, 256 x 2 of 160 13.8 -> 11.2.
 #include "attention_tiles.h"
 
@@ -28,7 +28,7 @@ namespace {
 // merged through LDS at the end.  SPLIT 1: 128 rows, every wave takes whole tiles.  Blocks go out in the order of falling work.
 //
 // A step is one fragment and its MFMA (EXACT: three in the second product).  Fragments are read PF steps ahead across the end of a tile, and a tile's barrier
-// stands PF steps before its end.
+// stands PF steps before its end.  A wave passes over the 32-row parts that none of its rows sees: they cost it the barriers and its share of the DMA, and what is in them does not reach its results.
 // what both kernels know of the head that a workgroup works on
 template <bool EXACT, int D>
 struct Head {

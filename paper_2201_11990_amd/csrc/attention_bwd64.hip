@@ -1,10 +1,10 @@
-// Backward of the fused causal attention for bf16 head size 64 and, with P and dS in fp32 (EXACT), for the smaller ones (the others: attention_bwd.hip), with the tiles and fragments of
-// attention_fwd16.hip.
+// Backward of the fused causal attention with 16 own rows to a wave: bf16 head size 64 and, with P and dS in fp32 (EXACT), head sizes up to 64 and the short sequences of the others up to 192
+// (attention_bwd.hip has the rest and says which), with the tiles and fragments of attention_fwd16.hip.
 //
 // dP = da v^T,  dS = P o (dP - D) with D_t = da_t . a_t,  dq = scale dS k,  dk = scale dS^T q,  dv = P^T da, on 16x16x32 MFMAs with 16 own rows to a wave:
 //   dq      : S^T and dP^T = V dO^T with the query on the lane column, dQ^T += K^T dS^T.
 //   dk / dv : S = Q K^T, dP = dO V^T with the key on the lane column, dV^T += dO^T P, dK^T += Q^T dS.
-// The vector unit bounds it: a tile's exponentials and dS take longer than its MFMAs at this head size, and what hides latency is the number of waves, for which these kernels are
+// The vector unit bounds it: a tile's exponentials and dS take longer than its MFMAs at head size 64 (the matrix pipes work 36 % of the time), and what hides latency is the number of waves, for which these kernels are
 // small (24 waves to a compute unit).  The kernels of attention_bwd.hip, with 32 own rows to a wave and 8 to 16 waves to a unit, took 50 us instead of
 // 56 at 2048 tokens x 16 heads and 153 instead of 167 at 4 times that, but 29 instead of 24 at 1024 x 20, 20 instead of 17.6 at 512 x 48 and 12 instead of 9.4 at 128 x 128.
 #include "attention_tiles.h"
@@ -18,11 +18,11 @@ namespace {
 // tile, and their partial results are merged through LDS at the end.  Half the tile per wave halves the registers
 // of its scores and its chain per tile, and no wave idles while the mask leaves work to the other half only.  Blocks are
 // handed out in the order of falling work, so a compute unit that got a long block gets a short one after it.  Measured with
-// paired blocks and whole tiles before, dq + dk/dv at 2048 tokens x 16 heads: 75 us, now 56.  (In the forward kernel, which has fewer registers to
+// paired blocks and whole tiles before, dq + dk/dv at 2048 tokens x 16 heads: 75 us, now 56.  (In the forward kernel of attention_fwd16.hip, which has fewer registers to
 // save, the merge costs more than it gives.)
 
 // Over many sequences the work evens out by itself, and what a workgroup costs besides its tiles counts instead.  PAIRED has half the workgroups: waves 0-3
-// and 4-7 own blocks p and nb - 1 - p and take whole tiles, as in the forward kernel, with nothing to merge.
+// and 4-7 own blocks p and nb - 1 - p and take whole tiles, as in attention_fwd16.hip, with nothing to merge.
 template <bool PAIRED>
 struct BackwardBlocks {
   int block;      // this wave's 64-row block

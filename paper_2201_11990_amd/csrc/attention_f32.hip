@@ -1,6 +1,6 @@
 // Causal softmax attention, forward and backward, on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32): scores,
 // probabilities and sums stay in fp32.  This is the attention of the fp32 path, and of bf16 head sizes other than 64, 128 and 160 in
-// small calls and above 192 (the rest: the EXACT kernels of attention_mfma.hip).  Head sizes: multiples of 8 up to 256; sequences up to 4096.
+// small calls and above 192 (the rest: the EXACT kernels of the four files of bf16 attention).  Head sizes: multiples of 8 up to 256; sequences up to 4096.
 //
 //   S[t,u] = scale * q_t . k_u  (u <= t),  P = rowsoftmax(S),  a_t = sum_u P[t,u] v_u
 //   lse[t] = log sum_u exp(S[t,u])

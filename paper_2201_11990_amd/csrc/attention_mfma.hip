@@ -1,5 +1,5 @@
 // Fused causal softmax attention on the gfx950 matrix cores (bf16 in, fp32 softmax and accumulation): forward, for head sizes 64, 128 and 160; and
-// with P in fp32 (EXACT) for the others up to 192.  Backward: attention_bwd.hip, attention_bwd64.hip.
+// with P in fp32 (EXACT) for the others up to 192.  Some calls, short sequences above all, go to attention_fwd16.hip.  Backward: attention_bwd.hip, attention_bwd64.hip.
 //
 //   S = scale * q k^T (causal),  P = rowsoftmax(S),  a = P v,  lse = log sum exp(S)
 //
@@ -11,7 +11,7 @@
 // the registers and nothing is transposed in software.  No atomics: every output element has one owner, results are run-to-run identical.
 //
 // What bounds it: in a tile the softmax (some 75 vector instructions and 16 exponentials for 16 MFMAs at head size 128), which hides behind the MFMAs of the other workgroup on the
-// unit only; in small calls the 3 to 4 us of a launch and the first trips to memory.  us against eight waves of 16 or 32 queries on 16x16x32 MFMAs, one workgroup to a unit: 16 heads, s = 2048, head
+// unit only (the matrix pipes work 33 to 48 % of the time of a busy unit, LDS 19 to 24 %); in small calls the 3 to 4 us of a launch and the first trips to memory.  us against eight waves of 16 or 32 queries on 16x16x32 MFMAs, one workgroup to a unit: 16 heads, s = 2048, head
 // size 64 24.6 -> 22.3, 128 36.0 -> 30.3, 160 38.8 -> 35.6; 20 heads of 128 51.9 -> 33.1; 128 of 128, s = 768 46.8 -> 36.9; 2 of 160, s = 256 9.3 -> 7.5; 64 of 128, s = 1024 32.2 -> 29.8.
 //
 // EXACT: any head size d that is a multiple of 8, in tiles of D = d rounded up to 32 columns (the DMA brings zeros past d).  P is not rounded to bf16: it goes into the second product as

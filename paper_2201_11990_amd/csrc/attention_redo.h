@@ -1,4 +1,4 @@
-// What the attention kernels that keep P and dS in fp32 share (attention_f32.hip, the EXACT ones of attention_mfma.hip): the slow path
+// What the attention kernels that keep P and dS in fp32 share (attention_f32.hip; the EXACT ones of attention_mfma.hip, attention_fwd16.hip, attention_bwd.hip, attention_bwd64.hip): the slow path
 // for inputs that are not finite.
 #pragma once
 #include "common.h"

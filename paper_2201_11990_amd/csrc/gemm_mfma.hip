@@ -822,7 +822,8 @@ int launch_tile(int tile, const GemmArgs &g, void *ws, size_t ws_bytes, hipStrea
 //     rings: two workgroups a compute unit, 1.0 us a slab for a full round of 512; a lone workgroup (0.88) waits for its
 //     DMA.  Rings of four stages: one workgroup a unit, 0.53 us a slab.
 // Measured (us; 256 x 256, split along K where that pays / 128 x 128 / with deep rings): 2048^3 42 / 28 / 21,
-// 2048 x 2048 x 8192 71 / 112 / 72, 1024 x 6144 x 2048 46 / 37 / 42, 2048 x 8192 x 2048 53 / 75 / 83, 256 x 960 x 512 13 / 9.3 / 7.5.
+// 1024 x 6144 x 2048 46 / 37 / 42, 2048 x 8192 x 2048 48 / 59 / 67, 256 x 960 x 512 13 / 9.3 / 7.5.  2048 x 2048 x 8192 75 / 71 / 62 (TN 75 / 70 / 65), where the estimates tie
+// (71.2 and 72.3 for the first and last) and take the first: a slab of the deep rings is dearer here than it measures at long K (4096: 32 against 38 estimated).
 double time_256(int64_t tiles, int nk, bool can_split, size_t ws_bytes) {
   const double slab = 1.45, round = 8.0;
   if (can_split) {
